@@ -196,11 +196,14 @@ int launch_std_scores(const lisa_desc* d, const void* q, const void* k, KeyStrid
 // CONCAT with the two-layer ReLU FFN on the matrix cores (dense prefill tensors only).
 constexpr int kComputeUnits = 256;   // MI355X
 
+bool std_prefill_fast_ok(const lisa_desc* d);
 bool scores_mfma_ok(const lisa_desc* d) {
   if (d->dtype != LISA_BF16 || d->mix != LISA_MIX_CONCAT) return false;
   if (d->act != LISA_ACT_RELU && d->act != LISA_ACT_SILU) return false;
   if (d->Lq == 1) return false;                            // decode rows: the generic kernel (strided caches)
-  if (d->H > 48 || d->F > 256 || d->r > 32 || d->Lk % 8 != 0) return false;
+  if (d->H > 48 || d->F > 256 || d->r > 32) return false;
+  // rows that are no multiple of 8 scores: where the matrix-core softmax follows (d_k = 128)
+  if (d->Lk % 8 != 0 && !std_prefill_fast_ok(d)) return false;
   return (long long)d->Lq * d->Lk < (1LL << 31);
 }
 
@@ -225,7 +228,6 @@ struct ConcatWs {
   size_t qp, kp, vt, total;
   int Lqp, Lkp;
 };
-bool std_prefill_fast_ok(const lisa_desc* d);
 // The CONCAT pipeline on tiled score tensors: the pipelined scores kernel (up to 32 heads) followed
 // by the matrix-core softmax kernel, which then reads tiles.
 bool concat_tiled_ok(const lisa_desc* d) { return scores_mfma_ok(d) && d->H <= 32 && std_prefill_fast_ok(d); }
@@ -562,7 +564,7 @@ int run_decode_fast(const lisa_desc* d, bool lisa_layer, DecodeArgs a, void* out
 bool prefill_fused_ok(const lisa_desc* d) {
   if (d->dtype != LISA_BF16 || d->d_k != 128) return false;
   if (d->mix != LISA_MIX_ADD || (d->act != LISA_ACT_RELU && d->act != LISA_ACT_SILU)) return false;
-  if (d->Lk % 8 != 0 || d->F > 128 || d->r > 32) return false;   // 16-byte aligned score rows
+  if (d->Lk < 8 || d->F > 128 || d->r > 32) return false;   // (scores are read 8 at a time)
   // 32-bit byte offsets inside one head's scores (tiled: rows and keys rounded up to whole tiles)
   if ((long long)(d->Lq + PF_ROWS) * (d->Lk + PF_TK) >= (1LL << 31)) return false;
   return d->H == 8 || d->H == 16 || d->H == 24 || d->H == 32 || d->H == 40;
@@ -777,7 +779,7 @@ int run_prefill_fused(const lisa_desc* d, const void* q_lr, const void* k_lr, co
 
 // ---- standard layer, prefill, MFMA (bf16) ---------------------------------------------
 bool std_prefill_fast_ok(const lisa_desc* d) {
-  return d->dtype == LISA_BF16 && d->d_k == 128 && d->Lk % 8 == 0 && d->Lq > 1;
+  return d->dtype == LISA_BF16 && d->d_k == 128 && d->Lk >= 8 && d->Lq > 1;
 }
 
 size_t std_prefill_ws(const lisa_desc* d) {   // V by key chunks
