@@ -1,0 +1,46 @@
+// Host-side helpers shared by the translation units of the library: status reporting, stage timing and
+// the launchers that live in files of their own (their kernels have many instantiations, which
+// compile side by side that way).
+#pragma once
+#include "../../include/lisa.h"
+
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
+#include <cstdio>
+
+#include "kernels_decode.h"
+#include "kernels_prefill.h"
+#include "kernels_scores_mfma.h"
+
+namespace lisa {
+
+constexpr int kComputeUnits = 256;   // MI355X
+
+inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+inline float pick_scale(float given, int n) { return given > 0.f ? given : 1.0f / std::sqrt((float)n); }
+
+int hip_fail(hipError_t e);          // remembers the error's text for lisa_last_hip_error()
+int check_launch();
+
+// ---- optional stage timing (lisa_profile_*) -------------------------------------------
+struct ProfRec {
+  const char* name;
+  hipEvent_t beg, end;
+};
+// Brackets the launches made while it is alive with two events on their stream.
+struct StageScope {
+  hipStream_t st;
+  ProfRec rec{nullptr, nullptr, nullptr};
+  StageScope(const char* name, hipStream_t s);
+  ~StageScope();
+};
+
+// launch_prefill.hip, launch_decode.hip, launch_scores.hip
+template <int NG, int HPW, int NW>
+int launch_prefill_fused_fs(const lisa_desc* d, const PrefillArgs& a, int slices, hipStream_t st);
+int launch_decode_part(const lisa_desc* d, bool lisa_layer, DecodeArgs a, hipStream_t st);
+int launch_scores_mfma_kernel(const lisa_desc* d, const ScoresMfmaArgs& a, hipStream_t st);
+
+}  // namespace lisa

@@ -848,7 +848,7 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
 // Merges the key-split partials of k_lisa_prefill_fused: for every (b, row, h)
 //   O = sum_s e^{m_s - M} o_s / sum_s e^{m_s - M} l_s,   M = max_s m_s   over the non-empty shares.
 // grid (Lq, B), block 256; thread -> (head, 4 features) pairs.
-__global__ __launch_bounds__(256) void k_prefill_combine(PrefillArgs a) {
+static __global__ __launch_bounds__(256) void k_prefill_combine(PrefillArgs a) {
   constexpr int DK = 128;
   const int i = blockIdx.x, b = blockIdx.y, H = a.H;
   const int rb = i / PF_ROWS;

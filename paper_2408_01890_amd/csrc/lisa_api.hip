@@ -1,23 +1,15 @@
 // C ABI of the LiSA attention-layer library: argument validation (host only, before any
 // HIP call), workspace accounting and kernel dispatch.  See include/lisa.h for the contract.
-#include "../../include/lisa.h"
-
-#include <hip/hip_runtime.h>
-
-#include <algorithm>
-#include <cmath>
-#include <cstdio>
-#include <cstring>
 #include <cstdlib>
+#include <cstring>
 #include <mutex>
+#include <vector>
 
-#include "kernels_decode.h"
-#include "kernels_kd.h"
+#include "host.h"
 #include "kernels_generic.h"
-#include "kernels_prefill.h"
+#include "kernels_kd.h"
 #include "kernels_probe.h"
 #include "kernels_project.h"
-#include "kernels_scores_mfma.h"
 #include "kernels_std_prefill.h"
 
 using namespace lisa;
@@ -58,7 +50,6 @@ int static_scratch(void** out) {
   return LISA_OK;
 }
 
-inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // Limits of the kernels in this library (see lisa_supported()).
@@ -129,23 +120,7 @@ size_t exact_bytes(const lisa_desc* d) {
   return round_up((size_t)d->B * d->H * d->Lq * d->Lk * sizeof(float), 256);
 }
 
-int hip_fail(hipError_t e) {
-  snprintf(g_hip_err, sizeof(g_hip_err), "%s", hipGetErrorString(e));
-  return LISA_ERR_HIP;
-}
-
-int check_launch() {
-  hipError_t e = hipGetLastError();
-  return e == hipSuccess ? LISA_OK : hip_fail(e);
-}
-
-float pick_scale(float given, int n) { return given > 0.f ? given : 1.0f / std::sqrt((float)n); }
-
 // ---- optional stage timing (lisa_profile_*) -------------------------------------------
-struct ProfRec {
-  const char* name;
-  hipEvent_t beg, end;
-};
 constexpr size_t kMaxProfRecs = 16384;
 thread_local bool g_prof_on = false;
 thread_local std::vector<ProfRec> g_prof_recs;
@@ -162,24 +137,38 @@ hipEvent_t prof_event() {
   return e;
 }
 
-// Brackets the launches made while it is alive with two events on their stream.
-struct StageScope {
-  hipStream_t st;
-  ProfRec rec{nullptr, nullptr, nullptr};
-  StageScope(const char* name, hipStream_t s) : st(s) {
-    if (!g_prof_on || g_prof_recs.size() >= kMaxProfRecs) return;
-    rec.beg = prof_event();
-    rec.end = prof_event();
-    if (!rec.beg || !rec.end) { rec.beg = rec.end = nullptr; return; }
-    rec.name = name;
-    (void)hipEventRecord(rec.beg, st);
-  }
-  ~StageScope() {
-    if (!rec.name) return;
-    (void)hipEventRecord(rec.end, st);
-    g_prof_recs.push_back(rec);
-  }
-};
+
+}  // namespace
+
+namespace lisa {
+
+int hip_fail(hipError_t e) {
+  snprintf(g_hip_err, sizeof(g_hip_err), "%s", hipGetErrorString(e));
+  return LISA_ERR_HIP;
+}
+
+int check_launch() {
+  hipError_t e = hipGetLastError();
+  return e == hipSuccess ? LISA_OK : hip_fail(e);
+}
+
+StageScope::StageScope(const char* name, hipStream_t s) : st(s) {
+  if (!g_prof_on || g_prof_recs.size() >= kMaxProfRecs) return;
+  rec.beg = prof_event();
+  rec.end = prof_event();
+  if (!rec.beg || !rec.end) { rec.beg = rec.end = nullptr; return; }
+  rec.name = name;
+  (void)hipEventRecord(rec.beg, st);
+}
+StageScope::~StageScope() {
+  if (!rec.name) return;
+  (void)hipEventRecord(rec.end, st);
+  g_prof_recs.push_back(rec);
+}
+
+}  // namespace lisa
+
+namespace {
 
 // ---- generic launches ----------------------------------------------------------------
 template <typename T, typename S>
@@ -194,8 +183,6 @@ int launch_std_scores(const lisa_desc* d, const void* q, const void* k, KeyStrid
 }
 
 // CONCAT with the two-layer ReLU FFN on the matrix cores (dense prefill tensors only).
-constexpr int kComputeUnits = 256;   // MI355X
-
 bool std_prefill_fast_ok(const lisa_desc* d);
 bool scores_mfma_ok(const lisa_desc* d) {
   if (d->dtype != LISA_BF16 || d->mix != LISA_MIX_CONCAT) return false;
@@ -205,21 +192,6 @@ bool scores_mfma_ok(const lisa_desc* d) {
   // rows that are no multiple of 8 scores: where the matrix-core softmax follows (d_k = 128)
   if (d->Lk % 8 != 0 && !std_prefill_fast_ok(d)) return false;
   return (long long)d->Lq * d->Lk < (1LL << 31);
-}
-
-template <int HBI, int FS, int HBO, bool TILED = false>
-int launch_scores_mfma_t(const lisa_desc* d, const ScoresMfmaArgs& a, hipStream_t st) {
-  const int lds = scores_mfma_lds<HBI, FS, HBO>(d->H);
-  auto kern = d->act == LISA_ACT_SILU ? k_lisa_scores_mfma<HBI, FS, HBO, 1, TILED>
-                                      : k_lisa_scores_mfma<HBI, FS, HBO, 0, TILED>;
-  hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  if (e != hipSuccess) return hip_fail(e);
-  // one workgroup per compute unit, each with an equal run of the tiles
-  const long long total = a.tiles_b * a.B;
-  dim3 grid((unsigned)std::min<long long>(total, kComputeUnits));
-  StageScope prof("k_lisa_scores_mfma", st);
-  kern<<<grid, 512, lds, st>>>(a);
-  return check_launch();
 }
 
 // Workspace of the CONCAT pipeline: A_n in the score type when the caller does not ask for it (the
@@ -282,15 +254,7 @@ int launch_scores_mfma(const lisa_desc* d, const void* q_lr, const void* k_lr, c
   a.causal = d->causal;
   a.dscale = pick_scale(d->delta_scale, d->r);
   a.tiled = d->score_tiled;
-  const bool wide = d->F > 128;
-  if (d->score_tiled) {                                      // (concat_tiled_ok: up to 32 heads)
-    if (d->H <= 16)
-      return wide ? launch_scores_mfma_t<2, 8, 1, true>(d, a, st) : launch_scores_mfma_t<2, 4, 1, true>(d, a, st);
-    return wide ? launch_scores_mfma_t<4, 8, 2, true>(d, a, st) : launch_scores_mfma_t<4, 4, 2, true>(d, a, st);
-  }
-  if (d->H <= 16) return wide ? launch_scores_mfma_t<2, 8, 1>(d, a, st) : launch_scores_mfma_t<2, 4, 1>(d, a, st);
-  if (d->H <= 32) return wide ? launch_scores_mfma_t<4, 8, 2>(d, a, st) : launch_scores_mfma_t<4, 4, 2>(d, a, st);
-  return wide ? launch_scores_mfma_t<6, 8, 3>(d, a, st) : launch_scores_mfma_t<6, 4, 3>(d, a, st);
+  return launch_scores_mfma_kernel(d, a, st);
 }
 
 template <typename T, typename S>
@@ -441,49 +405,6 @@ int flush_deferred_combine(hipStream_t st) {
   return launch_combine(g_dc.o, g_dc.ml, g_dc.out, g_dc.H, g_dc.B, g_dc.n_chunk, g_dc.dk, g_dc.out_f32, st);
 }
 
-template <int LISA_MODE, int HB, int FS, int ACT = 0>
-int launch_decode_part_dk(const lisa_desc* d, const DecodeArgs& a, size_t lds, hipStream_t st) {
-  dim3 grid(a.n_chunk, d->B);
-  if (a.cmb_units > 0) lds = std::max<size_t>(lds, 4608);   // (the combine units use the same LDS)
-  auto kern = d->d_k == 128 ? k_decode_part<LISA_MODE, HB, FS, 128, ACT> : k_decode_part<LISA_MODE, HB, FS, 64, ACT>;
-  if (lds > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)lds);
-    if (e != hipSuccess) return hip_fail(e);
-  }
-  StageScope prof(LISA_MODE == 3 ? "k_decode_part_share" : LISA_MODE ? "k_decode_part_lisa" : "k_decode_part_std", st);
-  kern<<<grid, DEC_THREADS, lds, st>>>(a);
-  return check_launch();
-}
-
-// CONCAT form: HBI blocks of 16 FFN inputs (2H of them), hidden width by thirds of the range
-template <int HBI, int ACT>
-int launch_decode_concat_act(const lisa_desc* d, const DecodeArgs& a, size_t lds, hipStream_t st) {
-  if (d->F <= 64) return launch_decode_part_dk<2, HBI, 2, ACT>(d, a, lds, st);
-  if (d->F <= 128) return launch_decode_part_dk<2, HBI, 4, ACT>(d, a, lds, st);
-  return launch_decode_part_dk<2, HBI, 8, ACT>(d, a, lds, st);
-}
-template <int HBI>
-int launch_decode_concat_fs(const lisa_desc* d, const DecodeArgs& a, size_t lds, hipStream_t st) {
-  return d->act == LISA_ACT_SILU ? launch_decode_concat_act<HBI, 1>(d, a, lds, st)
-                                 : launch_decode_concat_act<HBI, 0>(d, a, lds, st);
-}
-
-template <int HB, int ACT>
-int launch_decode_lisa_act(const lisa_desc* d, const DecodeArgs& a, size_t lds, hipStream_t st) {
-  switch ((d->F + 31) / 32) {
-    case 1: return launch_decode_part_dk<1, HB, 1, ACT>(d, a, lds, st);
-    case 2: return launch_decode_part_dk<1, HB, 2, ACT>(d, a, lds, st);
-    case 3: return launch_decode_part_dk<1, HB, 3, ACT>(d, a, lds, st);
-    default: return launch_decode_part_dk<1, HB, 4, ACT>(d, a, lds, st);
-  }
-}
-template <int HB>
-int launch_decode_lisa_fs(const lisa_desc* d, const DecodeArgs& a, size_t lds, hipStream_t st) {
-  return d->act == LISA_ACT_SILU ? launch_decode_lisa_act<HB, 1>(d, a, lds, st)
-                                 : launch_decode_lisa_act<HB, 0>(d, a, lds, st);
-}
-
 int run_decode_fast(const lisa_desc* d, bool lisa_layer, DecodeArgs a, void* out, void* workspace,
                     hipStream_t st) {
   const size_t units = (size_t)d->B * decode_chunks(d) * d->H;
@@ -513,34 +434,7 @@ int run_decode_fast(const lisa_desc* d, bool lisa_layer, DecodeArgs a, void* out
       if (frc) return frc;
     }
   }
-  size_t lds = (size_t)d->H * DEC_CK * sizeof(float);
-  int rc;
-  if (lisa_layer && d->mix == LISA_MIX_SHARE) {
-    a.scale = 0.f;
-    rc = launch_decode_part_dk<3, 1, 1>(d, a, lds, st);
-  } else if (lisa_layer && d->mix == LISA_MIX_CONCAT) {
-    const int hbi = d->H <= 16 ? 2 : d->H <= 32 ? 4 : 6, fs = d->F <= 64 ? 2 : d->F <= 128 ? 4 : 8;
-    const int ks1 = (hbi + 1) / 2, hbo = (hbi + 1) / 2;
-    lds += (size_t)((d->H * d->r + 3) & ~3) * sizeof(float) + (size_t)(2 * fs * ks1 + hbo * fs) * 1024;
-    a.scale = pick_scale(d->delta_scale, d->r);
-    rc = hbi == 2   ? launch_decode_concat_fs<2>(d, a, lds, st)
-         : hbi == 4 ? launch_decode_concat_fs<4>(d, a, lds, st)
-                    : launch_decode_concat_fs<6>(d, a, lds, st);
-  } else if (lisa_layer) {
-    // + q_lr [H][r] as float + the FFN weights in MFMA operand order (mfma_ffn.h: kStageBytes)
-    const int hb = (d->H + 15) / 16, fs = (d->F + 31) / 32, ks1 = (hb + 1) / 2;
-    lds += (size_t)((d->H * d->r + 3) & ~3) * sizeof(float) + (size_t)(2 * fs * ks1 + hb * fs) * 1024;
-    a.scale = pick_scale(d->delta_scale, d->r);
-    switch ((d->H + 15) / 16) {
-      case 1: rc = launch_decode_lisa_fs<1>(d, a, lds, st); break;
-      case 2: rc = launch_decode_lisa_fs<2>(d, a, lds, st); break;
-      case 3: rc = launch_decode_lisa_fs<3>(d, a, lds, st); break;
-      default: rc = launch_decode_lisa_fs<4>(d, a, lds, st); break;
-    }
-  } else {
-    a.scale = pick_scale(d->std_scale, d->d_k);
-    rc = launch_decode_part_dk<0, 1, 1>(d, a, lds, st);
-  }
+  int rc = launch_decode_part(d, lisa_layer, a, st);
   if (rc) return rc;
   if (g_dc.on) {                                             // left to the next layer's launch (or the stack's end)
     g_dc.pending = true;
@@ -655,58 +549,6 @@ PrefillWs prefill_fused_ws(const lisa_desc* d) {
   w.part_ml = w.part_o + round_up(rows * d->d_k * sizeof(float), 256);
   w.total = w.part_ml + round_up(rows * 2 * sizeof(float), 256);
   return w;
-}
-
-template <int NG, int FS, int HPW, int NW, int ACT, int RS, int SHG = 0, bool FTRIM = false>
-int launch_prefill_fused_t(const lisa_desc* d, const PrefillArgs& a, hipStream_t st) {
-  constexpr int GH = NW * HPW, H = NG * GH;
-  typedef MfmaFfn<(H + 15) / 16, FS, (GH + 15) / 16> Ffn;
-  // (all heads in one workgroup: the A_{n-1} piece is double buffered and doubles as A_n staging)
-  constexpr bool XSTG = NG == 1 && HPW == 4;
-  constexpr size_t lds = XSTG ? (size_t)2 * H * PF_XS_HEAD + (size_t)GH * PF_YS_HEAD + Ffn::kStageBytes
-                              : (size_t)H * PF_XS_HEAD + (size_t)GH * PF_YS_HEAD + Ffn::kStageBytes +
-                                    (size_t)GH * RS * PF_AS_HEAD;
-  static_assert(lds <= 160 * 1024, "LDS of one compute unit");
-  auto kern = k_lisa_prefill_fused<NG, FS, HPW, NW, ACT, RS, SHG, FTRIM>;
-  hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)lds);
-  if (e != hipSuccess) return hip_fail(e);
-  const long long units = (long long)((a.Lq + PF_ROWS * RS - 1) / (PF_ROWS * RS)) * a.split;
-  constexpr int CHU = pf_chunk_units(NG);                    // neighbouring units per chunk
-  const long long chunks = ((a.pair ? (units + 1) / 2 : units) + CHU - 1) / CHU * a.B;
-  const long long wgs = (chunks + 7) / 8 * 8 * CHU * NG;
-  if (wgs > 0x7fffffffLL) return LISA_ERR_UNSUPPORTED;
-  StageScope prof("k_lisa_prefill_fused", st);
-  kern<<<dim3((unsigned)wgs), NW * 64, lds, st>>>(a);
-  return check_launch();
-}
-
-template <int NG, int HPW, int NW, int ACT, int RS, int SHG = 0>
-int launch_prefill_fused_act(const lisa_desc* d, const PrefillArgs& a, hipStream_t st) {
-  if (RS > 1) {                                              // row slices: 33..96 hidden units (prefill_slices_ok)
-    if ((d->F + 31) / 32 == 2) return launch_prefill_fused_t<NG, 2, HPW, NW, ACT, RS, SHG>(d, a, st);
-    // (two slices, 65..80 hidden units: the last block of 16 is padding)
-    if (RS == 2 && d->F <= 80) return launch_prefill_fused_t<NG, 3, HPW, NW, ACT, RS, SHG, true>(d, a, st);
-    return launch_prefill_fused_t<NG, 3, HPW, NW, ACT, RS, SHG>(d, a, st);
-  }
-  switch ((d->F + 31) / 32) {
-    case 1: return launch_prefill_fused_t<NG, 1, HPW, NW, ACT, 1, SHG>(d, a, st);
-    case 2: return launch_prefill_fused_t<NG, 2, HPW, NW, ACT, 1, SHG>(d, a, st);
-    case 3: return launch_prefill_fused_t<NG, 3, HPW, NW, ACT, 1, SHG>(d, a, st);
-    default: return launch_prefill_fused_t<NG, 4, HPW, NW, ACT, 1, SHG>(d, a, st);
-  }
-}
-template <int NG, int HPW, int NW>
-int launch_prefill_fused_fs(const lisa_desc* d, const PrefillArgs& a, int slices, hipStream_t st) {
-  if (HPW == 1 && slices == 4) return launch_prefill_fused_act<NG, 1, NW, 0, 4>(d, a, st);
-  if (HPW == 1 && slices == 2) return launch_prefill_fused_act<NG, 1, NW, 0, 2>(d, a, st);
-  // the heads of a wave share their key/value head: one operand set for all of them
-  constexpr int HS = HPW == 3 ? 2 : HPW;                     // (no shared form of the 24-head kernel)
-  if (HPW > 1 && HPW != 3 && (d->H / d->Hkv) % HPW == 0)
-    return d->act == LISA_ACT_SILU ? launch_prefill_fused_act<NG, HS, NW, 1, 1, HS>(d, a, st)
-                                   : launch_prefill_fused_act<NG, HS, NW, 0, 1, HS>(d, a, st);
-  return d->act == LISA_ACT_SILU ? launch_prefill_fused_act<NG, HPW, NW, 1, 1>(d, a, st)
-                                 : launch_prefill_fused_act<NG, HPW, NW, 0, 1>(d, a, st);
 }
 
 int run_prefill_fused(const lisa_desc* d, const void* q_lr, const void* k_lr, const void* v,
