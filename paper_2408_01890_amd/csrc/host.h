@@ -41,6 +41,11 @@ struct StageScope {
 template <int NG, int HPW, int NW>
 int launch_prefill_fused_fs(const lisa_desc* d, const PrefillArgs& a, int slices, hipStream_t st);
 int launch_decode_part(const lisa_desc* d, bool lisa_layer, DecodeArgs a, hipStream_t st);
+// launch_stack.hip
+bool stack_chained_ok(const lisa_desc* d);
+size_t stack_chained_bytes(const lisa_desc* d);
+int run_stack_chained(const lisa_desc* d, const lisa_stack_layer* layers, int n_layers, void* const rows[2],
+                      void* workspace, hipStream_t st);
 int launch_scores_mfma_kernel(const lisa_desc* d, const ScoresMfmaArgs& a, hipStream_t st);
 
 }  // namespace lisa

@@ -1400,7 +1400,7 @@ StackWs stack_ws(const lisa_desc* d) {
   // (two of them, used in turn: the partial results of a layer wait there for the launch of the
   // next layer, which combines them)
   w.half = round_up(std::max(a, std::max(b, c)), 256);
-  w.total = w.layer + 2 * w.half;
+  w.total = w.layer + std::max(2 * w.half, stack_chained_ok(d) ? stack_chained_bytes(d) : 0);
   return w;
 }
 }  // namespace
@@ -1440,6 +1440,11 @@ int lisa_decode_stack(const lisa_desc* desc, const lisa_stack_layer* layers, int
   const size_t lws_bytes = w.half;
   const void* cur = nullptr;                                 // the row A_{n-1} that the next layer may share
   hipStream_t st = (hipStream_t)hip_stream;
+  if (stack_chained_ok(desc)) {                              // ADD-form stacks: by data flow, not layer by layer
+    rc = run_stack_chained(desc, layers, n_layers, own, ws + w.layer, st);
+    if (rc == LISA_OK) g_path = "decode_split";
+    return rc;
+  }
   g_dc = DeferredCombine{};
   g_dc.on = true;
   for (int n = 0; n < n_layers && rc == LISA_OK; ++n) {
