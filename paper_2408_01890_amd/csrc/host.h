@@ -46,6 +46,14 @@ bool stack_chained_ok(const lisa_desc* d);
 size_t stack_chained_bytes(const lisa_desc* d);
 int run_stack_chained(const lisa_desc* d, const lisa_stack_layer* layers, int n_layers, void* const rows[2],
                       void* workspace, hipStream_t st);
+// launch_f32.hip
+bool f32_attn_ok(const lisa_desc* d);
+int run_f32_std(const lisa_desc* d, const void* q, const void* k, const void* v, void* scores, void* out,
+                hipStream_t st);
+int run_f32_softmax_v(const lisa_desc* d, const void* scores, const void* v, void* out, hipStream_t st);
+bool f32_scores_ok(const lisa_desc* d);
+int run_f32_scores(const lisa_desc* d, const void* q_lr, const void* k_lr, const void* prev, const void* w1,
+                   const void* w2, void* scores, hipStream_t st);
 int launch_scores_mfma_kernel(const lisa_desc* d, const ScoresMfmaArgs& a, hipStream_t st);
 
 }  // namespace lisa

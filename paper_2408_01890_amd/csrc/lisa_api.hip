@@ -336,15 +336,22 @@ int run_lisa(const lisa_desc* d, const void* q_lr, const void* k_lr, KeyStrides 
     if (rc == LISA_OK) g_path = "mfma_scores";
     return rc;
   }
-  // Generic kernels: the softmax reads the unrounded float32 A_n from the workspace.
-  int rc = launch_lisa_scores<T, S>(d, q_lr, k_lr, ks, prev, w1, w2, scores, exact, st);
+  // Generic kernels: the softmax reads the unrounded float32 A_n, from the workspace where the score type
+  // is half; a float32 layer has it in the score tensor itself.
+  int rc;
+  if (d->dtype == LISA_F32 && scores) exact = nullptr;
+  const void* an = exact ? (void*)exact : scores;
+  if (f32_scores_ok(d)) rc = run_f32_scores(d, q_lr, k_lr, prev, w1, w2, const_cast<void*>(an), st);
+  else rc = launch_lisa_scores<T, S>(d, q_lr, k_lr, ks, prev, w1, w2, scores, exact, st);
   if (rc) return rc;
   // softmax and P V from the float32 scores: on the matrix cores where the standard layer's kernel
   // fits (it then reads the scores instead of computing Q K^T), else the generic kernel
   if (std_prefill_fast_ok(d))
     rc = run_softmax_given_fast(d, exact, false, v, out, (char*)exact + exact_bytes(d), st);
+  else if (f32_attn_ok(d))
+    rc = run_f32_softmax_v(d, an, v, out, st);
   else
-    rc = launch_softmax_v<T>(d, exact, v, vs, out, st);
+    rc = launch_softmax_v<T>(d, (const float*)an, v, vs, out, st);
   if (rc == LISA_OK) g_path = "generic";
   return rc;
 }
@@ -1517,9 +1524,12 @@ int std_attn_scores(const lisa_desc* desc, const void* q, const void* k, const v
     a.row_out = (half_t*)scores_out;
     return run_decode_fast(desc, false, a, out, workspace, st);
   }
-  if (desc->dtype == LISA_F32) {
+  if (f32_attn_ok(desc)) {
+    rc = run_f32_std(desc, q, k, v, scores_out, out, st);
+  } else if (desc->dtype == LISA_F32) {
+    if (scores_out) exact = nullptr;                         // (the score tensor is the unrounded copy)
     rc = launch_std_scores<float, float>(desc, q, k, ks, scores_out, exact, st);
-    if (rc == LISA_OK && out) rc = launch_softmax_v<float>(desc, exact, v, ks, out, st);
+    if (rc == LISA_OK && out) rc = launch_softmax_v<float>(desc, exact ? exact : (const float*)scores_out, v, ks, out, st);
   } else {
     rc = launch_std_scores<bf16_t, half_t>(desc, q, k, ks, scores_out, exact, st);
     if (rc == LISA_OK && out) rc = launch_softmax_v<bf16_t>(desc, exact, v, ks, out, st);
