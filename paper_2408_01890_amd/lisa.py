@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes as C
 import math
 import os
+import threading
 from typing import Optional
 
 import torch
@@ -158,6 +159,29 @@ def make_desc(dtype, B, H, Hkv, Lq, Lk, d_k, r=0, F=0, mix=MIX_ADD, act=ACT_RELU
                 write_scores, kcache_dim_major, Lmax, out_f32, score_tiled)
 
 
+# Descriptors and workspace sizes of the calls a thread makes, by what they are made from: a serving loop
+# makes the same few calls over and over, and building the two takes longer than a short kernel runs.
+# Per thread, because the geometry overrides of lisa_tune_set() (which change workspace sizes) are.
+_local = threading.local()
+_MAX_PLANS = 256
+
+
+def _plan(which, *key):
+    """(reference to the descriptor made by make_desc(*key), its workspace bytes for `which`)"""
+    try:
+        plans = _local.plans
+    except AttributeError:
+        plans = _local.plans = {}
+    key = (which,) + key
+    plan = plans.get(key)
+    if plan is None:
+        if len(plans) >= _MAX_PLANS:
+            plans.clear()
+        desc = make_desc(*key[1:])
+        plan = plans[key] = (C.byref(desc), workspace_bytes(desc, which) if which is not None else 0)
+    return plan
+
+
 TILE_ROWS, TILE_KEYS = 16, 32
 
 
@@ -200,7 +224,11 @@ def kcache_saved_bytes(desc: Desc, n_layers: int) -> int:
 
 
 def supported(desc: Desc) -> int:
-    return int(_lib().lisa_supported(C.byref(desc)))
+    return _supported(C.byref(desc))
+
+
+def _supported(desc_ref) -> int:
+    return int(_lib().lisa_supported(desc_ref))
 
 
 def last_path() -> str:
@@ -218,6 +246,7 @@ class tune:
         self.knobs = [(names[k], int(v)) for k, v in knobs.items()]
 
     def __enter__(self):
+        _local.plans = {}
         for k, v in self.knobs:
             rc = _lib().lisa_tune_set(k, v)
             if rc:
@@ -225,6 +254,7 @@ class tune:
         return self
 
     def __exit__(self, *exc):
+        _local.plans = {}
         for k, _ in self.knobs:
             _lib().lisa_tune_set(k, -1)
         return False
@@ -269,8 +299,11 @@ def profile_collect(max_stages: int = 32):
 
 
 def _ptr(t: Optional[torch.Tensor], name: str, shape=None, dtype=None):
+    """Address of a tensor the call takes (None stays None); raises ValueError if it is not what is expected."""
     if t is None:
         return None
+    if t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype == dtype) and (shape is None or t.shape == shape):
+        return t.data_ptr()
     if not t.is_cuda:
         raise ValueError(f"{name}: expected a GPU tensor (the library has no CPU path)")
     if not t.is_contiguous():
@@ -279,21 +312,21 @@ def _ptr(t: Optional[torch.Tensor], name: str, shape=None, dtype=None):
         raise ValueError(f"{name}: dtype {t.dtype}, expected {dtype}")
     if shape is not None and tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name}: shape {tuple(t.shape)}, expected {tuple(shape)}")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _workspace(nbytes: int, like: torch.Tensor, workspace: Optional[torch.Tensor]):
     if nbytes == 0:
-        return workspace, (C.c_void_p(workspace.data_ptr()) if workspace is not None else None), \
+        return workspace, (workspace.data_ptr() if workspace is not None else None), \
             (workspace.numel() * workspace.element_size() if workspace is not None else 0)
     if workspace is None:
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=like.device)
-    have = workspace.numel() * workspace.element_size()
-    return workspace, C.c_void_p(workspace.data_ptr()), have
+        return workspace, workspace.data_ptr(), nbytes
+    return workspace, workspace.data_ptr(), workspace.numel() * workspace.element_size()
 
 
 def _out_dtype(dt, out_dtype):
@@ -311,18 +344,17 @@ def std_attn_scores(q, k, v=None, *, want_scores=True, causal=True, std_scale=0.
     B, H, Lq, dk = q.shape
     _, Hkv, Lk, _ = k.shape
     odt, of32 = _out_dtype(q.dtype, out.dtype if out is not None else out_dtype)
-    desc = make_desc(q.dtype, B, H, Hkv, Lq, Lk, dk, causal=int(causal), std_scale=std_scale,
-                     out_f32=of32, score_tiled=int(tiled))
+    desc, need = _plan(WS_STD if v is not None or out is not None else None, q.dtype, B, H, Hkv, Lq, Lk, dk, 0, 0,
+                       MIX_ADD, ACT_RELU, 0.0, std_scale, int(causal), 0, 0, 0, of32, int(tiled))
     sdt = score_dtype(q.dtype)
     sshape = scores_shape(B, H, Lq, Lk, tiled)
     if want_scores and scores_out is None:
         scores_out = torch.empty(sshape, dtype=sdt, device=q.device)
     if v is not None and out is None:
         out = torch.empty((B, Lq, H, dk), dtype=odt, device=q.device)
-    need = workspace_bytes(desc, WS_STD) if out is not None else 0
     workspace, wp, wb = _workspace(need, q, workspace)
     rc = _lib().std_attn_scores(
-        C.byref(desc), _ptr(q, "q", dtype=q.dtype), _ptr(k, "k", (B, Hkv, Lk, dk), q.dtype),
+        desc, _ptr(q, "q", dtype=q.dtype), _ptr(k, "k", (B, Hkv, Lk, dk), q.dtype),
         _ptr(v, "v", (B, Hkv, Lk, dk), q.dtype), _ptr(scores_out, "scores_out", sshape, sdt),
         _ptr(out, "out", (B, Lq, H, dk), odt), wp, wb, _stream())
     if rc:
@@ -337,16 +369,15 @@ def std_attn_decode(q, k_cache, v_cache, Lk, *, want_scores=True, std_scale=0.0,
     B, H, dk = q.shape
     _, Hkv, Lmax, _ = k_cache.shape
     odt, of32 = _out_dtype(q.dtype, out.dtype if out is not None else out_dtype)
-    desc = make_desc(q.dtype, B, H, Hkv, 1, Lk, dk, std_scale=std_scale, Lmax=Lmax, out_f32=of32)
+    desc, need = _plan(WS_STD, q.dtype, B, H, Hkv, 1, Lk, dk, 0, 0, MIX_ADD, ACT_RELU, 0.0, std_scale, 1, 0, 0, Lmax, of32)
     sdt = score_dtype(q.dtype)
     if want_scores and score_row_out is None:
         score_row_out = torch.empty((B, H, Lk), dtype=sdt, device=q.device)
     if out is None:
         out = torch.empty((B, H, dk), dtype=odt, device=q.device)
-    need = workspace_bytes(desc, WS_STD)
     workspace, wp, wb = _workspace(need, q, workspace)
     rc = _lib().std_attn_scores(
-        C.byref(desc), _ptr(q, "q", dtype=q.dtype), _ptr(k_cache, "k_cache", dtype=q.dtype),
+        desc, _ptr(q, "q", dtype=q.dtype), _ptr(k_cache, "k_cache", dtype=q.dtype),
         _ptr(v_cache, "v_cache", (B, Hkv, Lmax, dk), q.dtype),
         _ptr(score_row_out, "score_row_out", (B, H, Lk), sdt), _ptr(out, "out", (B, H, dk), odt),
         wp, wb, _stream())
@@ -378,21 +409,19 @@ def lisa_attn_prefill(q_lr, k_lr, v, scores_prev, w1, w2, *, mix=MIX_ADD, act=AC
     dt = v.dtype
     sdt = score_dtype(dt)
     odt, of32 = _out_dtype(dt, out.dtype if out is not None else out_dtype)
-    desc = make_desc(dt, B, H, Hkv, Lq, Lk, dk, r, F, mix=mix, act=act, delta_scale=delta_scale,
-                     causal=int(causal), write_scores=int(write_scores), out_f32=of32,
-                     score_tiled=int(tiled))
+    desc, need = _plan(WS_PREFILL, dt, B, H, Hkv, Lq, Lk, dk, r, F, mix, act, delta_scale, 0.0, int(causal),
+                       int(write_scores), 0, 0, of32, int(tiled))
     if has_ffn and Din != (2 * H if mix == MIX_CONCAT else H):
         raise ValueError(f"w1 has {Din} rows, expected {2 * H if mix == MIX_CONCAT else H}")
     if out is None:
         out = torch.empty((B, Lq, H, dk), dtype=odt, device=v.device)
     if write_scores and scores_out is None:
         scores_out = torch.empty(sshape, dtype=sdt, device=v.device)
-    need = workspace_bytes(desc, WS_PREFILL)
-    if need == 0 and supported(desc) != 0:
-        raise LisaError(supported(desc), "lisa_attn_prefill")
+    if need == 0 and _supported(desc) != 0:
+        raise LisaError(_supported(desc), "lisa_attn_prefill")
     workspace, wp, wb = _workspace(need, v, workspace)
     rc = _lib().lisa_attn_prefill(
-        C.byref(desc), _ptr(q_lr, "q_lr", (B, H, Lq, r), dt), _ptr(k_lr, "k_lr", (B, Hkv, Lk, r), dt),
+        desc, _ptr(q_lr, "q_lr", (B, H, Lq, r), dt), _ptr(k_lr, "k_lr", (B, Hkv, Lk, r), dt),
         _ptr(v, "v", (B, Hkv, Lk, dk), dt), _ptr(scores_prev, "scores_prev", sshape, sdt),
         _ptr(w1 if has_ffn else None, "w1", (Din, F), dt),
         _ptr(w2 if has_ffn and act != ACT_SINGLE else None, "w2", (F, H), dt),
@@ -414,13 +443,12 @@ def lisa_kd_huber(scores, teacher, *, Lq=None, Lk=None, delta=1.0, weight=1.0, a
     else:
         B, H, Lq, Lk = scores.shape
     dt = torch.float32 if scores.dtype == torch.float32 else torch.bfloat16
-    desc = make_desc(dt, B, H, H, Lq, Lk, 1, causal=int(causal), score_tiled=int(tiled))
+    desc, need = _plan(WS_KD, dt, B, H, H, Lq, Lk, 1, 0, 0, MIX_ADD, ACT_RELU, 0.0, 0.0, int(causal), 0, 0, 0, 0, int(tiled))
     sshape = scores_shape(B, H, Lq, Lk, tiled)
     if out is None:
-        out = torch.zeros(2, dtype=torch.float64, device=scores.device)
-    need = workspace_bytes(desc, WS_KD)
+        out = (torch.zeros if accumulate else torch.empty)(2, dtype=torch.float64, device=scores.device)
     workspace, wp, wb = _workspace(need, scores, workspace)
-    rc = _lib().lisa_kd_huber(C.byref(desc), _ptr(scores, "scores", sshape, scores.dtype),
+    rc = _lib().lisa_kd_huber(desc, _ptr(scores, "scores", sshape, scores.dtype),
                               _ptr(teacher, "teacher", sshape, scores.dtype), float(delta), float(weight),
                               int(bool(accumulate)), _ptr(out, "out", (2,), torch.float64), wp, wb, _stream())
     if rc:
@@ -487,19 +515,18 @@ def lisa_layer_prefill(x, w_qkv, Hkv, r, d_k, scores_prev, w1, w2, *, rope_theta
     dt = x.dtype
     sdt = score_dtype(dt)
     odt, of32 = _out_dtype(dt, out.dtype if out is not None else out_dtype)
-    desc = make_desc(dt, B, H, Hkv, L, L, d_k, r, F, mix=mix, causal=int(causal),
-                     write_scores=int(write_scores), out_f32=of32, score_tiled=int(tiled))
+    desc, need = _plan(WS_LAYER, dt, B, H, Hkv, L, L, d_k, r, F, mix, ACT_RELU, 0.0, 0.0, int(causal), int(write_scores),
+                       0, 0, of32, int(tiled))
     sshape = scores_shape(B, H, L, L, tiled)
     if out is None:
         out = torch.empty((B, L, H, d_k), dtype=odt, device=x.device)
     if write_scores and scores_out is None:
         scores_out = torch.empty(sshape, dtype=sdt, device=x.device)
-    need = workspace_bytes(desc, WS_LAYER)
     if need == 0:
-        raise LisaError(supported(desc) or -2, "lisa_layer_prefill")
+        raise LisaError(_supported(desc) or -2, "lisa_layer_prefill")
     workspace, wp, wb = _workspace(need, x, workspace)
     rc = _lib().lisa_layer_prefill(
-        C.byref(desc), D, float(rope_theta or 0.0), _ptr(x, "x", dtype=dt),
+        desc, D, float(rope_theta or 0.0), _ptr(x, "x", dtype=dt),
         _ptr(w_qkv, "w_qkv", ((H + Hkv) * r + Hkv * d_k, D), dt),
         _ptr(scores_prev, "scores_prev", sshape, sdt), _ptr(w1, "w1", dtype=dt),
         _ptr(w2, "w2", (F, H), dt), _ptr(out, "out", (B, L, H, d_k), odt),
@@ -507,7 +534,7 @@ def lisa_layer_prefill(x, w_qkv, Hkv, r, d_k, scores_prev, w1, w2, *, rope_theta
     if rc:
         raise LisaError(rc, "lisa_layer_prefill")
     offs = [C.c_size_t() for _ in range(3)]
-    _lib().lisa_layer_offsets(C.byref(desc), *[C.byref(o) for o in offs])
+    _lib().lisa_layer_offsets(desc, *[C.byref(o) for o in offs])
     es = x.element_size()
 
     def view(off, shape):
@@ -539,19 +566,18 @@ def lisa_layer_decode(x, w_qkv, k_lr_cache, v_cache, Lk, score_row_prev, w1, w2,
     dt = x.dtype
     sdt = score_dtype(dt)
     odt, of32 = _out_dtype(dt, out.dtype if out is not None else out_dtype)
-    desc = make_desc(dt, B, H, Hkv, 1, Lk, dk, r, F, mix=mix, act=act, write_scores=int(write_scores),
-                     kcache_dim_major=int(dim_major), Lmax=Lmax, out_f32=of32)
+    desc, need = _plan(WS_LAYER_DECODE, dt, B, H, Hkv, 1, Lk, dk, r, F, mix, act, 0.0, 0.0, 1, int(write_scores),
+                       int(dim_major), Lmax, of32)
     kshape = (B, Hkv, r, Lmax) if dim_major else (B, Hkv, Lmax, r)
     if out is None:
         out = torch.empty((B, H, dk), dtype=odt, device=x.device)
     if write_scores and score_row_out is None:
         score_row_out = torch.empty((B, H, Lk), dtype=sdt, device=x.device)
-    need = workspace_bytes(desc, WS_LAYER_DECODE)
     if need == 0:
-        raise LisaError(supported(desc) or -2, "lisa_layer_decode")
+        raise LisaError(_supported(desc) or -2, "lisa_layer_decode")
     workspace, wp, wb = _workspace(need, x, workspace)
     rc = _lib().lisa_layer_decode(
-        C.byref(desc), D, float(rope_theta or 0.0), _ptr(x, "x", dtype=dt),
+        desc, D, float(rope_theta or 0.0), _ptr(x, "x", dtype=dt),
         _ptr(w_qkv, "w_qkv", ((H + Hkv) * r + Hkv * dk, D), dt), _ptr(k_lr_cache, "k_lr_cache", kshape, dt),
         _ptr(v_cache, "v_cache", dtype=dt), _ptr(score_row_prev, "score_row_prev", (B, H, Lk), sdt),
         _ptr(w1, "w1", (Din, F), dt), _ptr(w2, "w2", (F, H), dt), _ptr(out, "out", (B, H, dk), odt),
@@ -582,15 +608,14 @@ def lisa_attn_decode(q_lr, k_lr_cache, v_cache, Lk, score_row_prev, w1, w2, *, k
     dt = v_cache.dtype
     sdt = score_dtype(dt)
     odt, of32 = _out_dtype(dt, out.dtype if out is not None else out_dtype)
-    desc = make_desc(dt, B, H, Hkv, 1, Lk, dk, r, F, mix=mix, act=act, delta_scale=delta_scale,
-                     write_scores=int(write_scores), kcache_dim_major=int(dim_major), Lmax=Lmax,
-                     out_f32=of32)
+    desc, need = _plan(WS_DECODE, dt, B, H, Hkv, 1, Lk, dk, r, F, mix, act, delta_scale, 0.0, 1, int(write_scores),
+                       int(dim_major), Lmax, of32)
     kshape = (B, Hkv, r, Lmax) if dim_major else (B, Hkv, Lmax, r)
     if out is None:
         out = torch.empty((B, H, dk), dtype=odt, device=v_cache.device)
     if write_scores and score_row_out is None:
         score_row_out = torch.empty((B, H, Lk), dtype=sdt, device=v_cache.device)
-    args = [C.byref(desc), _ptr(q_lr, "q_lr", dtype=dt), _ptr(k_lr_new, "k_lr_new", (B, Hkv, r), dt),
+    args = [desc, _ptr(q_lr, "q_lr", dtype=dt), _ptr(k_lr_new, "k_lr_new", (B, Hkv, r), dt),
             _ptr(v_new, "v_new", (B, Hkv, dk), dt), _ptr(k_lr_cache, "k_lr_cache", kshape, dt),
             _ptr(v_cache, "v_cache", dtype=dt), _ptr(score_row_prev, "score_row_prev", (B, H, Lk), sdt),
             _ptr(w1, "w1", (Din, F), dt), _ptr(w2, "w2", (F, H), dt), _ptr(out, "out", (B, H, dk), odt),
@@ -598,7 +623,6 @@ def lisa_attn_decode(q_lr, k_lr_cache, v_cache, Lk, score_row_prev, w1, w2, *, k
     if static_scratch:
         rc = _lib().lisa_attn_decode_static(*args, _stream())
     else:
-        need = workspace_bytes(desc, WS_DECODE)
         workspace, wp, wb = _workspace(need, v_cache, workspace)
         rc = _lib().lisa_attn_decode(*args, wp, wb, _stream())
     if rc:
@@ -661,8 +685,8 @@ class DecodeStack:
         self.ws = torch.empty(need, dtype=torch.uint8, device=v0.device)
 
     def step(self):
-        rc = _lib().lisa_decode_stack(C.byref(self.desc), self.arr, len(self.arr), C.c_void_p(self.ws.data_ptr()),
-                                      self.ws.numel(), _stream())
+        rc = _lib().lisa_decode_stack(C.byref(self.desc), self.arr, len(self.arr), self.ws.data_ptr(), self.ws.numel(),
+                                      _stream())
         if rc:
             raise LisaError(rc, "lisa_decode_stack")
         return self.outs
