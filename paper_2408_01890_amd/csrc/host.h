@@ -44,6 +44,11 @@ int launch_decode_part(const lisa_desc* d, bool lisa_layer, DecodeArgs a, hipStr
 // launch_stack.hip
 bool stack_chained_ok(const lisa_desc* d);
 size_t stack_chained_bytes(const lisa_desc* d);
+bool decode_spread_ok(const lisa_desc* d);
+size_t decode_spread_bytes(const lisa_desc* d);
+FfnOperands decode_spread_operands(const lisa_desc* d, const bf16_t* w1, const bf16_t* w2, void* workspace);
+int run_decode_spread(const lisa_desc* d, bool lisa_layer, const DecodeArgs& da, void* out, void* workspace,
+                      hipStream_t st);
 int run_stack_chained(const lisa_desc* d, const lisa_stack_layer* layers, int n_layers, void* const rows[2],
                       void* workspace, hipStream_t st);
 // launch_f32.hip

@@ -45,6 +45,7 @@ struct DecodeArgs {
   const float* cmb_ml;
   void* cmb_out;
   int cmb_units, cmb_H, cmb_nchunk, cmb_out_f32;
+  int w_ready;           // the FFN weights are in the workspace already (run_decode_spread)
 };
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));

@@ -22,7 +22,7 @@
 // chunk c ^ ((m / 2) % 8), which makes both the tile writes and the operand reads free of
 // bank conflicts without padding.
 #pragma once
-#include "lisa_types.h"
+#include "mfma_ffn.h"
 
 namespace lisa {
 
@@ -36,6 +36,9 @@ struct ProjectArgs {
   int rope;          // 1: rotate Q_LR / K_LR
   double freq_log2;  // inverse frequency of pair t = 2^(t * freq_log2), freq_log2 = -2 log2(theta) / r
   int n_m, n_n, own_n;
+  // Workgroups from n_blocks on (few-row kernels) put an FFN's weights in operand order for the launch behind
+  int n_blocks;
+  FfnOperands ffn;
 };
 
 // cos and sin of pos * inv_freq.  The angle (up to ~1e5 rad) is formed and reduced to
@@ -536,7 +539,7 @@ __device__ __forceinline__ void project_skinny_finish(const ProjectArgs a, const
 #pragma unroll
     for (int v = 0; v < 16; ++v) red[((wv * MB + mb) * 16 + v) * 64 + lane] = acc[mb][v];
   __syncthreads();
-  // the 16 MB registers (row block mb, register v) of the result are dealt to the 8 waves
+  // the 16 MB registers (row block mb, register v) of the result are dealt to the waves
   constexpr int PER = 2 * MB;
   float y[PER];
 #pragma unroll
@@ -643,9 +646,15 @@ __global__ __launch_bounds__(512) void k_project_skinny(ProjectArgs a) {
 // are in flight meanwhile.  No barrier in the loop: the region is private to the wave, and LDS
 // operations of a wave execute in order.  Requires D % 512 == 0 (8 waves x whole chunks), MB <= 2
 // (LDS: 8 waves x (1 + MB) x 4.5 KB).
+// (One row block, 4096 wide, LLaMA3-8B heads: 8.5 us.  Sixteen waves with half the axis each: 9.2; four chunks
+// in flight per wave: 10.7.)
 constexpr int PJS_ROW = 128 + 16;                           // bytes per staged row (64 elements + pad)
 template <int MB>
 __global__ __launch_bounds__(512) void k_project_skinny_lds(ProjectArgs a) {
+  if ((int)blockIdx.x >= a.n_blocks) {                      // (the tail of the grid: see ProjectArgs)
+    ffn_operand_piece<false>(a.ffn, ((int)blockIdx.x - a.n_blocks) * 512 + (int)threadIdx.x);
+    return;
+  }
   extern __shared__ __align__(16) unsigned char pj_lds[];
   float* red = (float*)pj_lds;                              // after the loop: [8 waves][MB][16][64]
   const int tid = threadIdx.x, lane = tid & 63;

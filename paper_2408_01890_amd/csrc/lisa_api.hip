@@ -375,6 +375,7 @@ bool decode_fast_ok(const lisa_desc* d, bool lisa_layer) {
 int decode_chunks(const lisa_desc* d) { return (d->Lk + DEC_CK - 1) / DEC_CK; }
 
 size_t decode_fast_bytes(const lisa_desc* d) {
+  if (decode_spread_ok(d)) return decode_spread_bytes(d);
   const size_t units = (size_t)d->B * decode_chunks(d) * d->H;
   return round_up(units * d->d_k * sizeof(float), 256) + round_up(units * 2 * sizeof(float), 256);
 }
@@ -414,6 +415,11 @@ int flush_deferred_combine(hipStream_t st) {
 
 int run_decode_fast(const lisa_desc* d, bool lisa_layer, DecodeArgs a, void* out, void* workspace,
                     hipStream_t st) {
+  if (decode_spread_ok(d)) {
+    const int rc = run_decode_spread(d, lisa_layer, a, out, workspace, st);
+    if (rc == LISA_OK) g_path = "decode_split";
+    return rc;
+  }
   const size_t units = (size_t)d->B * decode_chunks(d) * d->H;
   a.part_o = (float*)workspace;
   a.part_ml = (float*)((char*)workspace + round_up(units * d->d_k * sizeof(float), 256));
@@ -767,8 +773,10 @@ int lisa_cache_fill(const lisa_desc* d, const void* k_lr, const void* v, void* k
   return rc;
 }
 
-int lisa_project_qkv(const lisa_proj_desc* d, const void* x, const void* w, void* q_lr, void* k_lr, void* v,
-                     void* hip_stream) {
+// `ffn`: an FFN whose weights the launch puts in operand order on the side, where it is one of the few-row
+// kernels (then *ffn_done is set).
+static int project_qkv(const lisa_proj_desc* d, const void* x, const void* w, void* q_lr, void* k_lr, void* v,
+                       const FfnOperands* ffn, int* ffn_done, void* hip_stream) {
   if (!d || !x || !w || !q_lr || !k_lr || !v) return LISA_ERR_NULL;
   if (d->dtype != LISA_F32 && d->dtype != LISA_BF16) return LISA_ERR_UNSUPPORTED;
   if (d->B < 1 || d->L < 1 || d->d_model < 1 || d->H < 1 || d->Hkv < 1 || d->r < 1 || d->d_k < 1 ||
@@ -804,11 +812,18 @@ int lisa_project_qkv(const lisa_proj_desc* d, const void* x, const void* w, void
     // chunks per wave and the staging regions fit
     const bool staged = d->d_model % 512 == 0 && mb <= 2;
     const int lds = std::max(8 * mb * 16 * 64 * (int)sizeof(float), staged ? 8 * (1 + mb) * 32 * PJS_ROW : 0);
+    a.n_blocks = (int)((n_virtual + 31) / 32);
+    int extra = 0;
+    if (staged && ffn) {
+      a.ffn = *ffn;
+      extra = (ffn->pieces() + 511) / 512;
+      *ffn_done = 1;
+    }
     StageScope scope("k_project_skinny", st);
     auto launch = [&](auto kern) -> int {
       hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
       if (e != hipSuccess) return hip_fail(e);
-      kern<<<dim3((unsigned)((n_virtual + 31) / 32)), 512, lds, st>>>(a);
+      kern<<<dim3((unsigned)(a.n_blocks + extra)), 512, lds, st>>>(a);
       return LISA_OK;
     };
     int lrc = staged ? (mb == 1 ? launch(k_project_skinny_lds<1>) : launch(k_project_skinny_lds<2>))
@@ -867,6 +882,11 @@ int lisa_project_qkv(const lisa_proj_desc* d, const void* x, const void* w, void
   int rc = check_launch();
   if (rc == LISA_OK) g_path = path;
   return rc;
+}
+
+int lisa_project_qkv(const lisa_proj_desc* d, const void* x, const void* w, void* q_lr, void* k_lr, void* v,
+                     void* hip_stream) {
+  return project_qkv(d, x, w, q_lr, k_lr, v, nullptr, nullptr, hip_stream);
 }
 
 size_t lisa_score_elem_bytes(const lisa_desc* desc) {
@@ -1057,6 +1077,14 @@ size_t lisa_workspace_bytes(const lisa_desc* desc, int which) {
   }
 }
 
+static int check_decode_args(const lisa_desc* desc, const void* q_lr, const void* k_lr_new, const void* v_new,
+                             void* k_lr_cache, void* v_cache, const void* score_row_prev, const void* w1,
+                             const void* w2, void* out, void* score_row_out);
+static int run_attn_decode(const lisa_desc* desc, const void* q_lr, const void* k_lr_new, const void* v_new,
+                           void* k_lr_cache, void* v_cache, const void* score_row_prev, const void* w1,
+                           const void* w2, void* out, void* score_row_out, void* workspace, hipStream_t st,
+                           int w_ready = 0);
+
 int lisa_layer_decode(const lisa_desc* desc, int32_t d_model, float rope_theta, const void* x,
                       const void* w_qkv, void* k_lr_cache, void* v_cache, const void* score_row_prev,
                       const void* w1, const void* w2, void* out, void* score_row_out, void* workspace,
@@ -1083,10 +1111,17 @@ int lisa_layer_decode(const lisa_desc* desc, int32_t d_model, float rope_theta, 
   pd.kcache_dim_major = desc->kcache_dim_major;
   pd.rope_theta = rope_theta;
   char* ws = (char*)workspace;
-  rc = lisa_project_qkv(&pd, x, w_qkv, ws + qo, k_lr_cache, v_cache, hip_stream);
+  rc = check_decode_args(desc, ws + qo, nullptr, nullptr, k_lr_cache, v_cache, score_row_prev, w1, w2, out, score_row_out);
   if (rc) return rc;
-  return lisa_attn_decode(desc, ws + qo, nullptr, nullptr, k_lr_cache, v_cache, score_row_prev, w1, w2, out,
-                          score_row_out, workspace, qo, hip_stream);
+  // the step's FFN weights are put in order by the projection's launch, where the step wants them that way
+  FfnOperands ffn{};
+  int ffn_done = 0;
+  const bool spread = decode_fast_ok(desc, true) && decode_spread_ok(desc);
+  if (spread) ffn = decode_spread_operands(desc, (const bf16_t*)w1, (const bf16_t*)w2, workspace);
+  rc = project_qkv(&pd, x, w_qkv, ws + qo, k_lr_cache, v_cache, spread ? &ffn : nullptr, &ffn_done, hip_stream);
+  if (rc) return rc;
+  return run_attn_decode(desc, ws + qo, nullptr, nullptr, k_lr_cache, v_cache, score_row_prev, w1, w2, out,
+                         score_row_out, workspace, (hipStream_t)hip_stream, ffn_done);
 }
 
 int lisa_layer_offsets(const lisa_desc* desc, size_t* q_lr_off, size_t* k_lr_off, size_t* v_off) {
@@ -1292,7 +1327,8 @@ static int check_decode_args(const lisa_desc* desc, const void* q_lr, const void
 // lisa_workspace_bytes(desc, LISA_WS_DECODE) bytes.
 static int run_attn_decode(const lisa_desc* desc, const void* q_lr, const void* k_lr_new, const void* v_new,
                            void* k_lr_cache, void* v_cache, const void* score_row_prev, const void* w1,
-                           const void* w2, void* out, void* score_row_out, void* workspace, hipStream_t st) {
+                           const void* w2, void* out, void* score_row_out, void* workspace, hipStream_t st,
+                           int w_ready) {
   int rc;
   void* scores = desc->write_scores ? score_row_out : nullptr;
   float* exact = (float*)workspace;
@@ -1335,6 +1371,7 @@ static int run_attn_decode(const lisa_desc* desc, const void* q_lr, const void* 
     a.w1 = (const bf16_t*)w1;
     a.w2 = (const bf16_t*)w2;
     a.row_out = (half_t*)scores;
+    a.w_ready = w_ready;
     return run_decode_fast(eff, true, a, out, workspace, st);
   }
   if (desc->dtype == LISA_F32)

@@ -46,15 +46,31 @@ __device__ __host__ __forceinline__ int n_visible(int i, int Lq, int Lk, int cau
   return n < 0 ? 0 : (n > Lk ? Lk : n);
 }
 
+// Reductions over a wave, the result in every lane: rotations inside the rows of 16 lanes (DPP), then the row
+// swaps of gfx950.  All on the vector ALU: a reduction through the LDS crossbar (shuffles) waits for it six
+// times, and short kernels spend most of their softmax there.
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float v) {
+  return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xF, 0xF, true));
+}
+template <class Op>
+__device__ __forceinline__ float wave_reduce(float v, Op op) {
+  v = op(v, dpp_move<0x128>(v));                             // row_ror:8, 4, 2, 1
+  v = op(v, dpp_move<0x124>(v));
+  v = op(v, dpp_move<0x122>(v));
+  v = op(v, dpp_move<0x121>(v));
+  const unsigned u = __float_as_uint(v);
+  auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  v = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  const unsigned w = __float_as_uint(v);
+  auto q = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return op(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+  return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); });
 }
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  return wave_reduce(v, [](float a, float b) { return a + b; });
 }
 
 }  // namespace lisa

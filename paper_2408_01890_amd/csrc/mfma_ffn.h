@@ -38,6 +38,39 @@ __device__ __forceinline__ unsigned short half_bits(float f) {
   return __builtin_bit_cast(unsigned short, h);
 }
 
+// The weights of a network in operand order, made once per call by whichever launch comes first instead of by
+// every workgroup: piece idx = (operand, lane), 8 halves each; operands W1 (hidden block fb, k-step ks), then W2
+// (output block hb, k-step s).  Same image as MfmaFfn::stage().
+struct FfnOperands {
+  const bf16_t* w1;     // [Din, F]
+  const bf16_t* w2;     // [F, HO]
+  unsigned short* out;
+  int Din, F, HO, KS, FS, HBO;
+  __host__ __device__ int pieces() const { return (2 * FS * KS + HBO * FS) * 64; }
+};
+// CHAIN: the rows of W1 are numbered like the hidden units of W2 (slot (k-step, g, e) = index
+// 16 (2 kstep + e / 4) + 4 g + e % 4): the input is then what a product before this one left in the lanes.
+template <bool CHAIN>
+__device__ __forceinline__ void ffn_operand_piece(const FfnOperands& w, int idx) {
+  if (idx >= w.pieces()) return;
+  const int o = idx >> 6, c = idx & 15, g = idx >> 4 & 3, N1 = 2 * w.FS * w.KS;
+  u16x8 x;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int slot = 4 * g + (e & 3) + 16 * (e >> 2);
+    float v = 0.f;
+    if (o < N1) {
+      const int f = 16 * (o / w.KS) + c, ch = 32 * (o % w.KS) + (CHAIN ? slot : 8 * g + e);
+      if (f < w.F && ch < w.Din) v = elem<bf16_t>::load(w.w1 + (size_t)ch * w.F + f);
+    } else {
+      const int h = 16 * ((o - N1) / w.FS) + c, f = 32 * ((o - N1) % w.FS) + slot;
+      if (f < w.F && h < w.HO) v = elem<bf16_t>::load(w.w2 + (size_t)f * w.HO + h);
+    }
+    x[e] = half_bits(v);
+  }
+  *(u16x8*)(w.out + (size_t)idx * 8) = x;
+}
+
 // HB = ceil(H / 16) input head blocks (KS = ceil(H / 32) k-steps of the first product),
 // FS = ceil(F / 32) hidden k-steps (2 FS hidden blocks of 16), HBO = blocks of 16 output heads
 // (the caller may ask for a sub-range of the H output heads: h_first .. h_first + n_out - 1).

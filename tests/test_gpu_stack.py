@@ -1,12 +1,16 @@
-"""Decode stacks by data flow: the sizes where the split can go wrong.  Every layer of every sequence
+"""Decode steps by data flow, stacks and single layers: the sizes where the split can go wrong.  Every layer of every sequence
 against the oracle, and kept score rows against rows that stay inside the workspace, bit for bit."""
 import pytest
+import torch
 
+from oracle import cref
+from paper_2408_01890_amd import lisa, synth
 from paper_2408_01890_amd import patterns as pt
-from paper_2408_01890_amd import synth
-from tests.test_gpu_parity import log, run_pattern_stack
+from tests import helpers as hp
+from tests.test_gpu_parity import log, oracle_decode_lisa, run_pattern_stack
 
 pytestmark = pytest.mark.gpu
+DEV = "cuda"
 
 MIXED = (pt.STD, pt.LISA, pt.SHARE, pt.LISA, pt.STD, pt.SHARE, pt.SHARE, pt.LISA, pt.LISA, pt.LISA, pt.LISA, pt.STD)
 # more layers than one group takes (48): the row passes from group to group, to a LiSA layer and, through
@@ -34,3 +38,33 @@ def test_decode_stack_sizes(case):
     # (the identity-like FFN of the shared inputs needs F >= 2H)
     stk = synth.DecodeStack(f"stack_h{H}_ctx{ctx}", "bf16", B, H, Hkv, ctx, 256, dk, r, max(F, 2 * H), len(kinds), 1)
     run_pattern_stack(stk, kinds, list(range(B)), dim_major=dim_major, Lmax=Lmax)
+
+
+SINGLE = [  # H, Hkv, ctx, d_k, r, F, B, concat: one workgroup's keys and one more; many spans; both forms of the V stream
+    (8, 8, 511, 128, 22, 16, 1, False), (8, 2, 512, 128, 22, 16, 2, False), (16, 4, 1030, 64, 20, 64, 1, True),
+    (8, 4, 5000, 128, 11, 40, 1, False), (32, 32, 600, 128, 20, 256, 8, True), (40, 40, 513, 128, 22, 80, 7, False)]
+
+
+@pytest.mark.parametrize("case", SINGLE, ids=lambda c: f"h{c[0]}_{c[1]}_ctx{c[2]}_dk{c[3]}_b{c[6]}")
+def test_single_layer_decode_spans(case):
+    H, Hkv, ctx, dk, r, F, B, concat = case
+    log(f"[case] single decode {case}")
+    Lk, tol = ctx + 1, hp.TOL[torch.bfloat16]
+    stk = synth.DecodeStack("single", "bf16", B, H, Hkv, ctx, 256, dk, r, F, 2, 1)
+    std = synth.make_decode_layer(stk, 0, device=DEV)
+    row, out = lisa.std_attn_decode(std["q"], std["k_cache"], std["v_cache"], Lk)
+    ly = synth.make_decode_layer(stk, 1, device=DEV, mix="concat" if concat else "add", ffn="fan_in")
+    o2, row2 = lisa.lisa_attn_decode(ly["q_lr"], ly["k_lr_cache"], ly["v_cache"], Lk, row, ly["w1"], ly["w2"],
+                                     mix=lisa.MIX_CONCAT if concat else lisa.MIX_ADD)
+    o3, row3 = lisa.lisa_attn_decode(None, None, ly["v_cache"], Lk, row, None, None, mix=lisa.MIX_SHARE)
+    torch.cuda.synchronize()
+    assert torch.equal(row3, row)
+    for b in range(0, B, 3):
+        ref = hp.oracle_std_rows(std["q"][:, :, None, :], std["k_cache"][:, :, :Lk], b, [0])
+        assert hp.row_rel_err(hp.f64(row[b])[None], ref) <= tol
+        o_ref = cref.softmax_v_rows(hp.f64(std["v_cache"][b])[:, :Lk], [0], ref, 1)
+        assert hp.row_rel_err(hp.f64(out[b])[None], o_ref) <= tol
+        a_ref, o_ref = oracle_decode_lisa(ly, b, Lk, hp.f64(row[b]), True, mix=int(concat))
+        assert hp.row_rel_err(hp.f64(row2[b])[None], a_ref) <= tol and hp.row_rel_err(hp.f64(o2[b])[None], o_ref) <= tol
+        o_ref = cref.softmax_v_rows(hp.f64(ly["v_cache"][b])[:, :Lk], [0], hp.f64(row[b])[None], 1)
+        assert hp.row_rel_err(hp.f64(o3[b])[None], o_ref) <= tol
