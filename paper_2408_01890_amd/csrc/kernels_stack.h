@@ -15,6 +15,7 @@
 // stack has that many times the number of layers.  Single layers with fewer units than that run on the
 // same kernels, the chain's place taken by k_decode_scores.
 #pragma once
+#include <cfloat>
 #include <type_traits>
 
 #include "kernels_decode.h"
@@ -509,7 +510,7 @@ __global__ __launch_bounds__(1024 / NB, NB == 1 ? 4 : GQ == 1 ? 4 : 3) void k_st
 #pragma unroll
     for (int q = 0; q < GQ; ++q) {
       half_t* rp = a.row[l] ? a.row[l] + ((size_t)b * d.H + h0 + q) * d.Lk + j0 : nullptr;
-      float mx = -INFINITY;
+      float mx = -FLT_MAX;                                   // (finite: a piece masked with -inf throughout weighs nothing)
 #pragma unroll
       for (int i = 0; i < PER; ++i) {
         const bool in = lane + 64 * i < n_here;
@@ -588,7 +589,7 @@ __global__ __launch_bounds__(1024 / NB, NB == 1 ? 4 : GQ == 1 ? 4 : 3) void k_st
       }
     }
   } else {                                                   // a piece without keys weighs nothing
-    if (lane < GQ) m_s[wv][lane] = -INFINITY, l_s[wv][lane] = 0.f;
+    if (lane < GQ) m_s[wv][lane] = -FLT_MAX, l_s[wv][lane] = 0.f;
     for (int e = lane; e < GQ * DK; e += 64) (&o_s[wv][0][0])[e] = 0.f;
   }
   __syncthreads();
@@ -645,7 +646,7 @@ __global__ __launch_bounds__(1024 / NB, NB == 1 ? 4 : GQ == 1 ? 4 : 3) void k_st
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
     const int e = min((int)threadIdx.x + THREADS * i, GQ * DK - 1), q = e / DK, f = e % DK;
-    float Mx = -INFINITY, nm = 0.f, dn = 0.f;
+    float Mx = -FLT_MAX, nm = 0.f, dn = 0.f;
     // eight spans at a time: their loads are in flight together
     for (int s0 = 0; s0 < d.n_span; s0 += 8) {
       float po[8], pm[8], pl[8];
@@ -659,7 +660,7 @@ __global__ __launch_bounds__(1024 / NB, NB == 1 ? 4 : GQ == 1 ? 4 : 3) void k_st
       float m8 = Mx;
 #pragma unroll
       for (int u = 0; u < 8; ++u) m8 = fmaxf(m8, pm[u]);
-      const float c0 = __expf(Mx - m8);                      // (0 the first time)
+      const float c0 = __expf(Mx - m8);
       nm *= c0;
       dn *= c0;
 #pragma unroll

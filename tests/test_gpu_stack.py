@@ -68,3 +68,25 @@ def test_single_layer_decode_spans(case):
         assert hp.row_rel_err(hp.f64(row2[b])[None], a_ref) <= tol and hp.row_rel_err(hp.f64(o2[b])[None], o_ref) <= tol
         o_ref = cref.softmax_v_rows(hp.f64(ly["v_cache"][b])[:, :Lk], [0], hp.f64(row[b])[None], 1)
         assert hp.row_rel_err(hp.f64(o3[b])[None], o_ref) <= tol
+
+
+@pytest.mark.parametrize("H,Hkv,dk,Lk,B,masked", [
+    (8, 8, 128, 128, 1, (0, 40)),       # all of a wave's first 32 keys
+    (8, 2, 64, 1500, 2, (0, 1100)),     # a whole workgroup's keys, merged with the next one's
+    (8, 8, 128, 700, 1, (512, 700)),    # the last workgroup's
+    (32, 32, 128, 2100, 4, (100, 400)),  # the long stream: 128 keys per wave
+])
+def test_masked_keys_weigh_nothing(H, Hkv, dk, Lk, B, masked):
+    """Keys whose shared score is -inf (padding in front of a prompt) over whole pieces of the split."""
+    log(f"[case] masked keys {H} {Hkv} {dk} {Lk} {B} {masked}")
+    g = torch.Generator().manual_seed(5)
+    row = torch.randn((B, H, Lk), generator=g).half()
+    row[..., masked[0]:masked[1]] = float("-inf")
+    v = torch.randn((B, Hkv, Lk, dk), generator=g).to(torch.bfloat16)
+    out, _ = lisa.lisa_attn_decode(None, None, v.to(DEV), Lk, row.to(DEV), None, None, mix=lisa.MIX_SHARE)
+    vh = v.double().repeat_interleave(H // Hkv, dim=1)
+    ref = (torch.softmax(row.double(), -1)[..., None] * vh).sum(2)
+    # float32 sums of exact products; the result leaves as the output type of the call
+    tol = 1e-5 if out.dtype == torch.float32 else hp.TOL[torch.bfloat16]
+    err = (out.double().cpu() - ref).norm(dim=-1) / ref.norm(dim=-1)
+    assert torch.isfinite(out).all() and float(err.max()) <= tol
