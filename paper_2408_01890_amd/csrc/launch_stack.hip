@@ -18,6 +18,8 @@ int pv_batches(const lisa_desc* d, int layers) {
   return (long long)layers * d->B * (d->H / pv_heads(d)) * pv_spans(d) >= kComputeUnits ? 4 : 1;
 }
 
+constexpr size_t kStackGroupBytes = (size_t)128 << 20;
+
 struct GroupWs {
   size_t s, part_o, part_ml, done, w, total;   // byte offsets
   int layers, w_elems, n_span, Lp;
@@ -34,7 +36,7 @@ GroupWs group_ws(const lisa_desc* d) {
   const size_t o1 = units * d->d_k * sizeof(float), ml1 = units * 2 * sizeof(float), w1 = (size_t)g.w_elems * 2;
   // Layers per group: the whole stack while its scratch stays small, else as many as 128 MB hold, so
   // that what one launch leaves for the next stays in the last-level cache; four at least.
-  g.layers = (int)std::min<size_t>(STK_MAXL, std::max<size_t>(4, ((size_t)128 << 20) / (s1 + o1 + ml1 + w1)));
+  g.layers = (int)std::min<size_t>(STK_MAXL, std::max<size_t>(4, kStackGroupBytes / (s1 + o1 + ml1 + w1)));
   g.s = 0;
   g.part_o = round_up(g.s + g.layers * s1, 256);
   g.part_ml = round_up(g.part_o + g.layers * o1, 256);
@@ -203,7 +205,14 @@ bool stack_chained_ok(const lisa_desc* d) {
   return blocks < (1LL << 31);
 }
 
-size_t stack_chained_bytes(const lisa_desc* d) { return group_ws(d).total; }
+// Fewer layers per group at a longer context may take less than more of them at a shorter one: from there on
+// at least what any group of more than four layers takes, so that a workspace for the longest
+// context fits the shorter ones.
+size_t stack_chained_bytes(const lisa_desc* d) {
+  const GroupWs g = group_ws(d);
+  if (g.layers == STK_MAXL) return g.total;
+  return std::max(g.total, kStackGroupBytes + (size_t)STK_MAXL * d->B * d->H * sizeof(unsigned) + 5 * 256);
+}
 
 // rows: two half rows [B,H,Lk], used in turn where a row passes from one group of layers to the next
 int run_stack_chained(const lisa_desc* d, const lisa_stack_layer* layers, int n_layers, void* const rows[2],
@@ -317,7 +326,7 @@ int run_stack_chained(const lisa_desc* d, const lisa_stack_layer* layers, int n_
 // stages the module's weights in every workgroup; this path needs none of that but passes A_n through
 // memory as float32, 8 bytes per head and key against 600 read.  The line is drawn where that scratch no
 // longer fits the buffer of lisa_attn_decode_static (about 900 units of 32 heads).
-bool decode_spread_ok(const lisa_desc* d) { return single_ws(d).total <= (size_t)LISA_STATIC_SCRATCH_BYTES; }
+bool decode_spread_ok(const lisa_desc* d) { return single_ws(d).total <= kDecodeSpreadMaxBytes; }
 size_t decode_spread_bytes(const lisa_desc* d) { return single_ws(d).total; }
 
 // Where the module's weights go in operand order; a launch in front of the step may write them

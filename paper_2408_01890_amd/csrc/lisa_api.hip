@@ -377,7 +377,10 @@ int decode_chunks(const lisa_desc* d) { return (d->Lk + DEC_CK - 1) / DEC_CK; }
 size_t decode_fast_bytes(const lisa_desc* d) {
   if (decode_spread_ok(d)) return decode_spread_bytes(d);
   const size_t units = (size_t)d->B * decode_chunks(d) * d->H;
-  return round_up(units * d->d_k * sizeof(float), 256) + round_up(units * 2 * sizeof(float), 256);
+  // no less than the spread form takes at most: a workspace that fits the longest context, the largest
+  // batch fits every smaller one
+  return std::max(round_up(units * d->d_k * sizeof(float), 256) + round_up(units * 2 * sizeof(float), 256),
+                  kDecodeSpreadMaxBytes);
 }
 
 // A decode stack leaves the combine of a layer to the launch of the layer behind it (its workgroups

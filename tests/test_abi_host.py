@@ -112,6 +112,25 @@ def test_static_scratch_decode_rejects_what_does_not_fit_before_any_launch():
     assert lib.lisa_attn_decode_static(C.byref(fits), *a, None) == -4
 
 
+@pytest.mark.parametrize("mix,act,F", [(lisa.MIX_ADD, lisa.ACT_RELU, 64), (lisa.MIX_CONCAT, lisa.ACT_RELU, 256),
+                                       (lisa.MIX_ADD, lisa.ACT_SINGLE, 32), (lisa.MIX_SHARE, lisa.ACT_RELU, 0)])
+@pytest.mark.parametrize("B", [1, 7, 32])
+def test_decode_workspace_of_the_longest_context_fits_the_shorter_ones(mix, act, F, B):
+    """A program sizes its workspace once; the kernels (and what they need) change with the context."""
+    H, need = 32, {}
+    for Lk in list(range(64, 9000, 61)):
+        r = 0 if mix == lisa.MIX_SHARE else 22
+        d = lisa.make_desc(lisa.BF16, B, H, H, 1, Lk, 128, r, F, mix=mix, act=act, write_scores=1, kcache_dim_major=1, Lmax=9088)
+        sizes = [lisa.workspace_bytes(d, w) for w in (lisa.WS_DECODE, lisa.WS_STD, lisa.WS_LAYER_DECODE)]
+        if mix != lisa.MIX_SHARE:
+            sizes.append(lisa.stack_workspace_bytes(d))
+        for i, n in enumerate(sizes):
+            assert n >= need.get(i, 0), (i, Lk)
+            need[i] = n
+        if B * ((Lk + 127) // 128) * H <= 32000:                            # the documented limit of the static buffer
+            assert sizes[0] <= (16 << 20), Lk
+
+
 def test_tune_set_accepts_known_knobs_only():
     lib = lisa.library()
     assert lib.lisa_tune_set(lisa.TUNE_PREFILL_SPLIT, 2) == 0
