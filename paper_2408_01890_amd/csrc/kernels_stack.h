@@ -10,7 +10,8 @@
 //   k_stack_chain    A_n = FFN(A_{n-1}) + a_delta along the layers, a wave per 16 key positions and
 //                    run of layers, A_{n-1} carried in registers from layer to layer;
 //   k_stack_pv       softmax and P V of all layers at once, split over the keys: the V stream, which is
-//                    most of the bytes.  The last of the workgroups that share an output merges them.
+//                    most of the bytes.  The last of the workgroups that share an output merges them, or
+//                    (long streams) k_stack_combine.
 // A layer by itself fills the chip only with hundreds of (sequence, 128 keys) units (k_decode_part); a
 // stack has that many times the number of layers.  Single layers with fewer units than that run on the
 // same kernels, the chain's place taken by k_decode_scores.

@@ -86,7 +86,7 @@ int launch_pv(const lisa_desc* d, StackPvArgs& a, int n_layers, hipStream_t st) 
   return nb == 4 ? launch_pv_nb<64, 4>(a, gq, grid, st) : launch_pv_nb<64, 1>(a, gq, grid, st);
 }
 
-// For launches of k_stack_pv without counters (nothing in front of them that could have cleared them).
+// For launches of k_stack_pv without counters (see the rule in run_stack_chained).
 int launch_stack_combine(const lisa_desc* d, const StackCombineArgs& a, int n_layers, hipStream_t st) {
   dim3 grid(d->H, d->B, n_layers);
   StageScope prof("k_stack_combine", st);
@@ -309,8 +309,12 @@ int run_stack_chained(const lisa_desc* d, const lisa_stack_layer* layers, int n_
       if ((rc = check_launch())) return rc;
     }
     if (n_chain && (rc = launch_chain(ca, d->act, st))) return rc;
-    // (a group of direct-sharing layers alone has no launch in front that clears the counters)
-    const bool merge = sa.n_std + sa.n_lisa == 0 && gw.n_span > 1;
+    // Who merges the splits: the last workgroup of an output where there are few (no launch more), a launch of
+    // its own behind the long stream, where every workgroup that waits for its stores and the counter
+    // keeps the next one's loads out: 16 users at 4096 tokens, 32 layers, 4732 us with the counters, 4394 without
+    // (one user at 1023: 83 with them, a launch more otherwise).  A group of direct-sharing layers alone
+    // has no launch in front that clears the counters.
+    const bool merge = gw.n_span > 1 && (sa.n_std + sa.n_lisa == 0 || pv_batches(d, n1 - n0) == 4);
     if (merge) pa.d.done = nullptr;
     if ((rc = launch_pv(d, pa, n1 - n0, st))) return rc;
     if (merge && (rc = launch_stack_combine(d, ma, n1 - n0, st))) return rc;
