@@ -290,6 +290,8 @@ __device__ __forceinline__ void store_row_part(void* p, pf_u32x4 v, int n) {
 // long and a short one, so that all workgroups carry the same number of tiles and stage the FFN
 // weights once.
 // Requires Lk >= 8 (row-major scores).
+// RAGGED: row-major scores with Lk % 8 != 0.  (A form of its own: the address clamp and the test per tile cost the
+// other one 0.3 - 0.8 %, LLaMA3-8B shape, 4 x 8192: 5739 us with them where 5692 had been.)
 // SHG > 0: every SHG consecutive heads of a wave share one key/value head (grouped KV heads, H / Hkv
 // a multiple of SHG, HPW a multiple of SHG): one set of K_LR / V operands per tile serves all of
 // them, and every such set is refilled behind its last head with the next tile's operands.  With
@@ -298,7 +300,7 @@ __device__ __forceinline__ void store_row_part(void* p, pf_u32x4 v, int n) {
 // key/value head for four query heads.
 // FTRIM: F <= 32 FS - 16, the last 16 hidden units are padding and their products are left out
 // (the 40 -> 80 -> 40 network of the LLaMA2-13B shape: 10 instead of 12 MFMAs of the first layer).
-template <int NG, int FS, int HPW, int NW, int ACT = 0, int RS = 1, int SHG = 0, bool FTRIM = false>
+template <int NG, int FS, int HPW, int NW, int ACT = 0, int RS = 1, int SHG = 0, bool FTRIM = false, bool RAGGED = false>
 __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
   static_assert(RS == 1 || HPW == 1, "row slices: one head per wave");
   // XSTG: the A_{n-1} piece is double buffered by tile parity and the buffers double as the staging
@@ -467,7 +469,7 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
     auto x_row_at = [&](int tile, int rs) {
       return (unsigned)min(i0 + PF_ROWS * rs + (lane >> 2), Lq - 1) * Lk + min(tile * PF_TK + xq8, (Lk - 1) & ~7);
     };
-    const bool ragged_end = !a.tiled && (Lk & 7) != 0 && i0 + R >= Lq;
+    const bool ragged_end = RAGGED && i0 + R >= Lq;
     auto load_x = [&](int tile, int rs, pf_u32x4 (&xr)[XCH]) {
       unsigned off;
       size_t at = 0;                                          // wave-uniform element offset of the tile
@@ -475,7 +477,7 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
         at = ((size_t)min((i0 >> 4) + rs, n_rb - 1) * n_kt + tile) * tile_stride;
         off = lane * 16;
       } else {
-        off = 2 * row_chunk_at(x_row_at(tile, rs), (unsigned)Lq * Lk);
+        off = 2 * (RAGGED ? row_chunk_at(x_row_at(tile, rs), (unsigned)Lq * Lk) : x_row_at(tile, rs));
       }
 #pragma unroll
       for (int u = 0; u < XCH; ++u) xr[u] = ld_uv_stream<pf_u32x4_a2>(x_base[u] + at, off);
