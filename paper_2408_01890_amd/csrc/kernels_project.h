@@ -133,7 +133,9 @@ constexpr int PJ_ROWB = PJ_TK * 2;              // bytes per LDS row
 // Tile geometry: WM x WN waves (8 in all), each BM x BN blocks of 32 x 32 outputs.
 //   <2,4,4,2>  256 x 256 outputs per workgroup, the densest in MFMA work per fetched byte;
 //   <4,2,2,3>  256 x 192, for problems whose 256-wide tiles would leave a quarter of the CUs
-//              idle or add a nearly empty last round of workgroups.
+//              idle or add a nearly empty last round of workgroups;
+//   <4,2,1,1>  128 x 64, where the others would leave half of the CUs idle: bound by the latency of a
+//              step's loads (0.6 us of 64 steps at d = 4096), four MFMAs a wave and step.
 template <int WM, int WN, int BM, int BN>
 struct ProjTile {
   static_assert(WM * WN == 8, "8 waves");
@@ -306,23 +308,23 @@ __global__ __launch_bounds__(512) void k_project_mfma(ProjectArgs a) {
     read_frags(buf, 0, 0);
     load_part(kt + 1, nb, 0);
     mfmas(1);
-    PJ_INTERLEAVE(0x020, BM * BN);
+    if constexpr (BM * BN >= 6) PJ_INTERLEAVE(0x020, BM * BN);
     __builtin_amdgcn_sched_barrier(0);
     // sub-step 0 | operands of sub-step 1, second half of the loads
     read_frags(buf, 1, 1);
     load_part(kt + 1, nb, 1);
     mfmas(0);
-    PJ_INTERLEAVE(0x020, BM * BN);
+    if constexpr (BM * BN >= 6) PJ_INTERLEAVE(0x020, BM * BN);
     __builtin_amdgcn_sched_barrier(0);
     // sub-step 1 | operands of sub-step 2
     read_frags(buf, 2, 0);
     mfmas(1);
-    PJ_INTERLEAVE(0x020, BM * BN);
+    if constexpr (BM * BN >= 6) PJ_INTERLEAVE(0x020, BM * BN);
     __builtin_amdgcn_sched_barrier(0);
     // sub-step 2 | operands of sub-step 3
     read_frags(buf, 3, 1);
     mfmas(0);
-    PJ_INTERLEAVE(0x020, BM * BN);
+    if constexpr (BM * BN >= 6) PJ_INTERLEAVE(0x020, BM * BN);
     __builtin_amdgcn_sched_barrier(0);
   }
   {                                                        // the last step: nothing left to load

@@ -844,20 +844,32 @@ static int project_qkv(const lisa_proj_desc* d, const void* x, const void* w, vo
     };
     // (the narrower tile does less MFMA work per fetched byte: it must win by a margin)
     int tn = rounds_cost(192) * 8 < rounds_cost(256) * 7 ? 192 : 256;
+    // Tiles that would leave half of the CUs or more without one: 128 x 64.  A step of the reduction takes
+    // about as long for a small tile as for a large one (its loads' latency), so more of them side by side
+    // win: LLaMA3-8B, 777 tokens, 48 tiles, 83 -> 39 us; LLaMA2-7B, 1024, 128 tiles, 87 -> 65; on the other side of
+    // the line LLaMA2-7B at 1500 tokens, 192 tiles, 86 us, where 256 CUs are nearly full.
+    bool small = ((M + 255) / 256) * ((n_virtual + tn - 1) / tn) <= kComputeUnits / 2;
     {                                                       // tests force either geometry
       const int v = g_tune[LISA_TUNE_PROJECT_TN];
-      if (v == 192 || v == 256) tn = v;
+      if (v == 192 || v == 256) tn = v, small = false;
     }
-    a.n_m = (int)((M + 255) / 256);
+    if (small) tn = 64;
+    a.n_m = (int)(small ? (M + 127) / 128 : (M + 255) / 256);
     a.n_n = (int)((n_virtual + tn - 1) / tn);
     // which axis of the tile grid an XCD keeps to: the one that is balanced over 8 XCDs and
     // re-reads fewer operand bytes
     const bool n_ok = a.n_n % 8 == 0 || a.n_n >= 40, m_ok = a.n_m % 8 == 0 || a.n_m >= 40;
     const double xb = (double)M * d->d_model, wb = (double)n_real * d->d_model;
-    a.own_n = n_ok && (!m_ok || wb / 8 + xb <= xb / 8 + wb);
+    // (small tiles: an XCD's share of the weights, 2 - 5 MB, stays in its L2)
+    a.own_n = small || (n_ok && (!m_ok || wb / 8 + xb <= xb / 8 + wb));
     const int per_xcd = a.own_n ? (a.n_n + 7) / 8 * a.n_m : (a.n_m + 7) / 8 * a.n_n;
     StageScope scope("k_project_mfma", st);
-    if (tn == 256) {
+    if (small) {
+      auto kern = k_project_mfma<4, 2, 1, 1>;
+      constexpr int lds = ProjTile<4, 2, 1, 1>::LDS;
+      static_assert(lds <= 64 * 1024, "no attribute needed");
+      kern<<<dim3(8 * per_xcd), 512, lds, st>>>(a);
+    } else if (tn == 256) {
       auto kern = k_project_mfma<2, 4, 4, 2>;
       constexpr int lds = ProjTile<2, 4, 4, 2>::LDS;
       hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
