@@ -111,12 +111,14 @@ __global__ __launch_bounds__(256) void k_f32_attn(F32AttnArgs a) {
       for (int v = 0; v < 4; ++v)
         if (j + v >= vis) s[v] = -INFINITY;
       const float m_new = rows_max(max2_raw(max2_raw(s[0], s[1]), max2_raw(s[2], s[3])), m_run);
-      const float m2 = (m_new == -INFINITY ? 0.f : m_new) * LOG2E;   // (no key seen yet: every p is 0)
-      const float alpha = fast_exp2(m_run * LOG2E - m2);
+      // (the maximum is subtracted before the change of base: m log2(e) on its own is rounded to the ulp of
+      // the maximum, differently in each wave, and at scores around 200 that is 3e-5 of the result)
+      const float m0 = m_new == -INFINITY ? 0.f : m_new;     // (no key seen yet: every p is 0)
+      const float alpha = fast_exp2((m_run - m0) * LOG2E);
       m_run = m_new;
       f32x4 p;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) p[v] = fast_exp2(__builtin_fmaf(s[v], LOG2E, -m2));
+      for (int v = 0; v < 4; ++v) p[v] = fast_exp2((s[v] - m0) * LOG2E);
       l_run = l_run * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
 #pragma unroll
       for (int i = 0; i < NP; ++i) o[i] *= alpha;

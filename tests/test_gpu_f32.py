@@ -51,3 +51,31 @@ def test_f32_layers(case):
                                       hp.f64(inp["w2"]), rows, hp.gather_score_rows(a0, b, rows))
         assert hp.scores_row_rel_err(hp.gather_score_rows(a1, b, rows), a_ref, rows, Lq, Lk) <= TOL
         assert hp.row_rel_err(hp.gather_out_rows(o1, b, rows), o_ref) <= TOL
+
+
+def _rows_err(out, scores, v, Lq):
+    """Worst row of `out` against the float64 softmax of the float32 scores that the layer took or emitted."""
+    worst, rows = 0.0, np.arange(Lq)
+    for b in range(out.shape[0]):
+        ref = cref.softmax_v_rows(hp.f64(v[b]), rows, hp.gather_score_rows(scores, b, rows), Lq)
+        worst = max(worst, hp.row_rel_err(hp.gather_out_rows(out, b, rows), ref))
+    return worst
+
+
+@pytest.mark.parametrize("dk", [64, 128])
+@pytest.mark.parametrize("shift", [0.0, 50.0, -200.0, 200.0, 1000.0])
+def test_f32_softmax_far_from_zero(shift, dk):
+    """The softmax depends on the differences of the scores alone, so the distance of all of them from zero costs
+    nothing: s - m is exact to its own float32 rounding (2^-24 of a difference of 8 or less)."""
+    log(f"[case] f32 softmax around {shift} dk{dk}")
+    B, H, Hkv, Lq, Lk = 1, 8, 4, 70, 301
+    g = torch.Generator(device=DEV).manual_seed(17)
+    prev = torch.randn((B, H, Lq, Lk), generator=g, device=DEV) + shift
+    q = torch.randn((B, H, Lq, dk), generator=g, device=DEV)
+    k, v = (torch.randn((B, Hkv, Lk, dk), generator=g, device=DEV) for _ in range(2))
+    q[..., 0], k[..., 0] = abs(shift) ** 0.5, shift / max(abs(shift), 1.0) ** 0.5 * dk ** 0.5
+    out, _ = lisa.lisa_attn_prefill(None, None, v, prev, None, None, mix=lisa.MIX_SHARE)
+    scores, o_std = lisa.std_attn_scores(q, k, v, scores_out=torch.zeros_like(prev))
+    torch.cuda.synchronize()
+    assert _rows_err(out, prev, v, Lq) <= TOL
+    assert _rows_err(o_std, scores, v, Lq) <= TOL
