@@ -150,6 +150,7 @@ __global__ __launch_bounds__(256) void k_f32_attn(F32AttnArgs a) {
     float M = m_s[0][r];
 #pragma unroll
     for (int w = 1; w < 4; ++w) M = fmaxf(M, m_s[w][r]);
+    if (M == -INFINITY) M = 0.f;                             // (every score of the row -inf: num = den = 0)
     float num = 0.f, den = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
@@ -157,7 +158,8 @@ __global__ __launch_bounds__(256) void k_f32_attn(F32AttnArgs a) {
       num += f * o_s[w][r][d];
       den += f * l_s[w][r];
     }
-    a.out[(((size_t)b * Lq + i0 + r) * a.H + h) * DK + d] = num / den;
+    // (a row that sees nothing gives zeros, as the generic kernel has it; NaN stays NaN)
+    a.out[(((size_t)b * Lq + i0 + r) * a.H + h) * DK + d] = den > 0.f ? num / den : num * 0.f;
   }
 }
 
