@@ -21,6 +21,10 @@ constexpr int kComputeUnits = 256;   // MI355X
 inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline float pick_scale(float given, int n) { return given > 0.f ? given : 1.0f / std::sqrt((float)n); }
 
+// Prefill scores that the bf16 and half matrix-core kernels can read and write: 8 at a time, at 16-byte boundaries
+// (whole tiles always are).
+inline bool score_rows_aligned(const lisa_desc* d) { return d->score_tiled ? d->Lk >= 8 : d->Lk % 8 == 0; }
+
 int hip_fail(hipError_t e);          // remembers the error's text for lisa_last_hip_error()
 int check_launch();
 
@@ -58,10 +62,13 @@ int run_stack_chained(const lisa_desc* d, const lisa_stack_layer* layers, int n_
 bool f32_attn_ok(const lisa_desc* d);
 int run_f32_std(const lisa_desc* d, const void* q, const void* k, const void* v, void* scores, void* out,
                 hipStream_t st);
-int run_f32_softmax_v(const lisa_desc* d, const void* scores, const void* v, void* out, hipStream_t st);
+int run_f32_softmax_v(const lisa_desc* d, const void* scores, int row0, int n_rows, const void* v, void* out,
+                      hipStream_t st);
+int f32_chunk_rows(const lisa_desc* d);
+size_t f32_chunk_bytes(const lisa_desc* d);
 bool f32_scores_ok(const lisa_desc* d);
 int run_f32_scores(const lisa_desc* d, const void* q_lr, const void* k_lr, const void* prev, const void* w1,
-                   const void* w2, void* scores, hipStream_t st);
+                   const void* w2, void* scores, float* exact, int row0, int n_rows, hipStream_t st);
 int launch_scores_mfma_kernel(const lisa_desc* d, const ScoresMfmaArgs& a, hipStream_t st);
 
 }  // namespace lisa

@@ -1,34 +1,79 @@
-// float32 prefill layers (Lq > 1): attention on the float32 matrix instructions, and the scores of an
-// ADD-form LiSA layer.  Same arithmetic as the generic kernels (float32
-// products and sums); they cover any other shape.
+// Prefill layers (Lq > 1) in float32 arithmetic on the matrix cores: attention, and the scores of a LiSA layer.
+// Same arithmetic as the generic kernels (float32 products and sums); they cover any other shape.
+// T is the type of the operands (float, or bf16, whose values and products float32 holds exactly), S the
+// score type.  bf16 layers come here where their score rows keep them off the bf16 and half matrix
+// instructions (row-major rows that are no multiple of 8 scores): probabilities, hidden units, A_delta
+// and A_n stay float32 there, which the 16-bit operands of those kernels would cut to 9 - 11 bits.
 #pragma once
+#include <type_traits>
 #include "kernels_prefill.h"
 
 namespace lisa {
 
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned f32_u32x2 __attribute__((ext_vector_type(2)));
+typedef f16x4 f16x4_a2 __attribute__((aligned(2)));
 
+// Four consecutive elements as they are loaded (8 or 16 bytes, aligned), and as numbers.
+template <typename T> struct Quad;
+template <> struct Quad<float> {
+  f32x4 raw;
+  static __device__ __forceinline__ Quad load(const float* p) { return {*(const f32x4*)p}; }
+  __device__ __forceinline__ float operator[](int e) const { return raw[e]; }
+};
+template <> struct Quad<bf16_t> {
+  f32_u32x2 raw;
+  static __device__ __forceinline__ Quad load(const bf16_t* p) { return {*(const f32_u32x2*)p}; }
+  __device__ __forceinline__ float operator[](int e) const {
+    return __uint_as_float(e & 1 ? raw[e >> 1] & 0xffff0000u : raw[e >> 1] << 16);
+  }
+};
+// Two elements, neighbours at an even offset or from anywhere.
+template <typename T> struct Pair;
+template <> struct Pair<float> {
+  float x, y;
+  static __device__ __forceinline__ Pair load(const float* p) {
+    const float2 v = *(const float2*)p;
+    return {v.x, v.y};
+  }
+  static __device__ __forceinline__ Pair load2(const float* p, const float* q) { return {*p, *q}; }
+  __device__ __forceinline__ float operator[](int e) const { return e ? y : x; }
+};
+template <> struct Pair<bf16_t> {
+  unsigned raw;
+  static __device__ __forceinline__ Pair load(const bf16_t* p) { return {*(const unsigned*)p}; }
+  static __device__ __forceinline__ Pair load2(const bf16_t* p, const bf16_t* q) { return {p->bits | (unsigned)q->bits << 16}; }
+  __device__ __forceinline__ float operator[](int e) const { return __uint_as_float(e ? raw & 0xffff0000u : raw << 16); }
+};
+// Four consecutive scores of a row, which starts at any element.
+__device__ __forceinline__ void store_scores4(float* p, f32x4 s) { *(f32x4_a4*)p = s; }
+__device__ __forceinline__ void store_scores4(half_t* p, f32x4 s) {
+  *(f16x4_a2*)p = f16x4{f32_to_half_sat(s[0]), f32_to_half_sat(s[1]), f32_to_half_sat(s[2]), f32_to_half_sat(s[3])};
+}
+
+template <typename T, typename S>
 struct F32AttnArgs {
-  const float* q;         // [B,H,Lq,DK]
-  const float* k;         // [B,Hkv,Lk,DK]
-  const float* v;         // [B,Hkv,Lk,DK] or null (scores only)
-  const float* given;     // GIVEN: scores [B,H,Lq,Lk] to take instead of Q K^T (then q, k unused)
-  float* scores;          // [B,H,Lq,Lk] or null
-  float* out;             // [B,Lq,H,DK] or null
-  int H, Hkv, Lq, Lk, causal;
+  const T* q;             // [B,H,Lq,DK]
+  const T* k;             // [B,Hkv,Lk,DK]
+  const T* v;             // [B,Hkv,Lk,DK] or null (scores only)
+  const float* given;     // GIVEN: scores [B,H,n_rows,Lk] to take instead of Q K^T (then q, k unused)
+  S* scores;              // [B,H,Lq,Lk] or null
+  void* out;              // [B,Lq,H,DK] (float where out_f32, else T) or null
+  int H, Hkv, Lq, Lk, causal, out_f32;
+  int row0, n_rows;       // query rows of this launch (row0 a multiple of 16)
   float scale;
 };
 
-// grid (ceil(Lq / 16), H, B), block 256: 16 query rows of one head, the 16-key tiles dealt to the four
+// grid (ceil(n_rows / 16), H, B), block 256: 16 query rows of one head, the 16-key tiles dealt to the four
 // waves, their softmax states merged through the LDS at the end.  16x16x4 float32 MFMAs with the
 // query row on lane % 16 for both products, so that a lane's four scores are its B operands of the
 // second one.  Short sequences are a matter of latency: a wave holds the operands of its next tile while
 // it works on this one, and nothing passes through the LDS before the end.
-// The contraction over the features is numbered so that a lane's operands are 16-byte pieces: step s of
+// The contraction over the features is numbered so that a lane's operands are pieces of four: step s of
 // piece i takes feature 16 i + 4 g + s.  For P V the 16 rows of output block i are the features 4 m + i.
-template <int NDK, bool GIVEN>
-__global__ __launch_bounds__(256) void k_f32_attn(F32AttnArgs a) {
-  constexpr int DK = 64 * NDK, NP = DK / 16;                 // 16-byte pieces of a row per lane group
+template <typename T, typename S, int NDK, bool GIVEN>
+__global__ __launch_bounds__(256) void k_f32_attn(F32AttnArgs<T, S> a) {
+  constexpr int DK = 64 * NDK, NP = DK / 16;                 // pieces of four of a row per lane group
   __shared__ float o_s[4][16][DK + 4];
   __shared__ float m_s[4][16], l_s[4][16];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -36,43 +81,45 @@ __global__ __launch_bounds__(256) void k_f32_attn(F32AttnArgs a) {
   const int c = lane & 15, g = lane >> 4;
   const int rb = gridDim.x - 1 - blockIdx.x;                 // long row blocks first
   const int h = blockIdx.y, b = blockIdx.z;
-  const int Lq = a.Lq, Lk = a.Lk, i0 = rb * 16;
+  const int Lq = a.Lq, Lk = a.Lk, i0 = a.row0 + rb * 16;
   const int kv = h / (a.H / a.Hkv);
   const int i_last = min(i0 + 15, Lq - 1), row = min(i0 + c, Lq - 1);
   const int n_keys = n_visible(i_last, Lq, Lk, a.causal), n_tiles = (n_keys + 15) / 16;
   const int vis = i0 + c < Lq ? n_visible(row, Lq, Lk, a.causal) : 0;
   const float LOG2E = 1.4426950408889634f;
   const bool with_v = a.out != nullptr;
-  f32x4 qr[NP];
+  Quad<T> qr[NP];
   if (!GIVEN) {
-    const float* qp = a.q + (((size_t)b * a.H + h) * Lq + row) * DK + 4 * g;
+    const T* qp = a.q + (((size_t)b * a.H + h) * Lq + row) * DK + 4 * g;
 #pragma unroll
-    for (int i = 0; i < NP; ++i) qr[i] = *(const f32x4*)(qp + 16 * i);
+    for (int i = 0; i < NP; ++i) qr[i] = Quad<T>::load(qp + 16 * i);
   }
-  const float* kb = GIVEN ? nullptr : a.k + ((size_t)b * a.Hkv + kv) * Lk * DK + 4 * g;
-  const float* vb = a.v + ((size_t)b * a.Hkv + kv) * Lk * DK + 4 * c;
+  const T* kb = GIVEN ? nullptr : a.k + ((size_t)b * a.Hkv + kv) * Lk * DK + 4 * g;
+  const T* vb = a.v + ((size_t)b * a.Hkv + kv) * Lk * DK + 4 * c;
   const size_t srow = (((size_t)b * a.H + h) * Lq + row) * Lk;
-  f32x4 kr[NP], sr, vr[4][NDK];
+  const size_t grow = (((size_t)b * a.H + h) * a.n_rows + row - a.row0) * Lk;
+  Quad<T> kr[NP], vr[4][NDK];
+  f32x4 sr;
   auto load_k = [&](int tile) {
     if (GIVEN) {
       const int j = tile * 16 + 4 * g;
       if (tile * 16 + 16 <= Lk) {
-        sr = *(const f32x4_a4*)(a.given + srow + j);
+        sr = *(const f32x4_a4*)(a.given + grow + j);
       } else {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) sr[v] = a.given[srow + min(j + v, Lk - 1)];
+        for (int v = 0; v < 4; ++v) sr[v] = a.given[grow + min(j + v, Lk - 1)];
       }
     } else {
-      const float* kp = kb + (size_t)min(tile * 16 + c, Lk - 1) * DK;
+      const T* kp = kb + (size_t)min(tile * 16 + c, Lk - 1) * DK;
 #pragma unroll
-      for (int i = 0; i < NP; ++i) kr[i] = *(const f32x4*)(kp + 16 * i);
+      for (int i = 0; i < NP; ++i) kr[i] = Quad<T>::load(kp + 16 * i);
     }
   };
   auto load_v = [&](int tile) {
 #pragma unroll
     for (int v = 0; v < 4; ++v)
 #pragma unroll
-      for (int n = 0; n < NDK; ++n) vr[v][n] = *(const f32x4*)(vb + (size_t)min(tile * 16 + 4 * g + v, Lk - 1) * DK + 64 * n);
+      for (int n = 0; n < NDK; ++n) vr[v][n] = Quad<T>::load(vb + (size_t)min(tile * 16 + 4 * g + v, Lk - 1) * DK + 64 * n);
   };
   f32x4 o[NP];
 #pragma unroll
@@ -99,11 +146,11 @@ __global__ __launch_bounds__(256) void k_f32_attn(F32AttnArgs a) {
     load_k(tile_n);
     if (!GIVEN && a.scores) {
       if (j + 4 <= vis) {
-        *(f32x4_a4*)(a.scores + srow + j) = s;
+        store_scores4(a.scores + srow + j, s);
       } else {
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-          if (j + v < vis) a.scores[srow + j + v] = s[v];
+          if (j + v < vis) elem<S>::store(a.scores + srow + j + v, s[v]);
       }
     }
     if (with_v) {
@@ -159,37 +206,47 @@ __global__ __launch_bounds__(256) void k_f32_attn(F32AttnArgs a) {
       den += f * l_s[w][r];
     }
     // (a row that sees nothing gives zeros, as the generic kernel has it; NaN stays NaN)
-    a.out[(((size_t)b * Lq + i0 + r) * a.H + h) * DK + d] = den > 0.f ? num / den : num * 0.f;
+    const size_t at = (((size_t)b * Lq + i0 + r) * a.H + h) * DK + d;
+    const float x = den > 0.f ? num / den : num * 0.f;
+    if (a.out_f32) ((float*)a.out)[at] = x;
+    else elem<T>::store((T*)a.out + at, x);
   }
 }
 
+template <typename T, typename S>
 struct F32ScoresArgs {
-  const float* q_lr;      // [B,H,Lq,r]
-  const float* k_lr;      // [B,Hkv,Lk,r]
-  const float* prev;      // [B,H,Lq,Lk]
-  const float* w1;        // [H,F]
-  const float* w2;        // [F,H]
-  float* scores;          // [B,H,Lq,Lk]
+  const T* q_lr;          // [B,H,Lq,r]
+  const T* k_lr;          // [B,Hkv,Lk,r]
+  const S* prev;          // [B,H,Lq,Lk]
+  const T* w1;            // [Din,F]
+  const T* w2;            // [F,H]
+  S* scores;              // [B,H,Lq,Lk] or null
+  float* exact;           // [B,H,n_rows,Lk] or null: the unrounded copy
   int H, Hkv, Lq, Lk, r, F, causal;
+  int row0, n_rows;       // query rows of this launch (row0 a multiple of 16)
   int tiles;              // key tiles per workgroup
   float dscale;
 };
 constexpr int F32_DROW = 20;                                 // floats per row of the A_delta tile (16 keys, padded)
 // LDS bytes for HT padded heads: A_delta tile, then the weights in operand order.
-constexpr int f32_scores_lds(int HT, int F) {
-  return (HT * 16 * F32_DROW + (F + 15) / 16 * (HT / 4 + (HT + 15) / 16 * 4) * 64) * (int)sizeof(float);
+constexpr int f32_scores_lds(int HT, int F, bool concat) {
+  return (HT * 16 * F32_DROW + (F + 15) / 16 * ((concat ? 2 : 1) * HT / 4 + (HT + 15) / 16 * 4) * 64) * (int)sizeof(float);
 }
 
-// A_n = FFN(A_{n-1}) + A_delta.  grid (ceil(key tiles / tiles), ceil(Lq / 16), B), block 256.  A tile = 16 query
-// rows x 16 keys, all heads: the waves make A_delta by heads (16x16x4 float32 MFMA, keys x rows) and
-// leave it in the LDS, then take the tile's rows, four each: FFN with the 16 keys of a row as the columns
-// (mfma_ffn.h's scheme in float32: a lane's hidden units are its operands of the second product).
-// Bound: the float32 MFMAs of the FFN.  (One position per lane with the weights through the scalar
+// A_n = FFN(A_{n-1}) + A_delta, or FFN([A_{n-1}; A_delta]) (CONCAT).  grid (ceil(key tiles / tiles), ceil(n_rows / 16), B),
+// block 256.  A tile = 16 query rows x 16 keys, all heads: the waves make A_delta by heads (16x16x4 float32
+// MFMA, keys x rows) and leave it in the LDS, then take the tile's rows, four each: FFN with the 16 keys of
+// a row as the columns (mfma_ffn.h's scheme in float32: a lane's hidden units are its operands of the second
+// product).
+// Bound: at most a third of the time is the float32 MFMAs, the rest loads and stores of 32- and 64-byte pieces in
+// H pages per tensor.  LLaMA2-7B heads, 2 x 509 rows behind 1022 keys, bf16: 316 us (589 with a wait per load of
+// A_delta and the tests of the stores inside their loops; the generic kernel and its softmax 3270).  (One position per lane with the weights through the scalar
 // cache took 17 us where this takes 4, 8 heads, 128 tokens: one wave per SIMD waits for every weight.)
-// HT: H rounded up to 8, 16 or 32.
-template <int HT, int ACT>
-__global__ __launch_bounds__(256) void k_f32_lisa_scores(F32ScoresArgs a) {
-  constexpr int KS = HT / 4, HB = (HT + 15) / 16, NB = 4;    // k-steps of the heads, output blocks, rows per wave
+// HT: H rounded up to 8, 16, 32 or 40.
+template <typename T, typename S, int HT, int ACT, bool CONCAT>
+__global__ __launch_bounds__(256) void k_f32_lisa_scores(F32ScoresArgs<T, S> a) {
+  constexpr int KH = HT / 4, KS = CONCAT ? 2 * KH : KH;      // k-steps of the heads, of the inputs
+  constexpr int HB = (HT + 15) / 16, NB = 4;                 // output blocks, rows per wave
   extern __shared__ __align__(16) float f32_lds[];
   float* d_s = f32_lds;                                      // [HT][16 rows][F32_DROW]
   const int FB = (a.F + 15) / 16;
@@ -199,17 +256,17 @@ __global__ __launch_bounds__(256) void k_f32_lisa_scores(F32ScoresArgs a) {
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, g = lane >> 4;
   const int H = a.H, Lq = a.Lq, Lk = a.Lk, r = a.r, group = H / a.Hkv;
-  const int rb = gridDim.y - 1 - blockIdx.y, b = blockIdx.z, i0 = rb * 16;
+  const int rb = gridDim.y - 1 - blockIdx.y, b = blockIdx.z, i0 = a.row0 + rb * 16;
   const int n_tiles = (n_visible(min(i0 + 15, Lq - 1), Lq, Lk, a.causal) + 15) / 16;
   const int t0 = blockIdx.x * a.tiles, t1 = min(n_tiles, t0 + a.tiles);
   if (t0 >= t1) return;                                      // (workgroup-uniform)
   for (int e = tid; e < FB * KS * 64; e += 256) {
-    const int o = e >> 6, f = 16 * (o / KS) + (e & 15), h = 4 * (o % KS) + ((e >> 4) & 3);
-    w1_s[e] = f < a.F && h < H ? a.w1[(size_t)h * a.F + f] : 0.f;
+    const int o = e >> 6, f = 16 * (o / KS) + (e & 15), s = o % KS, h = 4 * (s % KH) + ((e >> 4) & 3);
+    w1_s[e] = f < a.F && h < H ? elem<T>::load(a.w1 + (size_t)(s < KH ? h : H + h) * a.F + f) : 0.f;
   }
   for (int e = tid; e < FB * 4 * HB * 64; e += 256) {
     const int o = e >> 6, h = 16 * (o % HB) + (e & 15), f = 16 * (o / (4 * HB)) + 4 * ((e >> 4) & 3) + o / HB % 4;
-    w2_s[e] = f < a.F && h < H ? a.w2[(size_t)f * H + h] : 0.f;
+    w2_s[e] = f < a.F && h < H ? elem<T>::load(a.w2 + (size_t)f * H + h) : 0.f;
   }
   const size_t hs = (size_t)Lq * Lk;                         // from a head's scores to the next head's
   for (int tile = t0; tile < t1; ++tile) {
@@ -218,33 +275,72 @@ __global__ __launch_bounds__(256) void k_f32_lisa_scores(F32ScoresArgs a) {
     float x[NB][KS];
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
-      const float* xp = a.prev + ((size_t)b * H * Lq + min(i0 + wv * NB + n, Lq - 1)) * Lk + jc;
+      const S* xp = a.prev + ((size_t)b * H * Lq + min(i0 + wv * NB + n, Lq - 1)) * Lk + jc;
 #pragma unroll
-      for (int s = 0; s < KS; ++s) x[n][s] = 4 * s + g < H ? xp[(4 * s + g) * hs] : 0.f;
+      for (int s = 0; s < KH; ++s) {
+        const float xs = elem<S>::load(xp + min(4 * s + g, H - 1) * hs);
+        x[n][s] = 4 * s + g < H ? xs : 0.f;
+      }
     }
     if (tile > t0) __syncthreads();                          // d_s of the tile before has been read
-    for (int h = wv; h < H; h += 4) {
-      const float* kp = a.k_lr + (((size_t)b * a.Hkv + h / group) * Lk + jc) * r;
-      const float* qp = a.q_lr + (((size_t)b * H + h) * Lq + min(i0 + c, Lq - 1)) * r;
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-      for (int s = 0; s < (r + 3) / 4; ++s) {
-        const int t = 4 * s + g;
-        const float kx = t < r ? kp[t] : 0.f, qx = t < r ? qp[t] : 0.f;
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(kx, qx, acc, 0, 0, 0);
+    // A_delta, NH heads and 32 ranks at a time with all their loads in flight together: a load per step of the
+    // product, each waited for, made this the longest part of the kernel.  The ranks are numbered so that a lane's
+    // two steps 2 u, 2 u + 1 take neighbours, one load where the rows (r elements) keep them aligned.
+    constexpr int NH = HT >= 16 ? 4 : 2;
+    const bool pairs = (r & 1) == 0;
+    for (int h0 = wv; h0 < H; h0 += 4 * NH) {
+      f32x4 acc[NH];
+#pragma unroll
+      for (int m = 0; m < NH; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int r0 = 0; r0 < r; r0 += 32) {
+        Pair<T> kx[NH][4], qx[NH][4];
+#pragma unroll
+        for (int m = 0; m < NH; ++m) {
+          const int h = min(h0 + 4 * m, H - 1);
+          const T* kp = a.k_lr + (((size_t)b * a.Hkv + h / group) * Lk + jc) * r;
+          const T* qp = a.q_lr + (((size_t)b * H + h) * Lq + min(i0 + c, Lq - 1)) * r;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int t = r0 + 8 * u + 2 * g;
+            kx[m][u] = pairs ? Pair<T>::load(kp + min(t, r - 2)) : Pair<T>::load2(kp + min(t, r - 1), kp + min(t + 1, r - 1));
+            qx[m][u] = pairs ? Pair<T>::load(qp + min(t, r - 2)) : Pair<T>::load2(qp + min(t, r - 1), qp + min(t + 1, r - 1));
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const bool in = r0 + 8 * u + 2 * g + e < r;
+#pragma unroll
+            for (int m = 0; m < NH; ++m)
+              acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? kx[m][u][e] : 0.f, in ? qx[m][u][e] : 0.f, acc[m], 0, 0, 0);
+          }
       }
-      *(f32x4*)(d_s + (h * 16 + c) * F32_DROW + 4 * g) = acc * a.dscale;   // row c, keys 4 g ..
+#pragma unroll
+      for (int m = 0; m < NH; ++m) {
+        const int h = h0 + 4 * m;
+        if (h < H) *(f32x4*)(d_s + (h * 16 + c) * F32_DROW + 4 * g) = acc[m] * a.dscale;   // row c, keys 4 g ..
+      }
     }
     __syncthreads();                                         // (also publishes the weights)
     f32x4 y[NB][HB];
 #pragma unroll
-    for (int n = 0; n < NB; ++n)
+    for (int n = 0; n < NB; ++n) {
+      if constexpr (CONCAT) {
+#pragma unroll
+        for (int s = 0; s < KH; ++s) {
+          const int h = 4 * s + g;
+          x[n][KH + s] = h < H ? d_s[(h * 16 + wv * NB + n) * F32_DROW + c] : 0.f;
+        }
+      }
 #pragma unroll
       for (int hb = 0; hb < HB; ++hb)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int h = min(16 * hb + 4 * g + v, H - 1);
-          y[n][hb][v] = d_s[(h * 16 + wv * NB + n) * F32_DROW + c];
+          y[n][hb][v] = CONCAT ? 0.f : d_s[(h * 16 + wv * NB + n) * F32_DROW + c];
         }
+    }
     for (int fb = 0; fb < FB; ++fb) {
       f32x4 u[NB];
 #pragma unroll
@@ -267,19 +363,29 @@ __global__ __launch_bounds__(256) void k_f32_lisa_scores(F32ScoresArgs a) {
         }
       }
     }
+    // (one test of the tensor and of the heads around each run of stores, not one per element)
+    auto store = [&](auto* dst, size_t head_stride, int rows, int row0) {
+      typedef std::remove_pointer_t<decltype(dst)> D;
 #pragma unroll
-    for (int n = 0; n < NB; ++n) {
-      const int i = i0 + wv * NB + n;
-      if (i >= Lq || j >= n_visible(i, Lq, Lk, a.causal)) continue;
-      float* sp = a.scores + ((size_t)b * H * Lq + i) * Lk + j;
+      for (int n = 0; n < NB; ++n) {
+        const int i = i0 + wv * NB + n;
+        if (i >= Lq || j >= n_visible(i, Lq, Lk, a.causal)) continue;
+        D* p = dst + ((size_t)b * H * rows + i - row0) * Lk + j + 4 * g * head_stride;
 #pragma unroll
-      for (int hb = 0; hb < HB; ++hb)
+        for (int hb = 0; hb < HB; ++hb) {
+          if (16 * hb + 16 <= H) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int h = 16 * hb + 4 * g + v;
-          if (h < H) sp[h * hs] = y[n][hb][v];
+            for (int v = 0; v < 4; ++v) elem<D>::store(p + (16 * hb + v) * head_stride, y[n][hb][v]);
+          } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              if (16 * hb + 4 * g + v < H) elem<D>::store(p + (16 * hb + v) * head_stride, y[n][hb][v]);
+          }
         }
-    }
+      }
+    };
+    if (a.scores) store(a.scores, hs, Lq, 0);
+    if (a.exact) store(a.exact, (size_t)a.n_rows * Lk, a.n_rows, a.row0);
   }
 }
 

@@ -1,6 +1,6 @@
 // Shape-generic kernels of the LiSA path: correct for every supported descriptor, fp32
-// arithmetic on the vector ALUs.  They are the fp32 path and the fallback of the bf16 path
-// for shapes the MFMA kernels do not cover.
+// arithmetic on the vector ALUs.  They are the fallback for shapes and modules the matrix-core kernels do
+// not cover.
 //
 // Three kernels mirror the three stages of the layer:
 //   k_std_scores     A = Q K^T * scale                      (Sec. 2.1 Eq. 2, bracketed term)
@@ -80,9 +80,10 @@ __global__ __launch_bounds__(256) void k_std_scores(const T* __restrict__ q, con
 
 // ---------------------------------------------------------------------------------------
 // A_n for one block = 64 consecutive keys of one query row, all heads; written to `scores`
-// (score type, may be null) and, unrounded, to `exact` (float32, may be null).  Four waves; wave s takes
+// (score type, may be null) and, unrounded, to `exact` (float32, may be null).  The launch takes the rows
+// row0 .. row0 + gridDim.y - 1, which are all that `exact` holds.  Four waves; wave s takes
 // heads / hidden units s, s+4, ...  Dynamic LDS: x[Din][64], hid[F][64], a_delta[H][64].
-// grid (ceil(Lk/64), Lq, B), block 256.
+// grid (ceil(Lk/64), rows, B), block 256.
 // `mix`: 0 A_n = FFN(A_{n-1}) + A_delta, 1 A_n = FFN([A_{n-1}; A_delta]) (Sec. 5.1, Eq. 4),
 // 2 A_n = A_{n-1} + A_delta (LiSA_plus, Sec. 5.5), 3 A_n = A_{n-1} (direct sharing, Sec. 4).
 // `act`: 0 ReLU, 1 SiLU, 2 single layer y = W1^T x with F = H (Sec. 5.7).
@@ -96,16 +97,17 @@ __global__ __launch_bounds__(256) void k_lisa_scores(const T* __restrict__ q_lr,
                                                      S* __restrict__ scores,
                                                      float* __restrict__ exact, int H, int Hkv,
                                                      int Lq, int Lk, int r, int F, int mix, int act,
-                                                     float dscale, int causal) {
+                                                     float dscale, int causal, int row0) {
   extern __shared__ float sm[];
   const bool concat = mix == 1, has_ffn = mix <= 1, has_delta = mix != 3;
   const int Din = concat ? 2 * H : H;
   float* xs = sm;
   float* hs = xs + Din * 64;
   float* ds = hs + F * 64;
-  const int j0 = blockIdx.x * 64, i = blockIdx.y, b = blockIdx.z;
+  const int j0 = blockIdx.x * 64, i = row0 + blockIdx.y, b = blockIdx.z;
   const int nv = n_visible(i, Lq, Lk, causal);
   if (j0 >= nv) return;
+  auto exact_at = [&](int h) { return ((size_t)(b * H + h) * gridDim.y + blockIdx.y) * Lk + j0 + (threadIdx.x & 63); };
   const int pj = threadIdx.x & 63, sl = threadIdx.x >> 6;
   const int j = j0 + pj;
   const bool live = j < nv;
@@ -125,7 +127,7 @@ __global__ __launch_bounds__(256) void k_lisa_scores(const T* __restrict__ q_lr,
       if (live) {
         const size_t at = ((size_t)(b * H + h) * Lq + i) * Lk + j;
         if (scores) elem<S>::store(scores + at, x + acc);
-        if (exact) exact[at] = x + acc;
+        if (exact) exact[exact_at(h)] = x + acc;
       }
       continue;
     }
@@ -152,7 +154,7 @@ __global__ __launch_bounds__(256) void k_lisa_scores(const T* __restrict__ q_lr,
     if (live) {
       const size_t at = ((size_t)(b * H + h) * Lq + i) * Lk + j;
       if (scores) elem<S>::store(scores + at, acc);
-      if (exact) exact[at] = acc;
+      if (exact) exact[exact_at(h)] = acc;
     }
   }
 }

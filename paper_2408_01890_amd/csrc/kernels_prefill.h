@@ -236,37 +236,6 @@ template <class T>
 __device__ __forceinline__ void st_uv_stream(void* ubase, unsigned voff, T v) {
   *(T*)((char*)ubase + voff) = v;
 }
-// ---- 8 consecutive scores of a row-major row -------------------------------------------------
-// Rows of Lk scores start at any 2-byte boundary when Lk % 8 != 0; gfx950 takes 16-byte global
-// accesses at any address (a line boundary inside costs a second request), so a ragged row
-// length needs no path of its own: these types only tell the compiler the alignment.
-typedef pf_u32x4 pf_u32x4_a2 __attribute__((aligned(2)));
-typedef unsigned long long pf_u64_a2 __attribute__((aligned(2)));
-typedef unsigned pf_u32_a2 __attribute__((aligned(2)));
-// Element offset, inside a head of `elems` scores, at which the 8 scores from `off` on are loaded: the
-// last few of the head are fetched from `elems - 8` (the allocation ends there) and moved down by
-// row_chunk_shift() elements.
-__device__ __forceinline__ unsigned row_chunk_at(unsigned off, unsigned elems) { return min(off, elems - 8); }
-__device__ __forceinline__ int row_chunk_shift(unsigned off, unsigned elems) {
-  return off > elems - 8 ? (int)(off - (elems - 8)) : 0;
-}
-// element e of the result = element e + s of v (s = 0..7), zeros behind
-__device__ __forceinline__ pf_u32x4 row_chunk_down(pf_u32x4 v, int s) {
-  unsigned long long lo = v[0] | (unsigned long long)v[1] << 32, hi = v[2] | (unsigned long long)v[3] << 32;
-  if (s & 4) lo = hi, hi = 0;
-  const int sh = 16 * (s & 3);
-  if (sh) lo = lo >> sh | hi << (64 - sh), hi >>= sh;
-  return pf_u32x4{(unsigned)lo, (unsigned)(lo >> 32), (unsigned)hi, (unsigned)(hi >> 32)};
-}
-// The first n (1..7) of 8 half scores at p: at most three stores, nothing beyond them is touched.
-__device__ __forceinline__ void store_row_part(void* p, pf_u32x4 v, int n) {
-  if (n & 4) *(pf_u64_a2*)p = v[0] | (unsigned long long)v[1] << 32;
-  if (n & 2) *(pf_u32_a2*)((char*)p + 2 * (n & 4)) = n & 4 ? v[2] : v[0];
-  if (n & 1) {
-    const unsigned w = n & 4 ? (n & 2 ? v[3] : v[2]) : (n & 2 ? v[1] : v[0]);
-    *(unsigned short*)((char*)p + 2 * (n & 6)) = (unsigned short)w;
-  }
-}
 // H = NG * NW * HPW heads in NG groups; NW waves per workgroup, HPW heads per wave; FS hidden
 // k-steps of the FFN; RS slices of 16 query rows per workgroup (RS > 1 needs HPW = 1).
 //
@@ -289,9 +258,7 @@ __device__ __forceinline__ void store_row_part(void* p, pf_u32x4 v, int n) {
 // after the first of them has fetched it from HBM.  With a.pair the workgroup takes the units (last - x) and x, a
 // long and a short one, so that all workgroups carry the same number of tiles and stage the FFN
 // weights once.
-// Requires Lk >= 8 (row-major scores).
-// RAGGED: row-major scores with Lk % 8 != 0.  (A form of its own: the address clamp and the test per tile cost the
-// other one 0.3 - 0.8 %, LLaMA3-8B shape, 4 x 8192: 5739 us with them where 5692 had been.)
+// Requires Lk % 8 == 0.
 // SHG > 0: every SHG consecutive heads of a wave share one key/value head (grouped KV heads, H / Hkv
 // a multiple of SHG, HPW a multiple of SHG): one set of K_LR / V operands per tile serves all of
 // them, and every such set is refilled behind its last head with the next tile's operands.  With
@@ -300,7 +267,7 @@ __device__ __forceinline__ void store_row_part(void* p, pf_u32x4 v, int n) {
 // key/value head for four query heads.
 // FTRIM: F <= 32 FS - 16, the last 16 hidden units are padding and their products are left out
 // (the 40 -> 80 -> 40 network of the LLaMA2-13B shape: 10 instead of 12 MFMAs of the first layer).
-template <int NG, int FS, int HPW, int NW, int ACT = 0, int RS = 1, int SHG = 0, bool FTRIM = false, bool RAGGED = false>
+template <int NG, int FS, int HPW, int NW, int ACT = 0, int RS = 1, int SHG = 0, bool FTRIM = false>
 __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
   static_assert(RS == 1 || HPW == 1, "row slices: one head per wave");
   // XSTG: the A_{n-1} piece is double buffered by tile parity and the buffers double as the staging
@@ -465,11 +432,6 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
     // has usually left the L2 again: A_{n-1} was measured to come from HBM 2.5 times (22 GB on the
     // LLaMA3-8B shape at L = 8192; a 4-byte load of the other half issued next to each piece, to have
     // it fetched once, changed little).  Tiled scores: the piece is 1 KB of consecutive memory.
-    // (keys >= Lk: any chunk of the row will do, those positions are masked in stage B)
-    auto x_row_at = [&](int tile, int rs) {
-      return (unsigned)min(i0 + PF_ROWS * rs + (lane >> 2), Lq - 1) * Lk + min(tile * PF_TK + xq8, (Lk - 1) & ~7);
-    };
-    const bool ragged_end = RAGGED && i0 + R >= Lq;
     auto load_x = [&](int tile, int rs, pf_u32x4 (&xr)[XCH]) {
       unsigned off;
       size_t at = 0;                                          // wave-uniform element offset of the tile
@@ -477,18 +439,15 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
         at = ((size_t)min((i0 >> 4) + rs, n_rb - 1) * n_kt + tile) * tile_stride;
         off = lane * 16;
       } else {
-        off = 2 * (RAGGED ? row_chunk_at(x_row_at(tile, rs), (unsigned)Lq * Lk) : x_row_at(tile, rs));
+        const unsigned x_row = (unsigned)min(i0 + PF_ROWS * rs + (lane >> 2), Lq - 1) * Lk * 2;
+        // keys >= Lk: any in-bounds chunk will do, those positions are masked in stage B
+        off = x_row + 2 * min(tile * PF_TK + xq8, Lk - 8);
       }
 #pragma unroll
-      for (int u = 0; u < XCH; ++u) xr[u] = ld_uv_stream<pf_u32x4_a2>(x_base[u] + at, off);
+      for (int u = 0; u < XCH; ++u) xr[u] = ld_uv_stream<pf_u32x4>(x_base[u] + at, off);
     };
-    auto store_x = [&](pf_u32x4 (&xr)[XCH], int tile, int rs) {   // XSTG: into the buffer of the tile's parity
+    auto store_x = [&](const pf_u32x4 (&xr)[XCH], int tile) {   // XSTG: into the buffer of the tile's parity
       unsigned char* dst = xs + (XSTG ? (tile & 1) * (H * PF_XS_HEAD) : 0) + xdst;
-      if (ragged_end && tile * PF_TK + PF_TK > Lk) {          // (workgroup-uniform: last row block, last tile)
-        const int sh = row_chunk_shift(x_row_at(tile, rs), (unsigned)Lq * Lk);
-#pragma unroll
-        for (int u = 0; u < XCH; ++u) xr[u] = row_chunk_down(xr[u], sh);
-      }
 #pragma unroll
       for (int u = 0; u < XCH; ++u) *(pf_u32x4*)(dst + u * ((XSTG ? 1 : NW) * PF_XS_HEAD)) = xr[u];
     };
@@ -542,7 +501,7 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
     // K_LR / V loads wait for it anyway.)
     pf_u32x4 xr[XCH];
     load_x(t_begin, rs_min(t_begin), xr);
-    store_x(xr, t_begin, rs_min(t_begin));
+    store_x(xr, t_begin);
     // Stores of a staged pair of A_n tiles (head hh, slice rs of this wave); pending[rs] = last
     // tile of a pair whose stores are still to be issued.  They go out during stage A of the
     // slice's next step: all waves of a workgroup run the same stage at the same time, stage B is
@@ -583,13 +542,19 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
                        ((lane >> 3) + 8 * u) * (2 * PF_TK) + (lane & 3) * 16
                  : as_ + (hh * RS + rs) * PF_AS_HEAD + ((lane >> 3) + 8 * u) * PF_AS_ROW + (lane & 7) * 16;
         if (pair_full || jc + 8 <= a_vis) {
-          st_uv_stream<pf_u32x4_a2>(st, a_off, *(const pf_u32x4*)sp);
+          st_uv_stream<f16x8>(st, a_off, *(const f16x8*)sp);
         } else if (jc < a_vis) {
-          // the piece that holds the row's last visible key: what lies beyond it belongs to nobody, or
-          // (rows of ragged length) to the next row
-          int rel = a_vis - jc;                   // kept inside this branch, out of the tile loop's
-          asm volatile("" : "+v"(rel));           // live registers
-          store_row_part((char*)st + a_off, *(const pf_u32x4*)sp, rel);
+          // a piece that straddles the row's last visible key (diagonal tiles only): the entries
+          // beyond it keep what memory holds -- read, merge, write back; every piece has one writer.
+          // (Element-wise stores kept eight addresses per piece alive across the whole tile loop.)
+          const f16x8 old = ld_uv<f16x8>(st, a_off);
+          f16x8 hv = *(const f16x8*)sp;
+          int rel = a_vis - jc;                   // kept inside this branch: the eight compares
+          asm volatile("" : "+v"(rel));           // were hoisted into every pass of the tile loop
+#pragma unroll
+          for (int e = 1; e < 8; ++e)
+            if (e >= rel) hv[e] = old[e];
+          st_uv<f16x8>(st, a_off, hv);
         }
       }
     };
@@ -785,7 +750,7 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
       }
       // every wave left stage A of this step, the last reader of xs, before B2; stage A of the
       // next step reads the new piece after B1
-      store_x(xr, x_tile, x_rs);
+      store_x(xr, x_tile);
       }
     }
 #pragma unroll

@@ -19,7 +19,7 @@
 //      per row and tile: up to 32 heads as half in an array of their own, stored during the FFN of
 //      the next tile (two barriers per tile); wider forms as float32 over the input tile, stored
 //      before the next tile is staged (four barriers).
-// Requires Lk >= 8 (row-major scores), r <= 32, H <= 48, F <= 256.
+// Requires Lk % 8 == 0, r <= 32, H <= 48, F <= 256.
 #pragma once
 #include <type_traits>
 #include "kernels_prefill.h"
@@ -131,17 +131,6 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
   const int n_kt = (Lk + PF_TK - 1) / PF_TK;
   const size_t tile_stride = (size_t)H * (PF_ROWS * PF_TK);
   const size_t trow = ((size_t)b * n_rg + rg) * n_kt * tile_stride + lane * 8;   // + t tile_stride + h 512
-  // row-major: a tile's chunk of the lane's row, as an element offset in the head (see row_chunk_at)
-  const unsigned head_elems = (unsigned)Lq * Lk;
-  const bool ragged_end = !TILED && (Lk & 7) != 0 && i0 + PF_ROWS >= Lq;
-  auto x_at = [&](int tile) { return (unsigned)x_row * Lk + min(tile * PF_TK + xq8, (Lk - 1) & ~7); };
-  auto mend_x = [&](int tile) {
-    if (ragged_end && tile * PF_TK + PF_TK > Lk) {           // (workgroup-uniform: last row group, last tile)
-      const int sh = row_chunk_shift(x_at(tile), head_elems);
-#pragma unroll
-      for (int u = 0; u < XCH; ++u) xr[u] = row_chunk_down(xr[u], sh);
-    }
-  };
   auto prefetch = [&](int tile) {
     const int j0 = tile * PF_TK;
 #pragma unroll
@@ -150,7 +139,7 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
       if (TILED)
         xr[u] = *(const pf_u32x4*)(a.prev + trow + min(tile, n_kt - 1) * tile_stride + h * (PF_ROWS * PF_TK));
       else
-        xr[u] = *(const pf_u32x4_a2*)(a.prev + ((size_t)b * H + h) * head_elems + row_chunk_at(x_at(tile), head_elems));
+        xr[u] = *(const pf_u32x4*)(a.prev + (((size_t)b * H + h) * Lq + x_row) * Lk + min(j0 + xq8, Lk - 8));
     }
 #pragma unroll
     for (int u = 0; u < HPW; ++u) {
@@ -165,8 +154,7 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
   // (the barriers of the tile loop order LDS traffic only: __syncthreads() would also wait for the
   // global stores of the previous tile and for the prefetch)
 
-  auto stage_tile = [&](int tile) {
-    mend_x(tile);
+  auto stage_tile = [&]() {
 #pragma unroll
     for (int u = 0; u < XCH; ++u) {
       const int h = wv + NW * u;
@@ -220,7 +208,8 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
     half_t* const obase = a.scores + (((size_t)b * H + wv) * Lq + min(gi, Lq - 1)) * Lk + 8 * och;
     const size_t ohead = (size_t)NW * Lq * Lk;              // from a head of this wave to its next
     const unsigned char* const yrd = yh + wv * SM_YH_HEAD + orow * (PF_TK * 2) + 16 * och;
-    const half_t* const pbase = a.prev + (size_t)b * H * head_elems;
+    const half_t* const pbase = a.prev + ((size_t)b * H * Lq + x_row) * Lk;
+    const size_t phead = (size_t)Lq * Lk;
     f32x4 y[NBW][HBO];
     f16x8 held;
     auto out_read = [&](int u) {
@@ -235,8 +224,13 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
       const int jc = tile * PF_TK + 8 * och;                // first of the lane's 8 keys
       if (jc >= vis) return;
       half_t* sp = obase + u * ohead + jc - 8 * och;
-      if (jc + 8 <= vis) *(pf_u32x4_a2*)sp = __builtin_bit_cast(pf_u32x4, held);
-      else store_row_part(sp, __builtin_bit_cast(pf_u32x4, held), vis - jc);
+      if (jc + 8 <= vis) {
+        *(f16x8*)sp = held;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (jc + e < vis) sp[e] = held[e];
+      }
     };
     // The result leaves the registers as dwords of two keys: a lane holds one key of the four heads
     // 4 g + v; the lanes of a pair (keys c, c ^ 1) swap halves, after which the even lane has both
@@ -272,13 +266,13 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
     // before is in yh and leaves during this tile's FFN
     auto do_tile = [&](auto pend, int tile) {
       constexpr bool PEND = decltype(pend)::value;
-      stage_tile(tile);
+      stage_tile();
       if (PEND) write_y();
       lds_barrier();                                         // A: xs and yh are complete
       f16x8 x[NBW][KS];
       read_x(x, x_all);
       const int jn = (tile + 1) * PF_TK;
-      const unsigned xoff = row_chunk_at(x_at(tile + 1), head_elems);
+      const int xoff = min(jn + xq8, Lk - 8);
       const size_t toff = trow + min(tile + 1, n_kt - 1) * tile_stride;
       int koff[2];
 #pragma unroll
@@ -296,7 +290,7 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
           } else if (k <= 2 * XCH) {
             const int u = k - XCH - 1, h = min(wv + NW * u, H - 1);
             if (TILED) xr[u] = *(const pf_u32x4*)(a.prev + toff + h * (PF_ROWS * PF_TK));
-            else xr[u] = *(const pf_u32x4_a2*)(pbase + (size_t)h * head_elems + xoff);
+            else xr[u] = *(const pf_u32x4*)(pbase + h * phead + xoff);
           } else {
             const int u = (k - 2 * XCH - 1) >> 1, half = (k - 2 * XCH - 1) & 1;
             const int h = min(wv + NW * u, H - 1);
@@ -321,7 +315,6 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
     const int j0 = tile * PF_TK;
     lds_barrier();                                           // the stores of the previous tile have read ys
     // ---- 1. input tile -----------------------------------------------------------------------
-    mend_x(tile);
 #pragma unroll
     for (int u = 0; u < XCH; ++u) {
       const int h = wv + NW * u;
@@ -403,8 +396,13 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
         f16x8 hv;
 #pragma unroll
         for (int e = 0; e < 8; ++e) hv[e] = f32_to_half_sat(vals[e]);
-        if (jc + 8 <= vis) *(pf_u32x4_a2*)(a.scores + at) = __builtin_bit_cast(pf_u32x4, hv);
-        else store_row_part(a.scores + at, __builtin_bit_cast(pf_u32x4, hv), vis - jc);
+        if (jc + 8 <= vis) {
+          *(f16x8*)(a.scores + at) = hv;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (jc + e < vis) a.scores[at + e] = hv[e];
+        }
       }
     }
   }

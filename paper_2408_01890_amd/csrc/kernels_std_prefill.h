@@ -67,7 +67,7 @@ constexpr int std_prefill_head_lds(bool with_v) {
 // fastest grid index: consecutive workgroups go to different XCDs, so an XCD works on every
 // eighth head and its L2 fetches the K / V of those heads only (they are what every row group
 // of a head re-reads).
-// Requires d_k = 128, Lk >= 8.
+// Requires d_k = 128, Lk % 8 == 0.
 // GIVEN: the scores are read from a.given (the A_n that a LiSA scores kernel left there) instead
 // of being computed; the rest (masking, online softmax, P V) is the same.
 template <bool WITH_V, int GIVEN = 0>
@@ -121,14 +121,7 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
     }
     const size_t grow_at = (((size_t)b * H + h) * Lq + my_row) * Lk;
     const float* grow = GIVEN == 1 ? (const float*)a.given + grow_at : nullptr;
-    // GIVEN = 2, row-major: the head's scores and the row's place in them (a chunk of 8 that would
-    // pass the end of the head is loaded from before it and moved down, see row_chunk_at)
-    const half_t* ghead = GIVEN == 2 ? (const half_t*)a.given + ((size_t)b * H + h) * Lq * Lk : nullptr;
-    const unsigned head_elems = (unsigned)Lq * Lk;
-    const bool ragged_end = GIVEN == 2 && !a.tiled && (Lk & 7) != 0 && i0 + SP_ROWS >= Lq;
-    auto g_at = [&](int tile, int u) {
-      return (unsigned)my_row * Lk + min(tile * SP_TK + 16 * u + 8 * half, (Lk - 1) & ~7);
-    };
+    const half_t* grow_h = GIVEN == 2 ? (const half_t*)a.given + grow_at : nullptr;
     const int n_kt = (Lk + SP_TK - 1) / SP_TK;               // tile grid of the tiled score layout
     // (tiled: the H pieces of a tile follow each other, 1 KB each; see k_lisa_prefill_fused)
     const size_t seq_elems = a.tiled ? (size_t)((Lq + 15) / 16) * n_kt * H * (16 * SP_TK) : (size_t)H * Lq * Lk;
@@ -170,9 +163,8 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
     auto load_scores = [&](int tile, f16x8 (&dst)[2]) {
 #pragma unroll
       for (int u = 0; u < 2; ++u)    // (keys beyond Lk: any in-bounds 8 scores will do, those positions are masked)
-        dst[u] = __builtin_bit_cast(
-            f16x8, (pf_u32x4)*(const pf_u32x4_a2*)(a.tiled ? grow_t + (size_t)tile * H * (16 * SP_TK) + 16 * u
-                                                           : ghead + row_chunk_at(g_at(tile, u), head_elems)));
+        dst[u] = *(const f16x8*)(a.tiled ? grow_t + (size_t)tile * H * (16 * SP_TK) + 16 * u
+                                         : grow_h + min(tile * SP_TK + 16 * u + 8 * half, Lk - 8));
     };
     if (rep) __syncthreads();                              // the first pass is done with both buffers
     load_tile(0, regs_a);
@@ -205,9 +197,6 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
       if (GIVEN == 2) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-          if (ragged_end && j0 + SP_TK > Lk)                 // (wave-uniform: last rows, last tile)
-            gq[0][u] = __builtin_bit_cast(f16x8, row_chunk_down(__builtin_bit_cast(pf_u32x4, gq[0][u]),
-                                                                row_chunk_shift(g_at(tile, u), head_elems)));
 #pragma unroll
           for (int e = 0; e < 8; ++e) an[8 * u + e] = (float)gq[0][u][e];
           gq[0][u] = gq[1][u];
@@ -216,12 +205,10 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
       } else if (GIVEN == 1) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-          // (a chunk may run past its row, the last row's into the regrouped V behind the scores)
-          typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
-          const float* gp = grow + min(j0 + 16 * u + 8 * half, (Lk - 1) & ~7);
-          const f32x4 lo = *(const f32x4_a4*)gp, hi = *(const f32x4_a4*)(gp + 4);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) an[8 * u + e] = lo[e], an[8 * u + 4 + e] = hi[e];
+          const float* gp = grow + min(j0 + 16 * u + 8 * half, Lk - 8);
+          const float4 lo = *(const float4*)gp, hi = *(const float4*)(gp + 4);
+          an[8 * u + 0] = lo.x, an[8 * u + 1] = lo.y, an[8 * u + 2] = lo.z, an[8 * u + 3] = lo.w;
+          an[8 * u + 4] = hi.x, an[8 * u + 5] = hi.y, an[8 * u + 6] = hi.z, an[8 * u + 7] = hi.w;
         }
       } else {
         f32x16 acc;
@@ -273,11 +260,11 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
             const int vis = gi < Lq ? (a.causal ? min(Lk, gi + 1 + shift) : Lk) : 0;
             half_t* sp = sbase + (size_t)min(gi, Lq - 1) * Lk + jc;
             if (pair_full || jc + 8 <= vis) {
-              __builtin_nontemporal_store(__builtin_bit_cast(pf_u32x4, hv), (pf_u32x4_a2*)sp);
-            } else if (jc < vis) {
-              int rel = vis - jc;                              // (kept inside this branch: registers)
-              asm volatile("" : "+v"(rel));
-              store_row_part(sp, __builtin_bit_cast(pf_u32x4, hv), rel);
+              __builtin_nontemporal_store(__builtin_bit_cast(pf_u32x4, hv), (pf_u32x4*)sp);
+            } else {
+#pragma unroll
+              for (int e = 0; e < 8; ++e)
+                if (jc + e < vis) sp[e] = hv[e];
             }
           }
         }

@@ -1,79 +1,125 @@
-// float32 prefill layers on the kernels of kernels_f32.h: which shapes they take, and the launches.
+// Prefill layers in float32 arithmetic on the kernels of kernels_f32.h: which shapes they take, and the launches.
 #include "host.h"
 #include "kernels_f32.h"
 
 namespace lisa {
 
+// bf16: what the bf16 and half matrix instructions would take but for the length of its score rows.
+static bool bf16_ragged_rows(const lisa_desc* d) {
+  return d->dtype == LISA_BF16 && d->d_k == 128 && !score_rows_aligned(d);
+}
+
 bool f32_attn_ok(const lisa_desc* d) {
-  return d->dtype == LISA_F32 && d->Lq > 1 && (d->d_k == 64 || d->d_k == 128);
+  return d->Lq > 1 && (d->dtype == LISA_F32 ? d->d_k == 64 || d->d_k == 128 : bf16_ragged_rows(d));
 }
 
 namespace {
-int launch_attn(const lisa_desc* d, const F32AttnArgs& a, bool given, const char* name, hipStream_t st) {
-  dim3 grid((d->Lq + 15) / 16, d->H, d->B);
-  StageScope prof(name, st);
-  if (d->d_k == 64) {
-    if (given) k_f32_attn<1, true><<<grid, 256, 0, st>>>(a);
-    else k_f32_attn<1, false><<<grid, 256, 0, st>>>(a);
-  } else {
-    if (given) k_f32_attn<2, true><<<grid, 256, 0, st>>>(a);
-    else k_f32_attn<2, false><<<grid, 256, 0, st>>>(a);
-  }
+template <typename T, typename S, int NDK>
+int launch_attn(const lisa_desc* d, const F32AttnArgs<T, S>& a, hipStream_t st) {
+  dim3 grid((a.n_rows + 15) / 16, d->H, d->B);
+  StageScope prof(a.given ? "k_f32_softmax_v" : "k_f32_attn", st);
+  if (a.given) k_f32_attn<T, S, NDK, true><<<grid, 256, 0, st>>>(a);
+  else k_f32_attn<T, S, NDK, false><<<grid, 256, 0, st>>>(a);
   return check_launch();
 }
-F32AttnArgs attn_args(const lisa_desc* d) {
-  F32AttnArgs a{};
+
+// `given`: scores of the rows row0 .. row0 + n_rows - 1 to take instead of q k^T
+template <typename T, typename S>
+int run_attn(const lisa_desc* d, const void* q, const void* k, const void* given, int row0, int n_rows, const void* v,
+             void* scores, void* out, hipStream_t st) {
+  F32AttnArgs<T, S> a{};
+  a.q = (const T*)q; a.k = (const T*)k; a.v = (const T*)v; a.given = (const float*)given;
+  a.scores = (S*)scores; a.out = out;
   a.H = d->H; a.Hkv = d->Hkv; a.Lq = d->Lq; a.Lk = d->Lk; a.causal = d->causal;
+  a.out_f32 = d->out_f32 || d->dtype == LISA_F32;
+  a.row0 = row0; a.n_rows = n_rows;
   a.scale = pick_scale(d->std_scale, d->d_k);
-  return a;
+  if constexpr (sizeof(T) == 4)
+    if (d->d_k == 64) return launch_attn<T, S, 1>(d, a, st);
+  return launch_attn<T, S, 2>(d, a, st);
 }
 }  // namespace
 
 int run_f32_std(const lisa_desc* d, const void* q, const void* k, const void* v, void* scores, void* out,
                 hipStream_t st) {
-  F32AttnArgs a = attn_args(d);
-  a.q = (const float*)q; a.k = (const float*)k; a.v = (const float*)v;
-  a.scores = (float*)scores; a.out = (float*)out;
-  return launch_attn(d, a, false, "k_f32_attn", st);
+  return d->dtype == LISA_F32 ? run_attn<float, float>(d, q, k, nullptr, 0, d->Lq, v, scores, out, st)
+                              : run_attn<bf16_t, half_t>(d, q, k, nullptr, 0, d->Lq, v, scores, out, st);
 }
 
-int run_f32_softmax_v(const lisa_desc* d, const void* scores, const void* v, void* out, hipStream_t st) {
-  F32AttnArgs a = attn_args(d);
-  a.given = (const float*)scores; a.v = (const float*)v; a.out = (float*)out;
-  return launch_attn(d, a, true, "k_f32_softmax_v", st);
+int run_f32_softmax_v(const lisa_desc* d, const void* scores, int row0, int n_rows, const void* v, void* out,
+                      hipStream_t st) {
+  return d->dtype == LISA_F32 ? run_attn<float, float>(d, nullptr, nullptr, scores, row0, n_rows, v, nullptr, out, st)
+                              : run_attn<bf16_t, half_t>(d, nullptr, nullptr, scores, row0, n_rows, v, nullptr, out, st);
 }
+
+// bf16: the float32 scores pass through the workspace a chunk of query rows at a time, 256 MB of them (what the
+// last-level cache holds), at least one block of 16 rows.
+int f32_chunk_rows(const lisa_desc* d) {
+  const size_t row = (size_t)d->B * d->H * d->Lk * sizeof(float);
+  const size_t rows = std::max<size_t>(16, (((size_t)256 << 20) / row) & ~(size_t)15);
+  return (int)std::min<size_t>(rows, (size_t)d->Lq);
+}
+size_t f32_chunk_bytes(const lisa_desc* d) {
+  return round_up((size_t)d->B * d->H * f32_chunk_rows(d) * d->Lk * sizeof(float), 256);
+}
+
+namespace {
+int scores_heads(int H) { return H <= 8 ? 8 : H <= 16 ? 16 : H <= 32 ? 32 : 40; }
+int scores_lds(const lisa_desc* d) { return f32_scores_lds(scores_heads(d->H), d->F, d->mix == LISA_MIX_CONCAT); }
+}  // namespace
 
 bool f32_scores_ok(const lisa_desc* d) {
-  return d->dtype == LISA_F32 && d->Lq > 1 && d->mix == LISA_MIX_ADD && (d->act == LISA_ACT_RELU || d->act == LISA_ACT_SILU) &&
-         d->H <= 32 && f32_scores_lds(d->H <= 8 ? 8 : d->H <= 16 ? 16 : 32, d->F) <= 64 * 1024;
+  if (d->Lq == 1 || (d->act != LISA_ACT_RELU && d->act != LISA_ACT_SILU)) return false;
+  if (d->dtype == LISA_F32) return d->mix == LISA_MIX_ADD && d->H <= 32 && scores_lds(d) <= 64 * 1024;
+  return bf16_ragged_rows(d) && (d->mix == LISA_MIX_ADD || d->mix == LISA_MIX_CONCAT) && d->H <= 40 &&
+         scores_lds(d) <= 160 * 1024;
 }
 
-int run_f32_scores(const lisa_desc* d, const void* q_lr, const void* k_lr, const void* prev, const void* w1,
-                   const void* w2, void* scores, hipStream_t st) {
-  F32ScoresArgs a{};
-  a.q_lr = (const float*)q_lr; a.k_lr = (const float*)k_lr; a.prev = (const float*)prev;
-  a.w1 = (const float*)w1; a.w2 = (const float*)w2; a.scores = (float*)scores;
-  a.H = d->H; a.Hkv = d->Hkv; a.Lq = d->Lq; a.Lk = d->Lk; a.r = d->r; a.F = d->F; a.causal = d->causal;
-  a.dscale = pick_scale(d->delta_scale, d->r);
-  // a tile per workgroup until there are several workgroups per compute unit, then runs of tiles that share
-  // the staged weights
-  const int kt = (d->Lk + 15) / 16, rbs = (d->Lq + 15) / 16;
-  a.tiles = (int)std::min<long long>(16, std::max<long long>(1, (long long)kt * rbs * d->B / (16 * kComputeUnits)));
-  dim3 grid((kt + a.tiles - 1) / a.tiles, rbs, d->B);
-  const int lds = f32_scores_lds(d->H <= 8 ? 8 : d->H <= 16 ? 16 : 32, d->F);
-  StageScope prof("k_f32_lisa_scores", st);
-  const bool silu = d->act == LISA_ACT_SILU;
-  if (d->H <= 8) {
-    if (silu) k_f32_lisa_scores<8, 1><<<grid, 256, lds, st>>>(a);
-    else k_f32_lisa_scores<8, 0><<<grid, 256, lds, st>>>(a);
-  } else if (d->H <= 16) {
-    if (silu) k_f32_lisa_scores<16, 1><<<grid, 256, lds, st>>>(a);
-    else k_f32_lisa_scores<16, 0><<<grid, 256, lds, st>>>(a);
-  } else {
-    if (silu) k_f32_lisa_scores<32, 1><<<grid, 256, lds, st>>>(a);
-    else k_f32_lisa_scores<32, 0><<<grid, 256, lds, st>>>(a);
+namespace {
+template <typename T, typename S, int HT, bool CONCAT>
+int launch_scores_t(const lisa_desc* d, const F32ScoresArgs<T, S>& a, dim3 grid, hipStream_t st) {
+  const int lds = f32_scores_lds(HT, d->F, CONCAT);
+  auto kern = d->act == LISA_ACT_SILU ? k_f32_lisa_scores<T, S, HT, 1, CONCAT> : k_f32_lisa_scores<T, S, HT, 0, CONCAT>;
+  if (lds > 64 * 1024) {
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return hip_fail(e);
   }
+  StageScope prof("k_f32_lisa_scores", st);
+  kern<<<grid, 256, lds, st>>>(a);
   return check_launch();
+}
+
+template <typename T, typename S, bool CONCAT>
+int run_scores(const lisa_desc* d, const void* q_lr, const void* k_lr, const void* prev, const void* w1,
+               const void* w2, void* scores, float* exact, int row0, int n_rows, hipStream_t st) {
+  F32ScoresArgs<T, S> a{};
+  a.q_lr = (const T*)q_lr; a.k_lr = (const T*)k_lr; a.prev = (const S*)prev;
+  a.w1 = (const T*)w1; a.w2 = (const T*)w2; a.scores = (S*)scores; a.exact = exact;
+  a.H = d->H; a.Hkv = d->Hkv; a.Lq = d->Lq; a.Lk = d->Lk; a.r = d->r; a.F = d->F; a.causal = d->causal;
+  a.row0 = row0; a.n_rows = n_rows;
+  a.dscale = pick_scale(d->delta_scale, d->r);
+  // a tile per workgroup until there are six workgroups per compute unit, then runs of tiles that share the
+  // staged weights
+  const int kt = (d->Lk + 15) / 16, rbs = (n_rows + 15) / 16;
+  a.tiles = (int)std::min<long long>(16, std::max<long long>(1, (long long)kt * rbs * d->B / (6 * kComputeUnits)));
+  dim3 grid((kt + a.tiles - 1) / a.tiles, rbs, d->B);
+  switch (scores_heads(d->H)) {
+    case 8: return launch_scores_t<T, S, 8, CONCAT>(d, a, grid, st);
+    case 16: return launch_scores_t<T, S, 16, CONCAT>(d, a, grid, st);
+    case 32: return launch_scores_t<T, S, 32, CONCAT>(d, a, grid, st);
+    default:
+      if constexpr (sizeof(T) == 2) return launch_scores_t<T, S, 40, CONCAT>(d, a, grid, st);
+      return LISA_ERR_UNSUPPORTED;                           // (f32_scores_ok)
+  }
+}
+}  // namespace
+
+int run_f32_scores(const lisa_desc* d, const void* q_lr, const void* k_lr, const void* prev, const void* w1,
+                   const void* w2, void* scores, float* exact, int row0, int n_rows, hipStream_t st) {
+  auto* run = d->dtype == LISA_F32           ? run_scores<float, float, false>
+              : d->mix == LISA_MIX_CONCAT ? run_scores<bf16_t, half_t, true>
+                                          : run_scores<bf16_t, half_t, false>;
+  return run(d, q_lr, k_lr, prev, w1, w2, scores, exact, row0, n_rows, st);
 }
 
 }  // namespace lisa

@@ -13,8 +13,7 @@ int launch_prefill_fused_t(const lisa_desc* d, const PrefillArgs& a, hipStream_t
                               : (size_t)H * PF_XS_HEAD + (size_t)GH * PF_YS_HEAD + Ffn::kStageBytes +
                                     (size_t)GH * RS * PF_AS_HEAD;
   static_assert(lds <= 160 * 1024, "LDS of one compute unit");
-  auto kern = a.tiled || a.Lk % 8 == 0 ? k_lisa_prefill_fused<NG, FS, HPW, NW, ACT, RS, SHG, FTRIM, false>
-                                       : k_lisa_prefill_fused<NG, FS, HPW, NW, ACT, RS, SHG, FTRIM, true>;
+  auto kern = k_lisa_prefill_fused<NG, FS, HPW, NW, ACT, RS, SHG, FTRIM>;
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)lds);
   if (e != hipSuccess) return hip_fail(e);

@@ -182,15 +182,12 @@ int launch_std_scores(const lisa_desc* d, const void* q, const void* k, KeyStrid
   return check_launch();
 }
 
-// CONCAT with the two-layer ReLU FFN on the matrix cores (dense prefill tensors only).
-bool std_prefill_fast_ok(const lisa_desc* d);
+// CONCAT with the two-layer FFN on the matrix cores (dense prefill tensors only).
 bool scores_mfma_ok(const lisa_desc* d) {
   if (d->dtype != LISA_BF16 || d->mix != LISA_MIX_CONCAT) return false;
   if (d->act != LISA_ACT_RELU && d->act != LISA_ACT_SILU) return false;
   if (d->Lq == 1) return false;                            // decode rows: the generic kernel (strided caches)
-  if (d->H > 48 || d->F > 256 || d->r > 32) return false;
-  // rows that are no multiple of 8 scores: where the matrix-core softmax follows (d_k = 128)
-  if (d->Lk % 8 != 0 && !std_prefill_fast_ok(d)) return false;
+  if (d->H > 48 || d->F > 256 || d->r > 32 || !score_rows_aligned(d)) return false;
   return (long long)d->Lq * d->Lk < (1LL << 31);
 }
 
@@ -200,6 +197,7 @@ struct ConcatWs {
   size_t qp, kp, vt, total;
   int Lqp, Lkp;
 };
+bool std_prefill_fast_ok(const lisa_desc* d);
 // The CONCAT pipeline on tiled score tensors: the pipelined scores kernel (up to 32 heads) followed
 // by the matrix-core softmax kernel, which then reads tiles.
 bool concat_tiled_ok(const lisa_desc* d) { return scores_mfma_ok(d) && d->H <= 32 && std_prefill_fast_ok(d); }
@@ -260,7 +258,7 @@ int launch_scores_mfma(const lisa_desc* d, const void* q_lr, const void* k_lr, c
 template <typename T, typename S>
 int launch_lisa_scores(const lisa_desc* d, const void* q_lr, const void* k_lr, KeyStrides ks,
                        const void* prev, const void* w1, const void* w2, void* scores,
-                       float* exact, hipStream_t st) {
+                       float* exact, int row0, int n_rows, hipStream_t st) {
   const int Din = d->mix == LISA_MIX_CONCAT ? 2 * d->H : d->H;
   const size_t lds = has_ffn(d) ? (size_t)(Din + d->F + d->H) * 64 * sizeof(float) : 0;
   auto kern = k_lisa_scores<T, S>;
@@ -269,12 +267,12 @@ int launch_lisa_scores(const lisa_desc* d, const void* q_lr, const void* k_lr, K
                                        (int)lds);
     if (e != hipSuccess) return hip_fail(e);
   }
-  dim3 grid((d->Lk + 63) / 64, d->Lq, d->B);
+  dim3 grid((d->Lk + 63) / 64, n_rows, d->B);
   StageScope prof("k_lisa_scores", st);
   kern<<<grid, 256, lds, st>>>((const T*)q_lr, (const T*)k_lr, ks, (const S*)prev, (const T*)w1,
                                (const T*)w2, (S*)scores, exact, d->H, d->Hkv, d->Lq, d->Lk, d->r, d->F,
                                d->mix, d->act, has_delta(d) ? pick_scale(d->delta_scale, d->r) : 0.f,
-                               d->causal);
+                               d->causal, row0);
   return check_launch();
 }
 
@@ -316,6 +314,9 @@ size_t std_prefill_ws(const lisa_desc* d);
 int run_softmax_given_fast(const lisa_desc* d, const void* given, bool given_half, const void* v, void* out,
                            void* vt_ws, hipStream_t st);
 
+// bf16 layers in float32 arithmetic: scores and softmax by chunks of query rows.
+bool in_chunks(const lisa_desc* d) { return d->dtype == LISA_BF16 && f32_attn_ok(d); }
+
 template <typename T, typename S>
 int run_lisa(const lisa_desc* d, const void* q_lr, const void* k_lr, KeyStrides ks, const void* v,
              KeyStrides vs, const void* prev, const void* w1, const void* w2, void* out,
@@ -338,22 +339,26 @@ int run_lisa(const lisa_desc* d, const void* q_lr, const void* k_lr, KeyStrides 
   }
   // Generic kernels: the softmax reads the unrounded float32 A_n, from the workspace where the score type
   // is half; a float32 layer has it in the score tensor itself.
-  int rc;
   if (d->dtype == LISA_F32 && scores) exact = nullptr;
   const void* an = exact ? (void*)exact : scores;
-  if (f32_scores_ok(d)) rc = run_f32_scores(d, q_lr, k_lr, prev, w1, w2, const_cast<void*>(an), st);
-  else rc = launch_lisa_scores<T, S>(d, q_lr, k_lr, ks, prev, w1, w2, scores, exact, st);
-  if (rc) return rc;
-  // softmax and P V from the float32 scores: on the matrix cores where the standard layer's kernel
-  // fits (it then reads the scores instead of computing Q K^T), else the generic kernel
-  if (std_prefill_fast_ok(d))
-    rc = run_softmax_given_fast(d, exact, false, v, out, (char*)exact + exact_bytes(d), st);
-  else if (f32_attn_ok(d))
-    rc = run_f32_softmax_v(d, an, v, out, st);
-  else
-    rc = launch_softmax_v<T>(d, (const float*)an, v, vs, out, st);
-  if (rc == LISA_OK) g_path = "generic";
-  return rc;
+  const int step = in_chunks(d) ? f32_chunk_rows(d) : d->Lq;
+  for (int row0 = 0; row0 < d->Lq; row0 += step) {
+    const int n_rows = std::min(step, d->Lq - row0);
+    int rc = f32_scores_ok(d) ? run_f32_scores(d, q_lr, k_lr, prev, w1, w2, scores, exact, row0, n_rows, st)
+                              : launch_lisa_scores<T, S>(d, q_lr, k_lr, ks, prev, w1, w2, scores, exact, row0, n_rows, st);
+    if (rc) return rc;
+    // softmax and P V from the float32 scores: on the matrix cores where one of the standard layer's kernels
+    // fits (it then reads the scores instead of computing Q K^T), else the generic kernel
+    if (std_prefill_fast_ok(d))
+      rc = run_softmax_given_fast(d, exact, false, v, out, (char*)exact + exact_bytes(d), st);
+    else if (f32_attn_ok(d))
+      rc = run_f32_softmax_v(d, an, row0, n_rows, v, out, st);
+    else
+      rc = launch_softmax_v<T>(d, (const float*)an, v, vs, out, st);
+    if (rc) return rc;
+  }
+  g_path = "generic";
+  return LISA_OK;
 }
 
 // ---- split-context decode (bf16) -----------------------------------------------------
@@ -474,7 +479,7 @@ int run_decode_fast(const lisa_desc* d, bool lisa_layer, DecodeArgs a, void* out
 bool prefill_fused_ok(const lisa_desc* d) {
   if (d->dtype != LISA_BF16 || d->d_k != 128) return false;
   if (d->mix != LISA_MIX_ADD || (d->act != LISA_ACT_RELU && d->act != LISA_ACT_SILU)) return false;
-  if (d->Lk < 8 || d->F > 128 || d->r > 32) return false;   // (scores are read 8 at a time)
+  if (!score_rows_aligned(d) || d->F > 128 || d->r > 32) return false;
   // 32-bit byte offsets inside one head's scores (tiled: rows and keys rounded up to whole tiles)
   if ((long long)(d->Lq + PF_ROWS) * (d->Lk + PF_TK) >= (1LL << 31)) return false;
   return d->H == 8 || d->H == 16 || d->H == 24 || d->H == 32 || d->H == 40;
@@ -637,7 +642,7 @@ int run_prefill_fused(const lisa_desc* d, const void* q_lr, const void* k_lr, co
 
 // ---- standard layer, prefill, MFMA (bf16) ---------------------------------------------
 bool std_prefill_fast_ok(const lisa_desc* d) {
-  return d->dtype == LISA_BF16 && d->d_k == 128 && d->Lk >= 8 && d->Lq > 1;
+  return d->dtype == LISA_BF16 && d->d_k == 128 && score_rows_aligned(d) && d->Lq > 1;
 }
 
 size_t std_prefill_ws(const lisa_desc* d) {   // V by key chunks
@@ -1057,6 +1062,7 @@ size_t lisa_workspace_bytes(const lisa_desc* desc, int which) {
       if (scores_mfma_ok(desc)) return concat_ws(desc).total;
       if (relu_equivalent(desc, &eq) && scores_mfma_ok(&eq))
         return round_up(concat_ws(&eq).total, 256) + synth_ffn_bytes(desc);
+      if (in_chunks(desc)) return f32_chunk_bytes(desc);
       return exact_bytes(desc) + (std_prefill_fast_ok(desc) ? std_prefill_ws(desc) : 0);
     }
     case LISA_WS_DECODE: {
@@ -1071,6 +1077,7 @@ size_t lisa_workspace_bytes(const lisa_desc* desc, int which) {
       if (check_common(desc) != LISA_OK) return 0;
       // needed only when `out` is requested
       if (std_prefill_fast_ok(desc)) return std_prefill_ws(desc);
+      if (in_chunks(desc)) return 256;                       // (k_f32_attn keeps its scores in registers)
       return decode_fast_ok(desc, false) ? decode_fast_bytes(desc) : exact_bytes(desc);
     case LISA_WS_LAYER: {
       size_t q, k, v;

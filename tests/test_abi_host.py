@@ -131,6 +131,18 @@ def test_decode_workspace_of_the_longest_context_fits_the_shorter_ones(mix, act,
             assert sizes[0] <= (16 << 20), Lk
 
 
+@pytest.mark.parametrize("mix,act", [(lisa.MIX_ADD, lisa.ACT_RELU), (lisa.MIX_ADD, lisa.ACT_SINGLE), (lisa.MIX_CONCAT, lisa.ACT_RELU),
+                                     (lisa.MIX_PLUS, lisa.ACT_RELU), (lisa.MIX_SHARE, lisa.ACT_RELU)])
+def test_prefill_workspace_at_ragged_lengths_is_bounded(mix, act):
+    """Float32 scores of row-major layers at lengths that are no multiple of 8: a chunk of query rows at a time."""
+    for B, H, L in [(1, 32, 777), (4, 32, 4001), (8, 40, 8191)]:
+        d = lisa.make_desc(lisa.BF16, B, H, H, L, L, 128, 22, H if act == lisa.ACT_SINGLE else 64, mix=mix, act=act, write_scores=1)
+        rows16 = 16 * B * H * L * 4
+        need = lisa.workspace_bytes(d, lisa.WS_PREFILL)
+        assert min(B * H * L * L * 4, rows16) <= need <= max(256 << 20, rows16) + 256
+        assert 0 < lisa.workspace_bytes(d, lisa.WS_STD) <= 4096
+
+
 def test_tune_set_accepts_known_knobs_only():
     lib = lisa.library()
     assert lib.lisa_tune_set(lisa.TUNE_PREFILL_SPLIT, 2) == 0
