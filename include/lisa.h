@@ -224,8 +224,10 @@ int lisa_attn_decode_static(const lisa_desc* desc, const void* q_lr, const void*
  *   workspace    at least lisa_stack_workspace_bytes(desc) bytes
  * The call returns after the last launch.  Layers are enqueued by data flow, not one after the other (what
  * does not depend on another layer runs for all of them at once), so a layer's `out` and `score_row` are
- * complete when the call's work on the stream is, not before, and must not be an operand of another
- * layer of the same call.
+ * complete when the call's work on the stream is, not before.
+ * A stack in which an `out` or `score_row` shares memory with another one, or with an operand of any layer,
+ * runs layer by layer instead, as calls of the single layers in this order would (slower).  A sharing
+ * layer's score_row must not be the buffer of the row that it shares (LISA_ERR_SHAPE).
  */
 typedef enum { LISA_LAYER_STD = 0, LISA_LAYER_LISA = 1, LISA_LAYER_SHARE = 2 } lisa_layer_kind;
 typedef struct lisa_stack_layer {

@@ -1460,7 +1460,7 @@ StackWs stack_ws(const lisa_desc* d) {
   stack_descs(d, &sd, &hd);
   StackWs w;
   w.rows = 0;
-  w.layer = round_up(2 * scores_bytes(d), 256);
+  w.layer = 2 * round_up(scores_bytes(d), 256);
   const size_t a = lisa_workspace_bytes(d, LISA_WS_DECODE), b = lisa_workspace_bytes(&hd, LISA_WS_DECODE),
                c = lisa_workspace_bytes(&sd, LISA_WS_STD);
   // (two of them, used in turn: the partial results of a layer wait there for the launch of the
@@ -1468,6 +1468,46 @@ StackWs stack_ws(const lisa_desc* d) {
   w.half = round_up(std::max(a, std::max(b, c)), 256);
   w.total = w.layer + std::max(2 * w.half, stack_chained_ok(d) ? stack_chained_bytes(d) : 0);
   return w;
+}
+
+// Whether a result of the stack shares memory with another result or with an operand.  By data flow the results of
+// many layers are written at once: such a stack has to run layer by layer.  (Sorted results and a search per
+// operand: 0.3 us for 32 layers.  A stack of more than kMaxSorted layers counts as one that shares.)
+bool stack_shares_memory(const lisa_desc* d, const lisa_stack_layer* layers, int n_layers) {
+  constexpr int kMaxSorted = 256;
+  if (n_layers > kMaxSorted) return true;
+  struct Range { uintptr_t lo, hi; };
+  Range res[2 * kMaxSorted];
+  int n_res = 0;
+  const size_t heads = (size_t)d->B * d->H, kv_heads = (size_t)d->B * d->Hkv, es = score_elem(d);
+  const size_t out = heads * d->d_k * (d->out_f32 ? sizeof(float) : es), row = scores_bytes(d);
+  auto range = [](const void* p, size_t bytes) { return Range{(uintptr_t)p, (uintptr_t)p + bytes}; };
+  for (int n = 0; n < n_layers; ++n) {
+    res[n_res++] = range(layers[n].out, out);
+    if (layers[n].score_row) res[n_res++] = range(layers[n].score_row, row);
+  }
+  std::sort(res, res + n_res, [](const Range& x, const Range& y) { return x.lo < y.lo; });
+  for (int i = 1; i < n_res; ++i)
+    if (res[i].lo < res[i - 1].hi) return true;
+  // (the results are disjoint now: the last one that starts below an operand's end is the one to look at)
+  auto meets = [&](const void* p, size_t bytes) {
+    const Range x = range(p, bytes);
+    if (!p || x.hi <= res[0].lo || x.lo >= res[n_res - 1].hi) return false;
+    const Range* at = std::lower_bound(res, res + n_res, x.hi, [](const Range& r, uintptr_t hi) { return r.lo < hi; });
+    return at > res && at[-1].hi > x.lo;
+  };
+  const size_t kv = kv_heads * d->Lmax * es, w2 = (size_t)d->F * d->H * es;
+  const size_t w1 = d->mix == LISA_MIX_CONCAT ? 2 * w2 : w2;
+  for (int n = 0; n < n_layers; ++n) {
+    const lisa_stack_layer& ly = layers[n];
+    if (meets(ly.v_cache, kv * d->d_k)) return true;
+    if (ly.kind == LISA_LAYER_SHARE) continue;
+    const bool lisa_layer = ly.kind == LISA_LAYER_LISA;
+    const size_t width = lisa_layer ? d->r : d->d_k;
+    if (meets(ly.q, heads * width * es) || meets(ly.k_cache, kv * width)) return true;
+    if (lisa_layer && ((has_ffn(d) && meets(ly.w1, w1)) || (has_w2(d) && meets(ly.w2, w2)))) return true;
+  }
+  return false;
 }
 }  // namespace
 
@@ -1484,6 +1524,7 @@ int lisa_decode_stack(const lisa_desc* desc, const lisa_stack_layer* layers, int
   if (n_layers < 1) return LISA_ERR_SHAPE;
   if (desc->mix == LISA_MIX_SHARE) return LISA_ERR_SHAPE;   // (direct sharing is a kind of layer, not of stack)
   // the whole stack is checked on the host before the first launch
+  const void* shared_row = nullptr;                          // the caller's, where A_{n-1} is in one
   for (int n = 0; n < n_layers; ++n) {
     const lisa_stack_layer& ly = layers[n];
     if (ly.kind < LISA_LAYER_STD || ly.kind > LISA_LAYER_SHARE) return LISA_ERR_SHAPE;
@@ -1494,6 +1535,8 @@ int lisa_decode_stack(const lisa_desc* desc, const lisa_stack_layer* layers, int
     const void* ptrs[] = {ly.q, ly.k_cache, ly.v_cache, ly.w1, ly.w2, ly.out, ly.score_row};
     for (const void* p : ptrs)
       if (p && !aligned16(p)) return LISA_ERR_ALIGN;
+    if (ly.kind != LISA_LAYER_STD && ly.score_row && ly.score_row == shared_row) return LISA_ERR_SHAPE;
+    if (ly.kind != LISA_LAYER_SHARE || ly.score_row) shared_row = ly.score_row;
   }
   if (!workspace) return LISA_ERR_WORKSPACE;
   if (!aligned16(workspace)) return LISA_ERR_ALIGN;
@@ -1502,17 +1545,18 @@ int lisa_decode_stack(const lisa_desc* desc, const lisa_stack_layer* layers, int
   lisa_desc std_d, share_d;
   stack_descs(desc, &std_d, &share_d);
   char* ws = (char*)workspace;
-  void* own[2] = {ws + w.rows, ws + w.rows + scores_bytes(desc)};
+  void* own[2] = {ws + w.rows, ws + w.rows + round_up(scores_bytes(desc), 256)};
   const size_t lws_bytes = w.half;
   const void* cur = nullptr;                                 // the row A_{n-1} that the next layer may share
   hipStream_t st = (hipStream_t)hip_stream;
-  if (stack_chained_ok(desc)) {                              // ADD-form stacks: by data flow, not layer by layer
+  const bool in_order = stack_shares_memory(desc, layers, n_layers);
+  if (!in_order && stack_chained_ok(desc)) {                 // ADD-form stacks: by data flow, not layer by layer
     rc = run_stack_chained(desc, layers, n_layers, own, ws + w.layer, st);
     if (rc == LISA_OK) g_path = "decode_split";
     return rc;
   }
   g_dc = DeferredCombine{};
-  g_dc.on = true;
+  g_dc.on = !in_order;                                       // (a combine left to the next launch would write beside its reads)
   for (int n = 0; n < n_layers && rc == LISA_OK; ++n) {
     const lisa_stack_layer& ly = layers[n];
     void* lws = ws + w.layer + (n & 1) * w.half;

@@ -353,6 +353,10 @@ def test_decode_stack_rejects_bad_stacks_before_any_launch():
     assert call([layer(lisa.LAYER_STD), layer(7)]) == -2                    # unknown kind
     assert call([layer(lisa.LAYER_STD), layer(lisa.LAYER_LISA, w1=None)]) == -1
     assert call([layer(lisa.LAYER_STD, v_cache=None)]) == -1
+    # a row written over the one it is made from, also through layers that keep none
+    std_row = layer(lisa.LAYER_STD, score_row=P[7])
+    assert call([std_row, layer(lisa.LAYER_LISA, score_row=P[7])]) == -2
+    assert call([std_row, layer(lisa.LAYER_SHARE), layer(lisa.LAYER_SHARE, score_row=P[7])]) == -2
     assert call([layer(lisa.LAYER_STD), layer(lisa.LAYER_SHARE, out=ODD)]) == -4
     assert call([layer(lisa.LAYER_STD)], ws=None) == -5
     assert call([layer(lisa.LAYER_STD)], wsb=64) == -5

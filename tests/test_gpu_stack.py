@@ -40,6 +40,38 @@ def test_decode_stack_sizes(case):
     run_pattern_stack(stk, kinds, list(range(B)), dim_major=dim_major, Lmax=Lmax)
 
 
+@pytest.mark.parametrize("ctx", [200, 700])
+def test_stack_whose_layers_share_result_buffers(ctx):
+    """Two score rows used in turn and one output for all layers: what the single calls leave in this order."""
+    H, Hkv, dk, r, F, B, Lk = 8, 4, 128, 22, 32, 2, ctx + 1
+    log(f"[case] stack with shared result buffers, ctx {ctx}")
+    stk = synth.DecodeStack("shared", "bf16", B, H, Hkv, ctx, 256, dk, r, F, len(MIXED), 1)
+    code = {pt.STD: lisa.LAYER_STD, pt.LISA: lisa.LAYER_LISA, pt.SHARE: lisa.LAYER_SHARE}
+    rows = [torch.empty((B, H, Lk), dtype=torch.float16, device=DEV) for _ in range(4)]
+    outs = [torch.empty((B, H, dk), dtype=torch.float32, device=DEV) for _ in range(2)]
+    layers = []
+    for n, kind in enumerate(MIXED):
+        ly = synth.make_decode_layer(stk, n, device=DEV, kind=kind)
+        rec = dict(kind=code[kind], v_cache=ly["v_cache"], out=outs[0], score_row=rows[n % 2])
+        if kind == pt.STD:
+            rec.update(q=ly["q"], k_cache=ly["k_cache"])
+            lisa.std_attn_decode(ly["q"], ly["k_cache"], ly["v_cache"], Lk, out=outs[1], score_row_out=rows[2 + n % 2])
+        elif kind == pt.LISA:
+            rec.update(q=ly["q_lr"], k_cache=ly["k_lr_cache"], w1=ly["w1"], w2=ly["w2"])
+            lisa.lisa_attn_decode(ly["q_lr"], ly["k_lr_cache"], ly["v_cache"], Lk, rows[2 + (n + 1) % 2], ly["w1"], ly["w2"],
+                                  out=outs[1], score_row_out=rows[2 + n % 2], write_scores=True)
+        else:
+            lisa.lisa_attn_decode(None, None, ly["v_cache"], Lk, rows[2 + (n + 1) % 2], None, None, mix=lisa.MIX_SHARE,
+                                  out=outs[1], score_row_out=rows[2 + n % 2], write_scores=True)
+        layers.append(rec)
+    stack = lisa.DecodeStack(layers, Lk, r=r, F=F)
+    for _ in range(2):
+        stack.step()
+        torch.cuda.synchronize()
+        assert torch.equal(outs[0], outs[1])
+        assert torch.equal(rows[0], rows[2]) and torch.equal(rows[1], rows[3])
+
+
 SINGLE = [  # H, Hkv, ctx, d_k, r, F, B, concat: one workgroup's keys and one more; many spans; both forms of the V stream
     (8, 8, 511, 128, 22, 16, 1, False), (8, 2, 512, 128, 22, 16, 2, False), (16, 4, 1030, 64, 20, 64, 1, True),
     (8, 4, 5000, 128, 11, 40, 1, False), (32, 32, 600, 128, 20, 256, 8, True), (40, 40, 513, 128, 22, 80, 7, False)]
