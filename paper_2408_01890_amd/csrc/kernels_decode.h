@@ -15,6 +15,8 @@
 // The V (and, for a standard layer, K) stream is read with 16-byte loads, 8 features per lane,
 // 64 / (d_k / 8) keys per wave instruction, so every wave instruction covers 1 KB contiguous.
 #pragma once
+#include <cfloat>
+
 #include "kernels_generic.h"
 #include "mfma_ffn.h"
 
@@ -363,7 +365,8 @@ void k_decode_part(DecodeArgs a) {
       if (va) ro[lane] = f32_to_half_sat(sa);
       if (vb) ro[lane + 64] = f32_to_half_sat(sb);
     }
-    const float m = wave_max(fmaxf(sa, sb));
+    // (finite: a chunk masked with -inf throughout weighs nothing)
+    const float m = wave_max(fmaxf(fmaxf(sa, sb), -FLT_MAX));
     const float pa = va ? __expf(sa - m) : 0.f, pb = vb ? __expf(sb - m) : 0.f;
     const float s = wave_sum(pa + pb);
     row[lane] = pa;

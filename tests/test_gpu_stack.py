@@ -107,6 +107,7 @@ def test_single_layer_decode_spans(case):
     (8, 2, 64, 1500, 2, (0, 1100)),     # a whole workgroup's keys, merged with the next one's
     (8, 8, 128, 700, 1, (512, 700)),    # the last workgroup's
     (32, 32, 128, 2100, 4, (100, 400)),  # the long stream: 128 keys per wave
+    (32, 1, 128, 16500, 8, (300, 1000)),  # scratch beyond 16 MB: k_decode_part, chunks of 128 keys
 ])
 def test_masked_keys_weigh_nothing(H, Hkv, dk, Lk, B, masked):
     """Keys whose shared score is -inf (padding in front of a prompt) over whole pieces of the split."""
@@ -116,8 +117,7 @@ def test_masked_keys_weigh_nothing(H, Hkv, dk, Lk, B, masked):
     row[..., masked[0]:masked[1]] = float("-inf")
     v = torch.randn((B, Hkv, Lk, dk), generator=g).to(torch.bfloat16)
     out, _ = lisa.lisa_attn_decode(None, None, v.to(DEV), Lk, row.to(DEV), None, None, mix=lisa.MIX_SHARE)
-    vh = v.double().repeat_interleave(H // Hkv, dim=1)
-    ref = (torch.softmax(row.double(), -1)[..., None] * vh).sum(2)
+    ref = (torch.softmax(row.double(), -1).reshape(B, Hkv, H // Hkv, Lk) @ v.double()).reshape(B, H, dk)
     # float32 sums of exact products; the result leaves as the output type of the call
     tol = 1e-5 if out.dtype == torch.float32 else hp.TOL[torch.bfloat16]
     err = (out.double().cpu() - ref).norm(dim=-1) / ref.norm(dim=-1)
