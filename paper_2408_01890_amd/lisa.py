@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes as C
 import math
 import os
+import struct
 import threading
 from typing import Optional
 
@@ -162,24 +163,37 @@ def make_desc(dtype, B, H, Hkv, Lq, Lk, d_k, r=0, F=0, mix=MIX_ADD, act=ACT_RELU
 # Descriptors and workspace sizes of the calls a thread makes, by what they are made from: a serving loop
 # makes the same few calls over and over, and building the two takes longer than a short kernel runs.
 # Per thread, because the geometry overrides of lisa_tune_set() (which change workspace sizes) are.
+# The key is packed numbers: the arguments themselves would not do, as a tensor that a caller counts its tokens in is
+# the same key after `n += 1`, and 100.0, which no size may be, equals 100.
 _local = threading.local()
 _MAX_PLANS = 256
+_PLAN_KEY = struct.Struct("=10q2d6q")
 
 
-def _plan(which, *key):
-    """(reference to the descriptor made by make_desc(*key), its workspace bytes for `which`)"""
+def _plan(which, dtype, B, H, Hkv, Lq, Lk, d_k, r, F, mix, act, delta_scale, std_scale, causal, write_scores=0,
+          kcache_dim_major=0, Lmax=0, out_f32=0, score_tiled=0):
+    """(reference to the descriptor that make_desc() makes of the arguments, its workspace bytes for `which`)"""
+    args = (B, H, Hkv, Lq, Lk, d_k, r, F, mix, act, delta_scale, std_scale, causal, write_scores, kcache_dim_major, Lmax,
+            out_f32, score_tiled)
+    try:
+        key = which, dtype, _PLAN_KEY.pack(*args)
+    except (struct.error, TypeError, ValueError):
+        return _make_plan(which, dtype, args)               # (make_desc() says what it does not take)
     try:
         plans = _local.plans
     except AttributeError:
         plans = _local.plans = {}
-    key = (which,) + key
     plan = plans.get(key)
     if plan is None:
         if len(plans) >= _MAX_PLANS:
             plans.clear()
-        desc = make_desc(*key[1:])
-        plan = plans[key] = (C.byref(desc), workspace_bytes(desc, which) if which is not None else 0)
+        plan = plans[key] = _make_plan(which, dtype, args)
     return plan
+
+
+def _make_plan(which, dtype, args):
+    desc = make_desc(dtype, *args)
+    return C.byref(desc), workspace_bytes(desc, which) if which is not None else 0
 
 
 TILE_ROWS, TILE_KEYS = 16, 32

@@ -424,3 +424,24 @@ def test_reference_kernels_reject_bad_arguments_before_any_launch():
     assert lib.lisa_probe_mfma(0, 10, 16, None, None) == -1
     assert lib.lisa_probe_mfma(0, 0, 16, FAKE, None) == -2
     assert lib.lisa_probe_mfma(1, 10, 1 << 20, FAKE, None) == -2
+
+
+def test_plans_are_kept_by_value():
+    """The descriptors that a thread keeps follow what they are made from: a length counted in a tensor or an array
+    that changes in place, equal values of types that a size may not have, geometry overrides."""
+    import numpy as np
+    import torch
+
+    def plan(Lk):
+        ref, need = lisa._plan(lisa.WS_DECODE, torch.bfloat16, 1, 8, 8, 1, Lk, 128, 22, 32, 0, 0, 0.0, 0.0, 1, 1, 0, 4096)
+        desc = ref._obj
+        assert need == lisa.workspace_bytes(desc, lisa.WS_DECODE) > 0
+        return desc.Lk
+
+    for n in (torch.tensor(100), np.array(100), np.int64(100), 100):
+        for _ in range(3):
+            assert plan(n) == int(n)
+            n += 1000
+    assert plan(100) == plan(100) == 100
+    with pytest.raises(TypeError):
+        plan(100.0)
