@@ -47,6 +47,7 @@ struct DecodeArgs {
   const float* cmb_ml;
   void* cmb_out;
   int cmb_units, cmb_H, cmb_nchunk, cmb_out_f32;
+  int pass_through;      // the module is the identity: mask_to_finite(prev)
   int w_ready;           // the FFN weights are in the workspace already (run_decode_spread)
 };
 
@@ -342,6 +343,9 @@ void k_decode_part(DecodeArgs a) {
           const int ch = 32 * ks + 8 * g + e;
           x[0][ks][e] = (ch < H && j < Lk) ? xpre[q][ks][e] : (_Float16)0.f;
         }
+      if (a.pass_through)
+#pragma unroll
+        for (int ks = 0; ks < MfmaFfn<HB, FS, HB, ACT>::KS; ++ks) x[0][ks] = mask_to_finite(x[0][ks]);
       f32x4 y[1][HB];
       ffn.template apply<1>(x, y);
 #pragma unroll

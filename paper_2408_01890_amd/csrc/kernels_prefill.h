@@ -80,6 +80,7 @@ struct PrefillArgs {
   int pair;               // workgroup x takes the units (last - x) and x
   int B;                  // sequences
   int tiled;              // prev and scores are [B,ceil(Lq/16),ceil(Lk/32),H,16,32] (1 KB per head and tile)
+  int pass_through;       // ACT 2 (host side)
 };
 
 typedef unsigned short pf_u16x8 __attribute__((ext_vector_type(8)));
@@ -449,7 +450,11 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
     auto store_x = [&](const pf_u32x4 (&xr)[XCH], int tile) {   // XSTG: into the buffer of the tile's parity
       unsigned char* dst = xs + (XSTG ? (tile & 1) * (H * PF_XS_HEAD) : 0) + xdst;
 #pragma unroll
-      for (int u = 0; u < XCH; ++u) *(pf_u32x4*)(dst + u * ((XSTG ? 1 : NW) * PF_XS_HEAD)) = xr[u];
+      for (int u = 0; u < XCH; ++u) {
+        pf_u32x4 x = xr[u];
+        if (ACT == 2) x = __builtin_bit_cast(pf_u32x4, mask_to_finite(__builtin_bit_cast(f16x8, x)));
+        *(pf_u32x4*)(dst + u * ((XSTG ? 1 : NW) * PF_XS_HEAD)) = x;
+      }
     };
 
     // ---- per-head, per-slice state of stage B ---------------------------------------------------------

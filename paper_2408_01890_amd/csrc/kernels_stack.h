@@ -317,6 +317,7 @@ struct DecodeScoresArgs {
   const unsigned short* w;   // FFN weights in operand order (ffn_operand_piece<false>)
   float scale;
   int n_done;             // counters to clear for k_stack_pv
+  int pass_through;       // the module is the identity: mask_to_finite(prev)
 };
 constexpr int DS_KEYS = 64;
 constexpr int DS_ROW = DS_KEYS + 4;                          // floats per head of the a_delta tile
@@ -410,6 +411,9 @@ __global__ __launch_bounds__(256) void k_decode_scores(DecodeScoresArgs a) {
       if (CONCAT && ch >= H) x[0][ks][e] = ch < Din ? f32_to_half_sat(a_s[(ch - H) * DS_ROW + pj]) : (_Float16)0.f;
       else if (ch >= Din) x[0][ks][e] = (_Float16)0.f;
     }
+  if (!CONCAT && a.pass_through)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) x[0][ks] = mask_to_finite(x[0][ks]);
   f32x4 y[1][HBO];
   if (CONCAT) Ffn::template apply_lds_lean<1>(w_s, x, y);
   else Ffn::template apply_lds<1>(w_s, x, y);

@@ -280,7 +280,8 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
         for (int v = 1; v < 16; ++v) mx = fmaxf(mx, an[v]);
         mx = halves_max(mx);
         const float m_new = fmaxf(m_run, mx);
-        const float m2 = m_new * LOG2E;
+        // (given scores may be -inf, masked: no key seen yet, every p is 0)
+        const float m2 = GIVEN && m_new == -INFINITY ? 0.f : m_new * LOG2E;
         const float alpha = fast_exp2(m_run * LOG2E - m2);
         m_run = m_new;
         float ps = 0.f;
@@ -319,7 +320,8 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
 
     if (WITH_V) {
       // O[row][h][32 db + 8 (v/4) + 4 half + v%4] = o[db][v] / l
-      const float inv = 1.f / halves_sum(l_run);
+      const float l = halves_sum(l_run);
+      const float inv = GIVEN && l == 0.f ? 0.f : 1.f / l;   // (a row that sees nothing gives zeros)
       if (i0 + r < Lq) {
         const size_t at = (((size_t)b * Lq + i0 + r) * H + h) * DK + 4 * half;
 #pragma unroll

@@ -376,6 +376,7 @@ int run_decode_spread(const lisa_desc* d, bool lisa_layer, const DecodeArgs& da,
       if ((rc = check_launch())) return rc;
     }
     a.scale = pick_scale(d->delta_scale, d->r);
+    a.pass_through = da.pass_through;
     a.n_done = d->B * d->H;
     if ((rc = launch_decode_scores(d, a, st))) return rc;
   }

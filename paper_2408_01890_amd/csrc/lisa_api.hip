@@ -574,7 +574,7 @@ PrefillWs prefill_fused_ws(const lisa_desc* d) {
 
 int run_prefill_fused(const lisa_desc* d, const void* q_lr, const void* k_lr, const void* v,
                       const void* prev, const void* w1, const void* w2, void* out, void* scores,
-                      void* workspace, hipStream_t st) {
+                      void* workspace, bool pass_through, hipStream_t st) {
   const PrefillWs w = prefill_fused_ws(d);
   const PrefillGeom& geo = w.geom;
   char* ws = (char*)workspace;
@@ -598,6 +598,7 @@ int run_prefill_fused(const lisa_desc* d, const void* q_lr, const void* k_lr, co
   a.causal = d->causal;
   a.out_f32 = d->out_f32;
   a.tiled = d->score_tiled;
+  a.pass_through = pass_through;
   a.dscale = pick_scale(d->delta_scale, d->r);
   a.split = geo.split;
   a.pair = geo.pair;
@@ -1301,14 +1302,14 @@ int lisa_attn_prefill(const lisa_desc* desc, const void* q_lr, const void* k_lr,
   const KeyStrides ks = dense_keys(desc, desc->Lk, desc->r);
   const KeyStrides vs = dense_keys(desc, desc->Lk, desc->d_k);
   if (prefill_fused_ok(desc))
-    return run_prefill_fused(desc, q_lr, k_lr, v, scores_prev, w1, w2, out, scores, workspace, st);
+    return run_prefill_fused(desc, q_lr, k_lr, v, scores_prev, w1, w2, out, scores, workspace, false, st);
   lisa_desc eq;
   if (relu_equivalent(desc, &eq) && prefill_fused_ok(&eq)) {
     const void *w1e, *w2e;
     rc = synth_relu_ffn(desc, w1, workspace, round_up(prefill_fused_ws(&eq).total, 256), &w1e, &w2e, &q_lr, &k_lr,
                         st);
     if (rc) return rc;
-    return run_prefill_fused(&eq, q_lr, k_lr, v, scores_prev, w1e, w2e, out, scores, workspace, st);
+    return run_prefill_fused(&eq, q_lr, k_lr, v, scores_prev, w1e, w2e, out, scores, workspace, !has_ffn(desc), st);
   }
   // tiles are read and written by the fused kernels and by the matrix-core CONCAT pipeline alone
   if (desc->score_tiled && !concat_tiled_ok(desc) && !(relu_equivalent(desc, &eq) && concat_tiled_ok(&eq)))
@@ -1393,6 +1394,7 @@ static int run_attn_decode(const lisa_desc* desc, const void* q_lr, const void* 
     a.w1 = (const bf16_t*)w1;
     a.w2 = (const bf16_t*)w2;
     a.row_out = (half_t*)scores;
+    a.pass_through = !has_ffn(desc);
     a.w_ready = w_ready;
     return run_decode_fast(eff, true, a, out, workspace, st);
   }

@@ -38,6 +38,15 @@ __device__ __forceinline__ unsigned short half_bits(float f) {
   return __builtin_bit_cast(unsigned short, h);
 }
 
+// A layer without an alignment module passes A_{n-1} through these products as I (x)+ - I (-x)+, where a score masked
+// with -inf would make 0 * inf of every other head's: there it enters as the lowest finite half, which is also what
+// an emitted score of -inf is.
+__device__ __forceinline__ f16x8 mask_to_finite(f16x8 x) {
+  const f16x8 lowest = {(_Float16)-65504.f, (_Float16)-65504.f, (_Float16)-65504.f, (_Float16)-65504.f,
+                        (_Float16)-65504.f, (_Float16)-65504.f, (_Float16)-65504.f, (_Float16)-65504.f};
+  return __builtin_elementwise_max(x, lowest);
+}
+
 // The weights of a network in operand order, made once per call by whichever launch comes first instead of by
 // every workgroup: piece idx = (operand, lane), 8 halves each; operands W1 (hidden block fb, k-step ks), then W2
 // (output block hb, k-step s).  Same image as MfmaFfn::stage().
@@ -75,14 +84,14 @@ __device__ __forceinline__ void ffn_operand_piece(const FfnOperands& w, int idx)
 // FS = ceil(F / 32) hidden k-steps (2 FS hidden blocks of 16), HBO = blocks of 16 output heads
 // (the caller may ask for a sub-range of the H output heads: h_first .. h_first + n_out - 1).
 // ACT: activation of the hidden units, 0 = ReLU (Sec. 5.3), 1 = SiLU u * sigmoid(u) (ablated in
-// Sec. 5.7); both saturate at the half range.
+// Sec. 5.7); both saturate at the half range.  2 = ReLU, of a module that is the identity (see mask_to_finite).
 template <int HB, int FS, int HBO = HB, int ACT = 0>
 struct MfmaFfn {
   static constexpr int KS = (HB + 1) / 2;
   static constexpr int FB = 2 * FS;
 
   static __device__ __forceinline__ _Float16 activate(float u) {
-    if (ACT == 0) return (_Float16)__builtin_amdgcn_fmed3f(u, 0.f, 65504.f);
+    if (ACT != 1) return (_Float16)__builtin_amdgcn_fmed3f(u, 0.f, 65504.f);
     // exp2(-u log2 e) overflows to +inf for very negative u: 1 / inf = 0 and the product is -0
     const float sg = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * u));
     return (_Float16)fminf(u * sg, 65504.f);

@@ -15,6 +15,9 @@ CASES = [  # dtype, H, Hkv, L, d_k, pad
     ("f32", 4, 2, 33, 128, 17),
     ("bf16", 8, 8, 130, 128, 70),        # rows of ragged length: float32 arithmetic
     ("bf16", 12, 4, 77, 128, 32),
+    ("bf16", 8, 8, 136, 128, 70),        # the fused kernel
+    ("bf16", 32, 8, 160, 128, 64),
+    ("bf16", 12, 4, 128, 128, 64),       # generic scores, softmax on the matrix cores
 ]
 
 
@@ -33,7 +36,7 @@ def masked_layer(dtype, H, Hkv, L, dk, pad, mix, tiled=False):
         kx = k_lr.double().cpu().repeat_interleave(H // Hkv, dim=1)
         delta = (q_lr.double().cpu() @ kx.transpose(-1, -2).contiguous()) / 20 ** 0.5
     given = lisa.tile_scores(prev) if tiled else prev
-    out, scores = lisa.lisa_attn_prefill(q_lr, k_lr, v, given, None, None, mix=mix, tiled=tiled)
+    out, scores = lisa.lisa_attn_prefill(q_lr, k_lr, v, given, None, None, mix=mix, tiled=tiled, Lq=L)
     torch.cuda.synchronize()
     return out, lisa.untile_scores(scores, L, L) if tiled else scores, prev, v, delta
 
@@ -60,4 +63,28 @@ def check_masked(out, scores, prev, v, delta, tol, zeros):
 def test_masked_keys_weigh_nothing(case, mix):
     dtype, H, Hkv, L, dk, pad = case
     log(f"[case] masked prefill {case} mix={mix}")
-    check_masked(*masked_layer(dtype, H, Hkv, L, dk, pad, mix), tol=1e-5 if dtype == "f32" else 2e-2, zeros=dtype == "f32" or L % 8 != 0)
+    check_masked(*masked_layer(dtype, H, Hkv, L, dk, pad, mix), tol=1e-5 if dtype == "f32" else 2e-2, zeros=dtype == "f32" or L % 8 != 0 or H == 12)
+
+
+@pytest.mark.parametrize("mix", [lisa.MIX_SHARE, lisa.MIX_PLUS], ids=["share", "plus"])
+def test_masked_keys_weigh_nothing_on_tiled_scores(mix):
+    log(f"[case] masked prefill, tiled, mix={mix}")
+    check_masked(*masked_layer("bf16", 16, 4, 200, 128, 70, mix, tiled=True), tol=2e-2, zeros=False)
+
+
+@pytest.mark.parametrize("H,B,Lk", [(8, 2, 300), (16, 1, 1100), (32, 40, 2300)])   # (the last: beyond 16 MB of scratch)
+def test_masked_keys_weigh_nothing_in_a_decode_step(H, B, Lk):
+    """LiSA_plus: the row of the layer before plus the low-rank correction."""
+    log(f"[case] masked decode, LiSA_plus, {H} {B} {Lk}")
+    g = torch.Generator(device=DEV).manual_seed(32)
+    dt, r, dk, Lmax = torch.bfloat16, 20, 128, (Lk + 7) // 8 * 8
+    prev = torch.randn((B, H, Lk), generator=g, device=DEV).half()
+    prev[..., 30:290] = float("-inf")
+    v = torch.randn((B, 1, Lmax, dk), generator=g, device=DEV).to(dt)
+    q_lr = torch.randn((B, H, r), generator=g, device=DEV).to(dt)
+    k_lr = torch.randn((B, 1, r, Lmax), generator=g, device=DEV).to(dt)
+    out, _ = lisa.lisa_attn_decode(q_lr, k_lr, v, Lk, prev, None, None, mix=lisa.MIX_PLUS)
+    a = prev.double().cpu() + (q_lr.double().cpu() @ k_lr[:, 0].double().cpu())[..., :Lk] / r ** 0.5
+    ref = torch.softmax(a, -1) @ v[:, 0, :Lk].double().cpu()
+    err = (out.double().cpu() - ref).norm(dim=-1) / ref.norm(dim=-1)
+    assert torch.isfinite(out).all() and float(err.max()) <= 2e-2
