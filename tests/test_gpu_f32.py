@@ -1,5 +1,6 @@
-"""float32 prefill layers at the edges of their tiles (16 query rows, 16 keys, four waves of key tiles; 64
-keys per lane group in the scores kernel): every row against the float64 oracle at 1e-5."""
+"""float32 prefill layers at the edges of their tiles (attention: 16 query rows, the 16-key tiles dealt to four waves;
+scores: tiles of 16 rows x 16 keys, runs of them in a workgroup where there are many), against the float64
+oracle at 1e-5."""
 import numpy as np
 import pytest
 import torch
@@ -51,6 +52,29 @@ def test_f32_layers(case):
                                       hp.f64(inp["w2"]), rows, hp.gather_score_rows(a0, b, rows))
         assert hp.scores_row_rel_err(hp.gather_score_rows(a1, b, rows), a_ref, rows, Lq, Lk) <= TOL
         assert hp.row_rel_err(hp.gather_out_rows(o1, b, rows), o_ref) <= TOL
+
+
+@pytest.mark.parametrize("B,H,L,F,silu", [
+    (1, 4, 897, 16, False),      # 57 x 57 tiles: runs of two, the last one clipped
+    (3, 4, 900, 16, True),       # runs of six that share the staged weights
+    (1, 8, 50, 33, True),
+    (1, 32, 40, 128, True),      # weights that do not fit the LDS beside A_delta: the generic scores kernel
+])
+def test_f32_scores_in_runs_of_tiles(B, H, L, F, silu):
+    log(f"[case] f32 scores B{B} H{H} {L} F{F} silu={silu}")
+    cfg = synth.LayerShape(f"f32_runs_{L}", "f32", B, H, H, L, 128, 64, 11, F)
+    inp = synth.make_prefill_inputs(cfg, 500 + L, DEV, ffn="fan_in", std_layer=False)
+    g = torch.Generator(device=DEV).manual_seed(23)
+    prev = torch.randn((B, H, L, L), generator=g, device=DEV)
+    out, scores = lisa.lisa_attn_prefill(inp["q_lr"], inp["k_lr"], inp["v"], prev, inp["w1"], inp["w2"],
+                                         act=lisa.ACT_SILU if silu else lisa.ACT_RELU)
+    torch.cuda.synchronize()
+    rows = np.unique(np.clip([0, 15, 16, 31, 47, 95, 447, 448, L - 17, L - 2, L - 1], 0, L - 1))
+    for b in range(B):
+        a_ref, o_ref = cref.lisa_rows(*(hp.f64(inp[n][b]) for n in ("q_lr", "k_lr", "v")), hp.f64(inp["w1"]), hp.f64(inp["w2"]),
+                                      rows, hp.gather_score_rows(prev, b, rows), act=cref.ACT_SILU if silu else cref.ACT_RELU)
+        assert hp.scores_row_rel_err(hp.gather_score_rows(scores, b, rows), a_ref, rows, L, L) <= TOL
+        assert hp.row_rel_err(hp.gather_out_rows(out, b, rows), o_ref) <= TOL
 
 
 def _rows_err(out, scores, v, Lq):

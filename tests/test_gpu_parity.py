@@ -682,7 +682,11 @@ def run_pattern_stack(stk, kinds, sample_b, dim_major=True, Lmax=None):
     kept = lisa.DecodeStack(layers, Lk, r=stk.r, F=stk.F, dim_major=dim_major, keep_rows=True)
     lean = lisa.DecodeStack(layers, Lk, r=stk.r, F=stk.F, dim_major=dim_major, keep_rows=False)
     outs_k = kept.step()
-    outs_l = lean.step()
+    outs_l = [o.clone() for o in lean.step()]
+    for o in lean.outs:
+        o.zero_()
+    for n, o in enumerate(lean.step()):                      # (a second step on what the first left in the workspace)
+        assert torch.equal(o, outs_l[n]), f"layer {n}: the second step differs"
     torch.cuda.synchronize()
     tol = hp.TOL[stk.torch_dtype]
     worst = 0.0

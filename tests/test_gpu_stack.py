@@ -19,15 +19,22 @@ LONG = (pt.STD,) + (pt.LISA,) * 49 + (pt.STD,)
 LONG_SHARE = (pt.STD, pt.LISA) + (pt.SHARE,) * 96 + (pt.LISA, pt.SHARE, pt.STD)
 
 CASES = [  # H, Hkv, ctx, d_k, r, F, B, Lmax, dim_major, kinds
-    (8, 8, 15, 128, 22, 16, 1, 16, True, MIXED),       # one split, one block of positions
-    (8, 4, 127, 128, 7, 32, 2, 128, True, MIXED),      # exactly one split; odd rank; two heads per kv head
-    (40, 40, 128, 128, 22, 80, 1, 131, True, MIXED),   # one key in the second split; rows that are not 16-byte aligned
+    (8, 8, 15, 128, 22, 16, 1, 16, True, MIXED),       # one block of 16 positions
+    (8, 4, 127, 128, 7, 32, 2, 128, True, MIXED),      # exactly one block of 128 keys; odd rank; two heads per kv head
+    (40, 40, 128, 128, 22, 80, 1, 131, True, MIXED),   # one key in the second block; rows that are not 16-byte aligned
+    # few workgroups, so that the last one of an output merges its spans (512 keys of d_k = 128, 1024 of 64)
+    (8, 8, 511, 128, 22, 16, 1, 512, True, MIXED),     # exactly one span
+    (8, 8, 512, 128, 22, 16, 1, 520, True, MIXED),     # one key in the second
+    (8, 2, 1500, 128, 11, 32, 2, 1504, True, MIXED),   # three spans, four heads per kv head
+    (8, 8, 1023, 64, 20, 16, 1, 1024, True, MIXED),
+    (8, 4, 1024, 64, 20, 16, 1, 1025, False, MIXED),
     (16, 4, 300, 64, 20, 33, 2, 320, False, MIXED),    # row-major K_LR, d_k = 64, four heads per kv head
     (40, 8, 257, 128, 22, 80, 1, 264, True, MIXED),    # five heads per kv head
     (64, 2, 64, 64, 16, 128, 1, 72, True, MIXED),      # widest chain; 32 heads per kv head
     (33, 33, 40, 64, 3, 100, 1, 48, True, MIXED),      # heads in a block of their own
     (8, 8, 20, 64, 12, 16, 1, 24, True, LONG),
     (8, 8, 140, 64, 12, 16, 1, 144, True, LONG_SHARE),
+    (8, 2, 700, 128, 12, 16, 1, 704, True, LONG_SHARE),   # two spans: counters, then a group of sharing layers alone, which has none
 ]
 
 
