@@ -51,7 +51,8 @@ size_t stack_chained_bytes(const lisa_desc* d);
 // Scratch of a single layer on the kernels of the stacks at most: with what synth_relu_ffn() adds behind it
 // (under 64 KB here) it fits the buffer of lisa_attn_decode_static.
 constexpr size_t kDecodeSpreadMaxBytes = LISA_STATIC_SCRATCH_BYTES - 128 * 1024;
-bool decode_spread_ok(const lisa_desc* d);
+bool decode_spread_fits(const lisa_desc* d);
+bool decode_spread_ok(const lisa_desc* d, bool lisa_layer);
 size_t decode_spread_bytes(const lisa_desc* d);
 FfnOperands decode_spread_operands(const lisa_desc* d, const bf16_t* w1, const bf16_t* w2, void* workspace);
 int run_decode_spread(const lisa_desc* d, bool lisa_layer, const DecodeArgs& da, void* out, void* workspace,

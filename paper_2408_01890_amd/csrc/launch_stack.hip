@@ -325,12 +325,26 @@ int run_stack_chained(const lisa_desc* d, const lisa_stack_layer* layers, int n_
 }
 
 // ---- single layers ------------------------------------------------------------------------------------
-// k_decode_part, a workgroup per (sequence, 128 keys) that makes everything of it in one launch, needs about two
-// such units per compute unit before it reaches the memory's rate, reads V once per query head and
-// stages the module's weights in every workgroup; this path needs none of that but passes A_n through
-// memory as float32, 8 bytes per head and key against 600 read.  The line is drawn where that scratch no
-// longer fits the buffer of lisa_attn_decode_static (about 900 units of 32 heads).
-bool decode_spread_ok(const lisa_desc* d) { return single_ws(d).total <= kDecodeSpreadMaxBytes; }
+// k_decode_part, a workgroup per (sequence, 128 keys) that makes everything of it in one launch, reads V once per
+// query head, stages the module's weights in every workgroup and waits for them before its keys; this path needs
+// none of that, but passes A_n through memory as float32 between its launches, 8 bytes per head and key.
+// Where query heads share a key/value head, for direct sharing and for the CONCAT form it was the faster one at
+// every size measured (LLaMA3-8B heads, 16 users, 6000 tokens, ADD 70 against 106 us; CONCAT, LLaMA2-7B, 16 users,
+// 4096 tokens 124 against 142).  With a key/value head per query head those 8 bytes count once there are enough
+// units of 128 keys to keep k_decode_part at the memory's rate:
+//   3/2 per compute unit in standard layers, which stage no weights (LLaMA2-7B heads, 320 units 124 against
+//   134 - 142 us, 432 units 165 against 151, 736 units 279 - 290 against 259), and with ADD modules of narrow layers,
+//   where a launch more costs as much (32 heads of 64, 320 units 55 - 59 against 58 - 60, 448 units 71 - 77
+//   against 68; 8 heads of 128, 448 units 36 against 31);
+//   5/2 with ADD modules of wider ones (LLaMA2-7B, 576 units 130 - 138 against 145, 736 units 171 - 181 against 167).
+// The scratch has to fit the buffer of lisa_attn_decode_static (about 900 units of 32 heads).
+bool decode_spread_fits(const lisa_desc* d) { return single_ws(d).total <= kDecodeSpreadMaxBytes; }
+bool decode_spread_ok(const lisa_desc* d, bool lisa_layer) {
+  if (!decode_spread_fits(d)) return false;
+  if (d->H != d->Hkv || (lisa_layer && d->mix != LISA_MIX_ADD)) return true;
+  const long long units = (long long)d->B * ((d->Lk + DEC_CK - 1) / DEC_CK);
+  return units < (lisa_layer && d->H * d->d_k >= 3072 ? kComputeUnits * 5 / 2 : kComputeUnits * 3 / 2);
+}
 size_t decode_spread_bytes(const lisa_desc* d) { return single_ws(d).total; }
 
 // Where the module's weights go in operand order; a launch in front of the step may write them

@@ -380,12 +380,13 @@ bool decode_fast_ok(const lisa_desc* d, bool lisa_layer) {
 int decode_chunks(const lisa_desc* d) { return (d->Lk + DEC_CK - 1) / DEC_CK; }
 
 size_t decode_fast_bytes(const lisa_desc* d) {
-  if (decode_spread_ok(d)) return decode_spread_bytes(d);
   const size_t units = (size_t)d->B * decode_chunks(d) * d->H;
+  const size_t part = round_up(units * d->d_k * sizeof(float), 256) + round_up(units * 2 * sizeof(float), 256);
+  // (either form, whichever the kind of layer takes)
+  if (decode_spread_fits(d)) return std::max(decode_spread_bytes(d), part);
   // no less than the spread form takes at most: a workspace that fits the longest context, the largest
   // batch fits every smaller one
-  return std::max(round_up(units * d->d_k * sizeof(float), 256) + round_up(units * 2 * sizeof(float), 256),
-                  kDecodeSpreadMaxBytes);
+  return std::max(part, kDecodeSpreadMaxBytes);
 }
 
 // A decode stack leaves the combine of a layer to the launch of the layer behind it (its workgroups
@@ -423,7 +424,7 @@ int flush_deferred_combine(hipStream_t st) {
 
 int run_decode_fast(const lisa_desc* d, bool lisa_layer, DecodeArgs a, void* out, void* workspace,
                     hipStream_t st) {
-  if (decode_spread_ok(d)) {
+  if (decode_spread_ok(d, lisa_layer)) {
     const int rc = run_decode_spread(d, lisa_layer, a, out, workspace, st);
     if (rc == LISA_OK) g_path = "decode_split";
     return rc;
@@ -1139,7 +1140,7 @@ int lisa_layer_decode(const lisa_desc* desc, int32_t d_model, float rope_theta, 
   // the step's FFN weights are put in order by the projection's launch, where the step wants them that way
   FfnOperands ffn{};
   int ffn_done = 0;
-  const bool spread = decode_fast_ok(desc, true) && decode_spread_ok(desc);
+  const bool spread = decode_fast_ok(desc, true) && decode_spread_ok(desc, true);
   if (spread) ffn = decode_spread_operands(desc, (const bf16_t*)w1, (const bf16_t*)w2, workspace);
   rc = project_qkv(&pd, x, w_qkv, ws + qo, k_lr_cache, v_cache, spread ? &ffn : nullptr, &ffn_done, hip_stream);
   if (rc) return rc;

@@ -109,6 +109,39 @@ def test_single_layer_decode_spans(case):
         assert hp.row_rel_err(hp.f64(o3[b])[None], o_ref) <= tol
 
 
+@pytest.mark.parametrize("H,Hkv,B,std_spread,add_spread", [
+    (8, 8, 47, True, True), (8, 8, 48, False, False),         # 376 and 384 units of 128 keys: the line of narrow layers
+    (24, 24, 48, False, True), (24, 24, 80, False, False),    # 640 units: the line of wide ADD modules
+    (8, 4, 80, True, True),                                   # two query heads per kv head: below 16 MB of scratch always
+])
+def test_single_layers_on_both_sides_of_the_line(H, Hkv, B, std_spread, add_spread):
+    """Which kernels a single layer takes, and that both give the oracle's results there."""
+    Lk, dk, r, F, tol = 1024, 128, 22, 64, hp.TOL[torch.bfloat16]
+    log(f"[case] single decode, {H}/{Hkv} heads, {B} sequences")
+    stk = synth.DecodeStack("line", "bf16", B, H, Hkv, Lk - 1, 256, dk, r, F, 2, 1)
+    std, ly = synth.make_decode_layer(stk, 0, device=DEV), synth.make_decode_layer(stk, 1, device=DEV, ffn="fan_in")
+
+    def stages(call):
+        lisa.profile_enable(True)
+        try:
+            return call(), set(lisa.profile_collect())
+        finally:
+            lisa.profile_enable(False)
+
+    (row, out), names = stages(lambda: lisa.std_attn_decode(std["q"], std["k_cache"], std["v_cache"], Lk))
+    assert ("k_stack_pv" in names) == std_spread and ("k_decode_part_std" in names) != std_spread
+    (o2, row2), names = stages(lambda: lisa.lisa_attn_decode(ly["q_lr"], ly["k_lr_cache"], ly["v_cache"], Lk, row, ly["w1"], ly["w2"]))
+    assert ("k_stack_pv" in names) == add_spread and ("k_decode_part_lisa" in names) != add_spread
+    torch.cuda.synchronize()
+    for b in (0, B // 2, B - 1):
+        ref = hp.oracle_std_rows(std["q"][:, :, None, :], std["k_cache"][:, :, :Lk], b, [0])
+        assert hp.row_rel_err(hp.f64(row[b])[None], ref) <= tol
+        o_ref = cref.softmax_v_rows(hp.f64(std["v_cache"][b])[:, :Lk], [0], ref, 1)
+        assert hp.row_rel_err(hp.f64(out[b])[None], o_ref) <= tol
+        a_ref, o_ref = oracle_decode_lisa(ly, b, Lk, hp.f64(row[b]), True)
+        assert hp.row_rel_err(hp.f64(row2[b])[None], a_ref) <= tol and hp.row_rel_err(hp.f64(o2[b])[None], o_ref) <= tol
+
+
 @pytest.mark.parametrize("H,Hkv,dk,Lk,B,masked", [
     (8, 8, 128, 128, 1, (0, 40)),       # all of a wave's first 32 keys
     (8, 2, 64, 1500, 2, (0, 1100)),     # a whole workgroup's keys, merged with the next one's
