@@ -61,11 +61,12 @@ struct F32AttnArgs {
   void* out;              // [B,Lq,H,DK] (float where out_f32, else T) or null
   int H, Hkv, Lq, Lk, causal, out_f32;
   int row0, n_rows;       // query rows of this launch (row0 a multiple of 16)
+  int parts;              // workgroups that the tiles of a row block are dealt to (1 unless scores only)
   float scale;
 };
 
-// grid (ceil(n_rows / 16), H, B), block 256: 16 query rows of one head, the 16-key tiles dealt to the four
-// waves, their softmax states merged through the LDS at the end.  16x16x4 float32 MFMAs with the
+// grid (parts ceil(n_rows / 16), H, B), block 256: 16 query rows of one head, the 16-key tiles dealt to the four
+// waves (scores only: of `parts` workgroups), their softmax states merged through the LDS at the end.  16x16x4 float32 MFMAs with the
 // query row on lane % 16 for both products, so that a lane's four scores are its B operands of the
 // second one.  Short sequences are a matter of latency: a wave holds the operands of its next tile while
 // it works on this one, and nothing passes through the LDS before the end.
@@ -79,7 +80,13 @@ __global__ __launch_bounds__(256) void k_f32_attn(F32AttnArgs<T, S> a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, g = lane >> 4;
-  const int rb = gridDim.x - 1 - blockIdx.x;                 // long row blocks first
+  const int xr = gridDim.x - 1 - blockIdx.x;                 // long row blocks first
+  int rb = xr, t_first = wv, t_step = 4;
+  if (a.parts > 1) {
+    rb = xr / a.parts;
+    t_first += 4 * (xr - rb * a.parts);
+    t_step = 4 * a.parts;
+  }
   const int h = blockIdx.y, b = blockIdx.z;
   const int Lq = a.Lq, Lk = a.Lk, i0 = a.row0 + rb * 16;
   const int kv = h / (a.H / a.Hkv);
@@ -125,12 +132,12 @@ __global__ __launch_bounds__(256) void k_f32_attn(F32AttnArgs<T, S> a) {
 #pragma unroll
   for (int i = 0; i < NP; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.f;
-  if (wv < n_tiles) {
-    load_k(wv);
-    if (with_v) load_v(wv);
+  if (t_first < n_tiles) {
+    load_k(t_first);
+    if (with_v) load_v(t_first);
   }
-  for (int tile = wv; tile < n_tiles; tile += 4) {
-    const int tile_n = min(tile + 4, n_tiles - 1);
+  for (int tile = t_first; tile < n_tiles; tile += t_step) {
+    const int tile_n = min(tile + t_step, n_tiles - 1);
     const int j = tile * 16 + 4 * g;                         // this lane's keys j .. j + 3 of row c
     f32x4 s;
     if (GIVEN) {

@@ -16,7 +16,7 @@ bool f32_attn_ok(const lisa_desc* d) {
 namespace {
 template <typename T, typename S, int NDK>
 int launch_attn(const lisa_desc* d, const F32AttnArgs<T, S>& a, hipStream_t st) {
-  dim3 grid((a.n_rows + 15) / 16, d->H, d->B);
+  dim3 grid((a.n_rows + 15) / 16 * a.parts, d->H, d->B);
   StageScope prof(a.given ? "k_f32_softmax_v" : "k_f32_attn", st);
   if (a.given) k_f32_attn<T, S, NDK, true><<<grid, 256, 0, st>>>(a);
   else k_f32_attn<T, S, NDK, false><<<grid, 256, 0, st>>>(a);
@@ -33,6 +33,11 @@ int run_attn(const lisa_desc* d, const void* q, const void* k, const void* given
   a.H = d->H; a.Hkv = d->Hkv; a.Lq = d->Lq; a.Lk = d->Lk; a.causal = d->causal;
   a.out_f32 = d->out_f32 || d->dtype == LISA_F32;
   a.row0 = row0; a.n_rows = n_rows;
+  // Scores only: nothing to merge, so few row blocks of many keys are spread until there is a workgroup per
+  // compute unit, two tiles per wave at least (2 rows, 3000 keys, 8 heads of 64: 24.7 us in one workgroup per head,
+  // 5.9 spread, 11.2 on the generic kernel; two per compute unit cost 13 % at 700 rows, 4 heads).
+  const long long blocks = (long long)((n_rows + 15) / 16) * d->H * d->B;
+  a.parts = out ? 1 : (int)std::max<long long>(1, std::min<long long>((d->Lk + 127) / 128, kComputeUnits / blocks));
   a.scale = pick_scale(d->std_scale, d->d_k);
   if constexpr (sizeof(T) == 4)
     if (d->d_k == 64) return launch_attn<T, S, 1>(d, a, st);

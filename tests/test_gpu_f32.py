@@ -54,6 +54,32 @@ def test_f32_layers(case):
         assert hp.row_rel_err(hp.gather_out_rows(o1, b, rows), o_ref) <= TOL
 
 
+@pytest.mark.parametrize("dtype,dk", [("f32", 64), ("f32", 128), ("bf16", 128)])
+@pytest.mark.parametrize("B,H,Hkv,Lq,Lk", [
+    (1, 8, 8, 16, 128), (1, 8, 8, 17, 129),    # a workgroup's tiles, and a second workgroup with one
+    (1, 4, 2, 2, 3001), (2, 3, 3, 47, 1031),   # few rows, many keys; row blocks that see fewer tiles than there are workgroups
+])
+def test_f32_scores_alone_are_those_of_the_layer(B, H, Hkv, Lq, Lk, dtype, dk):
+    """Without V the tiles of a row block are dealt to several workgroups: the same scores bit for bit, and no others."""
+    if dtype == "bf16":
+        Lk += (Lk % 8 == 0)                                   # (row-major rows of ragged length run in float32)
+    log(f"[case] f32 scores alone {dtype} {B} {H} {Lq}x{Lk} dk{dk}")
+    g = torch.Generator(device=DEV).manual_seed(6)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    q = torch.randn((B, H, Lq, dk), generator=g, device=DEV).to(dt)
+    k, v = (torch.randn((B, Hkv, Lk, dk), generator=g, device=DEV).to(dt) for _ in range(2))
+    a, b = (torch.full((B, H, Lq, Lk), SENTINEL, dtype=lisa.score_dtype(dt), device=DEV) for _ in range(2))
+    lisa.std_attn_scores(q, k, v, scores_out=a)
+    lisa.std_attn_scores(q, k, scores_out=b)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b)
+    for n in range(B):
+        rows = np.arange(Lq)
+        ref = hp.oracle_std_rows(q, k, n, rows)
+        tol = TOL if dtype == "f32" else 2.0 ** -8           # half scores: see test_gpu_ragged_rows.py
+        assert hp.scores_row_rel_err(hp.gather_score_rows(b, n, rows), ref, rows, Lq, Lk) <= tol
+
+
 @pytest.mark.parametrize("B,H,L,F,silu", [
     (1, 4, 897, 16, False),      # 57 x 57 tiles: runs of two, the last one clipped
     (3, 4, 900, 16, True),       # runs of six that share the staged weights
