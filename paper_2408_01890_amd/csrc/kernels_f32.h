@@ -28,18 +28,8 @@ template <> struct Quad<bf16_t> {
     return __uint_as_float(e & 1 ? raw[e >> 1] & 0xffff0000u : raw[e >> 1] << 16);
   }
 };
-// Two elements, neighbours at an even offset or from anywhere.
-template <typename T> struct Pair;
-template <> struct Pair<float> {
-  float x, y;
-  static __device__ __forceinline__ Pair load(const float* p) {
-    const float2 v = *(const float2*)p;
-    return {v.x, v.y};
-  }
-  static __device__ __forceinline__ Pair load2(const float* p, const float* q) { return {*p, *q}; }
-  __device__ __forceinline__ float operator[](int e) const { return e ? y : x; }
-};
-template <> struct Pair<bf16_t> {
+// Two bf16 elements, neighbours at an even offset or from anywhere.
+struct Pair {
   unsigned raw;
   static __device__ __forceinline__ Pair load(const bf16_t* p) { return {*(const unsigned*)p}; }
   static __device__ __forceinline__ Pair load2(const bf16_t* p, const bf16_t* q) { return {p->bits | (unsigned)q->bits << 16}; }
@@ -290,43 +280,60 @@ __global__ __launch_bounds__(256) void k_f32_lisa_scores(F32ScoresArgs<T, S> a) 
       }
     }
     if (tile > t0) __syncthreads();                          // d_s of the tile before has been read
-    // A_delta, NH heads and 32 ranks at a time with all their loads in flight together: a load per step of the
+    // A_delta.  bf16: NH heads and 32 ranks at a time with all their loads in flight together; a load per step of the
     // product, each waited for, made this the longest part of the kernel.  The ranks are numbered so that a lane's
     // two steps 2 u, 2 u + 1 take neighbours, one load where the rows (r elements) keep them aligned.
-    constexpr int NH = HT >= 16 ? 4 : 2;
-    const bool pairs = (r & 1) == 0;
-    for (int h0 = wv; h0 < H; h0 += 4 * NH) {
-      f32x4 acc[NH];
-#pragma unroll
-      for (int m = 0; m < NH; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int r0 = 0; r0 < r; r0 += 32) {
-        Pair<T> kx[NH][4], qx[NH][4];
-#pragma unroll
-        for (int m = 0; m < NH; ++m) {
-          const int h = min(h0 + 4 * m, H - 1);
-          const T* kp = a.k_lr + (((size_t)b * a.Hkv + h / group) * Lk + jc) * r;
-          const T* qp = a.q_lr + (((size_t)b * H + h) * Lq + min(i0 + c, Lq - 1)) * r;
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int t = r0 + 8 * u + 2 * g;
-            kx[m][u] = pairs ? Pair<T>::load(kp + min(t, r - 2)) : Pair<T>::load2(kp + min(t, r - 1), kp + min(t + 1, r - 1));
-            qx[m][u] = pairs ? Pair<T>::load(qp + min(t, r - 2)) : Pair<T>::load2(qp + min(t, r - 1), qp + min(t + 1, r - 1));
-          }
+    // float32 operands take twice the registers for it, and what it does for ranks and heads that fill no batch
+    // costs the small layers more than the waits: a head and a step at a time there (4 heads, 1024 rows, 44 us
+    // against 96 in batches; 32 heads 267 against 328).
+    if constexpr (sizeof(T) == 4) {
+      for (int h = wv; h < H; h += 4) {
+        const T* kp = a.k_lr + (((size_t)b * a.Hkv + h / group) * Lk + jc) * r;
+        const T* qp = a.q_lr + (((size_t)b * H + h) * Lq + min(i0 + c, Lq - 1)) * r;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int s = 0; s < (r + 3) / 4; ++s) {
+          const int t = 4 * s + g;
+          const float kx = t < r ? kp[t] : 0.f, qx = t < r ? qp[t] : 0.f;
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(kx, qx, acc, 0, 0, 0);
         }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-          for (int e = 0; e < 2; ++e) {
-            const bool in = r0 + 8 * u + 2 * g + e < r;
-#pragma unroll
-            for (int m = 0; m < NH; ++m)
-              acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? kx[m][u][e] : 0.f, in ? qx[m][u][e] : 0.f, acc[m], 0, 0, 0);
-          }
+        *(f32x4*)(d_s + (h * 16 + c) * F32_DROW + 4 * g) = acc * a.dscale;   // row c, keys 4 g ..
       }
-#pragma unroll
-      for (int m = 0; m < NH; ++m) {
-        const int h = h0 + 4 * m;
-        if (h < H) *(f32x4*)(d_s + (h * 16 + c) * F32_DROW + 4 * g) = acc[m] * a.dscale;   // row c, keys 4 g ..
+    } else {
+      constexpr int NH = HT >= 16 ? 4 : 2;
+      const bool pairs = (r & 1) == 0;
+      for (int h0 = wv; h0 < H; h0 += 4 * NH) {
+        f32x4 acc[NH];
+  #pragma unroll
+        for (int m = 0; m < NH; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int r0 = 0; r0 < r; r0 += 32) {
+          Pair kx[NH][4], qx[NH][4];
+  #pragma unroll
+          for (int m = 0; m < NH; ++m) {
+            const int h = min(h0 + 4 * m, H - 1);
+            const T* kp = a.k_lr + (((size_t)b * a.Hkv + h / group) * Lk + jc) * r;
+            const T* qp = a.q_lr + (((size_t)b * H + h) * Lq + min(i0 + c, Lq - 1)) * r;
+  #pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const int t = r0 + 8 * u + 2 * g;
+              kx[m][u] = pairs ? Pair::load(kp + min(t, r - 2)) : Pair::load2(kp + min(t, r - 1), kp + min(t + 1, r - 1));
+              qx[m][u] = pairs ? Pair::load(qp + min(t, r - 2)) : Pair::load2(qp + min(t, r - 1), qp + min(t + 1, r - 1));
+            }
+          }
+  #pragma unroll
+          for (int u = 0; u < 4; ++u)
+  #pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              const bool in = r0 + 8 * u + 2 * g + e < r;
+  #pragma unroll
+              for (int m = 0; m < NH; ++m)
+                acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? kx[m][u][e] : 0.f, in ? qx[m][u][e] : 0.f, acc[m], 0, 0, 0);
+            }
+        }
+  #pragma unroll
+        for (int m = 0; m < NH; ++m) {
+          const int h = h0 + 4 * m;
+          if (h < H) *(f32x4*)(d_s + (h * 16 + c) * F32_DROW + 4 * g) = acc[m] * a.dscale;   // row c, keys 4 g ..
+        }
       }
     }
     __syncthreads();                                         // (also publishes the weights)
@@ -391,8 +398,12 @@ __global__ __launch_bounds__(256) void k_f32_lisa_scores(F32ScoresArgs<T, S> a) 
         }
       }
     };
-    if (a.scores) store(a.scores, hs, Lq, 0);
-    if (a.exact) store(a.exact, (size_t)a.n_rows * Lk, a.n_rows, a.row0);
+    if constexpr (sizeof(T) == 4) {                          // (scores and their copy are the same type and rows: one of them)
+      store(a.scores ? a.scores : a.exact, hs, Lq, 0);
+    } else {
+      if (a.scores) store(a.scores, hs, Lq, 0);
+      if (a.exact) store(a.exact, (size_t)a.n_rows * Lk, a.n_rows, a.row0);
+    }
   }
 }
 

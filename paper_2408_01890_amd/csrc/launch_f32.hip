@@ -103,10 +103,11 @@ int run_scores(const lisa_desc* d, const void* q_lr, const void* k_lr, const voi
   a.H = d->H; a.Hkv = d->Hkv; a.Lq = d->Lq; a.Lk = d->Lk; a.r = d->r; a.F = d->F; a.causal = d->causal;
   a.row0 = row0; a.n_rows = n_rows;
   a.dscale = pick_scale(d->delta_scale, d->r);
-  // a tile per workgroup until there are six workgroups per compute unit, then runs of tiles that share the
-  // staged weights
+  // a tile per workgroup until there are several workgroups per compute unit (16; bf16, whose larger weights are
+  // converted as they are staged: 6), then runs of tiles that share the staged weights
   const int kt = (d->Lk + 15) / 16, rbs = (n_rows + 15) / 16;
-  a.tiles = (int)std::min<long long>(16, std::max<long long>(1, (long long)kt * rbs * d->B / (6 * kComputeUnits)));
+  const int wgs = (sizeof(T) == 4 ? 16 : 6) * kComputeUnits;
+  a.tiles = (int)std::min<long long>(16, std::max<long long>(1, (long long)kt * rbs * d->B / wgs));
   dim3 grid((kt + a.tiles - 1) / a.tiles, rbs, d->B);
   switch (scores_heads(d->H)) {
     case 8: return launch_scores_t<T, S, 8, CONCAT>(d, a, grid, st);
