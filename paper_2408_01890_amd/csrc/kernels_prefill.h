@@ -259,7 +259,7 @@ __device__ __forceinline__ void st_uv_stream(void* ubase, unsigned voff, T v) {
 // after the first of them has fetched it from HBM.  With a.pair the workgroup takes the units (last - x) and x, a
 // long and a short one, so that all workgroups carry the same number of tiles and stage the FFN
 // weights once.
-// Requires Lk % 8 == 0.
+// Requires Lk % 8 == 0 of row-major scores; tiled ones may have any Lk >= 8.
 // SHG > 0: every SHG consecutive heads of a wave share one key/value head (grouped KV heads, H / Hkv
 // a multiple of SHG, HPW a multiple of SHG): one set of K_LR / V operands per tile serves all of
 // them, and every such set is refilled behind its last head with the next tile's operands.  With

@@ -19,7 +19,7 @@
 //      per row and tile: up to 32 heads as half in an array of their own, stored during the FFN of
 //      the next tile (two barriers per tile); wider forms as float32 over the input tile, stored
 //      before the next tile is staged (four barriers).
-// Requires Lk % 8 == 0, r <= 32, H <= 48, F <= 256.
+// Requires Lk % 8 == 0 of row-major scores (tiled ones: any Lk >= 8), r <= 32, H <= 48, F <= 256.
 #pragma once
 #include <type_traits>
 #include "kernels_prefill.h"

@@ -67,7 +67,7 @@ constexpr int std_prefill_head_lds(bool with_v) {
 // fastest grid index: consecutive workgroups go to different XCDs, so an XCD works on every
 // eighth head and its L2 fetches the K / V of those heads only (they are what every row group
 // of a head re-reads).
-// Requires d_k = 128, Lk % 8 == 0.
+// Requires d_k = 128, Lk % 8 == 0 of row-major scores (tiled ones: any Lk >= 8).
 // GIVEN: the scores are read from a.given (the A_n that a LiSA scores kernel left there) instead
 // of being computed; the rest (masking, online softmax, P V) is the same.
 template <bool WITH_V, int GIVEN = 0>

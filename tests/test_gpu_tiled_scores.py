@@ -157,6 +157,51 @@ def test_concat_pipeline_tiled_equals_row_major(case, causal):
     assert path == "mfma_scores"
 
 
+RAGGED = [  # mix, H, Hkv, Lq, Lk, F: keys that fill no octet of the last tile; odd chunks of rows
+    ("add", 32, 8, 77, 77, 64), ("add", 8, 8, 33, 129, 64), ("add", 40, 40, 65, 67, 80), ("add", 16, 16, 9, 9, 32),
+    ("add", 24, 8, 50, 95, 64), ("concat", 32, 8, 95, 97, 256), ("concat", 8, 8, 31, 31, 64)]
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("case", RAGGED, ids=lambda c: f"{c[0]}_h{c[1]}_{c[3]}x{c[4]}")
+def test_tiled_layers_of_ragged_length(case, causal):
+    """Row lengths that are no multiple of 8 (row-major ones do not run on these kernels): every visible score and all of O
+    against float64, with NaN in all that the tiles hold beside the visible scores."""
+    mix, H, Hkv, Lq, Lk, F = case
+    log(f"[case] tiled ragged {case} causal={causal}")
+    cfg = synth.LayerShape("tiled_ragged", "bf16", 2, H, Hkv, Lk, 256, 128, 20, F)
+    inp = synth.make_prefill_inputs(cfg, 61, DEV, mix=mix, ffn="fan_in")
+    q, q_lr = (inp[n][:, :, Lk - Lq:].contiguous() for n in ("q", "q_lr"))
+    a0, o0 = lisa.std_attn_scores(q, inp["k"], inp["v"], causal=causal, tiled=True)
+    vis = visible_mask(Lq, Lk, causal, DEV)
+    seen = lisa.tile_scores(vis[None, None].expand(2, H, Lq, Lk).half()) > 0
+    prev = torch.where(seen, a0, torch.full_like(a0, float("nan")))
+    o1, a1 = lisa.lisa_attn_prefill(q_lr, inp["k_lr"], inp["v"], prev, inp["w1"], inp["w2"], causal=causal, tiled=True, Lq=Lq,
+                                    mix=lisa.MIX_CONCAT if mix == "concat" else lisa.MIX_ADD)
+    torch.cuda.synchronize()
+    assert lisa.last_path() == ("mfma_scores" if mix == "concat" else "mfma_fused")
+    vis, x = vis.cpu(), {n: t.double().cpu() for n, t in inp.items() if torch.is_tensor(t)}
+    heads = lambda t: t.repeat_interleave(H // Hkv, dim=1)
+    scores = lambda qq, kk: qq.double().cpu() @ heads(kk).transpose(-1, -2).contiguous() / qq.shape[-1] ** 0.5
+
+    def check(got_a, got_o, ref_a):
+        ref_o = torch.softmax(ref_a.masked_fill(~vis, float("-inf")), -1) @ heads(x["v"])
+        got_a = lisa.untile_scores(got_a, Lq, Lk).double().cpu()
+        for i in range(Lq):
+            err = hp.row_rel_err(got_a[:, :, i, vis[i]].numpy(), ref_a[:, :, i, vis[i]].numpy())
+            assert err <= hp.TOL[torch.bfloat16], (i, err)
+        got_o = got_o.double().cpu().permute(0, 2, 1, 3)
+        assert hp.row_rel_err(got_o.permute(2, 0, 1, 3).numpy(), ref_o.permute(2, 0, 1, 3).numpy()) <= hp.TOL[torch.bfloat16]
+
+    check(a0, o0, scores(q, x["k"]))
+    p = lisa.untile_scores(a0, Lq, Lk).double().cpu().masked_fill(~vis, 0.0).permute(0, 2, 3, 1)
+    delta = scores(q_lr, x["k_lr"])
+    if mix == "concat":
+        p = torch.cat([p, delta.permute(0, 2, 3, 1)], -1)
+    y = (torch.relu(p @ x["w1"]) @ x["w2"]).permute(0, 3, 1, 2)
+    check(a1, o1, y if mix == "concat" else y + delta)
+
+
 def test_tiled_requests_outside_the_matrix_core_kernels_are_refused():
     cfg, inp = make_case("h32_l136", 1, 32, 32, 136, 136, 20, 160, 47)      # ADD with F = 160: not a fused shape
     prev_t, _ = lisa.std_attn_scores(inp["q"], inp["k"], tiled=True)
