@@ -131,6 +131,7 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
   const int n_kt = (Lk + PF_TK - 1) / PF_TK;
   const size_t tile_stride = (size_t)H * (PF_ROWS * PF_TK);
   const size_t trow = ((size_t)b * n_rg + rg) * n_kt * tile_stride + lane * 8;   // + t tile_stride + h 512
+  const unsigned head_elems = (unsigned)Lq * Lk;             // (32 bits inside a head: see scores_mfma_ok)
   auto prefetch = [&](int tile) {
     const int j0 = tile * PF_TK;
 #pragma unroll
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
       if (TILED)
         xr[u] = *(const pf_u32x4*)(a.prev + trow + min(tile, n_kt - 1) * tile_stride + h * (PF_ROWS * PF_TK));
       else
-        xr[u] = *(const pf_u32x4*)(a.prev + (((size_t)b * H + h) * Lq + x_row) * Lk + min(j0 + xq8, Lk - 8));
+        xr[u] = *(const pf_u32x4*)(a.prev + ((size_t)b * H + h) * head_elems + ((unsigned)x_row * Lk + min(j0 + xq8, Lk - 8)));
     }
 #pragma unroll
     for (int u = 0; u < HPW; ++u) {
@@ -224,13 +225,8 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
       const int jc = tile * PF_TK + 8 * och;                // first of the lane's 8 keys
       if (jc >= vis) return;
       half_t* sp = obase + u * ohead + jc - 8 * och;
-      if (jc + 8 <= vis) {
-        *(f16x8*)sp = held;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (jc + e < vis) sp[e] = held[e];
-      }
+      if (jc + 8 <= vis) *(f16x8*)sp = held;
+      else store_row_part(sp, __builtin_bit_cast(pf_u32x4, held), vis - jc);
     };
     // The result leaves the registers as dwords of two keys: a lane holds one key of the four heads
     // 4 g + v; the lanes of a pair (keys c, c ^ 1) swap halves, after which the even lane has both
@@ -396,13 +392,8 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
         f16x8 hv;
 #pragma unroll
         for (int e = 0; e < 8; ++e) hv[e] = f32_to_half_sat(vals[e]);
-        if (jc + 8 <= vis) {
-          *(f16x8*)(a.scores + at) = hv;
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            if (jc + e < vis) a.scores[at + e] = hv[e];
-        }
+        if (jc + 8 <= vis) *(f16x8*)(a.scores + at) = hv;
+        else store_row_part(a.scores + at, __builtin_bit_cast(pf_u32x4, hv), vis - jc);
       }
     }
   }

@@ -261,10 +261,10 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
             half_t* sp = sbase + (size_t)min(gi, Lq - 1) * Lk + jc;
             if (pair_full || jc + 8 <= vis) {
               __builtin_nontemporal_store(__builtin_bit_cast(pf_u32x4, hv), (pf_u32x4*)sp);
-            } else {
-#pragma unroll
-              for (int e = 0; e < 8; ++e)
-                if (jc + e < vis) sp[e] = hv[e];
+            } else if (jc < vis) {
+              int rel = vis - jc;                              // (kept inside this branch: registers)
+              asm volatile("" : "+v"(rel));
+              store_row_part(sp, __builtin_bit_cast(pf_u32x4, hv), rel);
             }
           }
         }
