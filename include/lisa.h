@@ -171,6 +171,9 @@ int lisa_attn_prefill(const lisa_desc* desc, const void* q_lr, const void* k_lr,
  *   out            [B,H,d_k]        out
  *   score_row_out  [B,H,Lk]         out  required iff write_scores = 1 (the "small weight
  *                                        matrix" of h*l elements in Sec. 5.2)
+ *   workspace      at least lisa_workspace_bytes(desc, LISA_WS_DECODE) bytes: bf16 about 5 bytes per head and key
+ *                  up to 16.6 MB, from there on 16.6 MB or the partial results, 4.1 bytes per head and key at
+ *                  d_k = 128 (it never falls with a longer context or a larger batch)
  */
 int lisa_attn_decode(const lisa_desc* desc, const void* q_lr, const void* k_lr_new,
                      const void* v_new, void* k_lr_cache, void* v_cache,
@@ -244,7 +247,9 @@ typedef struct lisa_stack_layer {
 int lisa_decode_stack(const lisa_desc* desc, const lisa_stack_layer* layers, int32_t n_layers,
                       void* workspace, size_t workspace_bytes, void* hip_stream);
 /* Scratch bytes of lisa_decode_stack for this descriptor (score rows, partial results and operands of the
- * layers that are under way together; it does not depend on the number of layers). */
+ * layers that are under way together; it does not depend on the number of layers).  ADD-form bf16 stacks: what up
+ * to 48 layers under way take, 4 bytes per layer, head and key and a little more; where that passes 128 MB, fewer
+ * layers are under way and the scratch is 128 MB, or what four layers take. */
 size_t lisa_stack_workspace_bytes(const lisa_desc* desc);
 
 /*

@@ -465,7 +465,8 @@ constexpr int stack_pv_keys(int dk) { return 65536 / dk; }
 // NB = 1, NW = 16: all of it in flight at once, where there are few workgroups.  The first batches of V are in
 // flight while the softmax statistics are made.  The waves' results are merged through the LDS, the
 // spans' by the workgroup that finishes last (in the order of the keys, whoever it is).
-// Bound: the V stream, 5.9 - 6.1 TB/s where there is enough of it.
+// Bound: the V stream.  16 users at 4096 tokens, 32 layers: 17.5 GB fetched in 2.65 ms, 6.6 TB/s; one user at 1023
+// tokens: 273 MB in 41 - 44 us.
 template <int DK, int GQ, int NB>
 __global__ __launch_bounds__(1024 / NB, NB == 1 ? 4 : GQ == 1 ? 4 : 3) void k_stack_pv(StackPvArgs a) {
   constexpr int NW = 16 / NB, THREADS = 64 * NW;

@@ -312,8 +312,9 @@ int run_stack_chained(const lisa_desc* d, const lisa_stack_layer* layers, int n_
     // Who merges the splits: the last workgroup of an output where there are few (no launch more), a launch of
     // its own behind the long stream, where every workgroup that waits for its stores and the counter
     // keeps the next one's loads out: 16 users at 4096 tokens, 32 layers, 4732 us with the counters, 4394 without
-    // (one user at 1023: 83 with them, a launch more otherwise).  A group of direct-sharing layers alone
-    // has no launch in front that clears the counters.
+    // (one user at 1023, 2048 workgroups: 83 with them, 81.5 with the launch).  So the line is that of the form of
+    // k_stack_pv: fewer workgroups than compute units keep the counters.  A group of direct-sharing layers alone
+    // has no launch in front that clears them.
     const bool merge = gw.n_span > 1 && (sa.n_std + sa.n_lisa == 0 || pv_batches(d, n1 - n0) == 4);
     if (merge) pa.d.done = nullptr;
     if ((rc = launch_pv(d, pa, n1 - n0, st))) return rc;

@@ -498,8 +498,8 @@ bool prefill_fused_ok(const lisa_desc* d) {
 //           small problems) and row slices become possible.
 //   split   small problems have too few units to fill the chip and their longest unit (the last
 //           row block) sets the run time: the key tiles of a row block are dealt to 2 or 4 units.
-//   pair    two units (a long and a short one) per workgroup once that still leaves two workgroups
-//           per compute unit: equal work per workgroup, FFN weights staged once for both.
+//   pair    two units (a long and a short one) per workgroup once that still leaves a workgroup per
+//           compute unit: equal work per workgroup, FFN weights staged once for both.
 struct PrefillGeom {
   int slices, groups, split, pair;
 };
