@@ -10,7 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblisa_mi355x.so")
 # (source, parts): a source with many kernel instantiations is compiled in parts, side by side, each with
 # -DLISA_PART=<its number>
-UNITS = [("launch_prefill.hip", 5), ("launch_decode.hip", 1), ("launch_stack.hip", 1), ("launch_f32.hip", 1),
+UNITS = [("launch_prefill.hip", 5), ("launch_decode.hip", 1), ("launch_stack.hip", 1), ("launch_f32.hip", 1), ("launch_split.hip", 1),
          ("launch_scores.hip", 1), ("lisa_api.hip", 1)]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]

@@ -1,0 +1,124 @@
+// Prefill layers of bf16 operands in float32 arithmetic on the kernels of kernels_split.h: which shapes they take, and the
+// launches.
+#include "host.h"
+#include "kernels_split.h"
+
+namespace lisa {
+
+// Row-major score rows of a length that the bf16 and half kernels do not take.
+bool bf16_ragged_rows(const lisa_desc* d) {
+  return d->dtype == LISA_BF16 && d->d_k == 128 && !score_rows_aligned(d);
+}
+
+// 32-bit offsets inside (two heads of) a score tensor and inside a head's operand rows; eight elements to read at least.
+static bool split_sizes_ok(const lisa_desc* d) {
+  return d->Lk >= 8 && (long long)(d->Lq + 16) * (d->Lk + PF_TK) < (1LL << 30);
+}
+
+bool split_attn_ok(const lisa_desc* d) { return bf16_ragged_rows(d) && d->Lq > 1; }
+
+namespace {
+int split_heads(int H) { return H <= 8 ? 8 : H <= 16 ? 16 : H <= 32 ? 32 : 40; }
+template <int HT, bool CONCAT>
+int keys_of(int F) {                                         // 16-key blocks per tile, 0: does not fit the LDS
+  return SplitScoresGeo<HT, CONCAT, 2>::lds(F) <= 160 * 1024   ? 2
+         : SplitScoresGeo<HT, CONCAT, 1>::lds(F) <= 160 * 1024 ? 1
+                                                               : 0;
+}
+int split_keys(const lisa_desc* d) {
+  const bool cc = d->mix == LISA_MIX_CONCAT;
+  switch (split_heads(d->H)) {
+    case 8: return cc ? keys_of<8, true>(d->F) : keys_of<8, false>(d->F);
+    case 16: return cc ? keys_of<16, true>(d->F) : keys_of<16, false>(d->F);
+    case 32: return cc ? keys_of<32, true>(d->F) : keys_of<32, false>(d->F);
+    // (40 heads, CONCAT: the operands of two 16-key blocks do not fit the register file)
+    default: return cc ? std::min(1, keys_of<40, true>(d->F)) : keys_of<40, false>(d->F);
+  }
+}
+}  // namespace
+
+bool split_scores_ok(const lisa_desc* d) {
+  if (!split_attn_ok(d) || !split_sizes_ok(d) || (d->act != LISA_ACT_RELU && d->act != LISA_ACT_SILU)) return false;
+  if (d->mix != LISA_MIX_ADD && d->mix != LISA_MIX_CONCAT) return false;
+  if (d->H > 40 || d->r > 32 || (long long)d->H * d->Lq * d->r < 8) return false;
+  return split_keys(d) > 0;
+}
+
+// The float32 scores pass through the workspace in tiles, a chunk of query rows at a time: 256 MB of them (what the
+// last-level cache holds), at least one block of 16 rows.
+int split_chunk_rows(const lisa_desc* d) {
+  const size_t row = (size_t)d->B * d->H * ((d->Lk + PF_TK - 1) / PF_TK * PF_TK) * sizeof(float);
+  const size_t rows = std::max<size_t>(16, (((size_t)256 << 20) / row) & ~(size_t)15);
+  return (int)std::min<size_t>(rows, (size_t)d->Lq);
+}
+size_t split_chunk_bytes(const lisa_desc* d) {
+  const size_t rows = (size_t)(split_chunk_rows(d) + 15) / 16 * 16;
+  return (size_t)d->B * d->H * rows * ((d->Lk + PF_TK - 1) / PF_TK * PF_TK) * sizeof(float);
+}
+
+namespace {
+template <int HT, bool CONCAT, int TKB>
+int launch_scores_t(const lisa_desc* d, SplitScoresArgs& a, hipStream_t st) {
+  typedef SplitScoresGeo<HT, CONCAT, TKB> Geo;
+  const int lds = Geo::lds(d->F);
+  auto kern = d->act == LISA_ACT_SILU ? k_split_scores<HT, 1, CONCAT, TKB> : k_split_scores<HT, 0, CONCAT, TKB>;
+  hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (e != hipSuccess) return hip_fail(e);
+  a.tiles_b = 0;
+  for (int i = a.row0; i < a.row0 + a.n_rows; i += 16)
+    a.tiles_b += split_scores_tiles(i, a.row0 + a.n_rows, d->Lq, d->Lk, d->causal, Geo::TK);
+  const long long wgs = std::min<long long>(kComputeUnits, a.tiles_b * a.B);
+  StageScope prof("k_split_scores", st);
+  kern<<<(unsigned)wgs, 512, lds, st>>>(a);
+  return check_launch();
+}
+template <int HT>
+int launch_scores_h(const lisa_desc* d, SplitScoresArgs& a, hipStream_t st) {
+  const int kb = split_keys(d);
+  if (d->mix == LISA_MIX_CONCAT) {
+    if constexpr (HT < 40)
+      if (kb == 2) return launch_scores_t<HT, true, 2>(d, a, st);
+    return launch_scores_t<HT, true, 1>(d, a, st);
+  }
+  return kb == 2 ? launch_scores_t<HT, false, 2>(d, a, st) : launch_scores_t<HT, false, 1>(d, a, st);
+}
+}  // namespace
+
+int run_split_scores(const lisa_desc* d, const void* q_lr, const void* k_lr, const void* prev, const void* w1,
+                     const void* w2, void* scores, float* exact, int row0, int n_rows, hipStream_t st) {
+  SplitScoresArgs a{};
+  a.q_lr = (const bf16_t*)q_lr; a.k_lr = (const bf16_t*)k_lr; a.prev = (const half_t*)prev;
+  a.w1 = (const bf16_t*)w1; a.w2 = (const bf16_t*)w2; a.scores = (half_t*)scores; a.exact = exact;
+  a.B = d->B; a.H = d->H; a.Hkv = d->Hkv; a.Lq = d->Lq; a.Lk = d->Lk; a.r = d->r; a.F = d->F; a.causal = d->causal;
+  a.row0 = row0; a.n_rows = n_rows;
+  a.dscale = pick_scale(d->delta_scale, d->r);
+  switch (split_heads(d->H)) {
+    case 8: return launch_scores_h<8>(d, a, st);
+    case 16: return launch_scores_h<16>(d, a, st);
+    case 32: return launch_scores_h<32>(d, a, st);
+    default: return launch_scores_h<40>(d, a, st);
+  }
+}
+
+int run_split_attn(const lisa_desc* d, const void* q, const void* k, const void* v, const float* given, bool given_tiled,
+                   int row0, int n_rows, void* scores, void* out, hipStream_t st) {
+  SplitAttnArgs a{};
+  a.q = (const bf16_t*)q; a.k = (const bf16_t*)k; a.v = (const bf16_t*)v; a.given = given;
+  a.scores = (half_t*)scores; a.out = out;
+  a.H = d->H; a.Hkv = d->Hkv; a.Lq = d->Lq; a.Lk = d->Lk; a.causal = d->causal; a.out_f32 = d->out_f32;
+  a.row0 = row0; a.n_rows = n_rows; a.given_tiled = given_tiled;
+  a.scale = pick_scale(d->std_scale, d->d_k);
+  const int groups = (n_rows + SP_ROWS - 1) / SP_ROWS;
+  // scores only: few row groups of many keys are spread until there is a workgroup per compute unit, two tiles per wave
+  // at least
+  a.parts = out ? 1 : (int)std::max<long long>(1, std::min<long long>((d->Lk + 8 * SP_TK - 1) / (8 * SP_TK),
+                                                                      kComputeUnits / ((long long)groups * d->H * d->B)));
+  dim3 grid(d->H, groups * a.parts, d->B);
+  StageScope prof(given ? "k_split_softmax_v" : "k_split_attn", st);
+  if (given) k_split_attn<true, true><<<grid, 256, 0, st>>>(a);
+  else if (out) k_split_attn<true, false><<<grid, 256, 0, st>>>(a);
+  else k_split_attn<false, false><<<grid, 256, 0, st>>>(a);
+  return check_launch();
+}
+
+}  // namespace lisa

@@ -315,7 +315,7 @@ int run_softmax_given_fast(const lisa_desc* d, const void* given, bool given_hal
                            void* vt_ws, hipStream_t st);
 
 // bf16 layers in float32 arithmetic: scores and softmax by chunks of query rows.
-bool in_chunks(const lisa_desc* d) { return d->dtype == LISA_BF16 && f32_attn_ok(d); }
+bool in_chunks(const lisa_desc* d) { return split_attn_ok(d); }
 
 template <typename T, typename S>
 int run_lisa(const lisa_desc* d, const void* q_lr, const void* k_lr, KeyStrides ks, const void* v,
@@ -341,18 +341,22 @@ int run_lisa(const lisa_desc* d, const void* q_lr, const void* k_lr, KeyStrides 
   // is half; a float32 layer has it in the score tensor itself.
   if (d->dtype == LISA_F32 && scores) exact = nullptr;
   const void* an = exact ? (void*)exact : scores;
-  const int step = in_chunks(d) ? f32_chunk_rows(d) : d->Lq;
+  const bool split = in_chunks(d) && split_scores_ok(d);     // (float32 scores in tiles)
+  const int step = split ? split_chunk_rows(d) : in_chunks(d) ? f32_chunk_rows(d) : d->Lq;
   for (int row0 = 0; row0 < d->Lq; row0 += step) {
     const int n_rows = std::min(step, d->Lq - row0);
-    int rc = f32_scores_ok(d) ? run_f32_scores(d, q_lr, k_lr, prev, w1, w2, scores, exact, row0, n_rows, st)
+    int rc = split              ? run_split_scores(d, q_lr, k_lr, prev, w1, w2, scores, exact, row0, n_rows, st)
+             : f32_scores_ok(d) ? run_f32_scores(d, q_lr, k_lr, prev, w1, w2, scores, exact, row0, n_rows, st)
                               : launch_lisa_scores<T, S>(d, q_lr, k_lr, ks, prev, w1, w2, scores, exact, row0, n_rows, st);
     if (rc) return rc;
     // softmax and P V from the float32 scores: on the matrix cores where one of the standard layer's kernels
     // fits (it then reads the scores instead of computing Q K^T), else the generic kernel
     if (std_prefill_fast_ok(d))
       rc = run_softmax_given_fast(d, exact, false, v, out, (char*)exact + exact_bytes(d), st);
+    else if (in_chunks(d))
+      rc = run_split_attn(d, nullptr, nullptr, v, exact, split, row0, n_rows, nullptr, out, st);
     else if (f32_attn_ok(d))
-      rc = run_f32_softmax_v(d, an, row0, n_rows, v, out, st);
+      rc = run_f32_softmax_v(d, an, v, out, st);
     else
       rc = launch_softmax_v<T>(d, (const float*)an, v, vs, out, st);
     if (rc) return rc;
@@ -1064,7 +1068,8 @@ size_t lisa_workspace_bytes(const lisa_desc* desc, int which) {
       if (scores_mfma_ok(desc)) return concat_ws(desc).total;
       if (relu_equivalent(desc, &eq) && scores_mfma_ok(&eq))
         return round_up(concat_ws(&eq).total, 256) + synth_ffn_bytes(desc);
-      if (in_chunks(desc)) return f32_chunk_bytes(desc);
+      if (in_chunks(desc))                                   // (k_split_attn reads up to 31 floats past row-major scores)
+        return std::max(split_scores_ok(desc) ? split_chunk_bytes(desc) : 0, f32_chunk_bytes(desc) + 256);
       return exact_bytes(desc) + (std_prefill_fast_ok(desc) ? std_prefill_ws(desc) : 0);
     }
     case LISA_WS_DECODE: {
@@ -1079,7 +1084,7 @@ size_t lisa_workspace_bytes(const lisa_desc* desc, int which) {
       if (check_common(desc) != LISA_OK) return 0;
       // needed only when `out` is requested
       if (std_prefill_fast_ok(desc)) return std_prefill_ws(desc);
-      if (in_chunks(desc)) return 256;                       // (k_f32_attn keeps its scores in registers)
+      if (in_chunks(desc)) return 256;                       // (k_split_attn keeps its scores in registers)
       return decode_fast_ok(desc, false) ? decode_fast_bytes(desc) : exact_bytes(desc);
     case LISA_WS_LAYER: {
       size_t q, k, v;
@@ -1630,7 +1635,9 @@ int std_attn_scores(const lisa_desc* desc, const void* q, const void* k, const v
     a.row_out = (half_t*)scores_out;
     return run_decode_fast(desc, false, a, out, workspace, st);
   }
-  if (f32_attn_ok(desc)) {
+  if (split_attn_ok(desc)) {
+    rc = run_split_attn(desc, q, k, v, nullptr, false, 0, desc->Lq, scores_out, out, st);
+  } else if (f32_attn_ok(desc)) {
     rc = run_f32_std(desc, q, k, v, scores_out, out, st);
   } else if (desc->dtype == LISA_F32) {
     if (scores_out) exact = nullptr;                         // (the score tensor is the unrounded copy)

@@ -1,0 +1,115 @@
+"""bf16 layers in float32 arithmetic on the bf16 matrix instructions (row-major score rows of any length): the sizes where
+tiles, operand rows and tensors end, against float64."""
+import pytest
+import torch
+
+from paper_2408_01890_amd import lisa
+from tests.test_gpu_parity import log
+from tests.test_gpu_ragged_rows import SENTINEL, guarded
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+# float32 sums of up to 2000 terms and three-part products: a few 2^-24 of the row's RMS; the benchmark's float32 tolerance
+TOL_O = 1e-5
+TOL_A = 2.0 ** -8                  # one rounding to half, of scores below 8 RMS (see test_gpu_ragged_rows)
+
+CASES = [  # B, H, Hkv, Lq, Lk, r, F, mix, causal
+    (1, 8, 8, 2, 9, 1, 32, "add", True),        # operand rows shorter than what a lane reads, at the tensor's end
+    (2, 8, 1, 31, 31, 7, 33, "add", True),
+    (1, 16, 16, 32, 33, 8, 31, "add", True),
+    (1, 32, 4, 33, 63, 9, 64, "add", True),
+    (1, 33, 11, 17, 65, 31, 96, "add", True),   # heads that fill no block of 8 waves
+    (1, 40, 8, 65, 97, 32, 97, "add", True),
+    (1, 40, 40, 16, 1003, 22, 128, "add", True),   # weights for which the tiles have 16 keys
+    (1, 8, 8, 40, 1111, 32, 64, "add", False),  # every key visible to every row
+    (1, 32, 32, 18, 41, 20, 256, "concat", True),
+    (1, 37, 37, 5, 23, 11, 40, "concat", True),    # an odd number of heads, two per load
+    (2, 16, 2, 47, 49, 20, 256, "concat", False),
+    (1, 8, 8, 20, 37, 33, 64, "add", True),     # more ranks than one product takes
+    (1, 8, 4, 3, 5, 4, 32, "add", True),        # fewer keys than a lane reads
+]
+
+
+def reference(q, k, v, prev, w1, w2, mix, causal):
+    d = torch.float64
+    q, k, v, prev, w1, w2 = (t.cpu().to(d) for t in (q, k, v, prev, w1, w2))
+    rep = lambda t: t.repeat_interleave(q.shape[1] // t.shape[1], 1)
+    delta = q @ rep(k).transpose(-1, -2).contiguous() / q.shape[-1] ** 0.5
+    x = torch.cat([prev, delta], 1) if mix == "concat" else prev
+    A = (torch.relu(x.permute(0, 2, 3, 1) @ w1) @ w2).permute(0, 3, 1, 2)
+    if mix == "add":
+        A = A + delta
+    return A, softmax_v(A, rep(v), causal)
+
+
+def softmax_v(A, v, causal):
+    Lq, Lk = A.shape[-2:]
+    if causal:
+        A = A.masked_fill(torch.ones(Lq, Lk, dtype=torch.bool).triu(Lk - Lq + 1), float("-inf"))
+    return (torch.softmax(A, -1) @ v).permute(0, 2, 1, 3)
+
+
+def err(got, ref):                 # largest difference over the RMS of its row
+    got, ref = got.cpu().double(), ref
+    return float(((got - ref).abs().amax(-1) / ref.pow(2).mean(-1).sqrt()).max())
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "_".join(map(str, c)))
+def test_lisa_layer(case):
+    B, H, Hkv, Lq, Lk, r, F, mix, causal = case
+    log(f"[case] split lisa {case}")
+    g = torch.Generator(device=DEV).manual_seed(Lk)
+    rn = lambda *s: torch.randn(s, generator=g, device=DEV)
+    q, k, v = rn(B, H, Lq, r).to(torch.bfloat16), rn(B, Hkv, Lk, r).to(torch.bfloat16), rn(B, Hkv, Lk, 128).to(torch.bfloat16)
+    din = 2 * H if mix == "concat" else H
+    w1, w2 = (rn(din, F) / din ** 0.5).to(torch.bfloat16), (rn(F, H) / F ** 0.5).to(torch.bfloat16)
+    prev = rn(B, H, Lq, Lk).to(torch.float16)
+    scores, *guards = guarded((B, H, Lq, Lk))
+    out, _ = lisa.lisa_attn_prefill(q, k, v, prev, w1, w2, mix=lisa.MIX_CONCAT if mix == "concat" else lisa.MIX_ADD,
+                                    causal=causal, scores_out=scores)
+    torch.cuda.synchronize()
+    A, O = reference(q, k, v, prev, w1, w2, mix, causal)
+    vis = torch.ones(Lq, Lk, dtype=torch.bool).tril(Lk - Lq) if causal else torch.ones(Lq, Lk, dtype=torch.bool)
+    assert all(bool(torch.all(t == SENTINEL)) for t in guards) and bool(torch.all(scores.cpu()[..., ~vis] == SENTINEL))
+    rms = (A * vis).pow(2).sum((1, 3)).div(vis.sum(-1) * H).sqrt()[:, None, :, None]
+    assert float((((scores.cpu().double() - A) / rms).abs() * vis).max()) <= TOL_A
+    assert err(out.flatten(2), O.flatten(2)) <= TOL_O
+
+
+@pytest.mark.parametrize("Lq,Lk,causal", [(2, 4097, True), (31, 1155, False), (32, 33, True), (33, 129, True), (64, 65, True), (3, 5, True)])
+def test_std_layer(Lq, Lk, causal):
+    B, H, Hkv = 2, 4, 2
+    log(f"[case] split std {Lq}x{Lk}")
+    g = torch.Generator(device=DEV).manual_seed(Lk)
+    q = torch.randn((B, H, Lq, 128), generator=g, device=DEV).to(torch.bfloat16)
+    k, v = (torch.randn((B, Hkv, Lk, 128), generator=g, device=DEV).to(torch.bfloat16) for _ in range(2))
+    only, *guards = guarded((B, H, Lq, Lk))
+    lisa.std_attn_scores(q, k, causal=causal, scores_out=only)       # scores alone: tiles dealt to several workgroups
+    scores, out = lisa.std_attn_scores(q, k, v, causal=causal)
+    torch.cuda.synchronize()
+    assert all(bool(torch.all(t == SENTINEL)) for t in guards)
+    rep = lambda t: t.cpu().double().repeat_interleave(H // Hkv, 1)
+    A = q.cpu().double() @ rep(k).transpose(-1, -2).contiguous() / 128 ** 0.5
+    vis = torch.ones(Lq, Lk, dtype=torch.bool).tril(Lk - Lq) if causal else torch.ones(Lq, Lk, dtype=torch.bool)
+    assert torch.equal(only.cpu()[..., vis], scores.cpu()[..., vis])
+    assert float((scores.cpu().double() - A).abs()[..., vis].max()) <= 2.0 ** -9 * float(A.abs().max())
+    assert err(out.flatten(2), softmax_v(A, rep(v), causal).flatten(2)) <= TOL_O
+
+
+def test_chunk_border():
+    """The rows on both sides of a chunk of float32 scores (256 MB of them, in tiles of 32 keys)."""
+    B, H, L = 2, 40, 1001
+    log("[case] split chunk border")
+    edge = (256 << 20) // (B * H * ((L + 31) // 32 * 32) * 4) // 16 * 16
+    assert 16 < edge < L - 16
+    g = torch.Generator(device=DEV).manual_seed(1)
+    rn = lambda *s: torch.randn(s, generator=g, device=DEV)
+    q, k, v = rn(B, H, L, 22).to(torch.bfloat16), rn(B, H, L, 22).to(torch.bfloat16), rn(B, H, L, 128).to(torch.bfloat16)
+    w1, w2 = (rn(H, 80) / 6).to(torch.bfloat16), (rn(80, H) / 9).to(torch.bfloat16)
+    prev = rn(B, H, L, L).to(torch.float16)
+    out, scores = lisa.lisa_attn_prefill(q, k, v, prev, w1, w2)
+    torch.cuda.synchronize()
+    for i in (0, edge - 17, edge - 1, edge, edge + 15, L - 1):       # row i alone: one row of i + 1 keys
+        A, O = reference(q[:, :, i:i + 1], k[:, :, :i + 1], v[:, :, :i + 1], prev[:, :, i:i + 1, :i + 1], w1, w2, "add", True)
+        assert err(out[:, i:i + 1].flatten(2), O.flatten(2)) <= TOL_O
+        assert err(scores[:, :, i, :i + 1].flatten(1), A[:, :, 0].flatten(1)) <= TOL_A
