@@ -65,7 +65,7 @@ typedef unsigned int pf_u32x4 __attribute__((ext_vector_type(4)));
 
 struct PrefillArgs {
   const bf16_t* qp;       // [B,H,Lqp,32]       Q_LR padded (Lqp = Lq rounded up to 16)
-  const bf16_t* kp;       // [B,Hkv,Lkp,32]     K_LR padded (Lkp = Lk rounded up to 64)
+  const bf16_t* kp;       // [B,Hkv,Lkp/32,2,64,8] K_LR padded, tiles in operand order (Lkp = Lk rounded up to 64)
   const bf16_t* vt;       // [B,Hkv,Lkp/8,128,8] V by key chunks
   const half_t* prev;     // [B,H,Lq,Lk]
   const bf16_t* w1;
@@ -128,7 +128,9 @@ __global__ __launch_bounds__(256) void k_regroup_v(const bf16_t* __restrict__ v,
 // The repacking of one fused prefill call in one launch, block 256:
 //   blocks [0, n_v):   V tiles as in k_regroup_v (tile index = x + nx (y + ny z))
 //   the rest:          Q_LR and K_LR rows zero-padded from r to 32 elements, one 16-byte chunk of
-//                      a padded row per thread (64 rows per block, Q rows first).
+//                      a padded row per thread (64 rows per block, Q rows first), K_LR by tiles of 32 keys in
+//                      operand order: operand u, lane 16 g + c holds elements 8 g .. of key 8 (c / 4) + c % 4 + 4 u.  (A wave
+//                      that loads an operand then names 8 lines on end, not 64 pieces of 16 rows.)
 template <bool VEC>
 __global__ __launch_bounds__(256) void k_prepare_prefill(const bf16_t* __restrict__ q_lr,
                                                          const bf16_t* __restrict__ k_lr,
@@ -161,7 +163,8 @@ __global__ __launch_bounds__(256) void k_prepare_prefill(const bf16_t* __restric
     const int j = rk % Lkp;
     const size_t bh = rk / Lkp;
     if (j < Lk) src = k_lr + (bh * Lk + j) * r;
-    dst = kp + rk * 32 + t0;
+    const int lane = 16 * (threadIdx.x & 3) + 4 * ((j >> 3) & 3) + (j & 3);
+    dst = kp + (bh * Lkp + (j & ~31)) * 32 + ((j >> 2) & 1) * 512 + lane * 8;
   } else {
     return;
   }
@@ -370,7 +373,7 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
   for (int u = 0; u < XCH; ++u)
     x_base[u] = a.prev + (size_t)b * seq_elems + (size_t)(XSTG ? wv * HPW + u : wv + NW * u) * head_elems;
   // per-lane byte offsets, the same for every head
-  const unsigned k_off = ((8 * (c >> 2) + (c & 3)) * 32 + 8 * g) * 2;   // MFMA row c -> key 8 (c/4) + c%4 (+4)
+  const unsigned k_off = lane * 16;                                     // operand order (+ 1 KB: the second operand)
   const unsigned v_off = (g * DK + c) * 16;                             // key chunk g, feature c (+16 nb)
   const int xq8 = 8 * (lane & 3);                                       // A_{n-1} chunk: row lane/4, 8 keys
   const int xdst = (XSTG ? wv * HPW : wv) * PF_XS_HEAD + lane * 16;     // + u NW PF_XS_HEAD (XSTG: + u PF_XS_HEAD)
@@ -500,7 +503,7 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
       if (hh >= NSET) continue;                                // (hh here numbers the operand sets)
       const bf16_t* kt = k_base[hh * SH] + (size_t)t_begin * (PF_TK * 32);
       ka[hh] = ld_uv<bf16x8>(kt, k_off);
-      kb[hh] = ld_uv<bf16x8>(kt, k_off, 4 * 32 * 2);
+      kb[hh] = ld_uv<bf16x8>(kt, k_off, 1024);
       if (SPREAD && hh == 1) continue;
       const bf16_t* vt = v_base[hh * SH] + (size_t)t_begin * (PF_TK / 8 * DK * 8);
 #pragma unroll
@@ -675,7 +678,7 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
         if (refill) {
           const bf16_t* kt = k_base[hn] + (size_t)t_next * (PF_TK * 32);
           ka[hs] = ld_uv<bf16x8>(kt, k_off);
-          kb[hs] = ld_uv<bf16x8>(kt, k_off, 4 * 32 * 2);
+          kb[hs] = ld_uv<bf16x8>(kt, k_off, 1024);
         }
         const float* yp = (const float*)(ys + (wv * HPW + hh) * PF_YS_HEAD + c * PF_YS_ROW + 8 * g * 4);
         const f32x4 y0 = *(const f32x4*)yp, y1 = *(const f32x4*)(yp + 4);

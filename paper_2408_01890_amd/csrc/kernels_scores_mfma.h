@@ -11,7 +11,7 @@
 // kernel).  Per tile:
 //   1. the A_{n-1} tile of all heads goes to LDS ([head][row][key], half); wave w computes the
 //      A_delta tile of heads w, w + 8, ... with two 16x16x32 MFMAs each (A = K_LR rows, B = Q_LR
-//      rows, both read from copies zero-padded to 32 elements per row: k_prepare_prefill) and
+//      rows, both read from copies zero-padded to 32 elements per row, K_LR in operand order: k_prepare_prefill) and
 //      appends it as heads H .. 2H-1 of the same LDS array;
 //   2. every wave runs the FFN (mfma_ffn.h, weights read from their LDS image) on 4 of the 32
 //      blocks of 16 positions, the 2H input "heads" fetched with transposing LDS reads;
@@ -28,7 +28,7 @@ namespace lisa {
 
 struct ScoresMfmaArgs {
   const bf16_t* qp;     // [B,H,Lqp,32]   Q_LR rows zero-padded to 32 elements
-  const bf16_t* kp;     // [B,Hkv,Lkp,32] K_LR rows likewise
+  const bf16_t* kp;     // [B,Hkv,Lkp/32,2,64,8] K_LR likewise, tiles in operand order (k_prepare_prefill)
   const half_t* prev;   // [B,H,Lq,Lk] (or tiled, see below)
   const bf16_t* w1;     // [2H,F]
   const bf16_t* w2;     // [F,H]
@@ -145,10 +145,10 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
 #pragma unroll
     for (int u = 0; u < HPW; ++u) {
       const int h = min(wv + NW * u, H - 1);
-      const bf16_t* kbase = a.kp + ((size_t)b * a.Hkv + h / group) * a.Lkp * 32 + 8 * g;
+      const bf16_t* kbase = a.kp + ((size_t)b * a.Hkv + h / group) * a.Lkp * 32 + lane * 8;
 #pragma unroll
       for (int half = 0; half < 2; ++half)
-        kop[u][half] = *(const bf16x8*)(kbase + (size_t)min(j0 + 16 * half + c, Lk - 1) * 32);
+        kop[u][half] = *(const bf16x8*)(kbase + (size_t)min(j0, a.Lkp - PF_TK) * 32 + 512 * half);
     }
   };
   prefetch(t_first);
@@ -169,11 +169,11 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
       for (int half = 0; half < 2; ++half) {
         f32x4 d = {0.f, 0.f, 0.f, 0.f};
         d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[u][half], qop[u], d, 0, 0, 0);
-        // d[v] = A_delta(row c, key 16 half + 4 g + v) / scale
+        // d[v] = A_delta(row c, key 8 g + 4 half + v) / scale
         f16x4 hv;
 #pragma unroll
         for (int v = 0; v < 4; ++v) hv[v] = f32_to_half_sat(d[v] * a.dscale);
-        *(f16x4*)(xs + (H + h) * PF_XS_HEAD + c * 64 + (16 * half + 4 * g) * 2) = hv;
+        *(f16x4*)(xs + (H + h) * PF_XS_HEAD + c * 64 + (8 * g + 4 * half) * 2) = hv;
       }
     }
   };
@@ -270,9 +270,7 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
       const int jn = (tile + 1) * PF_TK;
       const int xoff = min(jn + xq8, Lk - 8);
       const size_t toff = trow + min(tile + 1, n_kt - 1) * tile_stride;
-      int koff[2];
-#pragma unroll
-      for (int half = 0; half < 2; ++half) koff[half] = min(jn + 16 * half + c, Lk - 1) * 32 + 8 * g;
+      const int koff = min(jn, a.Lkp - PF_TK) * 32 + lane * 8;
       // (the loads are not conditional on a next tile: its clamped addresses are in bounds, and a
       // branch around a load makes the compiler wait for every earlier one)
       Ffn::template apply_lds_chunked_ahead<NBW, SC>(w_s, x, y, [&](int gidx) {
@@ -290,7 +288,7 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
           } else {
             const int u = (k - 2 * XCH - 1) >> 1, half = (k - 2 * XCH - 1) & 1;
             const int h = min(wv + NW * u, H - 1);
-            kop[u][half] = *(const bf16x8*)(a.kp + ((size_t)b * a.Hkv + h / group) * a.Lkp * 32 + koff[half]);
+            kop[u][half] = *(const bf16x8*)(a.kp + ((size_t)b * a.Hkv + h / group) * a.Lkp * 32 + koff + 512 * half);
           }
         }
       });
@@ -324,11 +322,11 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
       for (int half = 0; half < 2; ++half) {
         f32x4 d = {0.f, 0.f, 0.f, 0.f};
         d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[u][half], qop[u], d, 0, 0, 0);
-        // d[v] = A_delta(row c, key 16 half + 4 g + v) / scale
+        // d[v] = A_delta(row c, key 8 g + 4 half + v) / scale
         f16x4 hv;
 #pragma unroll
         for (int v = 0; v < 4; ++v) hv[v] = f32_to_half_sat(d[v] * a.dscale);
-        *(f16x4*)(xs + (H + h) * PF_XS_HEAD + c * 64 + (16 * half + 4 * g) * 2) = hv;
+        *(f16x4*)(xs + (H + h) * PF_XS_HEAD + c * 64 + (8 * g + 4 * half) * 2) = hv;
       }
     }
     if (tile + 1 < t_last) prefetch(tile + 1);

@@ -59,6 +59,10 @@ __device__ __forceinline__ void split_parts(const float (&x)[8], bf16x8 (&p)[PAR
   }
 }
 
+// Where a float32 tile of 16 rows x 32 keys has key 8 g + 4 q .. + 3 of row c: in the order of the lanes that hold it, so
+// that a store of a wave is one KB on end.
+__host__ __device__ constexpr int split_tile_at(int c, int g, int q) { return q * 256 + (g * 16 + c) * 4; }
+
 // ---- attention ---------------------------------------------------------------------------------
 struct SplitAttnArgs {
   const bf16_t* q;        // [B,H,Lq,128]
@@ -69,7 +73,7 @@ struct SplitAttnArgs {
   void* out;              // [B,Lq,H,128] float32 or bf16
   int H, Hkv, Lq, Lk, causal, out_f32;
   int row0, n_rows;       // query rows of this launch (row0 a multiple of 16)
-  int given_tiled;        // given is [B,ceil(n_rows/16),ceil(Lk/32),H,16,32], else [B,H,n_rows,Lk] with 32 floats behind it
+  int given_tiled;        // given is [B,ceil(n_rows/16),ceil(Lk/32),H] tiles (split_tile_at), else [B,H,n_rows,Lk] with 32 floats behind it
   int parts;              // scores only: workgroups that the key tiles of a row group are dealt to (1 with V, or not KEYS)
   float scale;
 };
@@ -161,17 +165,17 @@ __global__ __launch_bounds__(256, 2) void k_split_attn(SplitAttnArgs a) {
   // given scores: row my_row, keys 32 tile + 16 u + 8 half .. + 7, loaded a step ahead
   const int n_kt = (Lk + SP_TK - 1) / SP_TK, crow = my_row - a.row0;
   const size_t g_step = a.given_tiled ? (size_t)H * (16 * SP_TK) : SP_TK;
-  const float* grow = GIVEN ? a.given + 8 * half +
-                                  (a.given_tiled ? (((size_t)b * ((a.n_rows + 15) / 16) + (crow >> 4)) * n_kt * H + h) * (16 * SP_TK) +
-                                                       (crow & 15) * SP_TK
-                                                 : (((size_t)b * H + h) * a.n_rows + crow) * Lk)
-                            : nullptr;
+  const int g_u = a.given_tiled ? split_tile_at(0, 2, 0) : 16, g_q = a.given_tiled ? split_tile_at(0, 0, 1) : 4;
+  const float* grow =
+      !GIVEN          ? nullptr
+      : a.given_tiled ? a.given + (((size_t)b * ((a.n_rows + 15) / 16) + (crow >> 4)) * n_kt * H + h) * (16 * SP_TK) + split_tile_at(crow & 15, half, 0)
+                      : a.given + (((size_t)b * H + h) * a.n_rows + crow) * Lk + 8 * half;
   f32x4 gq[4];
   auto load_scores = [&](int tile) {
     const float* gp = grow + tile * g_step;
     if (GIVEN)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) gq[u] = *(const f32x4_a4b*)(gp + 16 * (u >> 1) + 4 * (u & 1));
+      for (int u = 0; u < 4; ++u) gq[u] = *(const f32x4_a4b*)(gp + g_u * (u >> 1) + g_q * (u & 1));
   };
   auto clamp_tile = [&](int t) { return min(t, n_tiles - 1); };
   load_kt(clamp_tile(t_begin));
@@ -352,14 +356,14 @@ __global__ __launch_bounds__(256, 2) void k_split_attn(SplitAttnArgs a) {
 
 // ---- scores of a LiSA layer --------------------------------------------------------------------
 struct SplitScoresArgs {
-  const bf16_t* q_lr;     // [B,H,Lq,r]
-  const bf16_t* k_lr;     // [B,Hkv,Lk,r]
+  const bf16_t* qp;       // [B,H,Lqp,32]   Q_LR rows zero-padded to 32 elements
+  const bf16_t* kp;       // [B,Hkv,Lkp/32] K_LR tiles in operand order (k_prepare_prefill)
   const half_t* prev;     // [B,H,Lq,Lk]
   const bf16_t* w1;       // [Din,F]
   const bf16_t* w2;       // [F,H]
   half_t* scores;         // [B,H,Lq,Lk] or null
-  float* exact;           // [B,ceil(n_rows/16),ceil(Lk/32),H,16,32] or null: the unrounded copy
-  int B, H, Hkv, Lq, Lk, r, F, causal;
+  float* exact;           // [B,ceil(n_rows/16),ceil(Lk/32),H] tiles of 512 (split_tile_at) or null: the unrounded copy
+  int B, H, Hkv, Lq, Lk, Lqp, Lkp, F, causal;
   int row0, n_rows;       // query rows of this launch (row0 a multiple of 16)
   long long tiles_b;      // tiles of one sequence: sum over the row blocks of split_scores_tiles()
   float dscale;
@@ -384,8 +388,9 @@ struct SplitScoresGeo {
 // Per tile: every wave runs the FFN on 2 TKB blocks of 16 positions (one row, 16 keys) with the operands in parts, y goes
 // to the LDS by heads; then a wave takes heads wv, wv + 8, ..: A_delta by one MFMA per 16 keys, added in registers,
 // A_n out in pieces of 8 keys.  CONCAT: A_delta goes through the LDS first, as input of the FFN.
-// The operands of Q_LR and K_LR are read from their rows of r elements, which start at any 2-byte boundary: 16 bytes
-// per lane and masked; what would reach past a tensor's end is read 8 elements before it and shifted.
+// What bounds it is the number of cache lines that a compute unit's loads and stores name (four lanes in a row, 64 bytes, are
+// looked up at a time): K_LR in operand order, the float32 tile in the order of the lanes and A_n turned through the
+// LDS into rows take 1/4 of what operand rows and pieces per lane did (11600 per tile of 32 heads: 149 -> 130 us at 2 x 509 rows behind 1022 keys, 32 heads).
 template <int HT, int ACT, bool CONCAT, int TKB>
 __global__ __launch_bounds__(512) void k_split_scores(SplitScoresArgs a) {
   typedef SplitScoresGeo<HT, CONCAT, TKB> Geo;
@@ -403,7 +408,7 @@ __global__ __launch_bounds__(512) void k_split_scores(SplitScoresArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, g = lane >> 4;
-  const int H = a.H, Lq = a.Lq, Lk = a.Lk, r = a.r, group = H / a.Hkv, shift = Lk - Lq;
+  const int H = a.H, Lq = a.Lq, Lk = a.Lk, group = H / a.Hkv;
   const int FS = (a.F + 31) / 32, row_end = a.row0 + a.n_rows;
   const int n_rg = (a.n_rows + 15) / 16, n_kt = (Lk + PF_TK - 1) / PF_TK;
   const long long total = a.tiles_b * a.B;
@@ -416,19 +421,16 @@ __global__ __launch_bounds__(512) void k_split_scores(SplitScoresArgs a) {
   for (int nt; tile0 >= (nt = tiles_of(rg)); ++rg) tile0 -= nt;
 
   // weights in operand order: W1 operands [hidden block][k-step], then W2 [hidden k-step][head block]
-  const int n_w1 = FS * 2 * KS, n_w = n_w1 + FS * HB;
-  for (int i = tid; i < n_w * 512; i += 512) {
-    const int e = i & 7, l = (i >> 3) & 63, o = i >> 9, lc = l & 15, lg = l >> 4;
-    unsigned short w = 0;
-    if (o < n_w1) {
-      const int f = 16 * (o / KS) + lc, ks = o % KS, hh = 32 * (ks % KSA) + 8 * lg + e;
-      if (f < a.F && hh < H) w = a.w1[(size_t)(ks < KSA ? hh : H + hh) * a.F + f].bits;
-    } else {
-      const int h = 16 * ((o - n_w1) % HB) + lc, f = 32 * ((o - n_w1) / HB) + 16 * (e >> 2) + 4 * lg + (e & 3);
-      if (f < a.F && h < H) w = a.w2[(size_t)f * H + h].bits;
-    }
-    ((unsigned short*)w_s)[i] = w;
-  }
+  const int n_w1 = FS * 2 * KS;
+  stage_weights((n_w1 + FS * HB) * 512, (unsigned short*)w_s, tid, 512, [&](int i, bool& in) -> const bf16_t* {
+    const int e = i & 7, l = (i >> 3) & 63, o = i >> 9, lc = l & 15, lg = l >> 4, ks = o % KS, o2 = o - n_w1;
+    const bool one = o < n_w1;
+    const int f = one ? 16 * (o / KS) + lc : 32 * (o2 / HB) + 16 * (e >> 2) + 4 * lg + (e & 3);
+    const int h = one ? 32 * (ks % KSA) + 8 * lg + e : 16 * (o2 % HB) + lc;
+    in = (f < a.F) & (h < H);
+    const int at = one ? (ks < KSA ? h : H + h) * a.F + f : f * H + h;
+    return (one ? a.w1 : a.w2) + (in ? at : 0);
+  }, [](unsigned short bits) { return bits; });
   for (int i = tid; i < XHEAD / 4; i += 512) ((unsigned*)(xs + HT * XHEAD))[i] = 0;
   const unsigned char* wl = w_s + lane * 16;
 
@@ -440,11 +442,6 @@ __global__ __launch_bounds__(512) void k_split_scores(SplitScoresArgs a) {
       const int h = 32 * ks + 8 * g + 4 * q + (c >> 2);
       xrd[ks][q] = (h < H ? h : HT) * XHEAD + 8 * (c & 3);
     }
-  // rows of r elements as operands: element 8 g + e of the row, zero beyond it
-  pf_u32x4 r_mask;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) r_mask[e] = (8 * g + 2 * e < r ? 0xffffu : 0u) | (8 * g + 2 * e + 1 < r ? 0xffff0000u : 0u);
-  const int g8 = 8 * g < r ? 8 * g : 0;
   // the 8 elements from `off` on, or (past `limit`) the last 8 of the tensor; shifted into place when they are used
   auto load8 = [&](const void* base, int off, int limit) { return *(const pf_u32x4_a2*)((const char*)base + 2u * (unsigned)min(off, limit)); };
   auto shift8 = [&](pf_u32x4 x, int by) {                      // drop the first `by` (0 .. 7) elements
@@ -455,27 +452,20 @@ __global__ __launch_bounds__(512) void k_split_scores(SplitScoresArgs a) {
     return pf_u32x4{(unsigned)lo, (unsigned)(lo >> 32), (unsigned)up, (unsigned)(up >> 32)};
   };
   auto limit_of = [&](size_t total_elems, size_t base) { return (int)min((long long)(total_elems - 8 - base), 0x7fffffffLL); };
-  const size_t hs = (size_t)Lq * Lk, s_elems = (size_t)a.B * H * hs, k_elems = (size_t)a.B * a.Hkv * Lk * r,
-               q_elems = (size_t)a.B * H * Lq * r;
+  const size_t hs = (size_t)Lq * Lk, s_elems = (size_t)a.B * H * hs;
   const int xl = lane & (32 * TKB - 1), x_hl = lane / (32 * TKB);   // A_{n-1} chunk: row, 8 keys, head of the load
   const int x_r = xl / (TK / 8), x_k = 8 * (xl % (TK / 8));
-  const int k_key = TKB == 2 ? 8 * (c >> 2) + (c & 3) : c;     // key of MFMA row c (+ 4 u): a lane ends with 4 TKB consecutive keys
-
   while (pos < hi) {
     // ---- one row block: key tiles [t_first, t_last) -----------------------------------------------
     const int i0 = a.row0 + 16 * rg, t_first = tile0;
     const int t_last = (int)min((long long)tiles_of(rg), tile0 + (hi - pos));
     const bool last_b = b == a.B - 1;
-    pf_u32x4 qop[HPW];
+    bf16x8 qop[HPW];
 #pragma unroll
-    for (int u = 0; u < HPW; ++u) {
-      const size_t base = ((size_t)b * H + min(wv + NW * u, H - 1)) * Lq * r;
-      const int off = min(i0 + c, Lq - 1) * r + g8, lim = limit_of(q_elems, base);
-      qop[u] = *(const pf_u32x4_a2*)(a.q_lr + (ptrdiff_t)base + min(off, lim));   // (few short rows: lim may be negative)
-      if (__any(off > lim)) qop[u] = shift8(qop[u], max(off - lim, 0));
-      qop[u] &= r_mask;
-    }
-    pf_u32x4 xr[XCH], kop[HPW][TKB];
+    for (int u = 0; u < HPW; ++u)
+      qop[u] = *(const bf16x8*)(a.qp + (((size_t)b * H + min(wv + NW * u, H - 1)) * a.Lqp + i0 + c) * 32 + 8 * g);
+    pf_u32x4 xr[XCH];
+    bf16x8 kop[HPW][TKB];
     auto x_off = [&](int tile) { return min(i0 + x_r, Lq - 1) * Lk + min(tile * TK + x_k, Lk - 1) + (HPL == 2 ? x_hl * (int)hs : 0); };
     auto x_head = [&](int u) { return min((wv + NW * u) * HPL, (H - 1) / HPL * HPL); };
     auto load_x = [&](int tile) {
@@ -497,31 +487,29 @@ __global__ __launch_bounds__(512) void k_split_scores(SplitScoresArgs a) {
         if (h < H) *(pf_u32x4*)(xs + h * XHEAD + xl * 16) = x;
       }
     };
-    auto k_off = [&](int tile, int u) { return min(tile * TK + k_key + 4 * u, Lk - 1) * r + g8; };
-    auto kv_base = [&](int u) { return ((size_t)b * a.Hkv + min(wv + NW * u, H - 1) / group) * Lk * r; };
+    // K_LR operand q of the tile: keys 8 (m / 4) + m % 4 + 4 q in MFMA row m, so that a lane ends with 8 consecutive ones
+    // (TKB = 1: key m in row m, 4 consecutive ones)
     auto load_k = [&](int tile, int u) {
-      const size_t base = kv_base(u);
-#pragma unroll
-      for (int q = 0; q < TKB; ++q) kop[u][q] = load8(a.k_lr + base, k_off(tile, q), limit_of(k_elems, base));
-    };
-    // A_delta of this wave's head u: row c, keys 4 TKB g + 4 q + v in d[q][v]
-    auto delta = [&](int tile, int u, f32x4 (&d)[TKB]) {
-      const bool tail = last_b && tile * TK + TK > Lk - 8;
+      const bf16_t* base = a.kp + (((size_t)b * a.Hkv + min(wv + NW * u, H - 1) / group) * a.Lkp + (size_t)(tile * TKB / 2) * PF_TK) * 32;
 #pragma unroll
       for (int q = 0; q < TKB; ++q) {
-        pf_u32x4 kx = kop[u][q];
-        if (tail) {
-          const int off = k_off(tile, q), lim = limit_of(k_elems, kv_base(u));
-          if (__any(off > lim)) kx = shift8(kx, max(off - lim, 0));
-        }
+        int at = q * 512 + lane * 8;
+        if (TKB == 1) at = ((c >> 2) & 1) * 512 + (16 * g + 8 * (tile & 1) + 4 * (c >> 3) + (c & 3)) * 8;   // key 16 (tile % 2) + c
+        kop[u][q] = *(const bf16x8*)(base + at);
+      }
+    };
+    // A_delta of this wave's head u: row c, keys 4 TKB g + 4 q + v in d[q][v]
+    auto delta = [&](int u, f32x4 (&d)[TKB]) {
+#pragma unroll
+      for (int q = 0; q < TKB; ++q) {
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-        d[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kx & r_mask), __builtin_bit_cast(bf16x8, qop[u]), zero, 0, 0, 0) *
-               a.dscale;
+        d[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[u][q], qop[u], zero, 0, 0, 0) * a.dscale;
       }
     };
     load_x(t_first);
+    if (CONCAT)
 #pragma unroll
-    for (int u = 0; u < HPW; ++u) load_k(t_first, u);
+      for (int u = 0; u < HPW; ++u) load_k(t_first, u);
     store_x(t_first);
 
     for (int tile = t_first; tile < t_last; ++tile) {
@@ -532,15 +520,19 @@ __global__ __launch_bounds__(512) void k_split_scores(SplitScoresArgs a) {
         for (int u = 0; u < HPW; ++u) {
           const int h = wv + NW * u;
           f32x4 d[TKB];
-          delta(tile, u, d);
-          load_k(tile_n, u);
+          delta(u, d);
           if (h < H)
 #pragma unroll
             for (int q = 0; q < TKB; ++q) *(f32x4*)(ys + h * YHEAD + c * YROW + (4 * TKB * g + 4 * q) * 4) = d[q];
         }
       }
       lds_barrier();                                           // xs (CONCAT: and A_delta) complete
+      // All loads of a tile go out here and are waited for behind the FFN, ahead of the stores: a load behind a store that
+      // sits in a branch could only be waited for together with it (13 us per tile, 32 heads, with the K_LR rows loaded
+      // head by head between the stores).
       load_x(tile_n);
+#pragma unroll
+      for (int u = 0; u < HPW; ++u) load_k(CONCAT ? tile_n : tile, u);
       f32x4 y[NBW][HB];
 #pragma unroll
       for (int n0 = 0; n0 < NBW; n0 += NBLK) {
@@ -631,48 +623,43 @@ __global__ __launch_bounds__(512) void k_split_scores(SplitScoresArgs a) {
       }
       lds_barrier();                                           // ys complete, xs free
       store_x(tile_n);
-      const int j = tile * TK + 4 * TKB * g;                   // this lane's keys j .. of row i0 + c
-      const int gi = i0 + c;
-      const int vis = gi < row_end ? n_visible(gi, Lq, Lk, a.causal) : 0;
-      const bool full = i0 + 16 <= row_end && tile * TK + TK <= n_visible(i0, Lq, Lk, a.causal);   // workgroup-uniform
+      f32x4 an[HPW][TKB];
+      if constexpr (!CONCAT)
+#pragma unroll
+        for (int u = 0; u < HPW; ++u) delta(u, an[u]);
+      // out as rows: lane -> row lane / (2 TKB), 8 keys
+      const int o_r = lane / (2 * TKB), o_k = 8 * (lane % (2 * TKB));
+      const int j = tile * TK + o_k, gi = i0 + o_r;
+      const int vis = o_r < 16 && gi < row_end ? n_visible(gi, Lq, Lk, a.causal) : 0;
+      const bool full = TKB == 2 && i0 + 16 <= row_end && tile * TK + TK <= n_visible(i0, Lq, Lk, a.causal);   // workgroup-uniform
 #pragma unroll
       for (int u = 0; u < HPW; ++u) {
         const int h = wv + NW * u;
         if (HT % NW != 0 || HT != H)
           if (h >= H) continue;                                // (wave-uniform)
-        f32x4 d[TKB];
-        if constexpr (!CONCAT) {
-          delta(tile, u, d);
-          load_k(tile_n, u);
-        }
-        const unsigned char* yp = ys + h * YHEAD + c * YROW + 4 * TKB * g * 4;
+        f32x4 (&d)[TKB] = an[u];
+        unsigned char* yh = ys + h * YHEAD;
 #pragma unroll
         for (int q = 0; q < TKB; ++q) {
-          const f32x4 yq = *(const f32x4*)(yp + 16 * q);
+          const f32x4 yq = *(const f32x4*)(yh + c * YROW + (4 * TKB * g + 4 * q) * 4);
           d[q] = CONCAT ? yq : d[q] + yq;
         }
         if (a.exact) {
-          float* ep = a.exact + ((((size_t)b * n_rg + rg) * n_kt + tile * TKB / 2) * H + h) * (16 * PF_TK) + c * PF_TK + 4 * TKB * g +
-                      (TKB == 1 ? 16 * (tile & 1) : 0);
+          float* ep = a.exact + ((((size_t)b * n_rg + rg) * n_kt + tile * TKB / 2) * H + h) * (16 * PF_TK);
 #pragma unroll
-          for (int q = 0; q < TKB; ++q) *(f32x4*)(ep + 4 * q) = d[q];
+          for (int q = 0; q < TKB; ++q)
+            *(f32x4*)(ep + (TKB == 2 ? split_tile_at(c, g, q) : split_tile_at(c, 2 * (tile & 1) + (g >> 1), g & 1))) = d[q];
         }
         if (a.scores) {
-          pf_u32x4 w = {0u, 0u, 0u, 0u};
+          // the head's y has been read (by this wave alone): its place takes the half tile, [row][key]
 #pragma unroll
-          for (int q = 0; q < TKB; ++q) {
-            const f16x4 hv = {f32_to_half_sat(d[q][0]), f32_to_half_sat(d[q][1]), f32_to_half_sat(d[q][2]), f32_to_half_sat(d[q][3])};
-            const uint2 p = __builtin_bit_cast(uint2, hv);
-            w[2 * q] = p.x;
-            w[2 * q + 1] = p.y;
-          }
+          for (int q = 0; q < TKB; ++q)
+            *(f16x4*)(yh + c * (2 * TK) + (4 * TKB * g + 4 * q) * 2) =
+                f16x4{f32_to_half_sat(d[q][0]), f32_to_half_sat(d[q][1]), f32_to_half_sat(d[q][2]), f32_to_half_sat(d[q][3])};
+          const pf_u32x4 w = *(const pf_u32x4*)(yh + (lane % (32 * TKB)) * 16);
           half_t* sp = a.scores + ((size_t)b * H + h) * hs + (unsigned)(min(gi, Lq - 1) * Lk + j);
-          if (full || j + 4 * TKB <= vis) {
-            if (TKB == 2) *(pf_u32x4_a2*)sp = w;
-            else *(u64_a2*)sp = w[0] | (unsigned long long)w[1] << 32;
-          } else if (j < vis) {
-            store_row_part_any(sp, w, vis - j);
-          }
+          if (full || j + 8 <= vis) *(pf_u32x4_a2*)sp = w;
+          else if (j < vis) store_row_part_any(sp, w, vis - j);
         }
       }
     }

@@ -10,7 +10,7 @@ bool bf16_ragged_rows(const lisa_desc* d) {
   return d->dtype == LISA_BF16 && d->d_k == 128 && !score_rows_aligned(d);
 }
 
-// 32-bit offsets inside (two heads of) a score tensor and inside a head's operand rows; eight elements to read at least.
+// 32-bit offsets inside two heads of a score tensor; eight elements of a row to read at least.
 static bool split_sizes_ok(const lisa_desc* d) {
   return d->Lk >= 8 && (long long)(d->Lq + 16) * (d->Lk + PF_TK) < (1LL << 30);
 }
@@ -40,7 +40,7 @@ int split_keys(const lisa_desc* d) {
 bool split_scores_ok(const lisa_desc* d) {
   if (!split_attn_ok(d) || !split_sizes_ok(d) || (d->act != LISA_ACT_RELU && d->act != LISA_ACT_SILU)) return false;
   if (d->mix != LISA_MIX_ADD && d->mix != LISA_MIX_CONCAT) return false;
-  if (d->H > 40 || d->r > 32 || (long long)d->H * d->Lq * d->r < 8) return false;
+  if (d->H > 40 || d->r > 32) return false;
   return split_keys(d) > 0;
 }
 
@@ -51,10 +51,24 @@ int split_chunk_rows(const lisa_desc* d) {
   const size_t rows = std::max<size_t>(16, (((size_t)256 << 20) / row) & ~(size_t)15);
   return (int)std::min<size_t>(rows, (size_t)d->Lq);
 }
-size_t split_chunk_bytes(const lisa_desc* d) {
+namespace {
+// Workspace: the float32 tiles of a chunk, then the padded operands.
+struct SplitWs {
+  size_t qp, kp, total;
+  int Lqp, Lkp;
+};
+SplitWs split_ws(const lisa_desc* d) {
+  SplitWs w;
+  w.Lqp = (d->Lq + PF_ROWS - 1) / PF_ROWS * PF_ROWS;
+  w.Lkp = (d->Lk + 63) / 64 * 64;
   const size_t rows = (size_t)(split_chunk_rows(d) + 15) / 16 * 16;
-  return (size_t)d->B * d->H * rows * ((d->Lk + PF_TK - 1) / PF_TK * PF_TK) * sizeof(float);
+  w.qp = (size_t)d->B * d->H * rows * ((d->Lk + PF_TK - 1) / PF_TK * PF_TK) * sizeof(float);
+  w.kp = w.qp + round_up((size_t)d->B * d->H * w.Lqp * 32 * 2, 256);
+  w.total = w.kp + round_up((size_t)d->B * d->Hkv * w.Lkp * 32 * 2, 256);
+  return w;
 }
+}  // namespace
+size_t split_bytes(const lisa_desc* d) { return split_ws(d).total; }
 
 namespace {
 template <int HT, bool CONCAT, int TKB>
@@ -84,12 +98,27 @@ int launch_scores_h(const lisa_desc* d, SplitScoresArgs& a, hipStream_t st) {
 }
 }  // namespace
 
-int run_split_scores(const lisa_desc* d, const void* q_lr, const void* k_lr, const void* prev, const void* w1,
-                     const void* w2, void* scores, float* exact, int row0, int n_rows, hipStream_t st) {
+// Q_LR and K_LR into the workspace as the scores kernel reads them.
+int run_split_prepare(const lisa_desc* d, const void* q_lr, const void* k_lr, void* workspace, hipStream_t st) {
+  const SplitWs w = split_ws(d);
+  char* ws = (char*)workspace;
+  const size_t rows = (size_t)d->B * d->H * w.Lqp + (size_t)d->B * d->Hkv * w.Lkp;
+  StageScope prof("k_prepare_prefill", st);
+  k_prepare_prefill<true><<<(unsigned)((rows + 63) / 64), 256, 0, st>>>(
+      (const bf16_t*)q_lr, (const bf16_t*)k_lr, nullptr, (bf16_t*)(ws + w.qp), (bf16_t*)(ws + w.kp), nullptr, d->B, d->H, d->Hkv,
+      d->Lq, d->Lk, w.Lqp, w.Lkp, d->r, 0);
+  return check_launch();
+}
+
+int run_split_scores(const lisa_desc* d, const void* prev, const void* w1, const void* w2, void* scores, void* workspace,
+                     int row0, int n_rows, hipStream_t st) {
+  const SplitWs w = split_ws(d);
   SplitScoresArgs a{};
-  a.q_lr = (const bf16_t*)q_lr; a.k_lr = (const bf16_t*)k_lr; a.prev = (const half_t*)prev;
-  a.w1 = (const bf16_t*)w1; a.w2 = (const bf16_t*)w2; a.scores = (half_t*)scores; a.exact = exact;
-  a.B = d->B; a.H = d->H; a.Hkv = d->Hkv; a.Lq = d->Lq; a.Lk = d->Lk; a.r = d->r; a.F = d->F; a.causal = d->causal;
+  a.qp = (const bf16_t*)((char*)workspace + w.qp); a.kp = (const bf16_t*)((char*)workspace + w.kp);
+  a.exact = (float*)workspace; a.Lqp = w.Lqp; a.Lkp = w.Lkp;
+  a.prev = (const half_t*)prev; a.scores = (half_t*)scores;
+  a.w1 = (const bf16_t*)w1; a.w2 = (const bf16_t*)w2;
+  a.B = d->B; a.H = d->H; a.Hkv = d->Hkv; a.Lq = d->Lq; a.Lk = d->Lk; a.F = d->F; a.causal = d->causal;
   a.row0 = row0; a.n_rows = n_rows;
   a.dscale = pick_scale(d->delta_scale, d->r);
   switch (split_heads(d->H)) {

@@ -343,9 +343,11 @@ int run_lisa(const lisa_desc* d, const void* q_lr, const void* k_lr, KeyStrides 
   const void* an = exact ? (void*)exact : scores;
   const bool split = in_chunks(d) && split_scores_ok(d);     // (float32 scores in tiles)
   const int step = split ? split_chunk_rows(d) : in_chunks(d) ? f32_chunk_rows(d) : d->Lq;
+  if (split)
+    if (int rc = run_split_prepare(d, q_lr, k_lr, exact, st)) return rc;
   for (int row0 = 0; row0 < d->Lq; row0 += step) {
     const int n_rows = std::min(step, d->Lq - row0);
-    int rc = split              ? run_split_scores(d, q_lr, k_lr, prev, w1, w2, scores, exact, row0, n_rows, st)
+    int rc = split              ? run_split_scores(d, prev, w1, w2, scores, exact, row0, n_rows, st)
              : f32_scores_ok(d) ? run_f32_scores(d, q_lr, k_lr, prev, w1, w2, scores, exact, row0, n_rows, st)
                               : launch_lisa_scores<T, S>(d, q_lr, k_lr, ks, prev, w1, w2, scores, exact, row0, n_rows, st);
     if (rc) return rc;
@@ -1069,7 +1071,7 @@ size_t lisa_workspace_bytes(const lisa_desc* desc, int which) {
       if (relu_equivalent(desc, &eq) && scores_mfma_ok(&eq))
         return round_up(concat_ws(&eq).total, 256) + synth_ffn_bytes(desc);
       if (in_chunks(desc))                                   // (k_split_attn reads up to 31 floats past row-major scores)
-        return std::max(split_scores_ok(desc) ? split_chunk_bytes(desc) : 0, f32_chunk_bytes(desc) + 256);
+        return std::max(split_scores_ok(desc) ? split_bytes(desc) : 0, f32_chunk_bytes(desc) + 256);
       return exact_bytes(desc) + (std_prefill_fast_ok(desc) ? std_prefill_ws(desc) : 0);
     }
     case LISA_WS_DECODE: {
