@@ -134,9 +134,12 @@ constexpr int PJ_ROWB = PJ_TK * 2;              // bytes per LDS row
 //   <2,4,4,2>  256 x 256 outputs per workgroup, the densest in MFMA work per fetched byte;
 //   <4,2,2,3>  256 x 192, for problems whose 256-wide tiles would leave a quarter of the CUs
 //              idle or add a nearly empty last round of workgroups;
-//   <4,2,1,1>  128 x 64, where the others would leave half of the CUs idle: bound by the latency of a
-//              step's loads (0.6 us of 64 steps at d = 4096), four MFMAs a wave and step.
-template <int WM, int WN, int BM, int BN>
+//   <4,2,1,1>  128 x 64, where the others would leave half of the CUs idle: four MFMAs a wave and step, so the loads of
+//              NBUF - 1 steps are in flight where a compute unit has one workgroup: 0.40 us a step of d = 4096 with two
+//              or more steps in flight, 0.58 with one; what is left is the 24 KB a step through the unit's
+//              vector memory path.  (Two workgroups hide each other's latency: two buffers there.)
+// NBUF: LDS buffers, a step of both operands each.
+template <int WM, int WN, int BM, int BN, int NBUF = 2>
 struct ProjTile {
   static_assert(WM * WN == 8, "8 waves");
   static constexpr int TM = WM * BM * 32, TN = WN * BN * 32;
@@ -145,7 +148,7 @@ struct ProjTile {
   static constexpr int STEP = XTILE + WTILE;              // one step of both operands
   static constexpr int STG_ROW = BN * 64 + 16;            // bytes per row of a wave's output staging piece (padded)
   static constexpr int STG_WAVE = BM * 32 * STG_ROW;
-  static constexpr int LDS = 2 * STEP > 8 * STG_WAVE ? 2 * STEP : 8 * STG_WAVE;
+  static constexpr int LDS = NBUF * STEP > 8 * STG_WAVE ? NBUF * STEP : 8 * STG_WAVE;
   static_assert(TM % 64 == 0 && TN % 64 == 0 && LDS <= 160 * 1024, "tile shape");
 };
 constexpr int PJ_HEADW = 32;                    // virtual columns of a Q_LR / K_LR head
@@ -167,15 +170,16 @@ constexpr int PJ_HEADW = 32;                    // virtual columns of a Q_LR / K
     __builtin_amdgcn_sched_group_barrier(0x008, (n_mfma) - 5, 0); \
   } while (0)
 
-// Barrier that publishes a tile loaded straight into the LDS: the wave's own loads have landed
+// Barrier that publishes a tile loaded straight into the LDS: the wave's own loads but the last LEFT have landed
 // (vmcnt) and its LDS reads are done (lgkmcnt) before it arrives.
+template <int LEFT>
 __device__ __forceinline__ void pj_tile_barrier() {
-  __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  __asm__ volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LEFT) : "memory");
 }
 
-template <int WM, int WN, int BM, int BN>
+template <int WM, int WN, int BM, int BN, int NBUF = 2>
 __global__ __launch_bounds__(512) void k_project_mfma(ProjectArgs a) {
-  typedef ProjTile<WM, WN, BM, BN> G;
+  typedef ProjTile<WM, WN, BM, BN, NBUF> G;
   extern __shared__ __align__(16) unsigned char pj_lds[];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int wm = wv / WN, wn = wv % WN;
@@ -186,7 +190,13 @@ __global__ __launch_bounds__(512) void k_project_mfma(ProjectArgs a) {
   int tm, tn;
   {
     const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-    if (a.own_n) {
+    if (NBUF > 2) {
+      // (a single round: equal shares of the tiles by columns, so that no XCD has more of them than compute units)
+      const int n_t = a.n_m * a.n_n, first = (int)((long long)n_t * xcd / 8), at = first + j;
+      if (at >= (int)((long long)n_t * (xcd + 1) / 8)) return;
+      tn = at / a.n_m;
+      tm = at - tn * a.n_m;
+    } else if (a.own_n) {
       tn = xcd + 8 * (j / a.n_m);
       tm = j % a.n_m;
     } else {
@@ -295,24 +305,27 @@ __global__ __launch_bounds__(512) void k_project_mfma(ProjectArgs a) {
     for (int e = 0; e < 8; ++e) fb[1][bn][e] = (__bf16)0.f;
 
   const int nk = D / PJ_TK;
-  load_part(0, 0, 0);
-  load_part(0, 0, 1);
-  int kt = 0;
+  constexpr int LEFT = (NBUF - 2) * (G::XN + G::WNLD);      // loads of the steps behind the one that is waited for
+#pragma unroll
+  for (int s = 0; s < NBUF - 1; ++s) {
+    load_part(min(s, nk - 1), s, 0);
+    load_part(min(s, nk - 1), s, 1);
+  }
+  int kt = 0, cb = 0, nb = NBUF - 1;                        // buffers of step kt and of the step loaded meanwhile
   for (; kt + 1 < nk; ++kt) {
-    // the loads of step kt have landed in buffer kt & 1 and every wave has read all it needs of
-    // the other buffer
-    pj_tile_barrier();
-    const unsigned char* buf = pj_lds + (kt & 1) * G::STEP;
-    const int nb = (kt + 1) & 1;
-    // sub-step 3 of step kt - 1 | operands of sub-step 0, first half of the loads of step kt + 1
+    // the loads of step kt have landed in its buffer and every wave has read all it needs of the buffer of step kt - 1
+    pj_tile_barrier<LEFT>();
+    const unsigned char* buf = pj_lds + cb * G::STEP;
+    const int kn = min(kt + NBUF - 1, nk - 1);              // (past the end: loads that nobody reads keep the count)
+    // sub-step 3 of step kt - 1 | operands of sub-step 0, first half of the loads of step kt + NBUF - 1
     read_frags(buf, 0, 0);
-    load_part(kt + 1, nb, 0);
+    load_part(kn, nb, 0);
     mfmas(1);
     if constexpr (BM * BN >= 6) PJ_INTERLEAVE(0x020, BM * BN);
     __builtin_amdgcn_sched_barrier(0);
     // sub-step 0 | operands of sub-step 1, second half of the loads
     read_frags(buf, 1, 1);
-    load_part(kt + 1, nb, 1);
+    load_part(kn, nb, 1);
     mfmas(0);
     if constexpr (BM * BN >= 6) PJ_INTERLEAVE(0x020, BM * BN);
     __builtin_amdgcn_sched_barrier(0);
@@ -326,10 +339,12 @@ __global__ __launch_bounds__(512) void k_project_mfma(ProjectArgs a) {
     mfmas(0);
     if constexpr (BM * BN >= 6) PJ_INTERLEAVE(0x020, BM * BN);
     __builtin_amdgcn_sched_barrier(0);
+    cb = cb + 1 == NBUF ? 0 : cb + 1;
+    nb = nb + 1 == NBUF ? 0 : nb + 1;
   }
   {                                                        // the last step: nothing left to load
-    pj_tile_barrier();
-    const unsigned char* buf = pj_lds + (kt & 1) * G::STEP;
+    pj_tile_barrier<0>();
+    const unsigned char* buf = pj_lds + cb * G::STEP;
     read_frags(buf, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
     mfmas(1);

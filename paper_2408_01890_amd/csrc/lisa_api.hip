@@ -857,11 +857,13 @@ static int project_qkv(const lisa_proj_desc* d, const void* x, const void* w, vo
     };
     // (the narrower tile does less MFMA work per fetched byte: it must win by a margin)
     int tn = rounds_cost(192) * 8 < rounds_cost(256) * 7 ? 192 : 256;
-    // Tiles that would leave half of the CUs or more without one: 128 x 64.  A step of the reduction takes
-    // about as long for a small tile as for a large one (its loads' latency), so more of them side by side
-    // win: LLaMA3-8B, 777 tokens, 48 tiles, 83 -> 39 us; LLaMA2-7B, 1024, 128 tiles, 87 -> 65; on the other side of
-    // the line LLaMA2-7B at 1500 tokens, 192 tiles, 86 us, where 256 CUs are nearly full.
-    bool small = ((M + 255) / 256) * ((n_virtual + tn - 1) / tn) <= kComputeUnits / 2;
+    // Tiles that would leave half of the CUs or more without one: 128 x 64, while those make three rounds at most.
+    // A step of the reduction takes about as long for a small tile as for a large one (its loads' latency), so
+    // more of them side by side win: LLaMA3-8B, 777 tokens, 48 tiles, 80 -> 28 us; LLaMA2-7B, 1024, 128 tiles,
+    // 80 -> 66; on the other side of the lines LLaMA2-7B at 1500 tokens, 192 tiles, 85 us, where 256 CUs are nearly
+    // full, and at 1100, 774 small tiles, 80 us against 91.
+    const long long small_tiles = ((M + 127) / 128) * ((n_virtual + 63) / 64);
+    bool small = ((M + 255) / 256) * ((n_virtual + tn - 1) / tn) <= kComputeUnits / 2 && small_tiles <= 3 * kComputeUnits;
     {                                                       // tests force either geometry
       const int v = g_tune[LISA_TUNE_PROJECT_TN];
       if (v == 192 || v == 256) tn = v, small = false;
@@ -878,10 +880,14 @@ static int project_qkv(const lisa_proj_desc* d, const void* x, const void* w, vo
     const int per_xcd = a.own_n ? (a.n_n + 7) / 8 * a.n_m : (a.n_m + 7) / 8 * a.n_n;
     StageScope scope("k_project_mfma", st);
     if (small) {
-      auto kern = k_project_mfma<4, 2, 1, 1>;
-      constexpr int lds = ProjTile<4, 2, 1, 1>::LDS;
-      static_assert(lds <= 64 * 1024, "no attribute needed");
-      kern<<<dim3(8 * per_xcd), 512, lds, st>>>(a);
+      // a single round: three steps in the LDS and equal shares per XCD (777 tokens, 252 tiles, 37 -> 28 us); more workgroups
+      // than compute units: two steps, and two of them per unit (LLaMA2-7B, 1024 tokens, 67 us against 73)
+      const bool one = small_tiles <= kComputeUnits;
+      auto kern = one ? k_project_mfma<4, 2, 1, 1, 3> : k_project_mfma<4, 2, 1, 1>;
+      const int lds = one ? ProjTile<4, 2, 1, 1, 3>::LDS : ProjTile<4, 2, 1, 1>::LDS;
+      hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+      if (e != hipSuccess) return hip_fail(e);
+      kern<<<dim3(one ? (unsigned)((small_tiles + 7) / 8 * 8) : 8 * per_xcd), 512, lds, st>>>(a);
     } else if (tn == 256) {
       auto kern = k_project_mfma<2, 4, 4, 2>;
       constexpr int lds = ProjTile<2, 4, 4, 2>::LDS;
