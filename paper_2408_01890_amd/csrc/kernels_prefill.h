@@ -278,9 +278,10 @@ __device__ __forceinline__ void store_row_part(void* p, pf_u32x4 v, int n) {
 // NG = 1 and 32 heads (XSTG below) the whole layer of a row block runs in one workgroup: the FFN is
 // computed once, the A_{n-1} tile is read once, and a wave issues 10 operand loads per tile and
 // key/value head for four query heads.
+// TE: tiled scores and A_n wanted, known at compile time (otherwise read from the arguments).
 // FTRIM: F <= 32 FS - 16, the last 16 hidden units are padding and their products are left out
 // (the 40 -> 80 -> 40 network of the LLaMA2-13B shape: 10 instead of 12 MFMAs of the first layer).
-template <int NG, int FS, int HPW, int NW, int ACT = 0, int RS = 1, int SHG = 0, bool FTRIM = false>
+template <int NG, int FS, int HPW, int NW, int ACT = 0, int RS = 1, int SHG = 0, bool FTRIM = false, bool TE = false>
 __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
   static_assert(RS == 1 || HPW == 1, "row slices: one head per wave");
   // XSTG: the A_{n-1} piece is double buffered by tile parity and the buffers double as the staging
@@ -303,6 +304,7 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
   constexpr int NBW = ((2 * PF_ROWS + NW - 1) / NW + 1) / 2 * 2;   // position blocks per wave in stage A (even)
   extern __shared__ __align__(16) unsigned char pf_lds[];
   const int Lq = a.Lq, Lk = a.Lk;
+  const bool tiled = TE || a.tiled, emit = TE || a.scores;
   unsigned char* xs = pf_lds;                               // A_{n-1} piece, half
   unsigned char* ys = xs + (XSTG ? 2 : 1) * H * PF_XS_HEAD; // y piece of the group, float
   unsigned short* w_s = (unsigned short*)(ys + GH * PF_YS_HEAD);
@@ -354,8 +356,8 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
   // translation cache of the compute unit for most of them: 36 misses per step).
   const int n_rb = (Lq + PF_ROWS - 1) / PF_ROWS, n_kt = (Lk + PF_TK - 1) / PF_TK;
   constexpr int TILE_ELEMS = PF_ROWS * PF_TK;
-  const size_t head_elems = a.tiled ? (size_t)TILE_ELEMS : (size_t)Lq * Lk;                 // head stride
-  const size_t seq_elems = a.tiled ? (size_t)n_rb * n_kt * H * TILE_ELEMS : (size_t)H * Lq * Lk;
+  const size_t head_elems = tiled ? (size_t)TILE_ELEMS : (size_t)Lq * Lk;                 // head stride
+  const size_t seq_elems = tiled ? (size_t)n_rb * n_kt * H * TILE_ELEMS : (size_t)H * Lq * Lk;
   const size_t tile_stride = (size_t)H * TILE_ELEMS;        // tiled: elements from one (rb, kt) to the next
   // wave-uniform bases of this wave's heads (scalar registers)
   const bf16_t* k_base[HPW];     // K_LR rows of the head's key/value head
@@ -366,7 +368,7 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
     const int h = h_first + hh, kv = h / group;
     k_base[hh] = a.kp + ((size_t)b * a.Hkv + kv) * a.Lkp * 32;
     v_base[hh] = a.vt + ((size_t)b * a.Hkv + kv) * (a.Lkp / 8) * (DK * 8);
-    s_base[hh] = a.scores ? a.scores + (size_t)b * seq_elems + (size_t)h * head_elems : nullptr;
+    s_base[hh] = emit ? a.scores + (size_t)b * seq_elems + (size_t)h * head_elems : nullptr;
   }
   const half_t* x_base[XCH];     // A_{n-1} of head wv + NW u (XSTG: of the wave's own heads)
 #pragma unroll
@@ -448,7 +450,7 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
     auto load_x = [&](int tile, int rs, pf_u32x4 (&xr)[XCH]) {
       unsigned off;
       size_t at = 0;                                          // wave-uniform element offset of the tile
-      if (a.tiled) {
+      if (tiled) {
         at = ((size_t)min((i0 >> 4) + rs, n_rb - 1) * n_kt + tile) * tile_stride;
         off = lane * 16;
       } else {
@@ -532,7 +534,7 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
       const bool pair_full = (tile | 1) < n_full_of(rs);      // workgroup-uniform
       const int jc = jp + 8 * (lane & 7);
       half_t* st = s_base[hh] + jp;
-      if (a.tiled) {
+      if (tiled) {
         // each staged tile of the pair is 1 KB of consecutive memory: lane -> row lane / 4, 16
         // bytes; what lies above the diagonal inside a stored tile is unspecified
         if (i0 + PF_ROWS * rs >= Lq) return;                 // (a slice without rows)
@@ -576,6 +578,20 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
     // loop then follow from the loop's own issue order alone (a load pending on entry would cap
     // them at what the first pass needs and drain the prefetch on every pass).
     __builtin_amdgcn_s_waitcnt(0x0F70);                       // vmcnt(0), others untouched
+    f16x8 hvs[HPW];
+    // TE: A_n of a step leaves at the start of stage A of the next one, where the load / store pipe has room, and ahead of
+    // the loads of stage A (loads and stores of a wave complete in one order).  Against stores where A_n is
+    // made: LLaMA2-7B heads, B = 4, L = 4096, 2517 -> 2186 us; LLaMA3-8B, 4 x 8192, 5731 -> 5560; LLaMA2-13B, 8 x 4096,
+    // 7866 -> 7628.  Behind the A_{n-1} loads of stage A: 5786 and 7896; at the end of stage B, behind those loads
+    // and ahead of them: 5961 and 8448.
+    size_t held_at = ~(size_t)0;
+    auto store_held = [&]() {
+      if (held_at == ~(size_t)0) return;
+#pragma unroll
+      for (int hh = 0; hh < HPW; ++hh)                        // (plain stores: 2 - 6 % longer)
+        __builtin_nontemporal_store(__builtin_bit_cast(pf_u32x4, hvs[hh]),
+                                    (pf_u32x4*)((char*)(s_base[hh] + held_at) + (unsigned)(c * 64 + g * 16)));
+    };
     for (int it = 0; it < n_mine; ++it) {
       const int tile = tile_at(it);
       const int j0 = tile * PF_TK;
@@ -640,6 +656,7 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
             }
           }
         }
+        if (TE && q == 0) store_held();                        // (behind the reads of the first blocks: 0.6 - 2.5 %)
         f32x4 y[NBLK][HBO];
         if (WREG) ffn.template apply<NBLK>(x, y);
         else Ffn::template apply_lds<NBLK, FTRIM>(w_s, x, y);
@@ -689,11 +706,13 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
           an[4 + e] = s1[e] * a.dscale + y1[e];
         }
         // A_n for the next layer: into this wave's staging tile, stored at the end of the stage
-        if (a.scores) {
+        if (emit) {
           f16x8 hv;
 #pragma unroll
           for (int e = 0; e < 8; ++e) hv[e] = f32_to_half_sat(an[e]);
-          if (a.tiled && !XSTG) {
+          if (TE) {
+            hvs[hh] = hv;                                      // (stored by store_held())
+          } else if (tiled && !XSTG) {
             // tiled scores: the lane's 8 keys of row c are 16 bytes of the head's KB and leave from
             // the registers (through the staging tile, which row-major scores need to pair two
             // tiles into whole lines, the layer took 1 - 3 % longer)
@@ -754,7 +773,7 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
       // A_n is written once both tiles of a pair are staged (64-byte pieces of a line reach HBM at
       // half the rate of whole lines): after the odd tile when walking upwards (or after the
       // slice's last tile, which may have no partner), after the even tile when walking downwards.
-      if (a.scores && (XSTG || !a.tiled) && (rep ? (tile & 1) == 0 : ((tile & 1) == 1 || tile >= last_tile_of(rs)))) pending[rs] = tile;
+      if (emit && (XSTG || !tiled) && (rep ? (tile & 1) == 0 : ((tile & 1) == 1 || tile >= last_tile_of(rs)))) pending[rs] = tile;
       if (XSTG && pending[rs] >= 0) {
         // the pair sits in the two A_{n-1} buffers, which the next pieces are about to overwrite
 #pragma unroll
@@ -764,8 +783,13 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
       // every wave left stage A of this step, the last reader of xs, before B2; stage A of the
       // next step reads the new piece after B1
       store_x(xr, x_tile);
+      if (TE) {
+        if (RS == 1 || i0 + PF_ROWS * rs < Lq) held_at = ((size_t)((i0 >> 4) + rs) * n_kt + tile) * tile_stride;   // wave-uniform
+        else held_at = ~(size_t)0;
+      }
       }
     }
+    if (TE) store_held();
 #pragma unroll
     for (int rs = 0; rs < RS; ++rs) {
       if (pending[rs] >= 0) {

@@ -14,6 +14,8 @@ int launch_prefill_fused_t(const lisa_desc* d, const PrefillArgs& a, hipStream_t
                                     (size_t)GH * RS * PF_AS_HEAD;
   static_assert(lds <= 160 * 1024, "LDS of one compute unit");
   auto kern = k_lisa_prefill_fused<NG, FS, HPW, NW, ACT, RS, SHG, FTRIM>;
+  if constexpr (ACT == 0 && !XSTG && RS <= 2)
+    if (a.tiled && a.scores) kern = k_lisa_prefill_fused<NG, FS, HPW, NW, ACT, RS, SHG, FTRIM, true>;
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)lds);
   if (e != hipSuccess) return hip_fail(e);
