@@ -117,16 +117,8 @@ __device__ __forceinline__ void regroup_v_tile(const bf16_t* __restrict__ v, bf1
   }
 }
 
-// grid (Lkp / 64, dk / 64, B * Hkv), block 256.
-template <bool VEC>
-__global__ __launch_bounds__(256) void k_regroup_v(const bf16_t* __restrict__ v, bf16_t* __restrict__ vt,
-                                                   int Lk, int Lkp, int dk) {
-  __shared__ __align__(16) unsigned short tile[64][72];
-  regroup_v_tile<VEC>(v, vt, Lk, Lkp, dk, blockIdx.x * 64, blockIdx.y * 64, blockIdx.z, tile);
-}
-
 // The repacking of one fused prefill call in one launch, block 256:
-//   blocks [0, n_v):   V tiles as in k_regroup_v (tile index = x + nx (y + ny z))
+//   blocks [0, n_v):   V tiles (tile index = x + nx (y + ny z)), none where dk is 0
 //   the rest:          Q_LR and K_LR rows zero-padded from r to 32 elements, one 16-byte chunk of
 //                      a padded row per thread (64 rows per block, Q rows first), K_LR by tiles of 32 keys in
 //                      operand order: operand u, lane 16 g + c holds elements 8 g .. of key 8 (c / 4) + c % 4 + 4 u.  (A wave

@@ -78,12 +78,9 @@ struct SplitAttnArgs {
   float scale;
 };
 
-constexpr int SA_VROW = 128 * 2 + 32;        // bytes per key row of the V tile in LDS: the four rows that 16 lanes of a
-                                             // transposing read touch fall into different banks
-constexpr int SA_VTILE = SP_TK * SA_VROW;
 constexpr int SA_OROW = 128 + 4;             // floats per row of a wave's partial result
 // LDS of four waves: a K tile, over which the emitted scores are staged, and a V tile each; at the end the partial results.
-constexpr int split_attn_wave_lds(bool with_v, bool given) { return (given ? 0 : SP_KTILE) + (with_v ? SA_VTILE : 0); }
+constexpr int split_attn_wave_lds(bool with_v, bool given) { return (given ? 0 : SP_KTILE) + (with_v ? SP_VTILE : 0); }
 constexpr int split_attn_lds(bool with_v, bool given) {
   const int tiles = 4 * split_attn_wave_lds(with_v, given), merge = with_v ? 4 * (SP_ROWS * SA_OROW + 2 * SP_ROWS) * 4 : 0;
   return tiles > merge ? tiles : merge;
@@ -127,7 +124,7 @@ __global__ __launch_bounds__(256, 2) void k_split_attn(SplitAttnArgs a) {
   const int k_rd = key_of_r * SP_KROW + half * 16;
   // transposing read: lane s of a 16-lane group passes the address of key s / 4, features 4 (s % 4) .. and receives
   // feature s of keys 0 .. 3; lanes 16 .. 31 of a half take the next 16 features
-  const int v_rd = (8 * half + ((lane & 15) >> 2)) * SA_VROW + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
+  const int v_rd = (8 * half + ((lane & 15) >> 2)) * SP_VROW + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
 
   bf16x8 qop[GIVEN ? 1 : DK / 16];
   if (!GIVEN) {
@@ -160,7 +157,7 @@ __global__ __launch_bounds__(256, 2) void k_split_attn(SplitAttnArgs a) {
   auto store_vt = [&]() {
     if (WITH_V)
 #pragma unroll
-      for (int u = 0; u < CH; ++u) *(pf_u32x4*)(vs_ + (ck_key + 4 * u) * SA_VROW + ck_c * 16) = vr[u];
+      for (int u = 0; u < CH; ++u) *(pf_u32x4*)(vs_ + (ck_key + 4 * u) * SP_VROW + ck_c * 16) = vr[u];
   };
   // given scores: row my_row, keys 32 tile + 16 u + 8 half .. + 7, loaded a step ahead
   const int n_kt = (Lk + SP_TK - 1) / SP_TK, crow = my_row - a.row0;
@@ -282,14 +279,7 @@ __global__ __launch_bounds__(256, 2) void k_split_attn(SplitAttnArgs a) {
       for (int db = 0; db < DK / 32; ++db) {
         bf16x8 vop[2];
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-          typedef s16x4 __attribute__((address_space(3))) lds_s16x4;
-          typedef short s16x8 __attribute__((ext_vector_type(8)));
-          const unsigned char* vp = vs_ + v_rd + 16 * s * SA_VROW + 64 * db;
-          const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)vp);
-          const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vp + 4 * SA_VROW));
-          vop[s] = __builtin_bit_cast(bf16x8, (s16x8){lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
-        }
+        for (int s = 0; s < 2; ++s) vop[s] = read_columns(vs_ + v_rd + 16 * s * SP_VROW + 64 * db);
         f32x16 t;
 #pragma unroll
         for (int v = 0; v < 16; ++v) t[v] = 0.f;

@@ -10,8 +10,8 @@
 //           MFMA row m is given key 16 (m/16) + 8 ((m/4)%2) + 4 ((m/8)%2) + m%4 so that lane
 //           (r, half) ends with keys 8 half .. 8 half + 7 and 16 + 8 half .. 16 + 8 half + 7:
 //           two 16-byte half stores.
-//   output  D[d, row] = sum_key V^T[d,key] P^T[key,row]   A = V by key chunks [L/8][128][8]
-//           (k_regroup_v), B = the lane's probabilities as they are.
+//   output  D[d, row] = sum_key V^T[d,key] P^T[key,row]   A = V^T, whose columns the transposing LDS read hands out
+//           of the V rows as they are, B = the lane's probabilities as they are.
 // A = Q K^T * scale is stored as half; the softmax works on the float32 values.
 // A workgroup takes two row groups, the x-th longest and the x-th shortest, so that all
 // workgroups stream the same number of tiles (large problems), or one row group (problems with
@@ -26,15 +26,14 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 struct StdPrefillArgs {
   const bf16_t* q;        // [B,H,Lq,128]
   const bf16_t* k;        // [B,Hkv,Lk,128]
-  const bf16_t* vt;       // [B,Hkv,Lkp/8,128,8] or null (scores only)
+  const bf16_t* v;        // [B,Hkv,Lk,128] or null (scores only)
   half_t* scores;         // [B,H,Lq,Lk] or null
   const void* given;      // GIVEN mode: scores [B,H,Lq,Lk] to take instead of Q K^T (then q, k unused):
                           // float32 (GIVEN = 1) or IEEE half (GIVEN = 2)
   void* out;              // [B,Lq,H,128] or null
-  int H, Hkv, Lq, Lk, Lkp, causal, out_f32;
+  int H, Hkv, Lq, Lk, causal, out_f32;
   int pair;               // 1: a workgroup takes two row groups (grid.y = ceil(n_groups / 2)), 0: one
   float scale;
-  int tiled;              // scores are written (GIVEN = 2: read) as [B,ceil(Lq/16),ceil(Lk/32),H,16,32]
 };
 
 __device__ __forceinline__ float halves_max(float v) {
@@ -54,9 +53,20 @@ constexpr int SP_GROUP = SP_ROWS * SP_WAVES;   // rows per workgroup pass
 constexpr int SP_TK = 32;
 constexpr int SP_KROW = 128 * 2 + 16;       // bytes per key row of the K tile in LDS (padded: no bank conflicts)
 constexpr int SP_KTILE = SP_TK * SP_KROW;   // 8704
-constexpr int SP_VTILE = SP_TK * 128 * 2;   // 8192
+constexpr int SP_VROW = 128 * 2 + 32;       // bytes per key row of the V tile in LDS: the four rows that 16 lanes of a
+                                            // transposing read touch fall into different banks
+constexpr int SP_VTILE = SP_TK * SP_VROW;   // 9216
 constexpr int SP_SROW = 2 * SP_TK * 2 + 16;  // bytes per row of a wave's score staging tile (64 keys, padded)
 constexpr int SP_STILE = SP_ROWS * SP_SROW;  // 4608
+
+// An operand of eight keys from rows of SP_VROW bytes: keys 0 .. 3 and 4 .. 7 of the lane's address (see k_std_prefill).
+__device__ __forceinline__ bf16x8 read_columns(const unsigned char* p) {
+  typedef s16x4 __attribute__((address_space(3))) lds_s16x4;
+  typedef short s16x8 __attribute__((ext_vector_type(8)));
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * SP_VROW));
+  return __builtin_bit_cast(bf16x8, (s16x8){lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+}
 
 // LDS bytes: two K tiles, the four staging tiles, two V tiles.
 constexpr int std_prefill_head_lds(bool with_v) {
@@ -70,7 +80,9 @@ constexpr int std_prefill_head_lds(bool with_v) {
 // Requires d_k = 128, Lk % 8 == 0 of row-major scores (tiled ones: any Lk >= 8).
 // GIVEN: the scores are read from a.given (the A_n that a LiSA scores kernel left there) instead
 // of being computed; the rest (masking, online softmax, P V) is the same.
-template <bool WITH_V, int GIVEN = 0>
+// TILED: scores are written (GIVEN = 2: read) as [B,ceil(Lq/16),ceil(Lk/32),H,16,32].
+// V is staged as it lies in memory (a launch that regrouped it by key chunks before was 8 - 11 us of a layer of 2048 tokens).
+template <bool WITH_V, int GIVEN = 0, bool TILED = false>
 __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
   constexpr int DK = 128;
   __shared__ __align__(16) unsigned char lds[std_prefill_head_lds(WITH_V)];
@@ -89,13 +101,14 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
   // key of MFMA row m = r (see the header)
   const int key_of_r = 16 * (r >> 4) + 8 * ((r >> 2) & 1) + 4 * ((r >> 3) & 1) + (r & 3);
   const bf16_t* kbase = GIVEN ? nullptr : a.k + ((size_t)b * a.Hkv + kv) * Lk * DK;
-  const bf16_t* vbase = WITH_V ? a.vt + ((size_t)b * a.Hkv + kv) * (a.Lkp / 8) * (DK * 8) : nullptr;
-  // cooperative tile loads: thread -> two 16-byte chunks of the K tile (key, 8 features) and two
-  // of the V tile (contiguous 8 KB)
+  const bf16_t* vbase = WITH_V ? a.v + ((size_t)b * a.Hkv + kv) * Lk * DK : nullptr;
+  // cooperative tile loads: thread -> two 16-byte chunks (key, 8 features) of the K and of the V tile
   const int ck_key = tid >> 4, ck_c = tid & 15;          // chunk u: key ck_key + 16 u
   // operand addresses in LDS
   const int k_rd = key_of_r * SP_KROW + half * 16;       // + 32 ks
-  const int v_rd = (half * DK + r) * 16;                 // + (2 s DK + 32 db) 16
+  // transposing read: lane s of a 16-lane group passes the address of key s / 4, features 4 (s % 4) .. and receives
+  // feature s of keys 0 .. 3; lanes 16 .. 31 of a half take the next 16 features.  + 16 s SP_VROW + 64 db
+  const int v_rd = (8 * half + ((lane & 15) >> 2)) * SP_VROW + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
 
   for (int rep = 0; rep < 2; ++rep) {
     const int grp = rep ? (int)blockIdx.y : n_groups - 1 - (int)blockIdx.y;
@@ -124,8 +137,8 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
     const half_t* grow_h = GIVEN == 2 ? (const half_t*)a.given + grow_at : nullptr;
     const int n_kt = (Lk + SP_TK - 1) / SP_TK;               // tile grid of the tiled score layout
     // (tiled: the H pieces of a tile follow each other, 1 KB each; see k_lisa_prefill_fused)
-    const size_t seq_elems = a.tiled ? (size_t)((Lq + 15) / 16) * n_kt * H * (16 * SP_TK) : (size_t)H * Lq * Lk;
-    half_t* sbase = a.scores ? a.scores + (size_t)b * seq_elems + (size_t)h * (a.tiled ? (size_t)16 * SP_TK : (size_t)Lq * Lk)
+    const size_t seq_elems = TILED ? (size_t)((Lq + 15) / 16) * n_kt * H * (16 * SP_TK) : (size_t)H * Lq * Lk;
+    half_t* sbase = a.scores ? a.scores + (size_t)b * seq_elems + (size_t)h * (TILED ? (size_t)16 * SP_TK : (size_t)Lq * Lk)
                              : nullptr;
     unsigned char* stg = ss_ + wv * SP_STILE;
 
@@ -142,14 +155,14 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
       for (int u = 0; u < 2; ++u) {
         const int j = min(tile * SP_TK + ck_key + 16 * u, Lk - 1);
         if (!GIVEN) tr[0][u] = *(const pf_u32x4*)(kbase + (size_t)j * DK + 8 * ck_c);
-        if (WITH_V) tr[1][u] = *(const pf_u32x4*)(vbase + (size_t)tile * (SP_TK / 8 * DK * 8) + (tid + 256 * u) * 8);
+        if (WITH_V) tr[1][u] = *(const pf_u32x4*)(vbase + (size_t)j * DK + 8 * ck_c);
       }
     };
     auto store_tile = [&](int buf, const TileRegs& tr) {
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         if (!GIVEN) *(pf_u32x4*)(ks_ + buf * SP_KTILE + (ck_key + 16 * u) * SP_KROW + ck_c * 16) = tr[0][u];
-        if (WITH_V) *(pf_u32x4*)(vs_ + buf * SP_VTILE + (tid + 256 * u) * 16) = tr[1][u];
+        if (WITH_V) *(pf_u32x4*)(vs_ + buf * SP_VTILE + (ck_key + 16 * u) * SP_VROW + ck_c * 16) = tr[1][u];
       }
     };
     // GIVEN = 2: the wave's scores of a tile are loaded two tiles ahead (nothing else hides the
@@ -163,7 +176,7 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
     auto load_scores = [&](int tile, f16x8 (&dst)[2]) {
 #pragma unroll
       for (int u = 0; u < 2; ++u)    // (keys beyond Lk: any in-bounds 8 scores will do, those positions are masked)
-        dst[u] = *(const f16x8*)(a.tiled ? grow_t + (size_t)tile * H * (16 * SP_TK) + 16 * u
+        dst[u] = *(const f16x8*)(TILED ? grow_t + (size_t)tile * H * (16 * SP_TK) + 16 * u
                                          : grow_h + min(tile * SP_TK + 16 * u + 8 * half, Lk - 8));
     };
     if (rep) __syncthreads();                              // the first pass is done with both buffers
@@ -236,7 +249,7 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
         unsigned char* sl = stg + r * SP_SROW + (tile & 1) * 64 + 16 * half;
         *(f16x8*)sl = hv0;
         *(f16x8*)(sl + 32) = hv1;
-        if (a.tiled) {
+        if (TILED) {
           // tiled layout: the wave's 32 rows are two row blocks, one 1 KB tile each per step
 #pragma unroll
           for (int q = 0; q < 2; ++q) {
@@ -270,14 +283,26 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
         }
       }
       if (WITH_V) {
+        // (TILED has the registers for it: the operands of P V are read ahead of the softmax)
+        bf16x8 vop[2][DK / 32];
+        auto read_v = [&]() {
+#pragma unroll
+          for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int db = 0; db < DK / 32; ++db) vop[s][db] = read_columns(vtl + v_rd + 16 * s * SP_VROW + 64 * db);
+        };
+        if (TILED) {
+          read_v();
+          __builtin_amdgcn_sched_barrier(0);
+        }
         if (!full) {
 #pragma unroll
           for (int v = 0; v < 16; ++v)
             if (jl + 16 * (v >> 3) + (v & 7) >= vis_row) an[v] = -INFINITY;
         }
-        float mx = an[0];
+        float mx = max2_raw(an[0], an[15]);
 #pragma unroll
-        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, an[v]);
+        for (int v = 1; v < 15; v += 2) mx = max3_raw(mx, an[v], an[v + 1]);
         mx = halves_max(mx);
         const float m_new = fmaxf(m_run, mx);
         // (given scores may be -inf, masked: no key seen yet, every p is 0)
@@ -299,13 +324,11 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
         }
+        if (!TILED) read_v();
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
-          for (int db = 0; db < DK / 32; ++db) {
-            const bf16x8 vop = *(const bf16x8*)(vtl + v_rd + (2 * s * DK + 32 * db) * 16);
-            o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop, pop[s], o[db], 0, 0, 0);
-          }
+          for (int db = 0; db < DK / 32; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop[s][db], pop[s], o[db], 0, 0, 0);
       }
     };
     // (everything loaded so far has arrived before the loop is entered: the wait counts inside the

@@ -192,9 +192,9 @@ bool scores_mfma_ok(const lisa_desc* d) {
 }
 
 // Workspace of the CONCAT pipeline: A_n in the score type when the caller does not ask for it (the
-// softmax kernel reads it from there), the padded low-rank operands, V by key chunks.
+// softmax kernel reads it from there), the padded low-rank operands.
 struct ConcatWs {
-  size_t qp, kp, vt, total;
+  size_t qp, kp, total;
   int Lqp, Lkp;
 };
 bool std_prefill_fast_ok(const lisa_desc* d);
@@ -207,27 +207,20 @@ ConcatWs concat_ws(const lisa_desc* d) {
   w.Lkp = (d->Lk + 63) / 64 * 64;
   w.qp = round_up(scores_bytes(d), 256);                   // (2-byte scores, in the layout of the call)
   w.kp = w.qp + round_up((size_t)d->B * d->H * w.Lqp * 32 * 2, 256);
-  w.vt = w.kp + round_up((size_t)d->B * d->Hkv * w.Lkp * 32 * 2, 256);
-  w.total = w.vt + (std_prefill_fast_ok(d) ? round_up((size_t)d->B * d->Hkv * d->d_k * w.Lkp * 2, 256) : 0);
+  w.total = w.kp + round_up((size_t)d->B * d->Hkv * w.Lkp * 32 * 2, 256);
   return w;
 }
 
-int launch_scores_mfma(const lisa_desc* d, const void* q_lr, const void* k_lr, const void* v, const void* prev,
-                       const void* w1, const void* w2, void* scores, void* workspace, hipStream_t st) {
+int launch_scores_mfma(const lisa_desc* d, const void* q_lr, const void* k_lr, const void* prev, const void* w1,
+                       const void* w2, void* scores, void* workspace, hipStream_t st) {
   const ConcatWs w = concat_ws(d);
   char* ws = (char*)workspace;
   {
-    // V is regrouped in the same launch when the MFMA softmax kernel follows (d_k = 128)
-    const bool with_v = std_prefill_fast_ok(d);
-    const int dk = with_v ? d->d_k : 0;
     StageScope prof("k_prepare_prefill", st);
     const size_t rows = (size_t)d->B * d->H * w.Lqp + (size_t)d->B * d->Hkv * w.Lkp;
-    const size_t blocks = (size_t)(w.Lkp / 64) * (dk / 64) * d->B * d->Hkv + (rows + 63) / 64;
-    const bool vec = (uintptr_t)v % 16 == 0;
-    auto kern = vec ? k_prepare_prefill<true> : k_prepare_prefill<false>;
-    kern<<<(unsigned)blocks, 256, 0, st>>>((const bf16_t*)q_lr, (const bf16_t*)k_lr, (const bf16_t*)v,
-                                          (bf16_t*)(ws + w.qp), (bf16_t*)(ws + w.kp), (bf16_t*)(ws + w.vt),
-                                          d->B, d->H, d->Hkv, d->Lq, d->Lk, w.Lqp, w.Lkp, d->r, dk);
+    k_prepare_prefill<true><<<(unsigned)((rows + 63) / 64), 256, 0, st>>>(
+        (const bf16_t*)q_lr, (const bf16_t*)k_lr, nullptr, (bf16_t*)(ws + w.qp), (bf16_t*)(ws + w.kp), nullptr, d->B, d->H,
+        d->Hkv, d->Lq, d->Lk, w.Lqp, w.Lkp, d->r, 0);
     int rc = check_launch();
     if (rc) return rc;
   }
@@ -310,9 +303,7 @@ KeyStrides dim_major_keys(const lisa_desc* d, int len, int width) {
 }
 
 bool std_prefill_fast_ok(const lisa_desc* d);
-size_t std_prefill_ws(const lisa_desc* d);
-int run_softmax_given_fast(const lisa_desc* d, const void* given, bool given_half, const void* v, void* out,
-                           void* vt_ws, hipStream_t st);
+int run_softmax_given_fast(const lisa_desc* d, const void* given, bool given_half, const void* v, void* out, hipStream_t st);
 
 // bf16 layers in float32 arithmetic: scores and softmax by chunks of query rows.
 bool in_chunks(const lisa_desc* d) { return split_attn_ok(d); }
@@ -328,10 +319,10 @@ int run_lisa(const lisa_desc* d, const void* q_lr, const void* k_lr, KeyStrides 
     // is the size of what the module's inputs already carry (A_{n-1} is stored as half, and A_delta
     // enters the FFN as a half MFMA operand).
     void* an = scores ? scores : (void*)exact;
-    int rc = launch_scores_mfma(d, q_lr, k_lr, v, prev, w1, w2, an, exact, st);
+    int rc = launch_scores_mfma(d, q_lr, k_lr, prev, w1, w2, an, exact, st);
     if (rc) return rc;
     if (std_prefill_fast_ok(d))
-      rc = run_softmax_given_fast(d, an, true, nullptr, out, (char*)exact + concat_ws(d).vt, st);
+      rc = run_softmax_given_fast(d, an, true, v, out, st);
     else
       rc = launch_softmax_v<T, half_t>(d, (const half_t*)an, v, vs, out, st);
     if (rc == LISA_OK) g_path = "mfma_scores";
@@ -354,7 +345,7 @@ int run_lisa(const lisa_desc* d, const void* q_lr, const void* k_lr, KeyStrides 
     // softmax and P V from the float32 scores: on the matrix cores where one of the standard layer's kernels
     // fits (it then reads the scores instead of computing Q K^T), else the generic kernel
     if (std_prefill_fast_ok(d))
-      rc = run_softmax_given_fast(d, exact, false, v, out, (char*)exact + exact_bytes(d), st);
+      rc = run_softmax_given_fast(d, exact, false, v, out, st);
     else if (in_chunks(d))
       rc = run_split_attn(d, nullptr, nullptr, v, exact, split, row0, n_rows, nullptr, out, st);
     else if (f32_attn_ok(d))
@@ -653,76 +644,46 @@ bool std_prefill_fast_ok(const lisa_desc* d) {
   return d->dtype == LISA_BF16 && d->d_k == 128 && score_rows_aligned(d) && d->Lq > 1;
 }
 
-size_t std_prefill_ws(const lisa_desc* d) {   // V by key chunks
-  const size_t Lkp = (size_t)(d->Lk + 63) / 64 * 64;
-  return round_up((size_t)d->B * d->Hkv * d->d_k * Lkp * 2, 256);
-}
-
 // softmax(A) V for scores A that are already in memory, float32 or IEEE half (k_std_prefill in
 // GIVEN mode).
 int run_softmax_given_fast(const lisa_desc* d, const void* given, bool given_half, const void* v, void* out,
-                           void* vt_ws, hipStream_t st) {
+                           hipStream_t st) {
   StdPrefillArgs a{};
-  a.vt = (const bf16_t*)vt_ws;
+  a.v = (const bf16_t*)v;
   a.given = given;
   a.out = out;
   a.H = d->H;
   a.Hkv = d->Hkv;
   a.Lq = d->Lq;
   a.Lk = d->Lk;
-  a.Lkp = (d->Lk + 63) / 64 * 64;
   a.causal = d->causal;
   a.out_f32 = d->out_f32;
   a.scale = 1.f;
-  a.tiled = given_half ? d->score_tiled : 0;
-  if (v) {                                                   // (null: vt_ws already holds the regrouped V)
-    dim3 grid(a.Lkp / 64, d->d_k / 64, d->B * d->Hkv);
-    StageScope prof("k_regroup_v", st);
-    if ((uintptr_t)v % 16 == 0)
-      k_regroup_v<true><<<grid, 256, 0, st>>>((const bf16_t*)v, (bf16_t*)vt_ws, d->Lk, a.Lkp, d->d_k);
-    else
-      k_regroup_v<false><<<grid, 256, 0, st>>>((const bf16_t*)v, (bf16_t*)vt_ws, d->Lk, a.Lkp, d->d_k);
-    int rc = check_launch();
-    if (rc) return rc;
-  }
   const int n_groups = (d->Lq + SP_GROUP - 1) / SP_GROUP;
   a.pair = 0;
   dim3 grid(d->H, n_groups, d->B);
   StageScope prof("k_softmax_v_mfma", st);
-  if (given_half)
-    k_std_prefill<true, 2><<<grid, 256, 0, st>>>(a);
-  else
-    k_std_prefill<true, 1><<<grid, 256, 0, st>>>(a);
+  if (!given_half) k_std_prefill<true, 1><<<grid, 256, 0, st>>>(a);
+  else if (d->score_tiled) k_std_prefill<true, 2, true><<<grid, 256, 0, st>>>(a);
+  else k_std_prefill<true, 2><<<grid, 256, 0, st>>>(a);
   return check_launch();
 }
 
 int run_std_prefill_fast(const lisa_desc* d, const void* q, const void* k, const void* v, void* scores,
-                         void* out, void* workspace, hipStream_t st) {
+                         void* out, hipStream_t st) {
   StdPrefillArgs a{};
   a.q = (const bf16_t*)q;
   a.k = (const bf16_t*)k;
-  a.vt = (const bf16_t*)workspace;
+  a.v = (const bf16_t*)v;
   a.scores = (half_t*)scores;
   a.out = out;
   a.H = d->H;
   a.Hkv = d->Hkv;
   a.Lq = d->Lq;
   a.Lk = d->Lk;
-  a.Lkp = (d->Lk + 63) / 64 * 64;
   a.causal = d->causal;
   a.out_f32 = d->out_f32;
-  a.tiled = d->score_tiled;
   a.scale = pick_scale(d->std_scale, d->d_k);
-  if (out) {
-    dim3 grid(a.Lkp / 64, d->d_k / 64, d->B * d->Hkv);
-    StageScope prof("k_regroup_v", st);
-    if ((uintptr_t)v % 16 == 0)
-      k_regroup_v<true><<<grid, 256, 0, st>>>((const bf16_t*)v, (bf16_t*)workspace, d->Lk, a.Lkp, d->d_k);
-    else
-      k_regroup_v<false><<<grid, 256, 0, st>>>((const bf16_t*)v, (bf16_t*)workspace, d->Lk, a.Lkp, d->d_k);
-    int rc = check_launch();
-    if (rc) return rc;
-  }
   const int n_groups = (d->Lq + SP_GROUP - 1) / SP_GROUP;
   // One row group per workgroup, long ones first: the dispatcher evens out the rest.  (The kernel
   // can also take the x-th longest and the x-th shortest row group in one workgroup, equal work
@@ -732,10 +693,10 @@ int run_std_prefill_fast(const lisa_desc* d, const void* q, const void* k, const
   if (g_tune[LISA_TUNE_STD_PAIR] >= 0) a.pair = g_tune[LISA_TUNE_STD_PAIR] != 0;   // tests force either
   dim3 grid(d->H, a.pair ? (n_groups + 1) / 2 : n_groups, d->B);
   StageScope prof("k_std_prefill", st);
-  if (out)
-    k_std_prefill<true><<<grid, 256, 0, st>>>(a);
-  else
-    k_std_prefill<false><<<grid, 256, 0, st>>>(a);
+  if (out && d->score_tiled) k_std_prefill<true, 0, true><<<grid, 256, 0, st>>>(a);
+  else if (out) k_std_prefill<true><<<grid, 256, 0, st>>>(a);
+  else if (d->score_tiled) k_std_prefill<false, 0, true><<<grid, 256, 0, st>>>(a);
+  else k_std_prefill<false><<<grid, 256, 0, st>>>(a);
   int rc = check_launch();
   if (rc == LISA_OK) g_path = "mfma_std";
   return rc;
@@ -1078,7 +1039,7 @@ size_t lisa_workspace_bytes(const lisa_desc* desc, int which) {
         return round_up(concat_ws(&eq).total, 256) + synth_ffn_bytes(desc);
       if (in_chunks(desc))                                   // (k_split_attn reads up to 31 floats past row-major scores)
         return std::max(split_scores_ok(desc) ? split_bytes(desc) : 0, f32_chunk_bytes(desc) + 256);
-      return exact_bytes(desc) + (std_prefill_fast_ok(desc) ? std_prefill_ws(desc) : 0);
+      return exact_bytes(desc);
     }
     case LISA_WS_DECODE: {
       if (check_decode(desc) != LISA_OK) return 0;
@@ -1091,8 +1052,7 @@ size_t lisa_workspace_bytes(const lisa_desc* desc, int which) {
     case LISA_WS_STD:
       if (check_common(desc) != LISA_OK) return 0;
       // needed only when `out` is requested
-      if (std_prefill_fast_ok(desc)) return std_prefill_ws(desc);
-      if (in_chunks(desc)) return 256;                       // (k_split_attn keeps its scores in registers)
+      if (std_prefill_fast_ok(desc) || in_chunks(desc)) return 256;   // (their kernels keep the scores in registers)
       return decode_fast_ok(desc, false) ? decode_fast_bytes(desc) : exact_bytes(desc);
     case LISA_WS_LAYER: {
       size_t q, k, v;
@@ -1631,7 +1591,7 @@ int std_attn_scores(const lisa_desc* desc, const void* q, const void* k, const v
   // With Lq = 1 and Lmax set, K and V are caches of capacity Lmax along the key axis.
   const int cap = (desc->Lq == 1 && desc->Lmax >= desc->Lk) ? desc->Lmax : desc->Lk;
   const KeyStrides ks = dense_keys(desc, cap, desc->d_k);
-  if (std_prefill_fast_ok(desc)) return run_std_prefill_fast(desc, q, k, v, scores_out, out, workspace, st);
+  if (std_prefill_fast_ok(desc)) return run_std_prefill_fast(desc, q, k, v, scores_out, out, st);
   if (desc->score_tiled) return LISA_ERR_UNSUPPORTED;       // the matrix-core prefill kernel alone writes tiles
   if (out && decode_fast_ok(desc, false)) {
     DecodeArgs a{};
