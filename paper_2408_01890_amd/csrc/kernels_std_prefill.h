@@ -68,12 +68,13 @@ __device__ __forceinline__ bf16x8 read_columns(const unsigned char* p) {
   return __builtin_bit_cast(bf16x8, (s16x8){lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
 }
 
-// LDS bytes: two K tiles, the four staging tiles, two V tiles.
+constexpr int SP_OROW = 128 + 4;            // floats per row of a partial result
+// LDS bytes of one key half: two K tiles, the four staging tiles, two V tiles.
 constexpr int std_prefill_head_lds(bool with_v) {
   return 2 * SP_KTILE + SP_WAVES * SP_STILE + (with_v ? 2 * SP_VTILE : 0);
 }
 
-// grid (H, pair ? ceil(n_groups / 2) : n_groups, B) with n_groups = ceil(Lq / 128), block 256.  The head is the
+// grid (H, pair ? ceil(n_groups / 2) : n_groups, B) with n_groups = ceil(Lq / 128), block 256 NH.  The head is the
 // fastest grid index: consecutive workgroups go to different XCDs, so an XCD works on every
 // eighth head and its L2 fetches the K / V of those heads only (they are what every row group
 // of a head re-reads).
@@ -82,15 +83,19 @@ constexpr int std_prefill_head_lds(bool with_v) {
 // of being computed; the rest (masking, online softmax, P V) is the same.
 // TILED: scores are written (GIVEN = 2: read) as [B,ceil(Lq/16),ceil(Lk/32),H,16,32].
 // V is staged as it lies in memory (a launch that regrouped it by key chunks before was 8 - 11 us of a layer of 2048 tokens).
-template <bool WITH_V, int GIVEN = 0, bool TILED = false>
-__global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
+// NH = 2: eight waves, two per row block, which take the even and the odd key tiles, each half with buffers of its own, and
+// merge their softmax states at the end: half the chain of tiles where there
+// are too few workgroups to hide it (std_key_halves).
+template <bool WITH_V, int GIVEN = 0, bool TILED = false, int NH = 1>
+__global__ __launch_bounds__(256 * NH, 2) void k_std_prefill(StdPrefillArgs a) {
   constexpr int DK = 128;
-  __shared__ __align__(16) unsigned char lds[std_prefill_head_lds(WITH_V)];
-  unsigned char* ks_ = lds;
-  unsigned char* ss_ = ks_ + 2 * SP_KTILE;              // score staging, one tile per wave
-  unsigned char* vs_ = ss_ + SP_WAVES * SP_STILE;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  __shared__ __align__(16) unsigned char lds[NH * std_prefill_head_lds(WITH_V)];
+  const int tid = threadIdx.x & 255, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);                               // row block of the wave
+  const int kh = NH == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);    // its key half
+  unsigned char* ks_ = lds + kh * (2 * SP_KTILE);
+  unsigned char* ss_ = lds + NH * (2 * SP_KTILE);       // score staging, one tile per wave
+  unsigned char* vs_ = ss_ + NH * (SP_WAVES * SP_STILE) + kh * (2 * SP_VTILE);
   const int r = lane & 31, half = lane >> 5;
   const int b = blockIdx.z, h = blockIdx.x;
   const int Lq = a.Lq, Lk = a.Lk, H = a.H;
@@ -140,7 +145,7 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
     const size_t seq_elems = TILED ? (size_t)((Lq + 15) / 16) * n_kt * H * (16 * SP_TK) : (size_t)H * Lq * Lk;
     half_t* sbase = a.scores ? a.scores + (size_t)b * seq_elems + (size_t)h * (TILED ? (size_t)16 * SP_TK : (size_t)Lq * Lk)
                              : nullptr;
-    unsigned char* stg = ss_ + wv * SP_STILE;
+    unsigned char* stg = ss_ + (kh * SP_WAVES + wv) * SP_STILE;
 
     // The K / V tile of a step travels through registers: loaded three tiles ahead into one of two
     // register sets, written to LDS one tile ahead.  Two sets rather than one because loads and
@@ -180,13 +185,15 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
                                          : grow_h + min(tile * SP_TK + 16 * u + 8 * half, Lk - 8));
     };
     if (rep) __syncthreads();                              // the first pass is done with both buffers
-    load_tile(0, regs_a);
+    const int n_steps = (n_tiles + NH - 1) / NH;
+    auto tile_of = [&](int st) { return min(NH * st + kh, n_tiles - 1); };
+    load_tile(tile_of(0), regs_a);
     store_tile(0, regs_a);
-    load_tile(min(1, n_tiles - 1), regs_a);                // set a: odd tiles, set b: even tiles
-    load_tile(min(2, n_tiles - 1), regs_b);
+    load_tile(tile_of(1), regs_a);                         // set a: odd steps, set b: even steps
+    load_tile(tile_of(2), regs_b);
     if (GIVEN == 2) {
-      load_scores(0, gq[0]);
-      load_scores(min(1, n_tiles - 1), gq[1]);
+      load_scores(tile_of(0), gq[0]);
+      load_scores(tile_of(1), gq[1]);
     }
 
     f32x16 o[DK / 32];
@@ -196,14 +203,41 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
       for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;
 
-    auto step = [&](int tile, TileRegs& tr) {              // tr holds tile + 1
-      // tile `tile` is complete in buffer tile & 1, and every wave is done with the other buffer
+    // Row-major scores leave in whole 128-byte pieces of a row (64 keys = the tiles t and t + 1 of the pair that `tile`
+    // belongs to; 64-byte pieces reach HBM at about half the rate): `n` pieces of 8 rows each from row 8 u0 on.
+    auto flush_rows = [&](int tile, const unsigned char* from, int u0, int n) {
+      const int jc = (tile >> 1) * (2 * SP_TK) + 8 * (lane & 7);
+      const bool pair_full = (tile | 1) < n_full;
+#pragma unroll
+      for (int u = 0; u < n; ++u) {
+        const int row = 8 * (u0 + u) + (lane >> 3), gi = i0 + row;
+        const f16x8 hv = *(const f16x8*)(from + row * SP_SROW + (lane & 7) * 16);
+        const int vis = gi < Lq ? (a.causal ? min(Lk, gi + 1 + shift) : Lk) : 0;
+        half_t* sp = sbase + (size_t)min(gi, Lq - 1) * Lk + jc;
+        if (pair_full || jc + 8 <= vis) {
+          __builtin_nontemporal_store(__builtin_bit_cast(pf_u32x4, hv), (pf_u32x4*)sp);
+        } else if (jc < vis) {
+          int rel = vis - jc;                              // (kept inside this branch: registers)
+          asm volatile("" : "+v"(rel));
+          store_row_part(sp, __builtin_bit_cast(pf_u32x4, hv), rel);
+        }
+      }
+    };
+    // NH = 2, row-major: the pair is made by both halves and leaves behind the next barrier, half of the rows each
+    auto flush_pair = [&](int st) {
+      if (!TILED && NH == 2 && !GIVEN && a.scores && st >= 0 && NH * st < n_tiles_w)
+        flush_rows(NH * st, ss_ + ((st & 1) * SP_WAVES + wv) * SP_STILE, 2 * kh, 2);
+    };
+    auto step = [&](int st, TileRegs& tr) {                // tr holds the tile of step st + 1
+      const int tile = NH * st + kh;
+      // the tile is complete in buffer st & 1, and every wave is done with the other buffer
       lds_barrier();
-      store_tile((tile + 1) & 1, tr);
-      load_tile(min(tile + 3, n_tiles - 1), tr);
+      store_tile((st + 1) & 1, tr);
+      load_tile(tile_of(st + 3), tr);
+      flush_pair(st - 1);
       if (tile >= n_tiles_w) return;                       // beyond this wave's diagonal (wave-uniform)
-      const unsigned char* kt = ks_ + (tile & 1) * SP_KTILE;
-      const unsigned char* vtl = vs_ + (tile & 1) * SP_VTILE;
+      const unsigned char* kt = ks_ + (st & 1) * SP_KTILE;
+      const unsigned char* vtl = vs_ + (st & 1) * SP_VTILE;
       const int j0 = tile * SP_TK;
       // an[8 u + e] = score of key j0 + 16 u + 8 half + e for row r
       float an[16];
@@ -214,7 +248,7 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
           for (int e = 0; e < 8; ++e) an[8 * u + e] = (float)gq[0][u][e];
           gq[0][u] = gq[1][u];
         }
-        load_scores(min(tile + 2, n_tiles - 1), gq[1]);
+        load_scores(tile_of(st + 2), gq[1]);
       } else if (GIVEN == 1) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -238,15 +272,14 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
       const bool full = tile < n_full;
       const int jl = j0 + 8 * half;
       if (a.scores) {
-        // A leaves through the wave's staging tile in whole 128-byte pieces of a row (64 keys =
-        // two tiles): 64-byte pieces reach HBM at about half the rate of whole lines
+        // A leaves through a staging tile
         f16x8 hv0, hv1;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           hv0[e] = f32_to_half_sat(an[e]);
           hv1[e] = f32_to_half_sat(an[8 + e]);
         }
-        unsigned char* sl = stg + r * SP_SROW + (tile & 1) * 64 + 16 * half;
+        unsigned char* sl = (!TILED && NH == 2 ? ss_ + ((st & 1) * SP_WAVES + wv) * SP_STILE : stg) + r * SP_SROW + (tile & 1) * 64 + 16 * half;
         *(f16x8*)sl = hv0;
         *(f16x8*)(sl + 32) = hv1;
         if (TILED) {
@@ -263,23 +296,8 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
             __builtin_nontemporal_store(__builtin_bit_cast(pf_u32x4, hv),
                                         (pf_u32x4*)((char*)sbase + ((size_t)rbq * n_kt + tile) * H * (16 * SP_TK * 2) + lane * 16));
           }
-        } else if ((tile & 1) == 1 || tile == n_tiles_w - 1) {
-          const int jc = (tile >> 1) * (2 * SP_TK) + 8 * (lane & 7);
-          const bool pair_full = (tile | 1) < n_full;
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int row = 8 * u + (lane >> 3), gi = i0 + row;
-            const f16x8 hv = *(const f16x8*)(stg + row * SP_SROW + (lane & 7) * 16);
-            const int vis = gi < Lq ? (a.causal ? min(Lk, gi + 1 + shift) : Lk) : 0;
-            half_t* sp = sbase + (size_t)min(gi, Lq - 1) * Lk + jc;
-            if (pair_full || jc + 8 <= vis) {
-              __builtin_nontemporal_store(__builtin_bit_cast(pf_u32x4, hv), (pf_u32x4*)sp);
-            } else if (jc < vis) {
-              int rel = vis - jc;                              // (kept inside this branch: registers)
-              asm volatile("" : "+v"(rel));
-              store_row_part(sp, __builtin_bit_cast(pf_u32x4, hv), rel);
-            }
-          }
+        } else if (NH == 1 && ((tile & 1) == 1 || tile == n_tiles_w - 1)) {
+          flush_rows(tile, stg, 0, 4);
         }
       }
       if (WITH_V) {
@@ -305,8 +323,8 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
         for (int v = 1; v < 15; v += 2) mx = max3_raw(mx, an[v], an[v + 1]);
         mx = halves_max(mx);
         const float m_new = fmaxf(m_run, mx);
-        // (given scores may be -inf, masked: no key seen yet, every p is 0)
-        const float m2 = GIVEN && m_new == -INFINITY ? 0.f : m_new * LOG2E;
+        // (no key seen yet, every p is 0: given scores may be -inf, masked, and a half may start beyond a row's diagonal)
+        const float m2 = (GIVEN || NH == 2) && m_new == -INFINITY ? 0.f : m_new * LOG2E;
         const float alpha = fast_exp2(m_run * LOG2E - m2);
         m_run = m_new;
         float ps = 0.f;
@@ -334,13 +352,50 @@ __global__ __launch_bounds__(256, 2) void k_std_prefill(StdPrefillArgs a) {
     // (everything loaded so far has arrived before the loop is entered: the wait counts inside the
     // loop then follow from the loop's own issue order, not from that of the prologue)
     __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0), others untouched
-    int tile = 0;
-    for (; tile + 1 < n_tiles; tile += 2) {                // (both steps on every path round the loop)
-      step(tile, regs_a);
-      step(tile + 1, regs_b);
+    int st = 0;
+    for (; st + 1 < n_steps; st += 2) {                    // (both steps on every path round the loop)
+      step(st, regs_a);
+      step(st + 1, regs_b);
     }
-    if (tile < n_tiles) step(tile, regs_a);
+    if (st < n_steps) step(st, regs_a);
+    if constexpr (!TILED && NH == 2 && !GIVEN) {
+      lds_barrier();
+      flush_pair(n_steps - 1);
+    }
 
+    if constexpr (WITH_V && NH == 2) {
+      // the odd half leaves its state in the LDS, the even one goes on with both
+      float* o_s = (float*)lds + wv * (SP_ROWS * SP_OROW);
+      float* ml_s = (float*)lds + SP_WAVES * SP_ROWS * SP_OROW + wv * (2 * SP_ROWS);
+      __syncthreads();
+      if (kh == 1) {
+        const float l1 = halves_sum(l_run);
+        if (half == 0) *(float2*)(ml_s + 2 * r) = make_float2(m_run, l1);
+#pragma unroll
+        for (int db = 0; db < DK / 32; ++db)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4)
+            *(float4*)(o_s + r * SP_OROW + 32 * db + 8 * q4 + 4 * half) =
+                make_float4(o[db][4 * q4], o[db][4 * q4 + 1], o[db][4 * q4 + 2], o[db][4 * q4 + 3]);
+      }
+      __syncthreads();
+      if (kh == 1) return;
+      const float2 ml = *(const float2*)(ml_s + 2 * r);
+      const float M = fmaxf(m_run, ml.x), M2 = M == -INFINITY ? 0.f : M * LOG2E;
+      const float f0 = fast_exp2(m_run * LOG2E - M2), f1 = fast_exp2(ml.x * LOG2E - M2);
+      // (l_run is this lane's share of the row's sum, ml.y the other half's whole: half of it to each of the two lanes)
+      l_run = l_run * f0 + 0.5f * ml.y * f1;
+#pragma unroll
+      for (int db = 0; db < DK / 32; ++db)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const float4 x = *(const float4*)(o_s + r * SP_OROW + 32 * db + 8 * q4 + 4 * half);
+          o[db][4 * q4] = o[db][4 * q4] * f0 + x.x * f1;
+          o[db][4 * q4 + 1] = o[db][4 * q4 + 1] * f0 + x.y * f1;
+          o[db][4 * q4 + 2] = o[db][4 * q4 + 2] * f0 + x.z * f1;
+          o[db][4 * q4 + 3] = o[db][4 * q4 + 3] * f0 + x.w * f1;
+        }
+    }
     if (WITH_V) {
       // O[row][h][32 db + 8 (v/4) + 4 half + v%4] = o[db][v] / l
       const float l = halves_sum(l_run);

@@ -644,6 +644,16 @@ bool std_prefill_fast_ok(const lisa_desc* d) {
   return d->dtype == LISA_BF16 && d->d_k == 128 && score_rows_aligned(d) && d->Lq > 1;
 }
 
+// Two waves per row block, a key half each (k_std_prefill<.., NH = 2>): the longest row group's chain of tiles bounds a
+// launch of few workgroups.  Scores + O, one against two waves: 32 heads, 1024 tokens (256 workgroups) 39.6 / 33.6 us,
+// 1400 tokens (352) 71.7 / 61.8, 2048 (512) 88.7 / 78.4, 8 heads, 16 rows of 4096 keys 128 / 90; beyond the lines
+// 4 x 512 tokens (512 workgroups of 16 tiles at most) 34.0 / 37.4, 2 x 2048 (1024) 126.7 / 142.7 (one barrier domain per
+// compute unit, the merge); 8 heads, 200 tokens, O alone 10.3 / 10.8.
+bool std_key_halves(const lisa_desc* d) {
+  const long long wgs = (long long)((d->Lq + SP_GROUP - 1) / SP_GROUP) * d->H * d->B;
+  return d->Lk > 256 && (wgs <= kComputeUnits || (wgs <= 2 * kComputeUnits && d->Lk >= 1280));
+}
+
 // softmax(A) V for scores A that are already in memory, float32 or IEEE half (k_std_prefill in
 // GIVEN mode).
 int run_softmax_given_fast(const lisa_desc* d, const void* given, bool given_half, const void* v, void* out,
@@ -663,9 +673,11 @@ int run_softmax_given_fast(const lisa_desc* d, const void* given, bool given_hal
   a.pair = 0;
   dim3 grid(d->H, n_groups, d->B);
   StageScope prof("k_softmax_v_mfma", st);
-  if (!given_half) k_std_prefill<true, 1><<<grid, 256, 0, st>>>(a);
-  else if (d->score_tiled) k_std_prefill<true, 2, true><<<grid, 256, 0, st>>>(a);
-  else k_std_prefill<true, 2><<<grid, 256, 0, st>>>(a);
+  const bool halves = std_key_halves(d);
+  auto kern = !given_half       ? (halves ? k_std_prefill<true, 1, false, 2> : k_std_prefill<true, 1>)
+              : d->score_tiled ? (halves ? k_std_prefill<true, 2, true, 2> : k_std_prefill<true, 2, true>)
+                               : (halves ? k_std_prefill<true, 2, false, 2> : k_std_prefill<true, 2>);
+  kern<<<grid, halves ? 512 : 256, 0, st>>>(a);
   return check_launch();
 }
 
@@ -693,10 +705,12 @@ int run_std_prefill_fast(const lisa_desc* d, const void* q, const void* k, const
   if (g_tune[LISA_TUNE_STD_PAIR] >= 0) a.pair = g_tune[LISA_TUNE_STD_PAIR] != 0;   // tests force either
   dim3 grid(d->H, a.pair ? (n_groups + 1) / 2 : n_groups, d->B);
   StageScope prof("k_std_prefill", st);
-  if (out && d->score_tiled) k_std_prefill<true, 0, true><<<grid, 256, 0, st>>>(a);
-  else if (out) k_std_prefill<true><<<grid, 256, 0, st>>>(a);
-  else if (d->score_tiled) k_std_prefill<false, 0, true><<<grid, 256, 0, st>>>(a);
-  else k_std_prefill<false><<<grid, 256, 0, st>>>(a);
+  const bool halves = std_key_halves(d) && !a.pair;
+  auto kern = out && d->score_tiled ? (halves ? k_std_prefill<true, 0, true, 2> : k_std_prefill<true, 0, true>)
+              : out                 ? (halves ? k_std_prefill<true, 0, false, 2> : k_std_prefill<true>)
+              : d->score_tiled      ? (halves ? k_std_prefill<false, 0, true, 2> : k_std_prefill<false, 0, true>)
+                                    : (halves ? k_std_prefill<false, 0, false, 2> : k_std_prefill<false>);
+  kern<<<grid, halves ? 512 : 256, 0, st>>>(a);
   int rc = check_launch();
   if (rc == LISA_OK) g_path = "mfma_std";
   return rc;
