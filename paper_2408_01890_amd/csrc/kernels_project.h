@@ -22,6 +22,7 @@
 // chunk c ^ ((m / 2) % 8), which makes both the tile writes and the operand reads free of
 // bank conflicts without padding.
 #pragma once
+#include <type_traits>
 #include "mfma_ffn.h"
 
 namespace lisa {
@@ -757,6 +758,93 @@ __global__ __launch_bounds__(512) void k_project_skinny_lds(ProjectArgs a) {
   }
   __syncthreads();                                          // every wave is done with its staging region
   project_skinny_finish<MB>(a, acc, red, nvb);
+}
+
+// ---- bf16, one to four token rows ------------------------------------------------------------
+// A wave = two weight rows (the two of a rotary pair, or neighbours of V) against all NB token rows, on the vector ALU:
+// the 73 blocks of 32 columns that the kernels above make of the LLaMA3-8B heads leave most of the chip without
+// work, and 31 of their 32 token rows are repeats.  All of a row pair's loads (16 KB at d = 4096) are in flight at once.
+// Bound: the latency of the loads and of one reduction over the wave.  Requires D % 512 == 0, an even r where it rotates.
+template <int NB>
+__global__ __launch_bounds__(256) void k_project_rows(ProjectArgs a) {
+  if ((int)blockIdx.x >= a.n_blocks) {                      // (the tail of the grid: see ProjectArgs)
+    ffn_operand_piece<false>(a.ffn, ((int)blockIdx.x - a.n_blocks) * 256 + (int)threadIdx.x);
+    return;
+  }
+  const int lane = threadIdx.x & 63;
+  const int unit = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int nqk = a.H + a.Hkv, hr = (a.r + 1) / 2, n_units = nqk * hr + a.Hkv * a.dk / 2;
+  if (unit >= n_units) return;
+  const int M = a.B * a.L, D = a.D;
+  int head, c0, c1;                                         // features c0, c1 of the head
+  if (unit < nqk * hr) {
+    head = unit / hr;
+    c0 = unit - head * hr;
+    c1 = c0 + hr;                                           // (r odd: the last one has no partner)
+  } else {
+    const int f = 2 * (unit - nqk * hr);
+    head = nqk + f / a.dk;
+    c0 = f % a.dk;
+    c1 = c0 + 1;
+  }
+  const bool two = head >= nqk || c1 < a.r;
+  const size_t row0 = head < nqk ? (size_t)head * a.r + c0 : (size_t)nqk * a.r + (size_t)(head - nqk) * a.dk + c0;
+  const bf16_t* w0 = (const bf16_t*)a.w + row0 * D + 8 * lane;
+  const bf16_t* w1 = w0 + (two ? (size_t)(c1 - c0) * D : 0);
+  const bf16_t* x = (const bf16_t*)a.x + 8 * lane;
+  float acc[2][NB] = {};
+  auto chunks = [&](auto n, int at) __attribute__((always_inline)) {   // n chunks of 512 elements
+    constexpr int N = decltype(n)::value;
+    pj_u32x4 wv[2][N], xv[NB][N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      wv[0][u] = *(const pj_u32x4*)(w0 + at + 512 * u);
+      wv[1][u] = *(const pj_u32x4*)(w1 + at + 512 * u);
+    }
+#pragma unroll
+    for (int m = 0; m < NB; ++m)
+#pragma unroll
+      for (int u = 0; u < N; ++u) xv[m][u] = *(const pj_u32x4*)(x + (size_t)min(m, M - 1) * D + at + 512 * u);
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int m = 0; m < NB; ++m) {
+          const float xl = __uint_as_float(xv[m][u][e] << 16), xh = __uint_as_float(xv[m][u][e] & 0xffff0000u);
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            acc[q][m] = __builtin_fmaf(xl, __uint_as_float(wv[q][u][e] << 16), acc[q][m]);
+            acc[q][m] = __builtin_fmaf(xh, __uint_as_float(wv[q][u][e] & 0xffff0000u), acc[q][m]);
+          }
+        }
+  };
+  const bool rot = a.rope && head < nqk;
+  const double inv_freq_rev = rot ? exp2((double)c0 * a.freq_log2) * 0.15915494309189535 : 0.0;
+  constexpr int NC = NB <= 2 ? 8 : 4;
+  int at = 0;
+  for (; at + 512 * NC <= D; at += 512 * NC) chunks(std::integral_constant<int, NC>{}, at);
+  for (; at < D; at += 512) chunks(std::integral_constant<int, 1>{}, at);
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int m = 0; m < NB; ++m) acc[q][m] = wave_sum(acc[q][m]);
+  float y0 = acc[0][0], y1 = acc[1][0];                     // lane m: token row m
+#pragma unroll
+  for (int m = 1; m < NB; ++m)
+    if (lane == m) y0 = acc[0][m], y1 = acc[1][m];
+  if (lane >= M) return;                                    // (M <= NB)
+  const int b = lane / a.L, l = lane - b * a.L;
+  if (rot) {
+    float cs, sn;
+    rope_cos_sin_fast(a.pos0 + l, inv_freq_rev, cs, sn);
+    const float lo = y0 * cs - y1 * sn, hi = y0 * sn + y1 * cs;
+    y0 = lo, y1 = hi;
+  }
+  bf16_t* dst = (bf16_t*)(head < a.H ? a.q_lr : head < nqk ? a.k_lr : a.v);
+  int which;
+  dst[project_dest(a, b, l, head, c0, which)].bits = (uint16_t)f32_to_bf16_bits(y0);
+  if (two) dst[project_dest(a, b, l, head, c1, which)].bits = (uint16_t)f32_to_bf16_bits(y1);
 }
 
 }  // namespace lisa
