@@ -73,13 +73,14 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
   extern __shared__ __align__(16) unsigned char sm_lds[];
   const int H = a.H, Din = 2 * H, Lq = a.Lq, Lk = a.Lk;
   // PIPE (up to 32 heads, where the LDS has room): the output tile (H heads, half) has an array of
-  // its own and leaves during the FFN of the next tile.  Otherwise it takes the place of the input
+  // its own (the padding heads as well: no test per write) and leaves during the FFN of the next tile; a head of
+  // zeros behind the input tile is what the padding of the contraction reads.  Otherwise it takes the place of the input
   // tile (2H heads, half) as float32 and leaves before the next tile is staged.
   constexpr bool PIPE = HBI <= 4;
-  const int io_bytes = PIPE ? Din * PF_XS_HEAD + H * SM_YH_HEAD : max(Din * PF_XS_HEAD, H * SM_YS_HEAD);
+  const int io_bytes = PIPE ? (Din + 1) * PF_XS_HEAD + HBO * 16 * SM_YH_HEAD : max(Din * PF_XS_HEAD, H * SM_YS_HEAD);
   unsigned char* xs = sm_lds;
   unsigned char* ys = sm_lds;
-  unsigned char* yh = sm_lds + Din * PF_XS_HEAD;
+  unsigned char* yh = sm_lds + (Din + 1) * PF_XS_HEAD;
   unsigned short* w_s = (unsigned short*)(sm_lds + ((io_bytes + 15) & ~15));
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -103,9 +104,11 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
   int xrd[KS][2];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
-    xrd[ks][0] = min(32 * ks + 8 * g + (c >> 2), Din - 1) * PF_XS_HEAD + 8 * (c & 3);
-    xrd[ks][1] = min(32 * ks + 8 * g + 4 + (c >> 2), Din - 1) * PF_XS_HEAD + 8 * (c & 3);
+    xrd[ks][0] = min(32 * ks + 8 * g + (c >> 2), PIPE ? Din : Din - 1) * PF_XS_HEAD + 8 * (c & 3);
+    xrd[ks][1] = min(32 * ks + 8 * g + 4 + (c >> 2), PIPE ? Din : Din - 1) * PF_XS_HEAD + 8 * (c & 3);
   }
+  if (PIPE)
+    for (int i = tid; i < PF_XS_HEAD / 4; i += NW * 64) ((unsigned*)(xs + Din * PF_XS_HEAD))[i] = 0;
   while (pos < hi) {
   // ---- one row group: tiles [t_first, t_last) of its key tiles -----------------------------------
   const int i0 = rg * PF_ROWS;
@@ -177,7 +180,7 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
       }
     }
   };
-  auto read_x = [&](f16x8 (&x)[NBW][KS], bool x_all) {     // x_all: 2H fills the k-steps, nothing to zero
+  auto read_x = [&](f16x8 (&x)[NBW][KS]) {
 #pragma unroll
     for (int n = 0; n < NBW; ++n) {
       const int nb = wv + n * NW;                           // block = (row nb / 2, key half nb % 2)
@@ -192,8 +195,8 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
                        (s16x4 __attribute__((address_space(3)))*)(xs + xrd[ks][1] + i * 64 + 32 * kh)));
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          x[n][ks][e] = (x_all || 32 * ks + 8 * g + e < Din) ? lo[e] : (_Float16)0.f;
-          x[n][ks][4 + e] = (x_all || 32 * ks + 8 * g + 4 + e < Din) ? hi[e] : (_Float16)0.f;
+          x[n][ks][e] = lo[e];
+          x[n][ks][4 + e] = hi[e];
         }
       }
     }
@@ -233,10 +236,11 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
     // keys of heads v = 0, 1 and the odd lane those of v = 2, 3 (2-byte LDS writes cost about three
     // times as much).
     const bool odd = c & 1;
+    const unsigned sel_lo = odd ? 0x05040100u : 0x01000504u, sel_hi = odd ? 0x07060302u : 0x03020706u;
+    unsigned char* const ywr = yh + (4 * g + 2 * (c & 1)) * SM_YH_HEAD + (wv >> 1) * (PF_TK * 2) + (16 * (wv & 1) + (c & ~1)) * 2;
     auto write_y = [&]() {
 #pragma unroll
       for (int qn = 0; qn < NBW; ++qn) {
-        const int nb = wv + qn * NW, i = nb >> 1, kh = nb & 1;
 #pragma unroll
         for (int hb = 0; hb < HBO; ++hb) {
           f16x4 hv;
@@ -245,18 +249,15 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
           const uint2 pq = __builtin_bit_cast(uint2, hv);   // (heads v = 0, 1), (heads v = 2, 3) of key c
           const unsigned keep = odd ? pq.y : pq.x;
           const unsigned got = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(odd ? pq.x : pq.y), 0xB1, 0xF, 0xF, true);
-          const unsigned first = odd ? got : keep, second = odd ? keep : got;   // keys c & ~1, c | 1
-          const int hl = 16 * hb + 4 * g + 2 * (c & 1);
-          unsigned char* yp = yh + hl * SM_YH_HEAD + i * (PF_TK * 2) + (16 * kh + (c & ~1)) * 2;
-          if (hl < H) *(unsigned*)yp = (first & 0xffffu) | (second << 16);
-          if (hl + 1 < H) *(unsigned*)(yp + SM_YH_HEAD) = (first >> 16) | (second & 0xffff0000u);
+          unsigned char* yp = ywr + 16 * hb * SM_YH_HEAD + (NW / 2) * qn * (PF_TK * 2);   // block wv + NW qn
+          *(unsigned*)yp = __builtin_amdgcn_perm(keep, got, sel_lo);
+          *(unsigned*)(yp + SM_YH_HEAD) = __builtin_amdgcn_perm(keep, got, sel_hi);
         }
       }
     };
     constexpr int N_OPS = XCH + 1 + XCH + 2 * HPW;          // read / store pairs of a tile, then the loads of the next
     constexpr int N_GROUPS = (FS / SC) * (2 * SC + HBO);
     constexpr int OPG = (N_OPS + N_GROUPS - 1) / N_GROUPS;
-    const bool x_all = Din == 32 * KS;
     // one tile; PEND (a compile-time constant: the first tile of a run has its own copy of the
     // loop body, so that no store of the others sits behind a branch): the result of the tile
     // before is in yh and leaves during this tile's FFN
@@ -266,7 +267,7 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
       if (PEND) write_y();
       lds_barrier();                                         // A: xs and yh are complete
       f16x8 x[NBW][KS];
-      read_x(x, x_all);
+      read_x(x);
       const int jn = (tile + 1) * PF_TK;
       const int xoff = min(jn + xq8, Lk - 8);
       const size_t toff = trow + min(tile + 1, n_kt - 1) * tile_stride;
@@ -404,7 +405,7 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
 // LDS bytes of k_lisa_scores_mfma<HBI, FS, HBO> for H heads.
 template <int HBI, int FS, int HBO>
 constexpr int scores_mfma_lds(int H) {
-  const int io = HBI <= 4 ? 2 * H * PF_XS_HEAD + H * SM_YH_HEAD
+  const int io = HBI <= 4 ? (2 * H + 1) * PF_XS_HEAD + HBO * 16 * SM_YH_HEAD
                           : (2 * H * PF_XS_HEAD > H * SM_YS_HEAD ? 2 * H * PF_XS_HEAD : H * SM_YS_HEAD);
   return ((io + 15) & ~15) + MfmaFfn<HBI, FS, HBO>::kStageBytes;
 }
