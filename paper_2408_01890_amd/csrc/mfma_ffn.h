@@ -379,35 +379,50 @@ struct MfmaFfn {
     };
 #pragma unroll
     for (int gi = 0; gi < AH && gi < NGR; ++gi) read_ops(gi);
+    // A group is worked off in halves of its blocks; the activation of a half runs between the MFMAs of the half after it,
+    // three vector instructions per MFMA.
+    constexpr int HN = NBLK / 2;
+    static_assert(NBLK % 2 == 0, "halves of the blocks");
     f16x8 hid[NBLK][SC];
+    f32x4 acc[2][HN];
 #pragma unroll
     for (int gi = 0; gi < NGR; ++gi) {
       const int s0 = (gi / GPC) * SC, idx = gi % GPC;
+      const bool first = idx < 2 * SC;                      // hidden block fb = 2 s + half
       between(gi);
       if (gi + AH < NGR) read_ops(gi + AH);
-      if (idx < 2 * SC) {                                   // hidden block fb = 2 s + half
-        const int fb = 2 * s0 + idx;
-        f32x4 acc[NBLK];
 #pragma unroll
-        for (int n = 0; n < NBLK; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int p = 0; p < 2; ++p) {
+        if (first) {
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
+          for (int n = 0; n < HN; ++n) acc[p][n] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int n = 0; n < NBLK; ++n)
-            acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[gi % NBUF][ks], x[n][ks], acc[n], 0, 0, 0);
+          for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-        for (int n = 0; n < NBLK; ++n)
+            for (int n = 0; n < HN; ++n)
+              acc[p][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[gi % NBUF][ks], x[HN * p + n][ks], acc[p][n], 0, 0, 0);
+        } else {
+          const int hb = idx - 2 * SC;
 #pragma unroll
-          for (int v = 0; v < 4; ++v) hid[n][(fb >> 1) - s0][4 * (fb & 1) + v] = activate(acc[n][v]);
-      } else {
-        const int hb = idx - 2 * SC;
+          for (int s = 0; s < SC; ++s)
 #pragma unroll
-        for (int s = 0; s < SC; ++s)
+            for (int n = HN * p; n < HN * p + HN; ++n)
+              y[n][hb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[gi % NBUF][s], hid[n][s], y[n][hb], 0, 0, 0);
+        }
+        const int fi = p ? idx : gi > 0 ? (gi - 1) % GPC : 2 * SC;
+        if (fi < 2 * SC) {                                    // the half before
 #pragma unroll
-          for (int n = 0; n < NBLK; ++n)
-            y[n][hb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[gi % NBUF][s], hid[n][s], y[n][hb], 0, 0, 0);
+          for (int n = 0; n < HN; ++n)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) hid[HN * (1 - p) + n][fi >> 1][4 * (fi & 1) + v] = activate(acc[1 - p][n][v]);
+#pragma unroll
+          for (int k = 0; k < (first ? KS : SC) * HN; ++k) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, ACT == 1 ? 16 : 3, 0);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
-      __builtin_amdgcn_sched_barrier(0);
     }
   }
 
