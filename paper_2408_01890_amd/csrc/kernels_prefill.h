@@ -24,8 +24,8 @@
 //           lane's 8 probabilities are exactly its B operand (k = 8 g + e), no data movement.
 //   Both leave "row" on the lane index c, where the softmax statistics of that row live.
 //
-// Inputs are repacked once per call into the workspace: Q_LR and K_LR rows zero-padded from r to
-// 32 elements (64-byte rows, aligned 16-byte operand loads) and V regrouped as
+// Inputs are repacked once per call into the workspace: Q_LR rows zero-padded from r to 32 elements (64-byte rows), K_LR
+// likewise as tiles of 32 keys in operand order (per MFMA u the 16 bytes of each lane in a row: one KB) and V regrouped as
 // [B,Hkv,Lkp/8,d_k,8] (8 consecutive keys of one feature = one 16-byte load, the 128 features of
 // a key chunk contiguous, so the 8 feature blocks of a lane differ by an immediate offset).
 //

@@ -13,9 +13,8 @@
 //   output  D[d, row] = sum_key V^T[d,key] P^T[key,row]   A = V^T, whose columns the transposing LDS read hands out
 //           of the V rows as they are, B = the lane's probabilities as they are.
 // A = Q K^T * scale is stored as half; the softmax works on the float32 values.
-// A workgroup takes two row groups, the x-th longest and the x-th shortest, so that all
-// workgroups stream the same number of tiles (large problems), or one row group (problems with
-// fewer than two such workgroups per compute unit: twice the waves in flight).
+// A workgroup takes one row group, long ones first (tests can make it take the x-th longest and the x-th shortest).  Where
+// there are few workgroups it has a second set of four waves, and each set takes half of the keys (NH, std_key_halves()).
 #pragma once
 #include "kernels_prefill.h"
 

@@ -37,37 +37,42 @@ int split_keys(const lisa_desc* d) {
 }
 }  // namespace
 
-bool split_scores_ok(const lisa_desc* d) {
-  if (!split_attn_ok(d) || !split_sizes_ok(d) || (d->act != LISA_ACT_RELU && d->act != LISA_ACT_SILU)) return false;
-  if (d->mix != LISA_MIX_ADD && d->mix != LISA_MIX_CONCAT) return false;
-  if (d->H > 40 || d->r > 32) return false;
-  return split_keys(d) > 0;
-}
-
-// The float32 scores pass through the workspace in tiles, a chunk of query rows at a time: 256 MB of them (what the
-// last-level cache holds), at least one block of 16 rows.
-int split_chunk_rows(const lisa_desc* d) {
-  const size_t row = (size_t)d->B * d->H * ((d->Lk + PF_TK - 1) / PF_TK * PF_TK) * sizeof(float);
-  const size_t rows = std::max<size_t>(16, (((size_t)256 << 20) / row) & ~(size_t)15);
-  return (int)std::min<size_t>(rows, (size_t)d->Lq);
-}
+// The float32 scores pass through the workspace in tiles, a chunk of query rows at a time: 256 MB (what the last-level cache
+// holds) with the padded operands behind them, at least one block of 16 rows.  Operands that would take more than half of that
+// (B H L around 1 M) leave the chunks too few rows: those calls keep the kernels that read the operands as they are.
 namespace {
-// Workspace: the float32 tiles of a chunk, then the padded operands.
+constexpr size_t kSplitBudget = (size_t)256 << 20;
+size_t split_row_bytes(const lisa_desc* d) {
+  return (size_t)d->B * d->H * ((d->Lk + PF_TK - 1) / PF_TK * PF_TK) * sizeof(float);
+}
 struct SplitWs {
   size_t qp, kp, total;
   int Lqp, Lkp;
 };
-SplitWs split_ws(const lisa_desc* d) {
+SplitWs split_ws(const lisa_desc* d, size_t rows) {
   SplitWs w;
   w.Lqp = (d->Lq + PF_ROWS - 1) / PF_ROWS * PF_ROWS;
   w.Lkp = (d->Lk + 63) / 64 * 64;
-  const size_t rows = (size_t)(split_chunk_rows(d) + 15) / 16 * 16;
-  w.qp = (size_t)d->B * d->H * rows * ((d->Lk + PF_TK - 1) / PF_TK * PF_TK) * sizeof(float);
+  w.qp = rows * split_row_bytes(d);
   w.kp = w.qp + round_up((size_t)d->B * d->H * w.Lqp * 32 * 2, 256);
   w.total = w.kp + round_up((size_t)d->B * d->Hkv * w.Lkp * 32 * 2, 256);
   return w;
 }
+SplitWs split_ws(const lisa_desc* d) { return split_ws(d, (size_t)(split_chunk_rows(d) + 15) / 16 * 16); }
 }  // namespace
+
+bool split_scores_ok(const lisa_desc* d) {
+  if (!split_attn_ok(d) || !split_sizes_ok(d) || (d->act != LISA_ACT_RELU && d->act != LISA_ACT_SILU)) return false;
+  if (d->mix != LISA_MIX_ADD && d->mix != LISA_MIX_CONCAT) return false;
+  if (d->H > 40 || d->r > 32) return false;
+  if (split_ws(d, 0).total > kSplitBudget / 2 || split_ws(d, 16).total > kSplitBudget) return false;
+  return split_keys(d) > 0;
+}
+
+int split_chunk_rows(const lisa_desc* d) {
+  const size_t rows = std::max<size_t>(16, ((kSplitBudget - split_ws(d, 0).total) / split_row_bytes(d)) & ~(size_t)15);
+  return (int)std::min<size_t>(rows, (size_t)d->Lq);
+}
 size_t split_bytes(const lisa_desc* d) { return split_ws(d).total; }
 
 namespace {
