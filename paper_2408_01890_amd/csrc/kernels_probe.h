@@ -48,8 +48,8 @@ __global__ __launch_bounds__(256) void k_probe_write(probe_u32x4* __restrict__ d
 
 // iters rounds of independent MFMAs on constant operands per wave: SHAPE 0: 8 x 16x16x32 f16 (the
 // shape of the library's FFNs), 1: 4 x 32x32x16 f16 (the same flops per round).  block 256.
-// SHAPE 0 takes two rounds at a time: over 8 accumulators the compiler's loop copies them between register sets, and
-// the copies were what was timed (1.24 PFLOP/s; 2.19 over 16).
+// (Sixteen rounds make a loop body: at the end of a loop body the compiler copies accumulators of SHAPE 0 between registers, and a body
+// of one round timed these copies, 1.24 PFLOP/s.)
 template <int SHAPE>
 __global__ __launch_bounds__(256) void k_probe_mfma(int iters, float seed, float* sink) {
   f16x8 a, b;
@@ -60,18 +60,18 @@ __global__ __launch_bounds__(256) void k_probe_mfma(int iters, float seed, float
   }
   float s = 0.f;
   if (SHAPE == 0) {
-    f32x4 acc[16];
+    f32x4 acc[8];
 #pragma unroll
-    for (int n = 0; n < 16; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int it = 0; it < iters / 2; ++it) {
+    for (int n = 0; n < 8; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int it = 0;
+    for (; it + 16 <= iters; it += 16)
 #pragma unroll
-      for (int n = 0; n < 16; ++n) acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, acc[n], 0, 0, 0);
-    }
-    if (iters & 1)
+      for (int n = 0; n < 16 * 8; ++n) acc[n & 7] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, acc[n & 7], 0, 0, 0);
+    for (; it < iters; ++it)
 #pragma unroll
       for (int n = 0; n < 8; ++n) acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, acc[n], 0, 0, 0);
 #pragma unroll
-    for (int n = 0; n < 16; ++n) s += acc[n][0] + acc[n][3];
+    for (int n = 0; n < 8; ++n) s += acc[n][0] + acc[n][3];
   } else {
     probe_f32x16 acc[4];
 #pragma unroll
