@@ -113,3 +113,25 @@ def test_chunk_border():
         A, O = reference(q[:, :, i:i + 1], k[:, :, :i + 1], v[:, :, :i + 1], prev[:, :, i:i + 1, :i + 1], w1, w2, "add", True)
         assert err(out[:, i:i + 1].flatten(2), O.flatten(2)) <= TOL_O
         assert err(scores[:, :, i, :i + 1].flatten(1), A[:, :, 0].flatten(1)) <= TOL_A
+
+
+@pytest.mark.parametrize("causal", [True, False])
+def test_batch_past_the_workspace_budget(causal):
+    """16 rows of float32 scores beside the padded operands pass 256 MB: the kernels without copies take the call, half of
+    the batch fits.  Both are float32 sums of the same terms."""
+    B, H, Lq, Lk, r, F = 16, 40, 2, 6561, 22, 64
+    log(f"[case] split budget causal={causal}")
+    g = torch.Generator(device=DEV).manual_seed(1)
+    rn = lambda *s: torch.randn(s, generator=g, device=DEV)
+    q, k, v = rn(B, H, Lq, r).to(torch.bfloat16), rn(B, 1, Lk, r).to(torch.bfloat16), rn(B, 1, Lk, 128).to(torch.bfloat16)
+    w1, w2 = (rn(H, F) / H ** 0.5).to(torch.bfloat16), (rn(F, H) / F ** 0.5).to(torch.bfloat16)
+    prev = rn(B, H, Lq, Lk).to(torch.float16)
+    run = lambda s: lisa.lisa_attn_prefill(q[s], k[s], v[s], prev[s], w1, w2, causal=causal)
+    whole, a = run(slice(None))
+    for s in (slice(0, B // 2), slice(B // 2, B)):
+        out, b = run(s)
+        torch.cuda.synchronize()
+        vis = slice(None, Lk - 1) if causal else slice(None)          # (the last key: row 1 alone)
+        assert err(whole[s], out.cpu().double()) <= TOL_O
+        x, y = a[s][..., vis].cpu().double(), b[..., vis].cpu().double()
+        assert float((x - y).abs().max()) <= TOL_A * float(y.pow(2).mean().sqrt())
