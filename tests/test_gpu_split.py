@@ -30,13 +30,13 @@ CASES = [  # B, H, Hkv, Lq, Lk, r, F, mix, causal
 ]
 
 
-def reference(q, k, v, prev, w1, w2, mix, causal):
+def reference(q, k, v, prev, w1, w2, mix, causal, act="relu"):
     d = torch.float64
     q, k, v, prev, w1, w2 = (t.cpu().to(d) for t in (q, k, v, prev, w1, w2))
     rep = lambda t: t.repeat_interleave(q.shape[1] // t.shape[1], 1)
     delta = q @ rep(k).transpose(-1, -2).contiguous() / q.shape[-1] ** 0.5
     x = torch.cat([prev, delta], 1) if mix == "concat" else prev
-    A = (torch.relu(x.permute(0, 2, 3, 1) @ w1) @ w2).permute(0, 3, 1, 2)
+    A = ((torch.relu if act == "relu" else torch.nn.functional.silu)(x.permute(0, 2, 3, 1) @ w1) @ w2).permute(0, 3, 1, 2)
     if mix == "add":
         A = A + delta
     return A, softmax_v(A, rep(v), causal)
