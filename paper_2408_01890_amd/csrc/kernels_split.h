@@ -92,6 +92,7 @@ struct SplitAttnArgs {
 
 constexpr int SA_OROW = 128 + 4;             // floats per row of a wave's partial result
 // LDS of four waves: a K tile, over which the emitted scores are staged, and a V tile each; at the end the partial results.
+constexpr int SA_PROW = SP_TK + 1;           // floats per row of a wave's probabilities
 constexpr int split_attn_wave_lds(bool with_v, bool given) { return (given ? 0 : SP_KTILE) + (with_v ? SP_VTILE : 0); }
 constexpr int split_attn_lds(bool with_v, bool given) {
   const int tiles = 4 * split_attn_wave_lds(with_v, given), merge = with_v ? 4 * (SP_ROWS * SA_OROW + 2 * SP_ROWS) * 4 : 0;
@@ -114,6 +115,9 @@ __global__ __launch_bounds__(256, 2) void k_split_attn(SplitAttnArgs a) {
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   unsigned char* ks_ = lds + wv * split_attn_wave_lds(WITH_V, GIVEN);   // K tile; the score staging lies over it
   unsigned char* vs_ = ks_ + (GIVEN ? 0 : SP_KTILE);
+  // probabilities of a second pass: over the K tile (which has been read), GIVEN behind the V tiles
+  float* ps_ = (float*)(GIVEN ? lds + 4 * SP_VTILE + wv * (SP_ROWS * SA_PROW * 4) : ks_);
+  static_assert(SP_ROWS * SA_PROW * 4 <= SP_KTILE && (!GIVEN || 4 * (SP_VTILE + SP_ROWS * SA_PROW * 4) <= split_attn_lds(WITH_V, GIVEN)), "");
   const int r = lane & 31, half = lane >> 5;
   const int b = blockIdx.z, h = blockIdx.x;
   const int Lq = a.Lq, Lk = a.Lk, H = a.H, shift = Lk - Lq;
@@ -187,127 +191,167 @@ __global__ __launch_bounds__(256, 2) void k_split_attn(SplitAttnArgs a) {
       for (int u = 0; u < 4; ++u) gq[u] = *(const f32x4_a4b*)(gp + g_u * (u >> 1) + g_q * (u & 1));
   };
   auto clamp_tile = [&](int t) { return min(t, n_tiles - 1); };
-  load_kt(clamp_tile(t_begin));
-  load_scores(clamp_tile(t_begin));
   f32x16 o[DK / 32];
+  float m_run, l_run;
+  // A part of a probability may be 0 (1.0 has one part only), and 0 times an infinite element of V is NaN where the probability
+  // itself gives infinity.  A wave that ends with NaN goes over its tiles again with `whole` probabilities: one float32
+  // product for each visible key.  (A pass of its own: as a branch inside the loop it cost 40 spilled registers.)
+  auto pass = [&](auto whole) __attribute__((always_inline)) {
+    load_kt(clamp_tile(t_begin));
+    load_scores(clamp_tile(t_begin));
+#pragma unroll
+    for (int db = 0; db < DK / 32; ++db)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
+    m_run = -INFINITY, l_run = 0.f;
+
+    // (the scheduling fences keep the order of the accesses to the tiles and the distance of the loads)
+    for (int tile = t_begin; tile < n_tiles; tile += t_step) {
+      store_kt();
+      load_vt(tile);
+      __builtin_amdgcn_sched_barrier(0);
+      const int j0 = tile * SP_TK;
+      float an[16];                                              // an[8 u + e]: key j0 + 16 u + 8 half + e of row r
+      if (GIVEN) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) an[4 * u + e] = gq[u][e];
+      } else {
+        f32x16 acc;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < DK / 16; ++ks)
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(ks_ + k_rd + 32 * ks), qop[ks], acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) an[v] = acc[v] * a.scale;
+      }
+      const bool full = tile < n_full;
+      const int jl = j0 + 8 * half;
+      if (!GIVEN && a.scores) {
+        __builtin_amdgcn_sched_barrier(0);                       // (the staging tile lies over the K tile, which has been read)
+        f16x8 hv0, hv1;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          hv0[e] = f32_to_half_sat(an[e]);
+          hv1[e] = f32_to_half_sat(an[8 + e]);
+        }
+        unsigned char* sl = ks_ + r * SP_SROW + 16 * half;
+        *(f16x8*)sl = hv0;
+        *(f16x8*)(sl + 32) = hv1;
+        const int jc = j0 + 8 * (lane & 3);                      // lane -> row lane / 4 (+ 16), 8 keys
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int row = 16 * u + (lane >> 2), gi = i0 + row;
+          const pf_u32x4 hv = *(const pf_u32x4*)(ks_ + row * SP_SROW + (lane & 3) * 16);
+          const int vis = gi < row_end ? (a.causal ? min(Lk, gi + 1 + shift) : Lk) : 0;
+          half_t* sp = sbase + (size_t)min(gi, Lq - 1) * Lk + jc;
+          if (full || jc + 8 <= vis) {
+            *(pf_u32x4_a2*)sp = hv;
+          } else if (jc < vis) {
+            int rel = vis - jc;                                  // (kept inside this branch: registers)
+            asm volatile("" : "+v"(rel));
+            store_row_part_any(sp, hv, rel);
+          }
+        }
+      }
+      if (WITH_V) {
+        if (!full) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v)
+            if (jl + 16 * (v >> 3) + (v & 7) >= vis_row) an[v] = -INFINITY;
+        }
+        float mx = an[0];
+#pragma unroll
+        for (int v = 1; v < 15; v += 2) mx = max3_raw(mx, an[v], an[v + 1]);
+        mx = halves_max(max2_raw(mx, an[15]));
+        const float m_new = max2_raw(m_run, mx);
+        // (the maximum is subtracted before the change of base, and no key may have been seen yet: see k_f32_attn)
+        const float m0 = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = fast_exp2((m_run - m0) * LOG2E);
+        m_run = m_new;
+        float ps = 0.f;
+        bf16x8 pop[2][3];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          float p[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            p[e] = fast_exp2((an[8 * s + e] - m0) * LOG2E);
+            ps += p[e];
+          }
+          split_parts<3, NO_INF>(p, pop[s]);
+        }
+        load_scores(clamp_tile(tile + t_step));
+        store_vt();
+        load_kt(clamp_tile(tile + t_step));
+        __builtin_amdgcn_sched_barrier(0);
+        l_run = l_run * alpha + ps;
+        if (__any(alpha != 1.f)) {                               // wave-uniform: the running maximum rarely moves
+#pragma unroll
+          for (int db = 0; db < DK / 32; ++db)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
+        }
+        if constexpr (decltype(whole)::value) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            float p = 0.f;
+#pragma unroll
+            for (int k = 2; k >= 0; --k) p += (float)pop[v >> 3][k][v & 7];
+            ps_[r * SA_PROW + 16 * (v >> 3) + 8 * half + (v & 7)] = p;
+          }
+#pragma unroll 1
+          for (int j = 0; j < SP_TK; ++j) {
+            const float p = ps_[r * SA_PROW + j];
+            const unsigned seen = j0 + j < vis_row ? ~0u : 0u;
+#pragma unroll
+            for (int db = 0; db < DK / 32; ++db) {
+#pragma unroll
+              for (int q4 = 0; q4 < 4; ++q4) {
+                const uint2 w = *(const uint2*)(vs_ + j * SP_VROW + (32 * db + 8 * q4 + 4 * half) * 2);
+                o[db][4 * q4] += p * __uint_as_float((w.x & seen) << 16);
+                o[db][4 * q4 + 1] += p * __uint_as_float(w.x & seen & 0xffff0000u);
+                o[db][4 * q4 + 2] += p * __uint_as_float((w.y & seen) << 16);
+                o[db][4 * q4 + 3] += p * __uint_as_float(w.y & seen & 0xffff0000u);
+              }
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          }
+        } else {
+          // The tile's products are summed from zero and added in one step: what a MFMA adds to its accumulator is
+          // rounded (at the accumulator's size) six times per tile otherwise, 4.0e-7 of O against 2.2e-7 (301 rows of 1301 keys).
+#pragma unroll
+          for (int db = 0; db < DK / 32; ++db) {
+            bf16x8 vop[2];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) vop[s] = read_columns(vs_ + v_rd + 16 * s * SP_VROW + 64 * db);
+            f32x16 t;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) t[v] = 0.f;
+#pragma unroll
+            for (int k = 2; k >= 0; --k)                           // small terms first
+#pragma unroll
+              for (int s = 0; s < 2; ++s) t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop[s], pop[s][k], t, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) o[db][v] += t[v];
+          }
+        }
+      } else {
+        load_kt(clamp_tile(tile + t_step));
+      }
+      __builtin_amdgcn_sched_barrier(0);                         // (the next step's tile goes over this one's)
+    }
+  };
+  pass(std::false_type{});
+  if (!WITH_V) return;
+  float any = 0.f;                                           // (NaN where an element is)
 #pragma unroll
   for (int db = 0; db < DK / 32; ++db)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-
-  // (the scheduling fences keep the order of the accesses to the tiles and the distance of the loads)
-  for (int tile = t_begin; tile < n_tiles; tile += t_step) {
-    store_kt();
-    load_vt(tile);
-    __builtin_amdgcn_sched_barrier(0);
-    const int j0 = tile * SP_TK;
-    float an[16];                                              // an[8 u + e]: key j0 + 16 u + 8 half + e of row r
-    if (GIVEN) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) an[4 * u + e] = gq[u][e];
-    } else {
-      f32x16 acc;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < DK / 16; ++ks)
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(ks_ + k_rd + 32 * ks), qop[ks], acc, 0, 0, 0);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) an[v] = acc[v] * a.scale;
-    }
-    const bool full = tile < n_full;
-    const int jl = j0 + 8 * half;
-    if (!GIVEN && a.scores) {
-      __builtin_amdgcn_sched_barrier(0);                       // (the staging tile lies over the K tile, which has been read)
-      f16x8 hv0, hv1;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        hv0[e] = f32_to_half_sat(an[e]);
-        hv1[e] = f32_to_half_sat(an[8 + e]);
-      }
-      unsigned char* sl = ks_ + r * SP_SROW + 16 * half;
-      *(f16x8*)sl = hv0;
-      *(f16x8*)(sl + 32) = hv1;
-      const int jc = j0 + 8 * (lane & 3);                      // lane -> row lane / 4 (+ 16), 8 keys
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int row = 16 * u + (lane >> 2), gi = i0 + row;
-        const pf_u32x4 hv = *(const pf_u32x4*)(ks_ + row * SP_SROW + (lane & 3) * 16);
-        const int vis = gi < row_end ? (a.causal ? min(Lk, gi + 1 + shift) : Lk) : 0;
-        half_t* sp = sbase + (size_t)min(gi, Lq - 1) * Lk + jc;
-        if (full || jc + 8 <= vis) {
-          *(pf_u32x4_a2*)sp = hv;
-        } else if (jc < vis) {
-          int rel = vis - jc;                                  // (kept inside this branch: registers)
-          asm volatile("" : "+v"(rel));
-          store_row_part_any(sp, hv, rel);
-        }
-      }
-    }
-    if (WITH_V) {
-      if (!full) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          if (jl + 16 * (v >> 3) + (v & 7) >= vis_row) an[v] = -INFINITY;
-      }
-      float mx = an[0];
-#pragma unroll
-      for (int v = 1; v < 15; v += 2) mx = max3_raw(mx, an[v], an[v + 1]);
-      mx = halves_max(max2_raw(mx, an[15]));
-      const float m_new = max2_raw(m_run, mx);
-      // (the maximum is subtracted before the change of base, and no key may have been seen yet: see k_f32_attn)
-      const float m0 = m_new == -INFINITY ? 0.f : m_new;
-      const float alpha = fast_exp2((m_run - m0) * LOG2E);
-      m_run = m_new;
-      float ps = 0.f;
-      bf16x8 pop[2][3];
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        float p[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          p[e] = fast_exp2((an[8 * s + e] - m0) * LOG2E);
-          ps += p[e];
-        }
-        split_parts<3, NO_INF>(p, pop[s]);
-      }
-      load_scores(clamp_tile(tile + t_step));
-      store_vt();
-      load_kt(clamp_tile(tile + t_step));
-      __builtin_amdgcn_sched_barrier(0);
-      l_run = l_run * alpha + ps;
-      if (__any(alpha != 1.f)) {                               // wave-uniform: the running maximum rarely moves
-#pragma unroll
-        for (int db = 0; db < DK / 32; ++db)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
-      }
-      // The tile's products are summed from zero and added in one step: what a MFMA adds to its accumulator is
-      // rounded (at the accumulator's size) six times per tile otherwise, 4.0e-7 of O against 2.2e-7 (301 rows of 1301 keys).
-#pragma unroll
-      for (int db = 0; db < DK / 32; ++db) {
-        bf16x8 vop[2];
-#pragma unroll
-        for (int s = 0; s < 2; ++s) vop[s] = read_columns(vs_ + v_rd + 16 * s * SP_VROW + 64 * db);
-        f32x16 t;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) t[v] = 0.f;
-#pragma unroll
-        for (int k = 2; k >= 0; --k)                           // small terms first
-#pragma unroll
-          for (int s = 0; s < 2; ++s) t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop[s], pop[s][k], t, 0, 0, 0);
-#pragma unroll
-        for (int v = 0; v < 16; ++v) o[db][v] += t[v];
-      }
-    } else {
-      load_kt(clamp_tile(tile + t_step));
-    }
-    __builtin_amdgcn_sched_barrier(0);                         // (the next step's tile goes over this one's)
-  }
-  if (!WITH_V) return;
+    for (int v = 0; v < 16; ++v) any += o[db][v];
+  if (__any(any != any)) pass(std::true_type{});
 
   auto store4 = [&](size_t at, const float (&x)[4]) {
     if (a.out_f32) {

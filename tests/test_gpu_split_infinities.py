@@ -5,7 +5,7 @@ import torch
 
 from paper_2408_01890_amd import lisa
 from tests.test_gpu_parity import log
-from tests.test_gpu_split import TOL_O, err, reference
+from tests.test_gpu_split import TOL_O, err, reference, softmax_v
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -63,3 +63,48 @@ def test_infinite_scores_at_masked_keys(case):
     assert bool((scores.cpu()[..., masked] <= -60000).all())
     assert torch.isfinite(out).all()
     assert err(out[:, rows].flatten(2), O[:, rows].flatten(2)) <= TOL_O
+
+
+@pytest.mark.parametrize("Lq,Lk,causal", [(301, 301, True), (40, 301, True), (33, 129, False), (2, 65, True), (19, 19, True)])
+@pytest.mark.parametrize("kind", ["std", "share", "add"])
+def test_infinite_v(kind, Lq, Lk, causal):
+    """An infinite element of V makes its feature infinite in the rows that see its key, whatever bits the probability has (all
+    of them 1 in half of the heads: equal scores), NaN makes it NaN, and the other rows and features stay what they are."""
+    B, H, Hkv, r, F = 2, 8, 4, 20, 32
+    log(f"[case] split infinite V {kind} {Lq}x{Lk}")
+    g = torch.Generator(device=DEV).manual_seed(Lk)
+    rn = lambda *s: torch.randn(s, generator=g, device=DEV)
+    v = rn(B, Hkv, Lk, 128).to(torch.bfloat16)
+    at = {(Lk // 2, 5): float("inf"), (Lk - 2, 70): float("-inf"), (0, 127): float("inf"), (Lk // 3, 33): float("nan")}
+    rep = lambda t: t.cpu().double().repeat_interleave(H // Hkv, 1)
+    if kind == "std":
+        q, k = rn(B, H, Lq, 128).to(torch.bfloat16), rn(B, Hkv, Lk, 128).to(torch.bfloat16)
+        q[:, ::2] = 0
+        A = q.cpu().double() @ rep(k).transpose(-1, -2).contiguous() / 128 ** 0.5
+    else:
+        q, k, prev = rn(B, H, Lq, r).to(torch.bfloat16), rn(B, Hkv, Lk, r).to(torch.bfloat16), rn(B, H, Lq, Lk).half()
+        w1, w2 = (rn(H, F) / H ** 0.5).to(torch.bfloat16), (rn(F, H) / F ** 0.5).to(torch.bfloat16)
+        prev[:, ::2] = 1.0
+        if kind == "add":
+            q[:, ::2] = 0
+            prev[:] = prev[:, :1]
+            w2[:, ::2] = 0                                   # (A_n = 0 in every other head)
+            A = reference(q, k, v, prev, w1, w2, "add", causal)[0]
+        else:
+            A = prev.cpu().double()
+    O = softmax_v(A, rep(v), causal)                         # [B,Lq,H,128], of the finite V
+    last = torch.arange(Lq) + Lk - Lq if causal else torch.full((Lq,), Lk - 1)
+    for (key, d), x in at.items():
+        v[:, :, key, d] = x
+        O[:, last >= key, :, d] = x
+    if kind == "std":
+        out = lisa.std_attn_scores(q, k, v, causal=causal)[1]
+    elif kind == "add":
+        out = lisa.lisa_attn_prefill(q, k, v, prev, w1, w2, causal=causal)[0]
+    else:
+        out = lisa.lisa_attn_prefill(None, None, v, prev, None, None, mix=lisa.MIX_SHARE, causal=causal)[0]
+    torch.cuda.synchronize()
+    got, fin = out.cpu().double(), torch.isfinite(O)
+    assert torch.equal(got[~fin].nan_to_num(nan=7.0), O[~fin].nan_to_num(nan=7.0))
+    rms = O.masked_fill(~fin, 0).pow(2).mean(-1, keepdim=True).sqrt()
+    assert float(((got - O).masked_fill(~fin, 0).abs() / rms).max()) <= TOL_O
