@@ -258,9 +258,9 @@ __global__ __launch_bounds__(256, 2) void k_split_attn(SplitAttnArgs a) {
       }
       if (WITH_V) {
         if (!full) {
+          const int rel = vis_row - jl;
 #pragma unroll
-          for (int v = 0; v < 16; ++v)
-            if (jl + 16 * (v >> 3) + (v & 7) >= vis_row) an[v] = -INFINITY;
+          for (int v = 0; v < 16; ++v) an[v] = 16 * (v >> 3) + (v & 7) < rel ? an[v] : -INFINITY;
         }
         float mx = an[0];
 #pragma unroll
@@ -346,12 +346,12 @@ __global__ __launch_bounds__(256, 2) void k_split_attn(SplitAttnArgs a) {
   };
   pass(std::false_type{});
   if (!WITH_V) return;
-  float any = 0.f;                                           // (NaN where an element is)
+  f32x4 any = {0.f, 0.f, 0.f, 0.f};                          // (NaN where an element is)
 #pragma unroll
-  for (int db = 0; db < DK / 32; ++db)
+  for (int v = 0; v < 16; ++v)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) any += o[db][v];
-  if (__any(any != any)) pass(std::true_type{});
+    for (int db = 0; db < DK / 32; ++db) any[db] += o[db][v];
+  if (const float x = (any[0] + any[1]) + (any[2] + any[3]); __any(x != x)) pass(std::true_type{});
 
   auto store4 = [&](size_t at, const float (&x)[4]) {
     if (a.out_f32) {
