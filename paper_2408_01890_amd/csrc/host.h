@@ -61,9 +61,8 @@ int run_stack_chained(const lisa_desc* d, const lisa_stack_layer* layers, int n_
                       void* workspace, hipStream_t st);
 // launch_f32.hip
 bool f32_attn_ok(const lisa_desc* d);
-int run_f32_std(const lisa_desc* d, const void* q, const void* k, const void* v, void* scores, void* out,
-                hipStream_t st);
-int run_f32_softmax_v(const lisa_desc* d, const void* scores, const void* v, void* out, hipStream_t st);
+int run_f32_attn(const lisa_desc* d, const void* q, const void* k, const void* v, const float* given, int row0, int n_rows,
+                 void* scores, void* out, hipStream_t st);
 int f32_chunk_rows(const lisa_desc* d);
 size_t f32_chunk_bytes(const lisa_desc* d);
 bool f32_scores_ok(const lisa_desc* d);

@@ -1,7 +1,8 @@
 // Prefill layers (Lq > 1) in float32 arithmetic on the matrix cores: attention, and the scores of a LiSA layer.
 // Same arithmetic as the generic kernels (float32 products and sums); they cover any other shape.
-// Scores: T is the type of the operands (float, or bf16, whose values and products float32 holds exactly), S the
-// score type; bf16 layers come here with the ranks and lengths that k_split_scores does not take.
+// T is the type of the operands (float, or bf16, whose values and products float32 holds exactly), S the
+// score type.  bf16 layers come here, from score rows that are no multiple of 8 scores, with the shapes that the
+// kernels of kernels_split.h do not take or are slower at (f32_attn_takes(), f32_scores_win()).
 #pragma once
 #include <type_traits>
 #include "kernels_prefill.h"
@@ -9,7 +10,23 @@
 namespace lisa {
 
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned f32_u32x2 __attribute__((ext_vector_type(2)));
+typedef f16x4 f16x4_a2 __attribute__((aligned(2)));
 
+// Four consecutive elements as they are loaded (8 or 16 bytes, aligned), and as numbers.
+template <typename T> struct Quad;
+template <> struct Quad<float> {
+  f32x4 raw;
+  static __device__ __forceinline__ Quad load(const float* p) { return {*(const f32x4*)p}; }
+  __device__ __forceinline__ float operator[](int e) const { return raw[e]; }
+};
+template <> struct Quad<bf16_t> {
+  f32_u32x2 raw;
+  static __device__ __forceinline__ Quad load(const bf16_t* p) { return {*(const f32_u32x2*)p}; }
+  __device__ __forceinline__ float operator[](int e) const {
+    return __uint_as_float(e & 1 ? raw[e >> 1] & 0xffff0000u : raw[e >> 1] << 16);
+  }
+};
 // Two bf16 elements, neighbours at an even offset or from anywhere.
 struct Pair {
   unsigned raw;
@@ -17,27 +34,35 @@ struct Pair {
   static __device__ __forceinline__ Pair load2(const bf16_t* p, const bf16_t* q) { return {p->bits | (unsigned)q->bits << 16}; }
   __device__ __forceinline__ float operator[](int e) const { return __uint_as_float(e ? raw & 0xffff0000u : raw << 16); }
 };
+// Four consecutive scores of a row, which starts at any element.
+__device__ __forceinline__ void store_scores4(float* p, f32x4 s) { *(f32x4_a4*)p = s; }
+__device__ __forceinline__ void store_scores4(half_t* p, f32x4 s) {
+  *(f16x4_a2*)p = f16x4{f32_to_half_sat(s[0]), f32_to_half_sat(s[1]), f32_to_half_sat(s[2]), f32_to_half_sat(s[3])};
+}
+
+template <typename T, typename S>
 struct F32AttnArgs {
-  const float* q;         // [B,H,Lq,DK]
-  const float* k;         // [B,Hkv,Lk,DK]
-  const float* v;         // [B,Hkv,Lk,DK] or null (scores only)
-  const float* given;     // GIVEN: scores [B,H,Lq,Lk] to take instead of Q K^T (then q, k unused)
-  float* scores;          // [B,H,Lq,Lk] or null
-  float* out;             // [B,Lq,H,DK] or null
-  int H, Hkv, Lq, Lk, causal;
+  const T* q;             // [B,H,Lq,DK]
+  const T* k;             // [B,Hkv,Lk,DK]
+  const T* v;             // [B,Hkv,Lk,DK] or null (scores only)
+  const float* given;     // GIVEN: scores [B,H,n_rows,Lk] to take instead of Q K^T (then q, k unused)
+  S* scores;              // [B,H,Lq,Lk] or null
+  void* out;              // [B,Lq,H,DK] (float where out_f32, else T) or null
+  int H, Hkv, Lq, Lk, causal, out_f32;
+  int row0, n_rows;       // query rows of this launch (row0 a multiple of 16)
   int parts;              // workgroups that the tiles of a row block are dealt to (1 unless scores only)
   float scale;
 };
 
-// grid (parts ceil(Lq / 16), H, B), block 256: 16 query rows of one head, the 16-key tiles dealt to the four
+// grid (parts ceil(n_rows / 16), H, B), block 256: 16 query rows of one head, the 16-key tiles dealt to the four
 // waves (scores only: of `parts` workgroups), their softmax states merged through the LDS at the end.  16x16x4 float32 MFMAs with the
 // query row on lane % 16 for both products, so that a lane's four scores are its B operands of the
 // second one.  Short sequences are a matter of latency: a wave holds the operands of its next tile while
 // it works on this one, and nothing passes through the LDS before the end.
 // The contraction over the features is numbered so that a lane's operands are pieces of four: step s of
 // piece i takes feature 16 i + 4 g + s.  For P V the 16 rows of output block i are the features 4 m + i.
-template <int NDK, bool GIVEN>
-__global__ __launch_bounds__(256) void k_f32_attn(F32AttnArgs a) {
+template <typename T, typename S, int NDK, bool GIVEN>
+__global__ __launch_bounds__(256) void k_f32_attn(F32AttnArgs<T, S> a) {
   constexpr int DK = 64 * NDK, NP = DK / 16;                 // pieces of four of a row per lane group
   __shared__ float o_s[4][16][DK + 4];
   __shared__ float m_s[4][16], l_s[4][16];
@@ -52,44 +77,45 @@ __global__ __launch_bounds__(256) void k_f32_attn(F32AttnArgs a) {
     t_step = 4 * a.parts;
   }
   const int h = blockIdx.y, b = blockIdx.z;
-  const int Lq = a.Lq, Lk = a.Lk, i0 = rb * 16;
+  const int Lq = a.Lq, Lk = a.Lk, i0 = a.row0 + rb * 16;
   const int kv = h / (a.H / a.Hkv);
   const int i_last = min(i0 + 15, Lq - 1), row = min(i0 + c, Lq - 1);
   const int n_keys = n_visible(i_last, Lq, Lk, a.causal), n_tiles = (n_keys + 15) / 16;
   const int vis = i0 + c < Lq ? n_visible(row, Lq, Lk, a.causal) : 0;
   const float LOG2E = 1.4426950408889634f;
   const bool with_v = a.out != nullptr;
-  f32x4 qr[NP];
+  Quad<T> qr[NP];
   if (!GIVEN) {
-    const float* qp = a.q + (((size_t)b * a.H + h) * Lq + row) * DK + 4 * g;
+    const T* qp = a.q + (((size_t)b * a.H + h) * Lq + row) * DK + 4 * g;
 #pragma unroll
-    for (int i = 0; i < NP; ++i) qr[i] = *(const f32x4*)(qp + 16 * i);
+    for (int i = 0; i < NP; ++i) qr[i] = Quad<T>::load(qp + 16 * i);
   }
-  const float* kb = GIVEN ? nullptr : a.k + ((size_t)b * a.Hkv + kv) * Lk * DK + 4 * g;
-  const float* vb = a.v + ((size_t)b * a.Hkv + kv) * Lk * DK + 4 * c;
+  const T* kb = GIVEN ? nullptr : a.k + ((size_t)b * a.Hkv + kv) * Lk * DK + 4 * g;
+  const T* vb = a.v + ((size_t)b * a.Hkv + kv) * Lk * DK + 4 * c;
   const size_t srow = (((size_t)b * a.H + h) * Lq + row) * Lk;
-  f32x4 kr[NP], vr[4][NDK];
+  const size_t grow = (((size_t)b * a.H + h) * a.n_rows + row - a.row0) * Lk;
+  Quad<T> kr[NP], vr[4][NDK];
   f32x4 sr;
   auto load_k = [&](int tile) {
     if (GIVEN) {
       const int j = tile * 16 + 4 * g;
       if (tile * 16 + 16 <= Lk) {
-        sr = *(const f32x4_a4*)(a.given + srow + j);
+        sr = *(const f32x4_a4*)(a.given + grow + j);
       } else {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) sr[v] = a.given[srow + min(j + v, Lk - 1)];
+        for (int v = 0; v < 4; ++v) sr[v] = a.given[grow + min(j + v, Lk - 1)];
       }
     } else {
-      const float* kp = kb + (size_t)min(tile * 16 + c, Lk - 1) * DK;
+      const T* kp = kb + (size_t)min(tile * 16 + c, Lk - 1) * DK;
 #pragma unroll
-      for (int i = 0; i < NP; ++i) kr[i] = *(const f32x4*)(kp + 16 * i);
+      for (int i = 0; i < NP; ++i) kr[i] = Quad<T>::load(kp + 16 * i);
     }
   };
   auto load_v = [&](int tile) {
 #pragma unroll
     for (int v = 0; v < 4; ++v)
 #pragma unroll
-      for (int n = 0; n < NDK; ++n) vr[v][n] = *(const f32x4*)(vb + (size_t)min(tile * 16 + 4 * g + v, Lk - 1) * DK + 64 * n);
+      for (int n = 0; n < NDK; ++n) vr[v][n] = Quad<T>::load(vb + (size_t)min(tile * 16 + 4 * g + v, Lk - 1) * DK + 64 * n);
   };
   f32x4 o[NP];
 #pragma unroll
@@ -116,11 +142,11 @@ __global__ __launch_bounds__(256) void k_f32_attn(F32AttnArgs a) {
     load_k(tile_n);
     if (!GIVEN && a.scores) {
       if (j + 4 <= vis) {
-        *(f32x4_a4*)(a.scores + srow + j) = s;
+        store_scores4(a.scores + srow + j, s);
       } else {
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-          if (j + v < vis) a.scores[srow + j + v] = s[v];
+          if (j + v < vis) elem<S>::store(a.scores + srow + j + v, s[v]);
       }
     }
     if (with_v) {
@@ -177,7 +203,9 @@ __global__ __launch_bounds__(256) void k_f32_attn(F32AttnArgs a) {
     }
     // (a row that sees nothing gives zeros, as the generic kernel has it; NaN stays NaN)
     const size_t at = (((size_t)b * Lq + i0 + r) * a.H + h) * DK + d;
-    a.out[at] = den > 0.f ? num / den : num * 0.f;
+    const float x = den > 0.f ? num / den : num * 0.f;
+    if (a.out_f32) ((float*)a.out)[at] = x;
+    else elem<T>::store((T*)a.out + at, x);
   }
 }
 

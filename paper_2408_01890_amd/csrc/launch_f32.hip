@@ -7,39 +7,41 @@ namespace lisa {
 bool f32_attn_ok(const lisa_desc* d) { return d->Lq > 1 && d->dtype == LISA_F32 && (d->d_k == 64 || d->d_k == 128); }
 
 namespace {
-template <int NDK>
-int launch_attn(const lisa_desc* d, const F32AttnArgs& a, hipStream_t st) {
-  dim3 grid((a.Lq + 15) / 16 * a.parts, d->H, d->B);
+template <typename T, typename S, int NDK>
+int launch_attn(const lisa_desc* d, const F32AttnArgs<T, S>& a, hipStream_t st) {
+  dim3 grid((a.n_rows + 15) / 16 * a.parts, d->H, d->B);
   StageScope prof(a.given ? "k_f32_softmax_v" : "k_f32_attn", st);
-  if (a.given) k_f32_attn<NDK, true><<<grid, 256, 0, st>>>(a);
-  else k_f32_attn<NDK, false><<<grid, 256, 0, st>>>(a);
+  if (a.given) k_f32_attn<T, S, NDK, true><<<grid, 256, 0, st>>>(a);
+  else k_f32_attn<T, S, NDK, false><<<grid, 256, 0, st>>>(a);
   return check_launch();
 }
 
-// `given`: scores to take instead of q k^T
-int run_attn(const lisa_desc* d, const void* q, const void* k, const void* given, const void* v, void* scores, void* out,
-             hipStream_t st) {
-  F32AttnArgs a{};
-  a.q = (const float*)q; a.k = (const float*)k; a.v = (const float*)v; a.given = (const float*)given;
-  a.scores = (float*)scores; a.out = (float*)out;
+// `given`: scores of the rows row0 .. row0 + n_rows - 1 to take instead of q k^T
+template <typename T, typename S>
+int run_attn(const lisa_desc* d, const void* q, const void* k, const void* given, int row0, int n_rows, const void* v,
+             void* scores, void* out, hipStream_t st) {
+  F32AttnArgs<T, S> a{};
+  a.q = (const T*)q; a.k = (const T*)k; a.v = (const T*)v; a.given = (const float*)given;
+  a.scores = (S*)scores; a.out = out;
   a.H = d->H; a.Hkv = d->Hkv; a.Lq = d->Lq; a.Lk = d->Lk; a.causal = d->causal;
+  a.out_f32 = d->out_f32 || d->dtype == LISA_F32;
+  a.row0 = row0; a.n_rows = n_rows;
   // Scores only: nothing to merge, so few row blocks of many keys are spread until there is a workgroup per
   // compute unit, two tiles per wave at least (2 rows, 3000 keys, 8 heads of 64: 24.7 us in one workgroup per head,
   // 5.9 spread, 11.2 on the generic kernel; two per compute unit cost 13 % at 700 rows, 4 heads).
-  const long long blocks = (long long)((d->Lq + 15) / 16) * d->H * d->B;
+  const long long blocks = (long long)((n_rows + 15) / 16) * d->H * d->B;
   a.parts = out ? 1 : (int)std::max<long long>(1, std::min<long long>((d->Lk + 127) / 128, kComputeUnits / blocks));
   a.scale = pick_scale(d->std_scale, d->d_k);
-  return d->d_k == 64 ? launch_attn<1>(d, a, st) : launch_attn<2>(d, a, st);
+  if constexpr (sizeof(T) == 4)
+    if (d->d_k == 64) return launch_attn<T, S, 1>(d, a, st);
+  return launch_attn<T, S, 2>(d, a, st);
 }
 }  // namespace
 
-int run_f32_std(const lisa_desc* d, const void* q, const void* k, const void* v, void* scores, void* out,
-                hipStream_t st) {
-  return run_attn(d, q, k, nullptr, v, scores, out, st);
-}
-
-int run_f32_softmax_v(const lisa_desc* d, const void* scores, const void* v, void* out, hipStream_t st) {
-  return run_attn(d, nullptr, nullptr, scores, v, nullptr, out, st);
+int run_f32_attn(const lisa_desc* d, const void* q, const void* k, const void* v, const float* given, int row0, int n_rows,
+                 void* scores, void* out, hipStream_t st) {
+  return d->dtype == LISA_F32 ? run_attn<float, float>(d, q, k, given, row0, n_rows, v, scores, out, st)
+                              : run_attn<bf16_t, half_t>(d, q, k, given, row0, n_rows, v, scores, out, st);
 }
 
 // bf16: the float32 scores pass through the workspace a chunk of query rows at a time, 256 MB of them (what the

@@ -134,8 +134,20 @@ int run_split_scores(const lisa_desc* d, const void* prev, const void* w1, const
   }
 }
 
+// A launch of one block of 16 rows that see few keys leaves most of k_split_attn's four waves and half of their 32 rows
+// without work, and its 70 KB of LDS two workgroups per compute unit; the float32 kernel's are half as large.  Both sides,
+// 1000 sequences of 32 heads, split / float32 kernel: scores given, 9 tokens 229 / 154 us, 15 rows of 31 keys 309 / 283, of 33
+// 320 / 286, 9 rows of 65 331 / 325; scores made, 9 tokens 286 / 213, 16 rows of 31 keys 341 / 322, 9 rows of 65 331 / 448,
+// and with 2000 workgroups in place of 32000 23 / 27; scores alone, 9 tokens 85 / 72, 16 rows of 17 keys 97 / 115.
+static bool f32_attn_takes(const lisa_desc* d, bool given, bool given_tiled, int row0, int n_rows, bool with_v) {
+  const int last = row0 + n_rows - 1, keys = d->causal ? std::min(d->Lk, last + 1 + d->Lk - d->Lq) : d->Lk;
+  if (n_rows > 16 || given_tiled) return false;
+  return keys <= (given ? 48 : with_v && (long long)d->B * d->H >= 16384 ? 32 : 16);
+}
+
 int run_split_attn(const lisa_desc* d, const void* q, const void* k, const void* v, const float* given, bool given_tiled,
                    int row0, int n_rows, void* scores, void* out, hipStream_t st) {
+  if (f32_attn_takes(d, given, given_tiled, row0, n_rows, out)) return run_f32_attn(d, q, k, v, given, row0, n_rows, scores, out, st);
   SplitAttnArgs a{};
   a.q = (const bf16_t*)q; a.k = (const bf16_t*)k; a.v = (const bf16_t*)v; a.given = given;
   a.scores = (half_t*)scores; a.out = out;

@@ -349,7 +349,7 @@ int run_lisa(const lisa_desc* d, const void* q_lr, const void* k_lr, KeyStrides 
     else if (in_chunks(d))
       rc = run_split_attn(d, nullptr, nullptr, v, exact, split, row0, n_rows, nullptr, out, st);
     else if (f32_attn_ok(d))
-      rc = run_f32_softmax_v(d, an, v, out, st);
+      rc = run_f32_attn(d, nullptr, nullptr, v, (const float*)an, 0, d->Lq, nullptr, out, st);
     else
       rc = launch_softmax_v<T>(d, (const float*)an, v, vs, out, st);
     if (rc) return rc;
@@ -1638,7 +1638,7 @@ int std_attn_scores(const lisa_desc* desc, const void* q, const void* k, const v
   if (split_attn_ok(desc)) {
     rc = run_split_attn(desc, q, k, v, nullptr, false, 0, desc->Lq, scores_out, out, st);
   } else if (f32_attn_ok(desc)) {
-    rc = run_f32_std(desc, q, k, v, scores_out, out, st);
+    rc = run_f32_attn(desc, q, k, v, nullptr, 0, desc->Lq, scores_out, out, st);
   } else if (desc->dtype == LISA_F32) {
     if (scores_out) exact = nullptr;                         // (the score tensor is the unrounded copy)
     rc = launch_std_scores<float, float>(desc, q, k, ks, scores_out, exact, st);

@@ -135,3 +135,37 @@ def test_batch_past_the_workspace_budget(causal):
         assert err(whole[s], out.cpu().double()) <= TOL_O
         x, y = a[s][..., vis].cpu().double(), b[..., vis].cpu().double()
         assert float((x - y).abs().max()) <= TOL_A * float(y.pow(2).mean().sqrt())
+
+
+def stages(call):
+    """What `call()` returns, and the names of the kernels that it launched."""
+    lisa.profile_enable(True)
+    try:
+        res = call()
+        torch.cuda.synchronize()
+        return res, set(lisa.profile_collect())
+    finally:
+        lisa.profile_enable(False)
+
+
+@pytest.mark.parametrize("B,Lq,Lk,std,given", [  # the side of the line that a standard layer and given scores fall on
+    (2, 2, 2, "f32", "f32"), (2, 9, 9, "f32", "f32"), (2, 15, 15, "f32", "f32"), (2, 16, 17, "split", "f32"), (1, 3, 47, "split", "f32"),
+    (1, 16, 49, "split", "split"), (2, 17, 17, "split", "split"), (4100, 5, 31, "f32", "f32"), (4100, 2, 33, "split", "f32")])
+def test_attention_of_few_keys(B, Lq, Lk, std, given):
+    """One block of 16 rows that sees few keys: float32 matrix instructions or three-part products, both in float32 arithmetic."""
+    H, Hkv = 4, 2
+    log(f"[case] split few keys {B}x{Lq}x{Lk}")
+    g = torch.Generator(device=DEV).manual_seed(Lk)
+    rn = lambda *s: torch.randn(s, generator=g, device=DEV).to(torch.bfloat16)
+    q, k, v = rn(B, H, Lq, 128), rn(B, Hkv, Lk, 128), rn(B, Hkv, Lk, 128)
+    prev = rn(B, H, Lq, Lk).half()
+    (scores, out), ran = stages(lambda: lisa.std_attn_scores(q, k, v))
+    assert ran == {f"k_{std}_attn"}
+    (shared, _), ran = stages(lambda: lisa.lisa_attn_prefill(None, None, v, prev, None, None, mix=lisa.MIX_SHARE))
+    assert f"k_{given}_softmax_v" in ran
+    rep = lambda t: t.cpu().double().repeat_interleave(H // Hkv, 1)
+    A = q.cpu().double() @ rep(k).transpose(-1, -2).contiguous() / 128 ** 0.5
+    vis = torch.ones(Lq, Lk, dtype=torch.bool).tril(Lk - Lq)
+    assert float((scores.cpu().double() - A).abs()[..., vis].max()) <= 2.0 ** -9 * float(A.abs().max())
+    assert err(out.flatten(2), softmax_v(A, rep(v), True).flatten(2)) <= TOL_O
+    assert err(shared.flatten(2), softmax_v(prev.cpu().double(), rep(v), True).flatten(2)) <= TOL_O
