@@ -243,6 +243,11 @@ template <typename T, typename S, int HT, int ACT, bool CONCAT>
 __global__ __launch_bounds__(256) void k_f32_lisa_scores(F32ScoresArgs<T, S> a) {
   constexpr int KH = HT / 4, KS = CONCAT ? 2 * KH : KH;      // k-steps of the heads, of the inputs
   constexpr int HB = (HT + 15) / 16, NB = 4;                 // output blocks, rows per wave
+  // bf16: the products of 16 hidden units are summed from zero and added in one step, A_delta last (each step of a sum is
+  // rounded at the size of what it has reached): error of O 4.9e-7 -> 1.3e-7 (16 heads, 255 tokens, F = 256), 2.0e-7 ->
+  // 1.2e-7 (8 heads, 201 tokens, F = 32); the kernel of three-part products has 1.4e-7 and 1.0e-7.  float32 layers keep one
+  // chain: A_delta last alone cost 21.8 -> 23.1 us for a pair of layers of 128 tokens.
+  constexpr bool BLOCKS = sizeof(T) == 2;
   extern __shared__ __align__(16) float f32_lds[];
   float* d_s = f32_lds;                                      // [HT][16 rows][F32_DROW]
   const int FB = (a.F + 15) / 16;
@@ -351,7 +356,7 @@ __global__ __launch_bounds__(256) void k_f32_lisa_scores(F32ScoresArgs<T, S> a) 
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int h = min(16 * hb + 4 * g + v, H - 1);
-          y[n][hb][v] = CONCAT ? 0.f : d_s[(h * 16 + wv * NB + n) * F32_DROW + c];
+          y[n][hb][v] = CONCAT || BLOCKS ? 0.f : d_s[(h * 16 + wv * NB + n) * F32_DROW + c];
         }
     }
     for (int fb = 0; fb < FB; ++fb) {
@@ -364,6 +369,13 @@ __global__ __launch_bounds__(256) void k_f32_lisa_scores(F32ScoresArgs<T, S> a) 
 #pragma unroll
         for (int n = 0; n < NB; ++n) u[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, x[n][s], u[n], 0, 0, 0);
       }
+      f32x4 block[NB][HB];
+      f32x4 (&sum)[NB][HB] = BLOCKS ? block : y;
+      if (BLOCKS)
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+          for (int hb = 0; hb < HB; ++hb) block[n][hb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
 #pragma unroll
@@ -372,9 +384,22 @@ __global__ __launch_bounds__(256) void k_f32_lisa_scores(F32ScoresArgs<T, S> a) 
         for (int hb = 0; hb < HB; ++hb) {
           const float w = w2_s[((fb * 4 + v) * HB + hb) * 64 + lane];
 #pragma unroll
-          for (int n = 0; n < NB; ++n) y[n][hb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, u[n][v], y[n][hb], 0, 0, 0);
+          for (int n = 0; n < NB; ++n) sum[n][hb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, u[n][v], sum[n][hb], 0, 0, 0);
         }
       }
+      if (BLOCKS)
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+          for (int hb = 0; hb < HB; ++hb) y[n][hb] += block[n][hb];
+    }
+    if constexpr (BLOCKS && !CONCAT) {
+#pragma unroll
+      for (int n = 0; n < NB; ++n)
+#pragma unroll
+        for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) y[n][hb][v] += d_s[(min(16 * hb + 4 * g + v, H - 1) * 16 + wv * NB + n) * F32_DROW + c];
     }
     // (one test of the tensor and of the heads around each run of stores, not one per element)
     auto store = [&](auto* dst, size_t head_stride, int rows, int row0) {

@@ -61,12 +61,42 @@ SplitWs split_ws(const lisa_desc* d, size_t rows) {
 SplitWs split_ws(const lisa_desc* d) { return split_ws(d, (size_t)(split_chunk_rows(d) + 15) / 16 * 16); }
 }  // namespace
 
+// Scores of few or short rows, which the float32 kernel makes sooner: it needs no launch that pads the operands (3 us), its
+// tiles of 16 x 16 are half as large, and several workgroups share a compute unit.  What it does per tile costs more, about
+// in proportion to heads x hidden units.  Both sides in us, split / float32 kernel, ADD unless said:
+//   a tile per compute unit at most: 8 heads, 129 tokens, F = 32, 16.5 / 13.3, CONCAT, F = 48, 20.8 / 14.5; 16 heads 17.5 / 15;
+//   32 heads, CONCAT, F = 16, 23.8 / 20.5, but F = 64 beyond the line 23.6 / 24.5; 8 heads, 401 tokens, F = 128, 27.2 / 30.5;
+//   rows of one 16-key tile: 1000 x 9 tokens, 8 heads, F = 32, 83 / 51 (softmax included, which is the float32 kernel's then);
+//   32 heads, F = 96, 280 / 187, one sequence of 9, F = 64, 18.3 / 20; CONCAT, F = 256, 133 / 168 (300 x 9);
+//   rows up to 64 keys: 8 heads, 100 x 33, F = 32, 35.5 / 29.7, 16 heads, F = 96, 57.4 / 61.4; 8 heads, 300 x 65, F = 32, 117 / 154;
+//   9 rows of 33 keys, CONCAT, F = 32: 12 heads, 1000 sequences, 160 / 133, 32 heads, 300, 118 / 100, 100, 58 / 59;
+//   a second round of a few tiles: 16 heads, 30 x 65, CONCAT, F = 48, 44.5 / 33.6; 100 x 65 59 / 62;
+//   chunks of one block of rows, which the operands leave room for: 32 heads, 1000 x 33, F = 32, 904 / 724; 300 x 33 209 / 215.
+static bool f32_scores_win(const lisa_desc* d) {
+  const bool concat = d->mix == LISA_MIX_CONCAT;
+  const int heads = split_heads(d->H), work = heads * d->F;
+  if (!f32_scores_ok(d)) return false;
+  if (d->Lk <= 16) return heads <= 16 || work <= 1024 || (d->B >= 16 && d->F <= (heads > 32 ? 64 : concat ? 128 : 256));
+  const long long rbs = (d->Lq + 15) / 16;
+  if (d->B * rbs * ((d->Lk + 15) / 16) <= kComputeUnits) return heads <= 16 ? work <= 4096 : heads == 32 && work <= 512;
+  if (d->Lk > 128) return false;
+  if (d->Lk <= 64 && work <= 2560 && split_chunk_rows(d) < std::min(d->Lq, 32)) return true;
+  if (heads > 32) return false;
+  long long t32 = d->causal ? 0 : rbs * ((d->Lk + 31) / 32);  // tiles of 32 keys
+  if (d->causal)
+    for (int i = 0; i < d->Lq; i += 16) t32 += split_scores_tiles(i, d->Lq, d->Lq, d->Lk, 1, 32);
+  t32 *= d->B;
+  if (t32 > kComputeUnits && t32 <= kComputeUnits * 19 / 16) return work <= (heads <= 16 ? 4096 : 1024);
+  if (heads == 8) return (d->Lk <= 64 || (rbs == 1 && (concat || t32 <= 3 * kComputeUnits))) && (d->F <= 64 || (d->F <= 128 && t32 <= 3 * kComputeUnits));
+  return rbs == 1 && d->Lk <= 48 && d->F <= 64 && (heads == 16 || t32 > kComputeUnits);
+}
+
 bool split_scores_ok(const lisa_desc* d) {
   if (!split_attn_ok(d) || !split_sizes_ok(d) || (d->act != LISA_ACT_RELU && d->act != LISA_ACT_SILU)) return false;
   if (d->mix != LISA_MIX_ADD && d->mix != LISA_MIX_CONCAT) return false;
   if (d->H > 40 || d->r > 32) return false;
   if (split_ws(d, 0).total > kSplitBudget / 2 || split_ws(d, 16).total > kSplitBudget) return false;
-  return split_keys(d) > 0;
+  return split_keys(d) > 0 && !f32_scores_win(d);
 }
 
 int split_chunk_rows(const lisa_desc* d) {

@@ -54,10 +54,20 @@ def err(got, ref):                 # largest difference over the RMS of its row
     return float(((got - ref).abs().amax(-1) / ref.pow(2).mean(-1).sqrt()).max())
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "_".join(map(str, c)))
-def test_lisa_layer(case):
-    B, H, Hkv, Lq, Lk, r, F, mix, causal = case
-    log(f"[case] split lisa {case}")
+def stages(call):
+    """What `call()` returns, and the names of the kernels that it launched."""
+    lisa.profile_enable(True)
+    try:
+        res = call()
+        torch.cuda.synchronize()
+        return res, set(lisa.profile_collect())
+    finally:
+        lisa.profile_enable(False)
+
+
+def check_layer(B, H, Hkv, Lq, Lk, r, F, mix, causal):
+    """Scores and output of one layer against float64; the names of the kernels it launched."""
+    log(f"[case] split lisa {B, H, Hkv, Lq, Lk, r, F, mix, causal}")
     g = torch.Generator(device=DEV).manual_seed(Lk)
     rn = lambda *s: torch.randn(s, generator=g, device=DEV)
     q, k, v = rn(B, H, Lq, r).to(torch.bfloat16), rn(B, Hkv, Lk, r).to(torch.bfloat16), rn(B, Hkv, Lk, 128).to(torch.bfloat16)
@@ -65,15 +75,40 @@ def test_lisa_layer(case):
     w1, w2 = (rn(din, F) / din ** 0.5).to(torch.bfloat16), (rn(F, H) / F ** 0.5).to(torch.bfloat16)
     prev = rn(B, H, Lq, Lk).to(torch.float16)
     scores, *guards = guarded((B, H, Lq, Lk))
-    out, _ = lisa.lisa_attn_prefill(q, k, v, prev, w1, w2, mix=lisa.MIX_CONCAT if mix == "concat" else lisa.MIX_ADD,
-                                    causal=causal, scores_out=scores)
-    torch.cuda.synchronize()
+    (out, _), ran = stages(lambda: lisa.lisa_attn_prefill(q, k, v, prev, w1, w2, causal=causal, scores_out=scores,
+                                                          mix=lisa.MIX_CONCAT if mix == "concat" else lisa.MIX_ADD))
     A, O = reference(q, k, v, prev, w1, w2, mix, causal)
     vis = torch.ones(Lq, Lk, dtype=torch.bool).tril(Lk - Lq) if causal else torch.ones(Lq, Lk, dtype=torch.bool)
     assert all(bool(torch.all(t == SENTINEL)) for t in guards) and bool(torch.all(scores.cpu()[..., ~vis] == SENTINEL))
     rms = (A * vis).pow(2).sum((1, 3)).div(vis.sum(-1) * H).sqrt()[:, None, :, None]
     assert float((((scores.cpu().double() - A) / rms).abs() * vis).max()) <= TOL_A
     assert err(out.flatten(2), O.flatten(2)) <= TOL_O
+    return ran
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "_".join(map(str, c)))
+def test_lisa_layer(case):
+    check_layer(*case)
+
+
+@pytest.mark.parametrize("kernel,B,H,Lq,Lk,F,mix", [         # both sides of each line, causal
+    ("f32", 1, 8, 201, 201, 256, "concat"), ("split", 2, 8, 201, 201, 64, "add"),     # 169 and 338 tiles of 16 x 16
+    ("f32", 1, 16, 255, 255, 33, "add"), ("split", 1, 16, 257, 257, 33, "add"),       # 256 and 289
+    ("f32", 1, 16, 255, 255, 256, "add"), ("split", 1, 16, 255, 255, 257, "add"),
+    ("f32", 1, 17, 65, 65, 16, "add"), ("split", 1, 17, 65, 65, 17, "add"),
+    ("f32", 2, 32, 9, 9, 32, "add"), ("split", 2, 32, 9, 9, 33, "add"),               # one key tile, more heads x units
+    ("f32", 16, 40, 9, 15, 64, "add"), ("split", 16, 40, 9, 15, 65, "add"), ("split", 16, 20, 9, 9, 129, "concat"),
+    ("split", 260, 12, 17, 17, 20, "add"), ("f32", 130, 12, 17, 17, 20, "add"),       # 520 and 260 tiles of 32 keys
+    ("f32", 152, 16, 17, 31, 64, "concat"), ("split", 153, 16, 17, 31, 64, "concat"),
+    ("f32", 140, 8, 60, 62, 64, "add"), ("split", 140, 8, 60, 66, 64, "add"),         # 8 heads, rows of up to 64 keys
+    ("f32", 140, 7, 9, 127, 64, "concat"), ("split", 140, 7, 9, 129, 64, "concat"),
+    ("f32", 90, 8, 33, 33, 128, "add"), ("split", 260, 8, 33, 33, 128, "add"),        # 360 and 1040 tiles
+    ("f32", 300, 32, 2, 33, 64, "add"), ("split", 120, 32, 2, 33, 64, "add"),
+])
+def test_scores_of_few_or_short_rows(kernel, B, H, Lq, Lk, F, mix):
+    """float32 matrix instructions where they are sooner, three-part products elsewhere."""
+    ran = check_layer(B, H, H, Lq, Lk, 20, F, mix, True)
+    assert {"f32": "k_f32_lisa_scores", "split": "k_split_scores"}[kernel] in ran
 
 
 @pytest.mark.parametrize("Lq,Lk,causal", [(2, 4097, True), (31, 1155, False), (32, 33, True), (33, 129, True), (64, 65, True), (3, 5, True)])
@@ -135,17 +170,6 @@ def test_batch_past_the_workspace_budget(causal):
         assert err(whole[s], out.cpu().double()) <= TOL_O
         x, y = a[s][..., vis].cpu().double(), b[..., vis].cpu().double()
         assert float((x - y).abs().max()) <= TOL_A * float(y.pow(2).mean().sqrt())
-
-
-def stages(call):
-    """What `call()` returns, and the names of the kernels that it launched."""
-    lisa.profile_enable(True)
-    try:
-        res = call()
-        torch.cuda.synchronize()
-        return res, set(lisa.profile_collect())
-    finally:
-        lisa.profile_enable(False)
 
 
 @pytest.mark.parametrize("B,Lq,Lk,std,given", [  # the side of the line that a standard layer and given scores fall on

@@ -5,7 +5,7 @@ import torch
 
 from paper_2408_01890_amd import lisa
 from tests.test_gpu_parity import log
-from tests.test_gpu_split import TOL_O, err, reference, softmax_v
+from tests.test_gpu_split import TOL_O, err, reference, softmax_v, stages
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -17,7 +17,7 @@ CASES = [  # H, Hkv, Lq, Lk, F, mix, act, what is infinite at the masked keys
     (40, 8, 77, 301, 128, "add", "relu", "+prev"),      # tiles of 16 keys
     (8, 8, 301, 301, 32, "add", "silu", "+prev"),
     (32, 32, 77, 301, 64, "concat", "relu", "-prev"),
-    (16, 4, 77, 301, 64, "concat", "relu", "delta"),    # A_delta = +inf
+    (16, 4, 141, 301, 64, "concat", "relu", "delta"),    # A_delta = +inf
 ]
 
 
@@ -49,9 +49,10 @@ def test_infinite_scores_at_masked_keys(case):
         k[:, :, :pad] = 3e38
         q[..., 0] = 2.0                                      # (2 * 3e38: past the float32 range)
     q, k, w1, w2, prev = q.to(torch.bfloat16), k.to(torch.bfloat16), w1.to(torch.bfloat16), w2.to(torch.bfloat16), prev.half()
-    out, scores = lisa.lisa_attn_prefill(q, k, v, prev, w1, w2, mix=lisa.MIX_CONCAT if mix == "concat" else lisa.MIX_ADD,
-                                         act=lisa.ACT_SILU if act == "silu" else lisa.ACT_RELU)
-    torch.cuda.synchronize()
+    (out, scores), ran = stages(lambda: lisa.lisa_attn_prefill(
+        q, k, v, prev, w1, w2, mix=lisa.MIX_CONCAT if mix == "concat" else lisa.MIX_ADD,
+        act=lisa.ACT_SILU if act == "silu" else lisa.ACT_RELU))
+    assert "k_split_scores" in ran
     seen = torch.ones(Lq, Lk, dtype=torch.bool).tril(Lk - Lq)
     rows = slice(max(0, pad + Lq - Lk), None)                # (rows that see more than masked keys)
     kd = k.clone()
