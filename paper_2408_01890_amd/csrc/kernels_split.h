@@ -111,6 +111,7 @@ template <bool WITH_V, bool GIVEN>
 __global__ __launch_bounds__(256, 2) void k_split_attn(SplitAttnArgs a) {
   constexpr int DK = 128, CH = 8;                              // 16-byte chunks of a tile per lane
   __shared__ __align__(16) unsigned char lds[split_attn_lds(WITH_V, GIVEN)];
+  __shared__ int again;                                        // NaN has come out: see `whole`
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   unsigned char* ks_ = lds + wv * split_attn_wave_lds(WITH_V, GIVEN);   // K tile; the score staging lies over it
@@ -194,7 +195,7 @@ __global__ __launch_bounds__(256, 2) void k_split_attn(SplitAttnArgs a) {
   f32x16 o[DK / 32];
   float m_run, l_run;
   // A part of a probability may be 0 (1.0 has one part only), and 0 times an infinite element of V is NaN where the probability
-  // itself gives infinity.  A wave that ends with NaN goes over its tiles again with `whole` probabilities: one float32
+  // itself gives infinity.  Where NaN comes out the workgroup goes over its tiles again with `whole` probabilities: one float32
   // product for each visible key.  (A pass of its own: as a branch inside the loop it cost 40 spilled registers.)
   auto pass = [&](auto whole) __attribute__((always_inline)) {
     load_kt(clamp_tile(t_begin));
@@ -346,12 +347,6 @@ __global__ __launch_bounds__(256, 2) void k_split_attn(SplitAttnArgs a) {
   };
   pass(std::false_type{});
   if (!WITH_V) return;
-  f32x4 any = {0.f, 0.f, 0.f, 0.f};                          // (NaN where an element is)
-#pragma unroll
-  for (int v = 0; v < 16; ++v)
-#pragma unroll
-    for (int db = 0; db < DK / 32; ++db) any[db] += o[db][v];
-  if (const float x = (any[0] + any[1]) + (any[2] + any[3]); __any(x != x)) pass(std::true_type{});
 
   auto store4 = [&](size_t at, const float (&x)[4]) {
     if (a.out_f32) {
@@ -365,38 +360,50 @@ __global__ __launch_bounds__(256, 2) void k_split_attn(SplitAttnArgs a) {
   };
   // O[row][h][32 db + 8 (v / 4) + 4 half + v % 4] = o[db][v] / l (a row that sees nothing gives zeros, as the generic kernel
   // has it; NaN stays NaN)
-  const float l = halves_sum(l_run);
   float* o_s = (float*)lds;                                  // [wave][row][SA_OROW]
   float* ml_s = o_s + 4 * SP_ROWS * SA_OROW;                 // [wave][row][m, l]
-  __syncthreads();                                           // every wave is done with its tiles
-  if (half == 0) *(float2*)(ml_s + (wv * SP_ROWS + r) * 2) = make_float2(m_run, l);
+  auto merge = [&]() __attribute__((always_inline)) {        // true: the thread has stored NaN
+    float nan = 0.f;
+    const float l = halves_sum(l_run);
+    __syncthreads();                                         // every wave is done with its tiles
+    if (half == 0) *(float2*)(ml_s + (wv * SP_ROWS + r) * 2) = make_float2(m_run, l);
 #pragma unroll
-  for (int db = 0; db < DK / 32; ++db)
+    for (int db = 0; db < DK / 32; ++db)
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4)
-      *(float4*)(o_s + (wv * SP_ROWS + r) * SA_OROW + 32 * db + 8 * q4 + 4 * half) =
-          make_float4(o[db][4 * q4], o[db][4 * q4 + 1], o[db][4 * q4 + 2], o[db][4 * q4 + 3]);
-  __syncthreads();
+      for (int q4 = 0; q4 < 4; ++q4)
+        *(float4*)(o_s + (wv * SP_ROWS + r) * SA_OROW + 32 * db + 8 * q4 + 4 * half) =
+            make_float4(o[db][4 * q4], o[db][4 * q4 + 1], o[db][4 * q4 + 2], o[db][4 * q4 + 3]);
+    __syncthreads();
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int e = tid + 256 * u, row = e >> 5, d = 4 * (e & 31);
-    if (i0 + row >= row_end) break;
-    float M = -INFINITY, den = 0.f, x[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int u = 0; u < 4; ++u) {
+      const int e = tid + 256 * u, row = e >> 5, d = 4 * (e & 31);
+      if (i0 + row >= row_end) break;
+      float M = -INFINITY, den = 0.f, x[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int w = 0; w < 4; ++w) M = fmaxf(M, ml_s[(w * SP_ROWS + row) * 2]);
-    if (M == -INFINITY) M = 0.f;
+      for (int w = 0; w < 4; ++w) M = fmaxf(M, ml_s[(w * SP_ROWS + row) * 2]);
+      if (M == -INFINITY) M = 0.f;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const float2 ml = *(const float2*)(ml_s + (w * SP_ROWS + row) * 2);
-      const float f = fast_exp2((ml.x - M) * LOG2E);         // (a wave without tiles: 0)
-      const float4 ow = *(const float4*)(o_s + (w * SP_ROWS + row) * SA_OROW + d);
-      den += f * ml.y;
-      x[0] += f * ow.x, x[1] += f * ow.y, x[2] += f * ow.z, x[3] += f * ow.w;
+      for (int w = 0; w < 4; ++w) {
+        const float2 ml = *(const float2*)(ml_s + (w * SP_ROWS + row) * 2);
+        const float f = fast_exp2((ml.x - M) * LOG2E);       // (a wave without tiles: 0)
+        const float4 ow = *(const float4*)(o_s + (w * SP_ROWS + row) * SA_OROW + d);
+        den += f * ml.y;
+        x[0] += f * ow.x, x[1] += f * ow.y, x[2] += f * ow.z, x[3] += f * ow.w;
+      }
+      const float inv = den > 0.f ? 1.f / den : 0.f;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) x[v] *= inv;
+      nan += (x[0] + x[1]) + (x[2] + x[3]);
+      store4((((size_t)b * Lq + i0 + row) * H + h) * DK + d, x);
     }
-    const float inv = den > 0.f ? 1.f / den : 0.f;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) x[v] *= inv;
-    store4((((size_t)b * Lq + i0 + row) * H + h) * DK + d, x);
+    return nan != nan;
+  };
+  if (tid == 0) again = 0;                                   // (written again behind the barriers of the merge)
+  if (merge()) again = 1;
+  __syncthreads();
+  if (again) {
+    pass(std::true_type{});
+    merge();
   }
 }
 
