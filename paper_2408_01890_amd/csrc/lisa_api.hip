@@ -646,12 +646,26 @@ bool std_prefill_fast_ok(const lisa_desc* d) {
 
 // Two waves per row block, a key half each (k_std_prefill<.., NH = 2>): the longest row group's chain of tiles bounds a
 // launch of few workgroups.  Scores + O, one against two waves: 32 heads, 1024 tokens (256 workgroups) 39.6 / 33.6 us,
-// 1400 tokens (352) 71.7 / 61.8, 2048 (512) 88.7 / 78.4, 8 heads, 16 rows of 4096 keys 128 / 90; beyond the lines
-// 4 x 512 tokens (512 workgroups of 16 tiles at most) 34.0 / 37.4, 2 x 2048 (1024) 126.7 / 142.7 (one barrier domain per
-// compute unit, the merge); 8 heads, 200 tokens, O alone 10.3 / 10.8.
-bool std_key_halves(const lisa_desc* d) {
-  const long long wgs = (long long)((d->Lq + SP_GROUP - 1) / SP_GROUP) * d->H * d->B;
-  return d->Lk > 256 && (wgs <= kComputeUnits || (wgs <= 2 * kComputeUnits && d->Lk >= 1280));
+// 1280 tokens (320) 51.0 / 39.3, 1400 (352) 71.7 / 61.8, 2048 (512) 88.7 / 78.4, 8 heads, 16 rows of 4096 keys 128 / 90.
+// 257 to 512 workgroups all run at once with one wave, and with two (one workgroup per compute unit, the merge) they pay only
+// where the chain counts: long rows, 4 x 512 tokens of 32 heads 34.3 / 37.5, 4 x 384 27.1 / 28.3, though 2 x 1024 56 / 45
+// and 2 x 640 31 / 25.5; and no more work per compute unit than the longest group is, or little more (row groups of a
+// prompt; those of a chunk behind many keys are equally long): 2048 rows of 4096 keys (1.5 times) 180 / 209, 8 x 256 of 1280
+// (1.9) 79.8 / 85.4, 8 heads, 4 x 2048 of 2560 (1.25) 123 / 121.  Scores alone gain there as well, 8 heads, 8 x 1024 rows of
+// 2048 keys 82 / 73, 64 heads, 1024 rows of 4096 keys 149 / 135 (2048 of 4096, row-major, 134 / 150).  Beyond 512 2 x 2048 tokens (1024 workgroups) 126.7 / 142.7.
+bool std_key_halves(const lisa_desc* d, bool with_v) {
+  const long long heads = (long long)d->H * d->B, groups = (d->Lq + SP_GROUP - 1) / SP_GROUP;
+  if (d->Lk <= 256 || groups * heads > 2 * kComputeUnits) return false;
+  if (groups * heads <= kComputeUnits) return true;
+  if (d->Lk < 1280) return false;
+  if (!with_v) return true;
+  auto tiles = [&](long long g) {
+    const int last = (int)std::min<long long>(SP_GROUP * (g + 1), d->Lq) - 1;
+    return (long long)((d->causal ? std::min(d->Lk, last + 1 + d->Lk - d->Lq) : d->Lk) + SP_TK - 1) / SP_TK;
+  };
+  long long all = 0;
+  for (long long g = 0; g < groups; ++g) all += tiles(g) * heads;
+  return 8 * all <= 11 * kComputeUnits * tiles(groups - 1);
 }
 
 // softmax(A) V for scores A that are already in memory, float32 or IEEE half (k_std_prefill in
@@ -673,7 +687,7 @@ int run_softmax_given_fast(const lisa_desc* d, const void* given, bool given_hal
   a.pair = 0;
   dim3 grid(d->H, n_groups, d->B);
   StageScope prof("k_softmax_v_mfma", st);
-  const bool halves = std_key_halves(d);
+  const bool halves = std_key_halves(d, true);
   auto kern = !given_half       ? (halves ? k_std_prefill<true, 1, false, 2> : k_std_prefill<true, 1>)
               : d->score_tiled ? (halves ? k_std_prefill<true, 2, true, 2> : k_std_prefill<true, 2, true>)
                                : (halves ? k_std_prefill<true, 2, false, 2> : k_std_prefill<true, 2>);
@@ -705,7 +719,7 @@ int run_std_prefill_fast(const lisa_desc* d, const void* q, const void* k, const
   if (g_tune[LISA_TUNE_STD_PAIR] >= 0) a.pair = g_tune[LISA_TUNE_STD_PAIR] != 0;   // tests force either
   dim3 grid(d->H, a.pair ? (n_groups + 1) / 2 : n_groups, d->B);
   StageScope prof("k_std_prefill", st);
-  const bool halves = std_key_halves(d) && !a.pair;
+  const bool halves = std_key_halves(d, out != nullptr) && !a.pair;
   auto kern = out && d->score_tiled ? (halves ? k_std_prefill<true, 0, true, 2> : k_std_prefill<true, 0, true>)
               : out                 ? (halves ? k_std_prefill<true, 0, false, 2> : k_std_prefill<true>)
               : d->score_tiled      ? (halves ? k_std_prefill<false, 0, true, 2> : k_std_prefill<false, 0, true>)
