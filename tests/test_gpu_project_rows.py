@@ -5,6 +5,7 @@ import pytest
 
 from paper_2408_01890_amd import synth
 from tests.test_gpu_parity import DEV, check_projection, log
+from tests.test_gpu_split import stages
 
 
 pytestmark = pytest.mark.gpu
@@ -19,4 +20,5 @@ def test_projection_of_few_rows(case):
     log(f"[case] projection rows {case}")
     cfg = synth.LayerShape("proj_rows", "bf16", B, H, Hkv, L, D, dk, r, 64, theta)
     pin = synth.make_projection_inputs(cfg, device=DEV)
-    assert check_projection(cfg, pin, {b: np.arange(L) for b in range(B)}, theta, pos0, dim_major, pos0 + L + extra) == "project_skinny"
+    path, ran = stages(lambda: check_projection(cfg, pin, {b: np.arange(L) for b in range(B)}, theta, pos0, dim_major, pos0 + L + extra))
+    assert path == "project_skinny" and "k_project_rows" in ran

@@ -115,7 +115,7 @@ def test_lisa_layer_ragged_rows(case, emit):
 
 
 def test_lisa_layer_ragged_rows_in_chunks():
-    """More float32 scores than the workspace holds at a time (256 MB): the rows on both sides of the border."""
+    """More float32 scores and padded operands than the workspace holds at a time (256 MB): the rows on both sides of the border."""
     B, H, L = 2, 32, 1031
     log(f"[case] ragged lisa in chunks {L}")
     cfg = synth.LayerShape("ragged_chunks", "bf16", B, H, 8, L, 256, 128, 22, 64)
@@ -123,12 +123,18 @@ def test_lisa_layer_ragged_rows_in_chunks():
     g = torch.Generator(device=DEV).manual_seed(9)
     prev = torch.randn((B, H, L, L), generator=g, device=DEV).to(torch.float16)
     scores, *guards = guarded((B, H, L, L))
-    out, _ = lisa.lisa_attn_prefill(inp["q_lr"], inp["k_lr"], inp["v"], prev, inp["w1"], inp["w2"], scores_out=scores)
-    torch.cuda.synchronize()
+    lisa.profile_enable(True)
+    try:
+        out, _ = lisa.lisa_attn_prefill(inp["q_lr"], inp["k_lr"], inp["v"], prev, inp["w1"], inp["w2"], scores_out=scores)
+        torch.cuda.synchronize()
+        assert lisa.profile_collect()["k_split_scores"][0] == 2        # (launches)
+    finally:
+        lisa.profile_enable(False)
     assert untouched(scores, guards, L, L)
-    edge = (256 << 20) // (B * H * L * 4) // 16 * 16
-    assert 0 < edge < L - 1
-    check_rows(inp, prev, out, scores, np.array([0, 17, edge - 1, edge, edge + 1, L - 1]))
+    operands = B * H * 1040 * 64 + B * 8 * 1088 * 64                   # rows of 64 bytes, L rounded up to 16 and to 64
+    edge = ((256 << 20) - operands) // (B * H * 1056 * 4) // 16 * 16   # float32 scores in tiles of 32 keys
+    assert edge == 960
+    check_rows(inp, prev, out, scores, np.array([0, 17, edge - 17, edge - 16, edge - 1, edge, edge + 1, edge + 15, edge + 16, L - 1]))
 
 
 @pytest.mark.parametrize("mix", [lisa.MIX_PLUS, lisa.MIX_SHARE])

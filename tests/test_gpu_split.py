@@ -13,19 +13,29 @@ DEV = "cuda"
 TOL_O = 1e-5
 TOL_A = 2.0 ** -8                  # one rounding to half, of scores below 8 RMS (see test_gpu_ragged_rows)
 
-CASES = [  # B, H, Hkv, Lq, Lk, r, F, mix, causal
-    (1, 8, 8, 2, 9, 1, 32, "add", True),        # operand rows shorter than what a lane reads, at the tensor's end
-    (2, 8, 1, 31, 31, 7, 33, "add", True),
-    (1, 16, 16, 32, 33, 8, 31, "add", True),
+CASES = [  # B, H, Hkv, Lq, Lk, r, F, mix, causal: three-part products
+    (1, 32, 32, 2, 9, 1, 64, "add", True),      # operand rows shorter than what a lane reads, at the tensor's end
+    (2, 24, 3, 31, 31, 7, 33, "add", True),
+    (1, 32, 16, 32, 33, 8, 31, "add", True),
     (1, 32, 4, 33, 63, 9, 64, "add", True),
+    (30, 8, 1, 31, 67, 7, 33, "add", True),
+    (3, 16, 16, 161, 171, 8, 31, "add", True),
     (1, 33, 11, 17, 65, 31, 96, "add", True),   # heads that fill no block of 8 waves
     (1, 40, 8, 65, 97, 32, 97, "add", True),
     (1, 40, 40, 16, 1003, 22, 128, "add", True),   # weights for which the tiles have 16 keys
-    (1, 8, 8, 40, 1111, 32, 64, "add", False),  # every key visible to every row
+    (2, 8, 8, 40, 1111, 32, 64, "add", False),  # every key visible to every row
     (1, 32, 32, 18, 41, 20, 256, "concat", True),
     (1, 37, 37, 5, 23, 11, 40, "concat", True),    # an odd number of heads, two per load
+    (2, 24, 3, 47, 49, 20, 256, "concat", False),
+    (2, 8, 2, 201, 211, 20, 40, "concat", False),
+    (2, 16, 2, 201, 211, 20, 256, "concat", True),
+]
+CASES_F32 = [  # the float32 kernel
+    (1, 8, 8, 2, 9, 1, 32, "add", True),
+    (2, 8, 1, 31, 31, 7, 33, "add", True),
+    (1, 16, 16, 32, 33, 8, 31, "add", True),
     (2, 16, 2, 47, 49, 20, 256, "concat", False),
-    (1, 8, 8, 20, 37, 33, 64, "add", True),     # more ranks than one product takes
+    (1, 32, 32, 20, 37, 33, 64, "add", True),   # more ranks than one product takes
     (1, 8, 4, 3, 5, 4, 32, "add", True),        # fewer keys than a lane reads
 ]
 
@@ -55,12 +65,12 @@ def err(got, ref):                 # largest difference over the RMS of its row
 
 
 def stages(call):
-    """What `call()` returns, and the names of the kernels that it launched."""
+    """What `call()` returns, and the kernels that it launched: {name: (launches, ms)}."""
     lisa.profile_enable(True)
     try:
         res = call()
         torch.cuda.synchronize()
-        return res, set(lisa.profile_collect())
+        return res, lisa.profile_collect()
     finally:
         lisa.profile_enable(False)
 
@@ -86,9 +96,9 @@ def check_layer(B, H, Hkv, Lq, Lk, r, F, mix, causal):
     return ran
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "_".join(map(str, c)))
+@pytest.mark.parametrize("case", CASES + CASES_F32, ids=lambda c: "_".join(map(str, c)))
 def test_lisa_layer(case):
-    check_layer(*case)
+    assert ("k_f32_lisa_scores" if case in CASES_F32 else "k_split_scores") in check_layer(*case)
 
 
 @pytest.mark.parametrize("kernel,B,H,Lq,Lk,F,mix", [         # both sides of each line, causal
@@ -131,20 +141,27 @@ def test_std_layer(Lq, Lk, causal):
     assert err(out.flatten(2), softmax_v(A, rep(v), causal).flatten(2)) <= TOL_O
 
 
+def chunk_rows(B, H, Hkv, L):
+    """Query rows per chunk: 256 MB less the padded operands, of float32 scores in tiles of 32 keys, in blocks of 16 rows."""
+    up = lambda n, m: (n + m - 1) // m * m
+    operands = up(B * H * up(L, 16) * 64, 256) + up(B * Hkv * up(L, 64) * 64, 256)
+    return ((256 << 20) - operands) // (B * H * up(L, 32) * 4) // 16 * 16
+
+
 def test_chunk_border():
-    """The rows on both sides of a chunk of float32 scores (256 MB of them, in tiles of 32 keys)."""
+    """The last two blocks of rows of a chunk of float32 scores and the first two of the next."""
     B, H, L = 2, 40, 1001
     log("[case] split chunk border")
-    edge = (256 << 20) // (B * H * ((L + 31) // 32 * 32) * 4) // 16 * 16
-    assert 16 < edge < L - 16
+    edge = chunk_rows(B, H, H, L)
+    assert edge == 784
     g = torch.Generator(device=DEV).manual_seed(1)
     rn = lambda *s: torch.randn(s, generator=g, device=DEV)
     q, k, v = rn(B, H, L, 22).to(torch.bfloat16), rn(B, H, L, 22).to(torch.bfloat16), rn(B, H, L, 128).to(torch.bfloat16)
     w1, w2 = (rn(H, 80) / 6).to(torch.bfloat16), (rn(80, H) / 9).to(torch.bfloat16)
     prev = rn(B, H, L, L).to(torch.float16)
-    out, scores = lisa.lisa_attn_prefill(q, k, v, prev, w1, w2)
-    torch.cuda.synchronize()
-    for i in (0, edge - 17, edge - 1, edge, edge + 15, L - 1):       # row i alone: one row of i + 1 keys
+    (out, scores), ran = stages(lambda: lisa.lisa_attn_prefill(q, k, v, prev, w1, w2))
+    assert ran["k_split_scores"][0] == 2                             # (launches)
+    for i in (0, edge - 17, edge - 16, edge - 1, edge, edge + 15, edge + 16, L - 1):   # row i alone: one row of i + 1 keys
         A, O = reference(q[:, :, i:i + 1], k[:, :, :i + 1], v[:, :, :i + 1], prev[:, :, i:i + 1, :i + 1], w1, w2, "add", True)
         assert err(out[:, i:i + 1].flatten(2), O.flatten(2)) <= TOL_O
         assert err(scores[:, :, i, :i + 1].flatten(1), A[:, :, 0].flatten(1)) <= TOL_A
@@ -162,10 +179,11 @@ def test_batch_past_the_workspace_budget(causal):
     w1, w2 = (rn(H, F) / H ** 0.5).to(torch.bfloat16), (rn(F, H) / F ** 0.5).to(torch.bfloat16)
     prev = rn(B, H, Lq, Lk).to(torch.float16)
     run = lambda s: lisa.lisa_attn_prefill(q[s], k[s], v[s], prev[s], w1, w2, causal=causal)
-    whole, a = run(slice(None))
+    (whole, a), ran = stages(lambda: run(slice(None)))
+    assert "k_f32_lisa_scores" in ran
     for s in (slice(0, B // 2), slice(B // 2, B)):
-        out, b = run(s)
-        torch.cuda.synchronize()
+        (out, b), ran = stages(lambda: run(s))
+        assert "k_split_scores" in ran
         vis = slice(None, Lk - 1) if causal else slice(None)          # (the last key: row 1 alone)
         assert err(whole[s], out.cpu().double()) <= TOL_O
         x, y = a[s][..., vis].cpu().double(), b[..., vis].cpu().double()
@@ -184,7 +202,7 @@ def test_attention_of_few_keys(B, Lq, Lk, std, given):
     q, k, v = rn(B, H, Lq, 128), rn(B, Hkv, Lk, 128), rn(B, Hkv, Lk, 128)
     prev = rn(B, H, Lq, Lk).half()
     (scores, out), ran = stages(lambda: lisa.std_attn_scores(q, k, v))
-    assert ran == {f"k_{std}_attn"}
+    assert set(ran) == {f"k_{std}_attn"}
     (shared, _), ran = stages(lambda: lisa.lisa_attn_prefill(None, None, v, prev, None, None, mix=lisa.MIX_SHARE))
     assert f"k_{given}_softmax_v" in ran
     rep = lambda t: t.cpu().double().repeat_interleave(H // Hkv, 1)
