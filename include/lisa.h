@@ -149,9 +149,10 @@ size_t lisa_scores_elems(const lisa_desc* desc);
  *                              matrix-core kernels of the CONCAT form pass it between their two
  *                              launches in the score type (the rounding its inputs carry).
  * Row-major score rows that are no multiple of 8 keep bf16 layers off the 16-bit matrix-core kernels:
- * they run in float32 arithmetic (d_k = 128: on the float32 matrix instructions, with at most 256 MB
- * of A_n in the workspace, or 16 query rows of it where those are more).  Tiled score tensors run at any
- * length on the kernels of the aligned ones.
+ * they run in float32 arithmetic (d_k = 128: three-part products on the bf16 matrix instructions, or the float32
+ * ones, with at most 256 MB of A_n and padded operands in the workspace, or of 16 query rows of A_n where those are
+ * more).  Infinite scores and elements of V give there what float32 arithmetic gives; w1 and w2 are finite.  Tiled
+ * score tensors run at any length on the kernels of the aligned ones.
  */
 int lisa_attn_prefill(const lisa_desc* desc, const void* q_lr, const void* k_lr, const void* v,
                       const void* scores_prev, const void* w1, const void* w2, void* out,

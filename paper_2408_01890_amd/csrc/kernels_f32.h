@@ -235,9 +235,10 @@ constexpr int f32_scores_lds(int HT, int F, bool concat) {
 // a row as the columns (mfma_ffn.h's scheme in float32: a lane's hidden units are its operands of the second
 // product).
 // Bound: at most a third of the time is the float32 MFMAs, the rest loads and stores of 32- and 64-byte pieces in
-// H pages per tensor.  LLaMA2-7B heads, 2 x 509 rows behind 1022 keys, bf16: 316 us (589 with a wait per load of
-// A_delta and the tests of the stores inside their loops; the generic kernel and its softmax 3270).  (One position per lane with the weights through the scalar
-// cache took 17 us where this takes 4, 8 heads, 128 tokens: one wave per SIMD waits for every weight.)
+// H pages per tensor.  32 heads, 2 x 509 rows behind 1022 keys, bf16: 316 us (589 with a wait per load of A_delta and the tests
+// of the stores inside their loops), where k_split_scores takes 130 now; few or short rows stay here (f32_scores_win()).
+// (One position per lane with the weights through the scalar cache took 17 us where this takes 4, 8 heads, 128 tokens: one
+// wave per SIMD waits for every weight.)
 // HT: H rounded up to 8, 16, 32 or 40.
 template <typename T, typename S, int HT, int ACT, bool CONCAT>
 __global__ __launch_bounds__(256) void k_f32_lisa_scores(F32ScoresArgs<T, S> a) {

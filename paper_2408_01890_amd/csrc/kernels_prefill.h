@@ -697,7 +697,8 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
           an[e] = s0[e] * a.dscale + y0[e];
           an[4 + e] = s1[e] * a.dscale + y1[e];
         }
-        // A_n for the next layer: into this wave's staging tile, stored at the end of the stage
+        // A_n for the next layer: held for store_held() (TE), stored from the registers (tiled), or into this wave's staging
+        // tile and from there in whole lines
         if (emit) {
           f16x8 hv;
 #pragma unroll

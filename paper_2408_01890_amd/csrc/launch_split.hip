@@ -39,7 +39,11 @@ int split_keys(const lisa_desc* d) {
 
 // The float32 scores pass through the workspace in tiles, a chunk of query rows at a time: 256 MB (what the last-level cache
 // holds) with the padded operands behind them, at least one block of 16 rows.  Operands that would take more than half of that
-// (B H L around 1 M) leave the chunks too few rows: those calls keep the kernels that read the operands as they are.
+// (B H L around 1 M) leave the chunks too few rows: those calls keep the float32 kernel, which reads the operands as they are.
+// Both sides, split / float32 kernel in ms: 32 heads, 28 x 1025 tokens (112 MB of operands) 3.57 / 5.17, 33 x 1025 (132 MB, chunks
+// of 16 rows) 5.66 / 6.48, 40 x 1025 6.56 / 7.90; 8 KV heads, 48 x 1025 (120 MB) 6.36 / 8.64, 64 x 1025 (160 MB) 7.85 / 13.7; short
+// rows lose beyond the line, 32 heads, 700 x 33 (153 MB) 0.67 / 0.56, 8 heads, 3000 x 33 (164 MB) 0.75 / 0.58, 16 heads,
+// 650 x 129 (213 MB) 1.50 / 1.38.  (Long ones would still gain 13 - 43 % there.)
 namespace {
 constexpr size_t kSplitBudget = (size_t)256 << 20;
 size_t split_row_bytes(const lisa_desc* d) {

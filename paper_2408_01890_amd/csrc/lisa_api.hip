@@ -887,7 +887,9 @@ static int project_qkv(const lisa_proj_desc* d, const void* x, const void* w, vo
     const int per_xcd = a.own_n ? (a.n_n + 7) / 8 * a.n_m : (a.n_m + 7) / 8 * a.n_n;
     StageScope scope("k_project_mfma", st);
     if (small) {
-      // a single round: three steps in the LDS and equal shares per XCD (777 tokens, 252 tiles, 37 -> 28 us); more workgroups
+      // a single round: three steps in the LDS and equal shares per XCD (777 tokens, 252 tiles, 37 -> 28 us, also with few
+      // tiles, 129 tokens, 72 tiles, weights from HBM 36.2 -> 25.9, d = 2048 21.4 -> 16.3, 1024 14.0 -> 11.7; repeated on weights
+      // that the L2s still hold, which a pass through a model does not have, 23.6 -> 25.6, 15.4 -> 16.3, 11.0 -> 11.5); more workgroups
       // than compute units: two steps, and two of them per unit (LLaMA2-7B, 1024 tokens, 67 us against 73)
       const bool one = small_tiles <= kComputeUnits;
       auto kern = one ? k_project_mfma<4, 2, 1, 1, 3> : k_project_mfma<4, 2, 1, 1>;
