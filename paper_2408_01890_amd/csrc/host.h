@@ -74,11 +74,12 @@ bool split_attn_ok(const lisa_desc* d);
 bool split_scores_ok(const lisa_desc* d);
 int split_chunk_rows(const lisa_desc* d);
 size_t split_bytes(const lisa_desc* d);
-int run_split_prepare(const lisa_desc* d, const void* q_lr, const void* k_lr, void* workspace, hipStream_t st);
-int run_split_scores(const lisa_desc* d, const void* prev, const void* w1, const void* w2, void* scores, void* workspace,
-                     int row0, int n_rows, hipStream_t st);
+int run_split_prepare(const lisa_desc* d, const void* q_lr, const void* k_lr, const void* w1, const void* w2, void* workspace,
+                      hipStream_t st);
+int run_split_scores(const lisa_desc* d, const void* prev, void* scores, void* workspace, int row0, int n_rows, hipStream_t st);
 int run_split_attn(const lisa_desc* d, const void* q, const void* k, const void* v, const float* given, bool given_tiled,
                    int row0, int n_rows, void* scores, void* out, hipStream_t st);
+FfnImage scores_mfma_image(const lisa_desc* d, const void* w1, const void* w2);
 int launch_scores_mfma_kernel(const lisa_desc* d, const ScoresMfmaArgs& a, hipStream_t st);
 
 }  // namespace lisa

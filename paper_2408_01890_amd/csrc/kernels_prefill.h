@@ -68,8 +68,7 @@ struct PrefillArgs {
   const bf16_t* kp;       // [B,Hkv,Lkp/32,2,64,8] K_LR padded, tiles in operand order (Lkp = Lk rounded up to 64)
   const bf16_t* vt;       // [B,Hkv,Lkp/8,128,8] V by key chunks
   const half_t* prev;     // [B,H,Lq,Lk]
-  const bf16_t* w1;
-  const bf16_t* w2;
+  const unsigned short* w;  // FFN weights as k_prepare_prefill leaves them (FfnImage)
   half_t* scores;         // [B,H,Lq,Lk] or null
   void* out;              // [B,Lq,H,128] float32 or bf16
   int H, Hkv, Lq, Lk, Lqp, Lkp, F, causal, out_f32;
@@ -123,13 +122,14 @@ __device__ __forceinline__ void regroup_v_tile(const bf16_t* __restrict__ v, bf1
 //                      a padded row per thread (64 rows per block, Q rows first), K_LR by tiles of 32 keys in
 //                      operand order: operand u, lane 16 g + c holds elements 8 g .. of key 8 (c / 4) + c % 4 + 4 u.  (A wave
 //                      that loads an operand then names 8 lines on end, not 64 pieces of 16 rows.)
+//   behind them:       the weights of the alignment FFN (FfnImage), a piece per thread
 template <bool VEC>
 __global__ __launch_bounds__(256) void k_prepare_prefill(const bf16_t* __restrict__ q_lr,
                                                          const bf16_t* __restrict__ k_lr,
                                                          const bf16_t* __restrict__ v, bf16_t* __restrict__ qp,
                                                          bf16_t* __restrict__ kp, bf16_t* __restrict__ vt, int B,
                                                          int H, int Hkv, int Lq, int Lk, int Lqp, int Lkp,
-                                                         int r, int dk) {
+                                                         int r, int dk, FfnImage w) {
   __shared__ __align__(16) unsigned short tile[64][72];
   const int nx = Lkp / 64, ny = dk / 64;
   const int n_v = nx * ny * B * Hkv;
@@ -141,6 +141,11 @@ __global__ __launch_bounds__(256) void k_prepare_prefill(const bf16_t* __restric
   }
   blk -= n_v;
   const size_t q_rows = (size_t)B * H * Lqp, k_rows = (size_t)B * Hkv * Lkp;
+  const long long w_blk = blk - (long long)((q_rows + k_rows + 63) / 64);
+  if (w_blk >= 0) {
+    ffn_image_piece(w, (int)w_blk * 256 + threadIdx.x);
+    return;
+  }
   const size_t row = (size_t)blk * 64 + (threadIdx.x >> 2);
   const int t0 = 8 * (threadIdx.x & 3);
   const bf16_t* src = nullptr;
@@ -326,7 +331,7 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
   const int hg0 = grp * GH;                                 // first head of the group
   const int h_first = hg0 + wv * HPW;
 
-  Ffn::stage(a.w1, a.w2, H, a.F, w_s, tid, THREADS, hg0, GH);
+  Ffn::stage(a.w, w_s, tid, THREADS, grp);
   // One head per wave, or two with shared operands, leave registers for the FFN weights: fetched
   // once per workgroup instead of read from LDS, each read followed by a wait, by every block
   // pair (5 % on the LLaMA3-8B shape once the score tensors are tiled; nothing before that, when

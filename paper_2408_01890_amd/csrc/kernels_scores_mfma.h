@@ -30,8 +30,7 @@ struct ScoresMfmaArgs {
   const bf16_t* qp;     // [B,H,Lqp,32]   Q_LR rows zero-padded to 32 elements
   const bf16_t* kp;     // [B,Hkv,Lkp/32,2,64,8] K_LR likewise, tiles in operand order (k_prepare_prefill)
   const half_t* prev;   // [B,H,Lq,Lk] (or tiled, see below)
-  const bf16_t* w1;     // [2H,F]
-  const bf16_t* w2;     // [F,H]
+  const unsigned short* w;  // FFN weights as k_prepare_prefill leaves them (FfnImage)
   half_t* scores;       // [B,H,Lq,Lk]: A_n, which the softmax kernel that follows reads as well
   int B, H, Hkv, Lq, Lk, Lqp, Lkp, F, causal;
   int tiled;            // prev and scores are [B,ceil(Lq/16),ceil(Lk/32),H,16,32] (TILED kernels only)
@@ -97,7 +96,7 @@ __global__ __launch_bounds__(512) void k_lisa_scores_mfma(ScoresMfmaArgs a) {
   int tile0 = (int)(pos - b * a.tiles_b);
   for (int nt; tile0 >= (nt = scores_mfma_tiles(rg, Lq, Lk, a.causal)); ++rg) tile0 -= nt;
 
-  Ffn::stage(a.w1, a.w2, Din, a.F, w_s, tid, NW * 64, 0, H, H);
+  Ffn::stage(a.w, w_s, tid, NW * 64);
 
   // transposing LDS reads of stage 2 (see the fused prefill kernel): lane 4 k' + q4 of a 16-lane
   // group passes the address of head k', keys 4 q4 .. 4 q4 + 3, and receives key c of heads k' = 0..3

@@ -412,8 +412,7 @@ struct SplitScoresArgs {
   const bf16_t* qp;       // [B,H,Lqp,32]   Q_LR rows zero-padded to 32 elements
   const bf16_t* kp;       // [B,Hkv,Lkp/32] K_LR tiles in operand order (k_prepare_prefill)
   const half_t* prev;     // [B,H,Lq,Lk]
-  const bf16_t* w1;       // [Din,F]
-  const bf16_t* w2;       // [F,H]
+  const unsigned short* w;  // FFN weights as k_prepare_prefill leaves them (FfnImage)
   half_t* scores;         // [B,H,Lq,Lk] or null
   float* exact;           // [B,ceil(n_rows/16),ceil(Lk/32),H] tiles of 512 (split_tile_at) or null: the unrounded copy
   int B, H, Hkv, Lq, Lk, Lqp, Lkp, F, causal;
@@ -475,15 +474,7 @@ __global__ __launch_bounds__(512) void k_split_scores(SplitScoresArgs a) {
 
   // weights in operand order: W1 operands [hidden block][k-step], then W2 [hidden k-step][head block]
   const int n_w1 = FS * 2 * KS;
-  stage_weights((n_w1 + FS * HB) * 512, (unsigned short*)w_s, tid, 512, [&](int i, bool& in) -> const bf16_t* {
-    const int e = i & 7, l = (i >> 3) & 63, o = i >> 9, lc = l & 15, lg = l >> 4, ks = o % KS, o2 = o - n_w1;
-    const bool one = o < n_w1;
-    const int f = one ? 16 * (o / KS) + lc : 32 * (o2 / HB) + 16 * (e >> 2) + 4 * lg + (e & 3);
-    const int h = one ? 32 * (ks % KSA) + 8 * lg + e : 16 * (o2 % HB) + lc;
-    in = (f < a.F) & (h < H);
-    const int at = one ? (ks < KSA ? h : H + h) * a.F + f : f * H + h;
-    return (one ? a.w1 : a.w2) + (in ? at : 0);
-  }, [](unsigned short bits) { return bits; });
+  stage_image(a.w, (n_w1 + FS * HB) * 64, a.w, (n_w1 + FS * HB) * 64, (unsigned short*)w_s, tid, 512);
   for (int i = tid; i < XHEAD / 4; i += 512) ((unsigned*)(xs + HT * XHEAD))[i] = 0;
   const unsigned char* wl = w_s + lane * 16;
 

@@ -20,6 +20,12 @@ int launch_scores_mfma_t(const lisa_desc* d, const ScoresMfmaArgs& a, hipStream_
 }
 }  // namespace
 
+// The weights as the kernel that launch_scores_mfma_kernel() chooses has them.
+FfnImage scores_mfma_image(const lisa_desc* d, const void* w1, const void* w2) {
+  const int HBO = d->H <= 16 ? 1 : d->H <= 32 ? 2 : 3;
+  return FfnImage{(const bf16_t*)w1, (const bf16_t*)w2, nullptr, 2 * d->H, d->F, d->H, HBO, d->F > 128 ? 8 : 4, HBO, 1, d->H, 0};
+}
+
 int launch_scores_mfma_kernel(const lisa_desc* d, const ScoresMfmaArgs& a, hipStream_t st) {
   const bool wide = d->F > 128;
   if (d->score_tiled) {                                      // (concat_tiled_ok: up to 32 heads)

@@ -107,7 +107,16 @@ int split_chunk_rows(const lisa_desc* d) {
   const size_t rows = std::max<size_t>(16, ((kSplitBudget - split_ws(d, 0).total) / split_row_bytes(d)) & ~(size_t)15);
   return (int)std::min<size_t>(rows, (size_t)d->Lq);
 }
-size_t split_bytes(const lisa_desc* d) { return split_ws(d).total; }
+namespace {
+// The weights as k_split_scores has them, behind the padded operands (and outside the budget: it decides the rows of a chunk).
+FfnImage split_image(const lisa_desc* d, const void* w1, const void* w2) {
+  const int HT = split_heads(d->H), KSA = (HT + 31) / 32;
+  const bool cc = d->mix == LISA_MIX_CONCAT;
+  return FfnImage{(const bf16_t*)w1, (const bf16_t*)w2, nullptr, cc ? 2 * d->H : d->H, d->F, d->H, cc ? 2 * KSA : KSA,
+                  (d->F + 31) / 32, (HT + 15) / 16, 1, d->H, KSA};
+}
+}  // namespace
+size_t split_bytes(const lisa_desc* d) { return split_ws(d).total + split_image(d, nullptr, nullptr).bytes(); }
 
 namespace {
 template <int HT, bool CONCAT, int TKB>
@@ -137,26 +146,28 @@ int launch_scores_h(const lisa_desc* d, SplitScoresArgs& a, hipStream_t st) {
 }
 }  // namespace
 
-// Q_LR and K_LR into the workspace as the scores kernel reads them.
-int run_split_prepare(const lisa_desc* d, const void* q_lr, const void* k_lr, void* workspace, hipStream_t st) {
+// Q_LR, K_LR and the weights into the workspace as the scores kernel reads them.
+int run_split_prepare(const lisa_desc* d, const void* q_lr, const void* k_lr, const void* w1, const void* w2, void* workspace,
+                      hipStream_t st) {
   const SplitWs w = split_ws(d);
   char* ws = (char*)workspace;
   const size_t rows = (size_t)d->B * d->H * w.Lqp + (size_t)d->B * d->Hkv * w.Lkp;
+  FfnImage img = split_image(d, w1, w2);
+  img.out = (unsigned short*)(ws + w.total);
   StageScope prof("k_prepare_prefill", st);
-  k_prepare_prefill<true><<<(unsigned)((rows + 63) / 64), 256, 0, st>>>(
+  k_prepare_prefill<true><<<(unsigned)((rows + 63) / 64 + (img.pieces() + 255) / 256), 256, 0, st>>>(
       (const bf16_t*)q_lr, (const bf16_t*)k_lr, nullptr, (bf16_t*)(ws + w.qp), (bf16_t*)(ws + w.kp), nullptr, d->B, d->H, d->Hkv,
-      d->Lq, d->Lk, w.Lqp, w.Lkp, d->r, 0);
+      d->Lq, d->Lk, w.Lqp, w.Lkp, d->r, 0, img);
   return check_launch();
 }
 
-int run_split_scores(const lisa_desc* d, const void* prev, const void* w1, const void* w2, void* scores, void* workspace,
-                     int row0, int n_rows, hipStream_t st) {
+int run_split_scores(const lisa_desc* d, const void* prev, void* scores, void* workspace, int row0, int n_rows, hipStream_t st) {
   const SplitWs w = split_ws(d);
   SplitScoresArgs a{};
   a.qp = (const bf16_t*)((char*)workspace + w.qp); a.kp = (const bf16_t*)((char*)workspace + w.kp);
   a.exact = (float*)workspace; a.Lqp = w.Lqp; a.Lkp = w.Lkp;
   a.prev = (const half_t*)prev; a.scores = (half_t*)scores;
-  a.w1 = (const bf16_t*)w1; a.w2 = (const bf16_t*)w2;
+  a.w = (const unsigned short*)((char*)workspace + w.total);
   a.B = d->B; a.H = d->H; a.Hkv = d->Hkv; a.Lq = d->Lq; a.Lk = d->Lk; a.F = d->F; a.causal = d->causal;
   a.row0 = row0; a.n_rows = n_rows;
   a.dscale = pick_scale(d->delta_scale, d->r);

@@ -194,7 +194,7 @@ bool scores_mfma_ok(const lisa_desc* d) {
 // Workspace of the CONCAT pipeline: A_n in the score type when the caller does not ask for it (the
 // softmax kernel reads it from there), the padded low-rank operands.
 struct ConcatWs {
-  size_t qp, kp, total;
+  size_t qp, kp, img, total;
   int Lqp, Lkp;
 };
 bool std_prefill_fast_ok(const lisa_desc* d);
@@ -207,7 +207,8 @@ ConcatWs concat_ws(const lisa_desc* d) {
   w.Lkp = (d->Lk + 63) / 64 * 64;
   w.qp = round_up(scores_bytes(d), 256);                   // (2-byte scores, in the layout of the call)
   w.kp = w.qp + round_up((size_t)d->B * d->H * w.Lqp * 32 * 2, 256);
-  w.total = w.kp + round_up((size_t)d->B * d->Hkv * w.Lkp * 32 * 2, 256);
+  w.img = w.kp + round_up((size_t)d->B * d->Hkv * w.Lkp * 32 * 2, 256);
+  w.total = w.img + scores_mfma_image(d, nullptr, nullptr).bytes();
   return w;
 }
 
@@ -218,9 +219,11 @@ int launch_scores_mfma(const lisa_desc* d, const void* q_lr, const void* k_lr, c
   {
     StageScope prof("k_prepare_prefill", st);
     const size_t rows = (size_t)d->B * d->H * w.Lqp + (size_t)d->B * d->Hkv * w.Lkp;
-    k_prepare_prefill<true><<<(unsigned)((rows + 63) / 64), 256, 0, st>>>(
+    FfnImage img = scores_mfma_image(d, w1, w2);
+    img.out = (unsigned short*)(ws + w.img);
+    k_prepare_prefill<true><<<(unsigned)((rows + 63) / 64 + (img.pieces() + 255) / 256), 256, 0, st>>>(
         (const bf16_t*)q_lr, (const bf16_t*)k_lr, nullptr, (bf16_t*)(ws + w.qp), (bf16_t*)(ws + w.kp), nullptr, d->B, d->H,
-        d->Hkv, d->Lq, d->Lk, w.Lqp, w.Lkp, d->r, 0);
+        d->Hkv, d->Lq, d->Lk, w.Lqp, w.Lkp, d->r, 0, img);
     int rc = check_launch();
     if (rc) return rc;
   }
@@ -228,8 +231,7 @@ int launch_scores_mfma(const lisa_desc* d, const void* q_lr, const void* k_lr, c
   a.qp = (const bf16_t*)(ws + w.qp);
   a.kp = (const bf16_t*)(ws + w.kp);
   a.prev = (const half_t*)prev;
-  a.w1 = (const bf16_t*)w1;
-  a.w2 = (const bf16_t*)w2;
+  a.w = (const unsigned short*)(ws + w.img);
   a.scores = (half_t*)scores;
   a.B = d->B;
   a.H = d->H;
@@ -335,10 +337,10 @@ int run_lisa(const lisa_desc* d, const void* q_lr, const void* k_lr, KeyStrides 
   const bool split = in_chunks(d) && split_scores_ok(d);     // (float32 scores in tiles)
   const int step = split ? split_chunk_rows(d) : in_chunks(d) ? f32_chunk_rows(d) : d->Lq;
   if (split)
-    if (int rc = run_split_prepare(d, q_lr, k_lr, exact, st)) return rc;
+    if (int rc = run_split_prepare(d, q_lr, k_lr, w1, w2, exact, st)) return rc;
   for (int row0 = 0; row0 < d->Lq; row0 += step) {
     const int n_rows = std::min(step, d->Lq - row0);
-    int rc = split              ? run_split_scores(d, prev, w1, w2, scores, exact, row0, n_rows, st)
+    int rc = split              ? run_split_scores(d, prev, scores, exact, row0, n_rows, st)
              : f32_scores_ok(d) ? run_f32_scores(d, q_lr, k_lr, prev, w1, w2, scores, exact, row0, n_rows, st)
                               : launch_lisa_scores<T, S>(d, q_lr, k_lr, ks, prev, w1, w2, scores, exact, row0, n_rows, st);
     if (rc) return rc;
@@ -549,8 +551,16 @@ PrefillGeom prefill_geom(const lisa_desc* d) {
   return g;
 }
 
+// The weights as MfmaFfn<(H + 15) / 16, (F + 31) / 32, (heads of a group + 15) / 16> has them, which is what
+// launch_prefill_fused_fs() chooses in every form.
+FfnImage prefill_image(const lisa_desc* d, const PrefillGeom& g, const void* w1, const void* w2) {
+  const int GH = d->H / g.groups;
+  return FfnImage{(const bf16_t*)w1, (const bf16_t*)w2, nullptr, d->H, d->F, d->H, ((d->H + 15) / 16 + 1) / 2, (d->F + 31) / 32,
+                  (GH + 15) / 16, g.groups, GH, 0};
+}
+
 struct PrefillWs {
-  size_t qp, kp, vt, part_o, part_ml, total;   // byte offsets in the workspace
+  size_t qp, kp, vt, part_o, part_ml, img, total;   // byte offsets in the workspace
   int Lqp, Lkp;
   PrefillGeom geom;
 };
@@ -566,7 +576,8 @@ PrefillWs prefill_fused_ws(const lisa_desc* d) {
   w.geom = prefill_geom(d);
   const size_t rows = w.geom.split > 1 ? (size_t)w.geom.split * d->B * w.Lqp * d->H : 0;
   w.part_ml = w.part_o + round_up(rows * d->d_k * sizeof(float), 256);
-  w.total = w.part_ml + round_up(rows * 2 * sizeof(float), 256);
+  w.img = w.part_ml + round_up(rows * 2 * sizeof(float), 256);
+  w.total = w.img + prefill_image(d, w.geom, nullptr, nullptr).bytes();
   return w;
 }
 
@@ -581,8 +592,7 @@ int run_prefill_fused(const lisa_desc* d, const void* q_lr, const void* k_lr, co
   a.kp = (const bf16_t*)(ws + w.kp);
   a.vt = (const bf16_t*)(ws + w.vt);
   a.prev = (const half_t*)prev;
-  a.w1 = (const bf16_t*)w1;
-  a.w2 = (const bf16_t*)w2;
+  a.w = (const unsigned short*)(ws + w.img);
   a.scores = (half_t*)scores;
   a.out = out;
   a.B = d->B;
@@ -605,12 +615,14 @@ int run_prefill_fused(const lisa_desc* d, const void* q_lr, const void* k_lr, co
   {
     StageScope prof("k_prepare_prefill", st);
     const size_t rows = (size_t)d->B * d->H * w.Lqp + (size_t)d->B * d->Hkv * w.Lkp;
-    const size_t blocks = (size_t)(w.Lkp / 64) * (d->d_k / 64) * d->B * d->Hkv + (rows + 63) / 64;
+    FfnImage img = prefill_image(d, geo, w1, w2);
+    img.out = (unsigned short*)(ws + w.img);
+    const size_t blocks = (size_t)(w.Lkp / 64) * (d->d_k / 64) * d->B * d->Hkv + (rows + 63) / 64 + (img.pieces() + 255) / 256;
     const bool vec = (uintptr_t)v % 16 == 0;
     auto kern = vec ? k_prepare_prefill<true> : k_prepare_prefill<false>;
     kern<<<(unsigned)blocks, 256, 0, st>>>((const bf16_t*)q_lr, (const bf16_t*)k_lr, (const bf16_t*)v,
                                           (bf16_t*)(ws + w.qp), (bf16_t*)(ws + w.kp), (bf16_t*)(ws + w.vt),
-                                          d->B, d->H, d->Hkv, d->Lq, d->Lk, w.Lqp, w.Lkp, d->r, d->d_k);
+                                          d->B, d->H, d->Hkv, d->Lq, d->Lk, w.Lqp, w.Lkp, d->r, d->d_k, img);
     int rc = check_launch();
     if (rc) return rc;
   }

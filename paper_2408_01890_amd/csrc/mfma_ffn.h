@@ -80,6 +80,63 @@ __device__ __forceinline__ void ffn_operand_piece(const FfnOperands& w, int idx)
   *(u16x8*)(w.out + (size_t)idx * 8) = x;
 }
 
+// The weights of a prefill call in the order of the LDS image of the kernel that uses them, made once per call by
+// k_prepare_prefill instead of by every workgroup from scattered 2-byte loads, which took the first 6000 of the 30000 cycles of
+// a workgroup with one tile to do (32 -> 64 -> 32).  What a call of few tiles gains: CONCAT, 64 -> 256 -> 32, 333 tokens 52.3 -> 41.5 us,
+// 3 x 224 tokens tiled 31.5 -> 27.4; 40 -> 80 -> 40, 3 x 182 rows behind 189 keys 65.7 -> 61.3; 32 -> 64 -> 32, 201 tokens
+// 24.6 -> 23.6.  Halves as MfmaFfn::stage() orders them, W2 for each group of GH
+// output heads in turn; or (KSA > 0) the bf16 values themselves as k_split_scores has them: the A_{n-1} and A_delta
+// inputs padded apart to KSA k-steps each, W2 by hidden k-steps.
+struct FfnImage {
+  const bf16_t* w1;     // [Din, F]
+  const bf16_t* w2;     // [F, HO]
+  unsigned short* out;
+  int Din, F, HO, KS, FS, HBO, groups, GH, KSA;
+  __host__ __device__ int pieces() const { return (2 * FS * KS + groups * HBO * FS) * 64; }   // of 16 bytes
+  __host__ __device__ size_t bytes() const { return (size_t)pieces() * 16; }
+};
+__device__ __forceinline__ void ffn_image_piece(const FfnImage& w, int idx) {
+  if (idx >= w.pieces()) return;
+  const int o = idx >> 6, c = idx & 15, g = idx >> 4 & 3, o2 = o - 2 * w.FS * w.KS, per = w.HBO * w.FS;
+  const int ks = o % w.KS, og = o2 % per;
+  const int hl = 16 * (w.KSA ? og % w.HBO : og / w.FS) + c, h = o2 / per * w.GH + hl, s = w.KSA ? og / w.HBO : og % w.FS;
+  unsigned short x[8];
+  bool in[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {                             // (unconditional loads: all eight in flight)
+    int row, col;
+    if (o2 < 0) {
+      row = w.KSA ? 32 * (ks % w.KSA) + 8 * g + e : 32 * ks + 8 * g + e, col = 16 * (o / w.KS) + c;
+      in[e] = row < (w.KSA ? w.HO : w.Din) && col < w.F;
+      if (w.KSA && ks >= w.KSA) row += w.HO;
+    } else {
+      row = 32 * s + 16 * (e >> 2) + 4 * g + (e & 3), col = h;
+      in[e] = row < w.F && hl < w.GH && h < w.HO;
+    }
+    const size_t at = in[e] ? (size_t)row * (o2 < 0 ? w.F : w.HO) + col : 0;
+    x[e] = (o2 < 0 ? w.w1 : w.w2)[at].bits;
+  }
+  u16x8 v;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = !in[e] ? 0 : w.KSA ? x[e] : half_bits(bf16_bits_to_f32(x[e]));
+  *(u16x8*)(w.out + (size_t)idx * 8) = v;
+}
+// lds[0 .. n) of 16-byte pieces: the first n1 from `a`, the others from `b`.  Eight loads of a thread in flight.
+__device__ __forceinline__ void stage_image(const unsigned short* a, int n1, const unsigned short* b, int n, unsigned short* lds,
+                                            int tid, int nthreads) {
+  for (int i0 = tid; i0 < n; i0 += 8 * nthreads) {
+    u16x8 x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int i = min(i0 + u * nthreads, n - 1);
+      x[u] = *(const u16x8*)(i < n1 ? a + i * 8 : b + (i - n1) * 8);
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (i0 + u * nthreads < n) *(u16x8*)(lds + (i0 + u * nthreads) * 8) = x[u];
+  }
+}
+
 // Fills lds[0 .. n) with conv(*src(i)), zero where src() says that element i is padding (it then returns any address
 // that may be read).  Eight unconditional loads of a thread are in flight at a time: with a test around each load the
 // threads waited for every one of them, 48 times over for the 64 -> 256 -> 32 network (30 us of a 139 us launch).
@@ -117,6 +174,12 @@ struct MfmaFfn {
 
   // Bytes of LDS that stage() fills.
   static constexpr int kStageBytes = (FB * KS + HBO * FS) * 64 * 16;
+
+  // The same image from the one that k_prepare_prefill has made: W1, and W2 of output group `grp`.
+  __device__ __forceinline__ static void stage(const unsigned short* img, unsigned short* lds, int tid, int nthreads, int grp = 0) {
+    constexpr int N1 = FB * KS * 64, N2 = HBO * FS * 64;     // pieces of 16 bytes
+    stage_image(img, N1, img + (size_t)(N1 + grp * N2) * 8, N1 + N2, lds, tid, nthreads);
+  }
 
   // All `nthreads` threads of the workgroup convert the weights (w1g [H][F], w2g [F][H],
   // bfloat16, global memory) once into `lds` in operand order (operand o, lane l -> 16 bytes at
