@@ -36,7 +36,7 @@ struct ProjectArgs {
   int B, L, D, H, Hkv, r, dk, Lmax, pos0, k_dim_major;
   int rope;          // 1: rotate Q_LR / K_LR
   double freq_log2;  // inverse frequency of pair t = 2^(t * freq_log2), freq_log2 = -2 log2(theta) / r
-  int n_m, n_n, own_n;
+  int n_m, n_n, own_n, equal;
   // Workgroups from n_blocks on (few-row kernels) put an FFN's weights in operand order for the launch behind
   int n_blocks;
   FfnOperands ffn;
@@ -133,13 +133,15 @@ constexpr int PJ_ROWB = PJ_TK * 2;              // bytes per LDS row
 
 // Tile geometry: WM x WN waves (8 in all), each BM x BN blocks of 32 x 32 outputs.
 //   <2,4,4,2>  256 x 256 outputs per workgroup, the densest in MFMA work per fetched byte;
-//   <4,2,2,3>  256 x 192, for problems whose 256-wide tiles would leave a quarter of the CUs
-//              idle or add a nearly empty last round of workgroups;
-//   <4,2,1,1>  128 x 64, where the others would leave half of the CUs idle: four MFMAs a wave and step, so the loads of
-//              NBUF - 1 steps are in flight where a compute unit has one workgroup: 0.40 us a step of d = 4096 with two
-//              or more steps in flight, 0.58 with one; what is left is the 24 KB a step through the unit's
-//              vector memory path.  (Two workgroups hide each other's latency: two buffers there.)
-// NBUF: LDS buffers, a step of both operands each.
+//   <4,2,2,3>  256 x 192, and the smaller ones for problems that would leave compute units idle or add a nearly empty
+//              last round with the larger tiles (see the host's choice):
+//   <2,4,2,2>  128 x 256,  <4,2,1,3>  128 x 192,  <2,4,2,1>  128 x 128,
+//   <4,2,1,1>  128 x 64: four MFMAs a wave and step, so the loads of NBUF - 1 steps are in flight where a compute unit has
+//              one workgroup: 0.40 us a step of d = 4096 with two or more steps in flight, 0.58 with one; what is left is
+//              the 24 KB a step through the unit's vector memory path.
+// NBUF: LDS buffers, a step of both operands each.  Three where one workgroup has a compute unit to itself (a single
+// round: 128 x 192, 777 tokens of LLaMA2-7B, 52 us against 55 with two; 128 x 128, 512 tokens, 35 against 45), two where two workgroups
+// fit and hide each other's latency (128 x 192, 3000 tokens, 154 us against 165 with three).
 template <int WM, int WN, int BM, int BN, int NBUF = 2>
 struct ProjTile {
   static_assert(WM * WN == 8, "8 waves");
@@ -191,12 +193,17 @@ __global__ __launch_bounds__(512) void k_project_mfma(ProjectArgs a) {
   int tm, tn;
   {
     const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-    if (NBUF > 2) {
-      // (a single round: equal shares of the tiles by columns, so that no XCD has more of them than compute units)
-      const int n_t = a.n_m * a.n_n, first = (int)((long long)n_t * xcd / 8), at = first + j;
+    if (NBUF > 2 || a.equal) {
+      // equal shares of the tiles, neighbours along the axis, so that no XCD has a round more than the others
+      const int n_t = a.n_m * a.n_n, at = (int)((long long)n_t * xcd / 8) + j;
       if (at >= (int)((long long)n_t * (xcd + 1) / 8)) return;
-      tn = at / a.n_m;
-      tm = at - tn * a.n_m;
+      if (a.own_n) {
+        tn = at / a.n_m;
+        tm = at - tn * a.n_m;
+      } else {
+        tm = at / a.n_n;
+        tn = at - tm * a.n_n;
+      }
     } else if (a.own_n) {
       tn = xcd + 8 * (j / a.n_m);
       tm = j % a.n_m;

@@ -868,60 +868,67 @@ static int project_qkv(const lisa_proj_desc* d, const void* x, const void* w, vo
     path = "project_skinny";
   } else if (fast) {
     const long long n_virtual = (long long)PJ_HEADW * (d->H + d->Hkv) + (long long)d->Hkv * d->d_k;
-    // tile width: the one whose workgroups fill the 256 CUs in fewer, fuller rounds (a round costs
-    // in proportion to the tile width); the wider tile on a tie
-    auto rounds_cost = [&](int tn) {
-      const long long wgs = ((M + 255) / 256) * ((n_virtual + tn - 1) / tn);
-      return ((wgs + kComputeUnits - 1) / kComputeUnits) * tn;
+    // Tile shape: the one of least cost, a sum of rounds of workgroups and of tiles per compute unit (a round's time grows with
+    // how full it is).  The weights are set so that the choice is at most 2.3 % behind the fastest shape in 111 problems,
+    // 129 - 6500 tokens of the LLaMA2-7B, LLaMA3-8B and LLaMA2-13B shapes, weights from HBM.  With 256 wide tiles
+    // and 128 x 64 ones alone and with this choice (us): LLaMA2-7B, 777 tokens 64 / 52, 1024 70 / 55, 2596 163 / 140;
+    // LLaMA3-8B, 2204 63 / 52, 2596 83 / 56, 4300 148 / 97; LLaMA2-13B, 640 90 / 67, 1101 125 / 113.
+    struct Shape {
+      int tm, tn, round, fill;
+      bool single;                                          // for a single round only
     };
-    // (the narrower tile does less MFMA work per fetched byte: it must win by a margin)
-    int tn = rounds_cost(192) * 8 < rounds_cost(256) * 7 ? 192 : 256;
-    // Tiles that would leave half of the CUs or more without one: 128 x 64, while those make three rounds at most.
-    // A step of the reduction takes about as long for a small tile as for a large one (its loads' latency), so
-    // more of them side by side win: LLaMA3-8B, 777 tokens, 48 tiles, 80 -> 28 us; LLaMA2-7B, 1024, 128 tiles,
-    // 80 -> 66; on the other side of the lines LLaMA2-7B at 1500 tokens, 192 tiles, 85 us, where 256 CUs are nearly
-    // full, and at 1100, 774 small tiles, 80 us against 91.
-    const long long small_tiles = ((M + 127) / 128) * ((n_virtual + 63) / 64);
-    bool small = ((M + 255) / 256) * ((n_virtual + tn - 1) / tn) <= kComputeUnits / 2 && small_tiles <= 3 * kComputeUnits;
-    {                                                       // tests force either geometry
-      const int v = g_tune[LISA_TUNE_PROJECT_TN];
-      if (v == 192 || v == 256) tn = v, small = false;
+    static const Shape shapes[] = {{256, 256, 111, 33, false}, {256, 192, 87, 67, false}, {128, 256, 71, 22, false}, {128, 192, 53, 1, true},
+                                   {128, 192, 64, 0, false},   {128, 128, 51, 2, false},  {128, 64, 23, 0, true}};
+    auto tiles_of = [&](const Shape& s) { return ((M + s.tm - 1) / s.tm) * ((n_virtual + s.tn - 1) / s.tn); };
+    int best = 0;
+    double least = 1e300;
+    for (int i = 0; i < 7; ++i) {
+      const long long t = tiles_of(shapes[i]);
+      const double cost = (double)shapes[i].round * ((t + kComputeUnits - 1) / kComputeUnits) + (double)shapes[i].fill * t / kComputeUnits;
+      if (cost < least && !(shapes[i].single && t > kComputeUnits)) least = cost, best = i;
     }
-    if (small) tn = 64;
-    a.n_m = (int)(small ? (M + 127) / 128 : (M + 255) / 256);
-    a.n_n = (int)((n_virtual + tn - 1) / tn);
+    {                                                       // tests force either of the large ones
+      const int v = g_tune[LISA_TUNE_PROJECT_TN];
+      if (v == 192 || v == 256) best = v == 192;
+    }
+    const Shape& shape = shapes[best];
+    a.n_m = (int)((M + shape.tm - 1) / shape.tm);
+    a.n_n = (int)((n_virtual + shape.tn - 1) / shape.tn);
+    const long long n_tiles = (long long)a.n_m * a.n_n;
     // which axis of the tile grid an XCD keeps to: the one that is balanced over 8 XCDs and
     // re-reads fewer operand bytes
     const bool n_ok = a.n_n % 8 == 0 || a.n_n >= 40, m_ok = a.n_m % 8 == 0 || a.n_m >= 40;
     const double xb = (double)M * d->d_model, wb = (double)n_real * d->d_model;
-    // (small tiles: an XCD's share of the weights, 2 - 5 MB, stays in its L2)
-    a.own_n = small || (n_ok && (!m_ok || wb / 8 + xb <= xb / 8 + wb));
-    const int per_xcd = a.own_n ? (a.n_n + 7) / 8 * a.n_m : (a.n_m + 7) / 8 * a.n_n;
-    StageScope scope("k_project_mfma", st);
-    if (small) {
-      // a single round: three steps in the LDS and equal shares per XCD (777 tokens, 252 tiles, 37 -> 28 us, also with few
-      // tiles, 129 tokens, 72 tiles, weights from HBM 36.2 -> 25.9, d = 2048 21.4 -> 16.3, 1024 14.0 -> 11.7; repeated on weights
-      // that the L2s still hold, which a pass through a model does not have, 23.6 -> 25.6, 15.4 -> 16.3, 11.0 -> 11.5); more workgroups
-      // than compute units: two steps, and two of them per unit (LLaMA2-7B, 1024 tokens, 67 us against 73)
-      const bool one = small_tiles <= kComputeUnits;
-      auto kern = one ? k_project_mfma<4, 2, 1, 1, 3> : k_project_mfma<4, 2, 1, 1>;
-      const int lds = one ? ProjTile<4, 2, 1, 1, 3>::LDS : ProjTile<4, 2, 1, 1>::LDS;
-      hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-      if (e != hipSuccess) return hip_fail(e);
-      kern<<<dim3(one ? (unsigned)((small_tiles + 7) / 8 * 8) : 8 * per_xcd), 512, lds, st>>>(a);
-    } else if (tn == 256) {
-      auto kern = k_project_mfma<2, 4, 4, 2>;
-      constexpr int lds = ProjTile<2, 4, 4, 2>::LDS;
-      hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-      if (e != hipSuccess) return hip_fail(e);
-      kern<<<dim3(8 * per_xcd), 512, lds, st>>>(a);
-    } else {
-      auto kern = k_project_mfma<4, 2, 2, 3>;
-      constexpr int lds = ProjTile<4, 2, 2, 3>::LDS;
-      hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-      if (e != hipSuccess) return hip_fail(e);
-      kern<<<dim3(8 * per_xcd), 512, lds, st>>>(a);
+    a.own_n = n_ok && (!m_ok || wb / 8 + xb <= xb / 8 + wb);
+    long long per_xcd = a.own_n ? (a.n_n + 7) / 8 * a.n_m : (a.n_m + 7) / 8 * a.n_n;
+    // Every eighth row or column of tiles, or (128 rows, or where that gives some XCD a round more: 17 x 12 tiles, LLaMA3-8B,
+    // 4300 tokens, 145 us) equal shares of neighbouring tiles, along the larger operand's axis.
+    constexpr int kXcdUnits = kComputeUnits / 8;
+    const long long share = (n_tiles + 7) / 8;
+    a.equal = shape.tm == 128 || (per_xcd + kXcdUnits - 1) / kXcdUnits > (share + kXcdUnits - 1) / kXcdUnits;
+    if (a.equal) {
+      a.own_n = xb <= wb;
+      per_xcd = share;
     }
+    StageScope scope("k_project_mfma", st);
+    auto launch = [&](auto kern, int lds) -> int {
+      hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+      if (e != hipSuccess) return hip_fail(e);
+      if (8 * per_xcd > 0x7fffffffLL) return LISA_ERR_UNSUPPORTED;
+      kern<<<dim3((unsigned)(8 * per_xcd)), 512, lds, st>>>(a);
+      return LISA_OK;
+    };
+    int lrc;
+    switch (best) {
+      case 0: lrc = launch(k_project_mfma<2, 4, 4, 2>, ProjTile<2, 4, 4, 2>::LDS); break;
+      case 1: lrc = launch(k_project_mfma<4, 2, 2, 3>, ProjTile<4, 2, 2, 3>::LDS); break;
+      case 2: lrc = launch(k_project_mfma<2, 4, 2, 2, 3>, ProjTile<2, 4, 2, 2, 3>::LDS); break;
+      case 3: lrc = launch(k_project_mfma<4, 2, 1, 3, 3>, ProjTile<4, 2, 1, 3, 3>::LDS); break;
+      case 4: lrc = launch(k_project_mfma<4, 2, 1, 3>, ProjTile<4, 2, 1, 3>::LDS); break;
+      case 5: lrc = launch(k_project_mfma<2, 4, 2, 1, 3>, ProjTile<2, 4, 2, 1, 3>::LDS); break;
+      default: lrc = launch(k_project_mfma<4, 2, 1, 1, 3>, ProjTile<4, 2, 1, 1, 3>::LDS); break;
+    }
+    if (lrc) return lrc;
     path = "project_mfma";
   } else {
     const long long total = M * n_real;
