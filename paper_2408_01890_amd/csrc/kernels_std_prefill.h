@@ -31,7 +31,8 @@ struct StdPrefillArgs {
                           // float32 (GIVEN = 1) or IEEE half (GIVEN = 2)
   void* out;              // [B,Lq,H,128] or null
   int H, Hkv, Lq, Lk, causal, out_f32;
-  int pair;               // 1: a workgroup takes two row groups (grid.y = ceil(n_groups / 2)), 0: one
+  int pair;               // 1: a workgroup takes two row groups (ceil(n_groups / 2) slots), 0: one
+  int by_length;          // grid (H, B, slots), else (H, slots, B)
   float scale;
 };
 
@@ -96,7 +97,7 @@ __global__ __launch_bounds__(256 * NH, 2) void k_std_prefill(StdPrefillArgs a) {
   unsigned char* ss_ = lds + NH * (2 * SP_KTILE);       // score staging, one tile per wave
   unsigned char* vs_ = ss_ + NH * (SP_WAVES * SP_STILE) + kh * (2 * SP_VTILE);
   const int r = lane & 31, half = lane >> 5;
-  const int b = blockIdx.z, h = blockIdx.x;
+  const int b = a.by_length ? blockIdx.y : blockIdx.z, h = blockIdx.x, slot = a.by_length ? blockIdx.z : blockIdx.y;
   const int Lq = a.Lq, Lk = a.Lk, H = a.H;
   const int shift = Lk - Lq;
   const int kv = h / (H / a.Hkv);
@@ -115,7 +116,7 @@ __global__ __launch_bounds__(256 * NH, 2) void k_std_prefill(StdPrefillArgs a) {
   const int v_rd = (8 * half + ((lane & 15) >> 2)) * SP_VROW + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
 
   for (int rep = 0; rep < 2; ++rep) {
-    const int grp = rep ? (int)blockIdx.y : n_groups - 1 - (int)blockIdx.y;
+    const int grp = rep ? slot : n_groups - 1 - slot;
     if (rep && (!a.pair || grp >= n_groups - 1 - grp)) break;   // (the middle group of an odd count is alone)
     const int i0 = grp * SP_GROUP + wv * SP_ROWS;          // first row of this wave
     const bool have_rows = i0 < Lq;

@@ -9,10 +9,19 @@ bool f32_attn_ok(const lisa_desc* d) { return d->Lq > 1 && d->dtype == LISA_F32 
 namespace {
 template <typename T, typename S, int NDK>
 int launch_attn(const lisa_desc* d, const F32AttnArgs<T, S>& a, hipStream_t st) {
-  dim3 grid((a.n_rows + 15) / 16 * a.parts, d->H, d->B);
+  const long long wgs = (long long)((a.n_rows + 15) / 16) * a.parts * d->H * d->B;
+  if (wgs > 0x7fffffffLL) return LISA_ERR_UNSUPPORTED;
+  // Eight waves where rows are long and workgroups few: the chain of a wave's tiles bounds them, with scores given (no K stream
+  // beside it) up to four workgroups per compute unit.  float32, 8 heads of 64, four / eight waves in us: scores given, 430 tokens
+  // 12.1 / 10.2, 2 x 504 14.2 / 10.9, 3 x 504 15.1 / 13.9, 3 x 700 (1056 workgroups) 19.8 / 20.2, 128 tokens 7.2 / 7.8; scores made,
+  // 430 tokens (216) 14.8 / 13.4, 700 (352) 19.4 / 19.2, 2 x 504 (512) 16.7 / 17.7.
+  const bool wide = sizeof(T) == 4 && a.out && d->Lk > 256 && wgs <= (a.given ? 4 : 1) * kComputeUnits;
+  const dim3 grid((unsigned)wgs);
   StageScope prof(a.given ? "k_f32_softmax_v" : "k_f32_attn", st);
-  if (a.given) k_f32_attn<T, S, NDK, true><<<grid, 256, 0, st>>>(a);
-  else k_f32_attn<T, S, NDK, false><<<grid, 256, 0, st>>>(a);
+  auto kern = a.given ? k_f32_attn<T, S, NDK, true, 4> : k_f32_attn<T, S, NDK, false, 4>;
+  if constexpr (sizeof(T) == 4)
+    if (wide) kern = a.given ? k_f32_attn<T, S, NDK, true, 8> : k_f32_attn<T, S, NDK, false, 8>;
+  kern<<<grid, wide ? 512 : 256, 0, st>>>(a);
   return check_launch();
 }
 
@@ -23,7 +32,7 @@ int run_attn(const lisa_desc* d, const void* q, const void* k, const void* given
   F32AttnArgs<T, S> a{};
   a.q = (const T*)q; a.k = (const T*)k; a.v = (const T*)v; a.given = (const float*)given;
   a.scores = (S*)scores; a.out = out;
-  a.H = d->H; a.Hkv = d->Hkv; a.Lq = d->Lq; a.Lk = d->Lk; a.causal = d->causal;
+  a.B = d->B; a.H = d->H; a.Hkv = d->Hkv; a.Lq = d->Lq; a.Lk = d->Lk; a.causal = d->causal;
   a.out_f32 = d->out_f32 || d->dtype == LISA_F32;
   a.row0 = row0; a.n_rows = n_rows;
   // Scores only: nothing to merge, so few row blocks of many keys are spread until there is a workgroup per

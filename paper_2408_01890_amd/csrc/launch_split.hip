@@ -204,7 +204,8 @@ int run_split_attn(const lisa_desc* d, const void* q, const void* k, const void*
   // at least
   a.parts = out ? 1 : (int)std::max<long long>(1, std::min<long long>((d->Lk + 8 * SP_TK - 1) / (8 * SP_TK),
                                                                       kComputeUnits / ((long long)groups * d->H * d->B)));
-  dim3 grid(d->H, groups * a.parts, d->B);
+  // (sequence by sequence 2 x 704 rows of 40 heads, standard layer, take 42.5 us instead of 35, 3 x 501 52 instead of 47.5)
+  dim3 grid(d->H, d->B, groups * a.parts);
   StageScope prof(given ? "k_split_softmax_v" : "k_split_attn", st);
   if (given) k_split_attn<true, true><<<grid, 256, 0, st>>>(a);
   else if (out) k_split_attn<true, false><<<grid, 256, 0, st>>>(a);

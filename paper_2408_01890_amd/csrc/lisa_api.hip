@@ -680,6 +680,17 @@ bool std_key_halves(const lisa_desc* d, bool with_v) {
   return 8 * all <= 11 * kComputeUnits * tiles(groups - 1);
 }
 
+// The order of the workgroups: row groups of all sequences by length, long ones first, where (nearly) all of them run at once.
+// A compute unit then has numbers i and i + 256 whatever they are, and sequence by sequence these are two long groups as often as
+// not.  Scores + O, sequence by sequence / by length: 2 x 1024 tokens of 32 heads (512 workgroups) 59.7 / 49.4 us, 2 x 544 of 40
+// (400) 34.0 / 29.7, softmax alone, 2 x 672 of 32 24.8 / 22.7, 6 x 352 of 32 (576) 29.7 / 28.6.  Beyond that the dispatcher evens most of
+// it out (4 x 960 of 32, 1024 workgroups, 78 / 74, 2 x 1280 of 40, 800, 75.9 / 78.6, 8 x 608 of 40, 1600, 90.8 / 98.2).
+bool std_by_length(const lisa_desc* d) {
+  const long long groups = (d->Lq + SP_GROUP - 1) / SP_GROUP;
+  return groups * d->H * d->B <= 5 * kComputeUnits / 2;
+}
+dim3 std_grid(const lisa_desc* d, bool by_length, int n) { return by_length ? dim3(d->H, d->B, n) : dim3(d->H, n, d->B); }
+
 // softmax(A) V for scores A that are already in memory, float32 or IEEE half (k_std_prefill in
 // GIVEN mode).
 int run_softmax_given_fast(const lisa_desc* d, const void* given, bool given_half, const void* v, void* out,
@@ -697,7 +708,8 @@ int run_softmax_given_fast(const lisa_desc* d, const void* given, bool given_hal
   a.scale = 1.f;
   const int n_groups = (d->Lq + SP_GROUP - 1) / SP_GROUP;
   a.pair = 0;
-  dim3 grid(d->H, n_groups, d->B);
+  a.by_length = std_by_length(d);
+  const dim3 grid = std_grid(d, a.by_length, n_groups);
   StageScope prof("k_softmax_v_mfma", st);
   const bool halves = std_key_halves(d, true);
   auto kern = !given_half       ? (halves ? k_std_prefill<true, 1, false, 2> : k_std_prefill<true, 1>)
@@ -729,7 +741,8 @@ int run_std_prefill_fast(const lisa_desc* d, const void* q, const void* k, const
   // grouped keys and 10 % slower at L = 2048, where it leaves one workgroup per compute unit.)
   a.pair = 0;
   if (g_tune[LISA_TUNE_STD_PAIR] >= 0) a.pair = g_tune[LISA_TUNE_STD_PAIR] != 0;   // tests force either
-  dim3 grid(d->H, a.pair ? (n_groups + 1) / 2 : n_groups, d->B);
+  a.by_length = std_by_length(d);
+  const dim3 grid = std_grid(d, a.by_length, a.pair ? (n_groups + 1) / 2 : n_groups);
   StageScope prof("k_std_prefill", st);
   const bool halves = std_key_halves(d, out != nullptr) && !a.pair;
   auto kern = out && d->score_tiled ? (halves ? k_std_prefill<true, 0, true, 2> : k_std_prefill<true, 0, true>)
