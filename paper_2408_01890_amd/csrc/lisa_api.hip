@@ -488,17 +488,15 @@ bool prefill_fused_ok(const lisa_desc* d) {
 
 // Geometry of the fused prefill launch: row slices per workgroup (R = 16 * slices query rows), head
 // groups, key splits, paired units.
-//   slices  A workgroup of R rows fetches each K_LR / V tile once for all its rows: 4 slices where
-//           the problem still gives every compute unit several units of work (>= 1024 units), which
-//           needs one head per wave (groups of 8 heads); ReLU layers with 33..96 hidden units.
+//   slices  A workgroup of R rows fetches each K_LR / V tile once for all its rows; needs one head per wave (groups of
+//           8 heads) and a ReLU layer with 33..96 hidden units.
 //   groups  H = 32 (16) runs as two (one) groups of 16 heads, two heads per wave, or as four (two)
 //           groups of 8, one head per wave: the first FFN layer is computed once more per extra
-//           group, but there are more units (no key splits, partial results and combine passes on
-//           small problems) and row slices become possible.
+//           group, but there are more units and row slices become possible.
 //   split   small problems have too few units to fill the chip and their longest unit (the last
-//           row block) sets the run time: the key tiles of a row block are dealt to 2 or 4 units.
-//   pair    two units (a long and a short one) per workgroup once that still leaves a workgroup per
-//           compute unit: equal work per workgroup, FFN weights staged once for both.
+//           row block) sets the run time: the key tiles of a row block are dealt to 2 units.
+//   pair    two units (a long and a short one) per workgroup: equal work per workgroup, FFN weights staged once for both.
+// prefill_cost() weighs them against each other.
 struct PrefillGeom {
   int slices, groups, split, pair;
 };
@@ -507,48 +505,87 @@ bool prefill_slices_ok(const lisa_desc* d) {
   return d->act == LISA_ACT_RELU && d->F > 32 && d->F <= 96 && (d->H == 8 || d->H == 16 || d->H == 32 || d->H == 40);
 }
 
+// What a launch of a geometry takes, in us, up to what all of them have in common: the workgroups of the fullest XCD on its 32
+// compute units, `start` for each (its Q_LR rows, the first tiles on their way) and `step` for 16 rows x 32 keys, which grows with
+// how full the chip is.  A workgroup of two units (a long and a short one, equal work for all) has kPair more of the former; single
+// units, long ones first, fill the units unevenly by about kTail of one.  Key shares pay a combine pass and the bytes of the
+// partial results.  The numbers are set over 118 problems, 224 - 7552 tokens and 1 - 8 sequences of the LLaMA2-7B, LLaMA3-8B and
+// LLaMA2-13B shapes on tiled scores, all 6 - 10 geometries timed: the choice is 0.7 % behind the fastest one on average, 9 % at most.
+// Before, counts of units alone decided (us, then / now): LLaMA2-7B, 768 tokens 69 / 51, 3 x 1312 299 / 185; LLaMA3-8B, 1248
+// 110 / 78, 2720 345 / 214, 4 x 640 106 / 66; LLaMA2-13B, 640 79 / 61, 3 x 512 124 / 76; four key shares are never the best one.
+double prefill_cost(const lisa_desc* d, const PrefillGeom& g, long long tiles_all, int tiles_max) {
+  struct Form {
+    double start, step, full;
+  };
+  constexpr double kPair = 2.3, kTail = 0.465, kCombine = 4.0, kPerMB = 0.373;
+  const bool heavy = d->H > 32 || d->F > 64;
+  const int hpw = d->H / (8 * g.groups);                    // heads per wave
+  Form f = hpw == 1 ? (g.slices > 1 ? (heavy ? Form{8.6, 2.33, 0.4} : Form{7.8, 1.8, 0.28})
+                                    : (heavy ? Form{7.0, 2.5, 0.42} : Form{4.2, 1.87, 0.26}))
+           : (d->H / d->Hkv) % hpw == 0 && hpw != 3 ? Form{5.9, 1.98, 0.54} : Form{5.2, 2.32, 1.15};
+  if (hpw > 2) f.step *= 0.5 * hpw, f.full *= 0.5 * hpw;
+  const long long rbs = (d->Lq + 16 * g.slices - 1) / (16 * g.slices), units = rbs * g.split;
+  long long load;
+  pf_chunk(g.groups, g.pair ? (units + 1) / 2 : units, d->B, &load);
+  const double mean = (double)tiles_all * g.slices / units, per_unit = load / 32.0;
+  const double step = f.step + f.full * std::min(1.0, per_unit);
+  const int longest = (tiles_max / (2 * g.split) * 2 + std::min(tiles_max % (2 * g.split), 2)) * g.slices;
+  double us;
+  // (equal workgroups go in rounds; over many of them a last one that is not full is made up for)
+  if (g.pair) us = (per_unit > 8 ? per_unit : std::ceil(per_unit)) * (f.start + kPair + step * 2 * mean);
+  else if (load <= 32) us = f.start + step * longest;
+  else us = std::max(f.start + step * longest, f.start * per_unit + step * mean * (per_unit + kTail));
+  // (over many rounds single units lose the neighbours that read the same tiles: 4 x 8192 tokens of LLaMA3-8B, 16 rounds, 5.89 ms
+  // against 5.69 in pairs, 8 x 4096 of LLaMA2-13B, 20, 7.87 / 7.77; LLaMA2-7B, 4 x 4096, 8, 2.16 / 2.19)
+  if (!g.pair && per_unit > 12) us *= 1.03;
+  if (g.split > 1) us += kCombine + kPerMB * 1e-6 * g.split * d->B * d->Lq * d->H * d->d_k * sizeof(float);
+  return us;
+}
+
 PrefillGeom prefill_geom(const lisa_desc* d) {
-  PrefillGeom g{1, 1, 1, 0};
-  const long long blocks16 = (long long)((d->Lq + PF_ROWS - 1) / PF_ROWS) * d->B;
-  const int few = d->H == 40 ? 5 : d->H == 32 ? 2 : 1;      // groups of 16 heads (H = 40, 8: of 8)
-  const int many = d->H / 8;
+  const int few = d->H == 40 ? 5 : d->H == 32 ? 2 : 1;      // groups of 16 heads (H = 40, 8: of 8; 24: of 24)
+  const int many = d->H == 24 ? 1 : d->H / 8;
   const bool two_forms = d->H == 32 || d->H == 16;
   // H = 32 with key/value heads shared by (a multiple of) four query heads can keep the whole layer
   // of a row block in one workgroup, a wave per group of four heads.  It is correct and tested but
   // never chosen: its 128 accumulator registers per lane leave the compiler 50 short (spills), and
   // it measured 11.8 ms against 7.6 ms for two groups of 16 on the LLaMA3-8B shape at L = 8192.
+  // Nor are four slices, whose 128 accumulators spill as well: 16 - 20 ms on the same shapes.
   const bool whole_ok = d->H == 32 && (d->H / d->Hkv) % 4 == 0;
-  const bool large = blocks16 * few >= 2 * kComputeUnits;
-  if (prefill_slices_ok(d)) {
-    // two slices where the problem still gives every compute unit several units of work; not where
-    // groups of 16 heads, two per wave, are the alternative (measured with two slices against two
-    // groups: 10.2 / 7.6 ms on the LLaMA3-8B shape, where the pair of heads shares its operands;
-    // 2.8 / 2.5 ms on LLaMA2-7B heads at B = 4, L = 4096; on the LLaMA2-13B shape, which has no
-    // such form, 8.5 ms with two slices against 9.3 ms with one).  Four slices exist and are
-    // tested, but their 128 accumulators spill: 16 - 20 ms on the same shapes.
-    if (!(two_forms && large) && (long long)((d->Lq + 31) / 32) * d->B * many >= 4 * kComputeUnits) g.slices = 2;
-    const int forced = g_tune[LISA_TUNE_PREFILL_SLICES];
-    if (forced == 1 || forced == 2 || forced == 4) g.slices = forced;
+  const int want = g_tune[LISA_TUNE_PREFILL_GROUPS], want_slices = g_tune[LISA_TUNE_PREFILL_SLICES],
+            want_split = g_tune[LISA_TUNE_PREFILL_SPLIT], want_pair = g_tune[LISA_TUNE_PREFILL_PAIR];
+  const bool forced_slices = prefill_slices_ok(d) && (want_slices == 1 || want_slices == 2 || want_slices == 4);
+  const bool forced_split = want_split == 1 || want_split == 2 || want_split == 4;
+  auto tiles_of = [&](long long rows) {                     // key tiles of a row block that ends before `rows`
+    const int last = (int)std::min<long long>(rows, d->Lq) - 1;
+    return ((d->causal ? std::min(d->Lk, last + 1 + d->Lk - d->Lq) : d->Lk) + PF_TK - 1) / PF_TK;
+  };
+  PrefillGeom best{1, 1, 1, 0};
+  double least = -1.;
+  for (int slices = 1; slices <= 4; slices *= 2) {
+    if (forced_slices ? slices != want_slices : slices == 4 || (slices == 2 && !prefill_slices_ok(d))) continue;
+    long long tiles_all = 0;
+    const int R = PF_ROWS * slices;
+    for (long long i = 0; i < d->Lq; i += R) tiles_all += tiles_of(i + R);
+    const int tiles_max = tiles_of(d->Lq);
+    // SiLU costs two quarter-rate instructions per hidden unit, once more per extra group: measured
+    // 0.27 ms with two groups (and a key split) against 0.32 ms with four on the LLaMA2-7B shape.
+    const int lo = slices > 1 || !two_forms ? many : want >= 0 ? (want == many ? many : few) : few;
+    const int hi = slices > 1 || !two_forms ? many : want >= 0 ? lo : d->act == LISA_ACT_SILU ? few : many;
+    for (int groups = lo; groups <= hi; groups += hi > lo ? hi - lo : 1)
+      for (int split = 1; split <= 4; split *= 2) {
+        if (slices > 1 ? split > 1 : forced_split ? split != want_split : split > 2 || (split > 1 && tiles_max < 4)) continue;
+        for (int pair = 0; pair < 2; ++pair) {
+          if (want_pair >= 0 && pair != (want_pair != 0)) continue;
+          PrefillGeom g{1, 1, 1, 0};
+          g.groups = whole_ok && slices == 1 && want == 1 ? 1 : groups;
+          g.slices = slices, g.split = split, g.pair = pair;
+          const double us = prefill_cost(d, g, tiles_all, tiles_max);
+          if (least < 0 || us < least) least = us, best = g;
+        }
+      }
   }
-  const int want = g_tune[LISA_TUNE_PREFILL_GROUPS];
-  if (d->H == 24) g.groups = 1;
-  else if (whole_ok && g.slices == 1 && want == 1) g.groups = 1;
-  else if (!two_forms || g.slices > 1) g.groups = many;
-  else if (want >= 0) g.groups = want == many ? many : few;
-  // SiLU costs two quarter-rate instructions per hidden unit, once more per extra group: measured
-  // 0.27 ms with two groups (and a key split) against 0.32 ms with four on the LLaMA2-7B shape.
-  else if (d->act == LISA_ACT_SILU) g.groups = few;
-  else g.groups = large ? few : many;
-  const long long units = (long long)((d->Lq + 16 * g.slices - 1) / (16 * g.slices)) * d->B * g.groups;
-  if (g.slices == 1) {
-    const int tiles_max = (d->Lk + PF_TK - 1) / PF_TK;
-    while (g.split < 4 && units * g.split < 2 * kComputeUnits && tiles_max / (2 * g.split) >= 4) g.split *= 2;
-    const int forced = g_tune[LISA_TUNE_PREFILL_SPLIT];
-    if (forced == 1 || forced == 2 || forced == 4) g.split = forced;
-  }
-  g.pair = units * g.split >= 2 * kComputeUnits;
-  if (g_tune[LISA_TUNE_PREFILL_PAIR] >= 0) g.pair = g_tune[LISA_TUNE_PREFILL_PAIR] != 0;
-  return g;
+  return best;
 }
 
 // The weights as MfmaFfn<(H + 15) / 16, (F + 31) / 32, (heads of a group + 15) / 16> has them, which is what
@@ -610,6 +647,10 @@ int run_prefill_fused(const lisa_desc* d, const void* q_lr, const void* k_lr, co
   a.dscale = pick_scale(d->delta_scale, d->r);
   a.split = geo.split;
   a.pair = geo.pair;
+  {
+    const long long units = (long long)((d->Lq + 16 * geo.slices - 1) / (16 * geo.slices)) * geo.split;
+    a.chunk = pf_chunk(geo.groups, geo.pair ? (units + 1) / 2 : units, d->B);
+  }
   a.part_o = (float*)(ws + w.part_o);
   a.part_ml = (float*)(ws + w.part_ml);
   {
