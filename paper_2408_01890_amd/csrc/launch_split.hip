@@ -119,6 +119,22 @@ FfnImage split_image(const lisa_desc* d, const void* w1, const void* w2) {
 size_t split_bytes(const lisa_desc* d) { return split_ws(d).total + split_image(d, nullptr, nullptr).bytes(); }
 
 namespace {
+long long tiles_of(const lisa_desc* d, const SplitScoresArgs& a, int tk) {
+  long long n = 0;
+  for (int i = a.row0; i < a.row0 + a.n_rows; i += 16)
+    n += split_scores_tiles(i, a.row0 + a.n_rows, d->Lq, d->Lk, d->causal, tk);
+  return n;
+}
+// Tiles of 16 keys in place of 32: a workgroup is done with one in 0.6 - 0.9 of the time, which pays where there are no more than
+// one and a half times as many rounds of them, in one or two rounds (beyond, wider rows of the tensors count).  32 and 40 heads, 32 /
+// 16 keys in us: CONCAT, 64 -> 256 -> 32, 150 tokens 27.6 / 18.2, 333 30.9 / 23.1, 2 x 345 (2 / 3 rounds) 51.4 / 37.8; ADD, 32 heads,
+// 250 tokens 16.1 / 13.7, 40 heads 20.3 / 17.0, 3 x 182 rows of 371 keys (2 / 3) 44.3 / 41.3; on the other side (1 / 2) CONCAT, 421
+// tokens 33.0 / 35.1, ADD, 40 heads, 2 x 130 rows of 430 keys 25.1 / 30.4.
+bool small_tiles_win(const lisa_desc* d, const SplitScoresArgs& a) {
+  auto rounds = [&](int tk) { return (tiles_of(d, a, tk) * a.B + kComputeUnits - 1) / kComputeUnits; };
+  const long long r = rounds(32);
+  return d->H > 16 && r <= 2 && 2 * rounds(16) <= 3 * r;
+}
 template <int HT, bool CONCAT, int TKB>
 int launch_scores_t(const lisa_desc* d, SplitScoresArgs& a, hipStream_t st) {
   typedef SplitScoresGeo<HT, CONCAT, TKB> Geo;
@@ -126,9 +142,7 @@ int launch_scores_t(const lisa_desc* d, SplitScoresArgs& a, hipStream_t st) {
   auto kern = d->act == LISA_ACT_SILU ? k_split_scores<HT, 1, CONCAT, TKB> : k_split_scores<HT, 0, CONCAT, TKB>;
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return hip_fail(e);
-  a.tiles_b = 0;
-  for (int i = a.row0; i < a.row0 + a.n_rows; i += 16)
-    a.tiles_b += split_scores_tiles(i, a.row0 + a.n_rows, d->Lq, d->Lk, d->causal, Geo::TK);
+  a.tiles_b = tiles_of(d, a, Geo::TK);
   const long long wgs = std::min<long long>(kComputeUnits, a.tiles_b * a.B);
   StageScope prof("k_split_scores", st);
   kern<<<(unsigned)wgs, 512, lds, st>>>(a);
@@ -136,7 +150,7 @@ int launch_scores_t(const lisa_desc* d, SplitScoresArgs& a, hipStream_t st) {
 }
 template <int HT>
 int launch_scores_h(const lisa_desc* d, SplitScoresArgs& a, hipStream_t st) {
-  const int kb = split_keys(d);
+  const int kb = split_keys(d) == 2 && small_tiles_win(d, a) ? 1 : split_keys(d);
   if (d->mix == LISA_MIX_CONCAT) {
     if constexpr (HT < 40)
       if (kb == 2) return launch_scores_t<HT, true, 2>(d, a, st);
