@@ -87,6 +87,7 @@ struct SplitAttnArgs {
   int row0, n_rows;       // query rows of this launch (row0 a multiple of 16)
   int given_tiled;        // given is [B,ceil(n_rows/16),ceil(Lk/32),H] tiles (split_tile_at), else [B,H,n_rows,Lk] with 32 floats behind it
   int parts;              // scores only: workgroups that the key tiles of a row group are dealt to (1 with V, or not KEYS)
+  int by_length;          // row groups of all sequences by length, else sequence by sequence
   float scale;
 };
 
@@ -99,7 +100,7 @@ constexpr int split_attn_lds(bool with_v, bool given) {
   return tiles > merge ? tiles : merge;
 }
 
-// grid (H, B, parts * row groups of 32), block 256: 32 query rows of one head, the tiles of 32 keys dealt to the four
+// grid (H, B, parts * row groups of 32), or the last two swapped, block 256: 32 query rows of one head, the tiles of 32 keys dealt to the four
 // waves, each with LDS of its own (no barrier in the loop); their softmax states are merged at the end.  The scheme of
 // k_std_prefill (see there for the operand layouts) with float32 probabilities in three parts, V staged as it is (the
 // transposing LDS read hands out its columns), and scores at any 2-byte boundary.  GIVEN: the scores come from memory.
@@ -120,11 +121,11 @@ __global__ __launch_bounds__(256, 2) void k_split_attn(SplitAttnArgs a) {
   float* ps_ = (float*)(GIVEN ? lds + 4 * SP_VTILE + wv * (SP_ROWS * SA_PROW * 4) : ks_);
   static_assert(SP_ROWS * SA_PROW * 4 <= SP_KTILE && (!GIVEN || 4 * (SP_VTILE + SP_ROWS * SA_PROW * 4) <= split_attn_lds(WITH_V, GIVEN)), "");
   const int r = lane & 31, half = lane >> 5;
-  const int b = blockIdx.y, h = blockIdx.x;
+  const int b = a.by_length ? blockIdx.y : blockIdx.z, h = blockIdx.x;
   const int Lq = a.Lq, Lk = a.Lk, H = a.H, shift = Lk - Lq;
   const int kv = h / (H / a.Hkv);
   const float LOG2E = 1.4426950408889634f;
-  const int xr = gridDim.z - 1 - blockIdx.z;                   // long row groups first, of all sequences
+  const int xr = a.by_length ? gridDim.z - 1 - blockIdx.z : gridDim.y - 1 - blockIdx.y;   // long row groups first
   const int grp = xr / a.parts, part = xr - grp * a.parts;
   const int row_end = a.row0 + a.n_rows;
   const int i0 = a.row0 + grp * SP_ROWS;

@@ -218,8 +218,11 @@ int run_split_attn(const lisa_desc* d, const void* q, const void* k, const void*
   // at least
   a.parts = out ? 1 : (int)std::max<long long>(1, std::min<long long>((d->Lk + 8 * SP_TK - 1) / (8 * SP_TK),
                                                                       kComputeUnits / ((long long)groups * d->H * d->B)));
-  // (sequence by sequence 2 x 704 rows of 40 heads, standard layer, take 42.5 us instead of 35, 3 x 501 52 instead of 47.5)
-  dim3 grid(d->H, d->B, groups * a.parts);
+  // A prompt's row groups differ in length: by length, over all sequences (2 x 704 rows of 40 heads, standard layer, 42.5 -> 35 us,
+  // 3 x 501 52 -> 47.5).  Rows behind as many keys or more are about equally long: a sequence at a time, whose V the L2s then hold
+  // (softmax of 2 x 509 rows behind 1022 keys 69.6 us, by length 70.9).
+  a.by_length = d->Lk - d->Lq < d->Lq;
+  const dim3 grid = a.by_length ? dim3(d->H, d->B, groups * a.parts) : dim3(d->H, groups * a.parts, d->B);
   StageScope prof(given ? "k_split_softmax_v" : "k_split_attn", st);
   if (given) k_split_attn<true, true><<<grid, 256, 0, st>>>(a);
   else if (out) k_split_attn<true, false><<<grid, 256, 0, st>>>(a);
