@@ -49,12 +49,13 @@ struct F32AttnArgs {
   S* scores;              // [B,H,Lq,Lk] or null
   void* out;              // [B,Lq,H,DK] (float where out_f32, else T) or null
   int B, H, Hkv, Lq, Lk, causal, out_f32;
+  int flat;               // more workgroups than compute units: their order counts (a division or four cost 0.25 us a launch)
   int row0, n_rows;       // query rows of this launch (row0 a multiple of 16)
   int parts;              // workgroups that the tiles of a row block are dealt to (1 unless scores only)
   float scale;
 };
 
-// grid (parts ceil(n_rows / 16) H B), block 64 NW: 16 query rows of one head, the 16-key tiles dealt to the NW
+// grid (H, B, parts ceil(n_rows / 16)), or all of it in x (flat), block 64 NW: 16 query rows of one head, the 16-key tiles dealt to the NW
 // waves (scores only: of `parts` workgroups), their softmax states merged through the LDS at the end.  16x16x4 float32 MFMAs with the
 // query row on lane % 16 for both products, so that a lane's four scores are its B operands of the
 // second one.  Short sequences are a matter of latency: a wave holds the operands of its next tile while
@@ -72,16 +73,18 @@ __global__ __launch_bounds__(64 * NW) void k_f32_attn(F32AttnArgs<T, S> a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, g = lane >> 4;
-  const int heads = a.H * a.B, chunk = blockIdx.x & ~255u;
-  const int pos = chunk & 256 ? chunk + min((int)gridDim.x, chunk + 256) - 1 - (int)blockIdx.x : blockIdx.x;
-  const int xr = (int)gridDim.x / heads - 1 - pos / heads;   // long row blocks first
+  int h = blockIdx.x, b = blockIdx.y, xr = gridDim.z - 1 - blockIdx.z;   // long row blocks first
+  if (a.flat) {
+    const int heads = a.H * a.B, chunk = blockIdx.x & ~255u;
+    const int pos = chunk & 256 ? chunk + min((int)gridDim.x, chunk + 256) - 1 - (int)blockIdx.x : blockIdx.x;
+    xr = (int)gridDim.x / heads - 1 - pos / heads, h = pos % heads % a.H, b = pos % heads / a.H;
+  }
   int rb = xr, t_first = wv, t_step = NW;
   if (a.parts > 1) {
     rb = xr / a.parts;
     t_first += NW * (xr - rb * a.parts);
     t_step = NW * a.parts;
   }
-  const int h = pos % heads % a.H, b = pos % heads / a.H;
   const int Lq = a.Lq, Lk = a.Lk, i0 = a.row0 + rb * 16;
   const int kv = h / (a.H / a.Hkv);
   const int i_last = min(i0 + 15, Lq - 1), row = min(i0 + c, Lq - 1);

@@ -8,7 +8,7 @@ bool f32_attn_ok(const lisa_desc* d) { return d->Lq > 1 && d->dtype == LISA_F32 
 
 namespace {
 template <typename T, typename S, int NDK>
-int launch_attn(const lisa_desc* d, const F32AttnArgs<T, S>& a, hipStream_t st) {
+int launch_attn(const lisa_desc* d, F32AttnArgs<T, S> a, hipStream_t st) {
   const long long wgs = (long long)((a.n_rows + 15) / 16) * a.parts * d->H * d->B;
   if (wgs > 0x7fffffffLL) return LISA_ERR_UNSUPPORTED;
   // Eight waves where rows are long and workgroups few: the chain of a wave's tiles bounds them, with scores given (no K stream
@@ -16,7 +16,8 @@ int launch_attn(const lisa_desc* d, const F32AttnArgs<T, S>& a, hipStream_t st) 
   // 12.1 / 10.2, 2 x 504 14.2 / 10.9, 3 x 504 15.1 / 13.9, 3 x 700 (1056 workgroups) 19.8 / 20.2, 128 tokens 7.2 / 7.8; scores made,
   // 430 tokens (216) 14.8 / 13.4, 700 (352) 19.4 / 19.2, 2 x 504 (512) 16.7 / 17.7.
   const bool wide = sizeof(T) == 4 && a.out && d->Lk > 256 && wgs <= (a.given ? 4 : 1) * kComputeUnits;
-  const dim3 grid((unsigned)wgs);
+  a.flat = wgs > kComputeUnits || d->B > 65535;
+  const dim3 grid = a.flat ? dim3((unsigned)wgs) : dim3(d->H, d->B, (unsigned)((a.n_rows + 15) / 16 * a.parts));
   StageScope prof(a.given ? "k_f32_softmax_v" : "k_f32_attn", st);
   auto kern = a.given ? k_f32_attn<T, S, NDK, true, 4> : k_f32_attn<T, S, NDK, false, 4>;
   if constexpr (sizeof(T) == 4)
