@@ -425,6 +425,17 @@ typedef enum {
 int lisa_tune_set(int knob, int value);
 
 /*
+ * What the dispatch chooses for a call (host only, nothing is launched; for tests and reports, no call needs it).
+ *   LISA_CHOICE_STD_ORDER     out[0] = order of the workgroups of the standard layer's prefill kernel (with V): 0 = sequence by
+ *                             sequence, 1 = row groups of all sequences by length
+ * Returns the number of values written to `out` (room for LISA_CHOICE_MAX), or LISA_ERR_NULL / LISA_ERR_SHAPE (unknown
+ * `which`) / LISA_ERR_UNSUPPORTED (the call runs on other kernels).
+ */
+#define LISA_CHOICE_MAX 8
+typedef enum { LISA_CHOICE_STD_ORDER = 0 } lisa_choice;
+int lisa_launch_choice(const lisa_desc* desc, int which, int32_t* out);
+
+/*
  * Reference kernels for benchmarks (diagnostic; nothing of the method is computed).  The caller times
  * them with events on the stream it passes; bench.py reports their rates next to the roofline
  * fractions of the library's kernels, as what a plain kernel reaches on the chip at hand.

@@ -79,6 +79,7 @@ int run_split_prepare(const lisa_desc* d, const void* q_lr, const void* k_lr, co
 int run_split_scores(const lisa_desc* d, const void* prev, void* scores, void* workspace, int row0, int n_rows, hipStream_t st);
 int run_split_attn(const lisa_desc* d, const void* q, const void* k, const void* v, const float* given, bool given_tiled,
                    int row0, int n_rows, void* scores, void* out, hipStream_t st);
+int split_attn_order(const lisa_desc* d, int n_rows, int parts);
 FfnImage scores_mfma_image(const lisa_desc* d, const void* w1, const void* w2);
 int launch_scores_mfma_kernel(const lisa_desc* d, const ScoresMfmaArgs& a, hipStream_t st);
 

@@ -204,6 +204,23 @@ static bool f32_attn_takes(const lisa_desc* d, bool given, bool given_tiled, int
   return keys <= (given ? 48 : with_v && (long long)d->B * d->H >= 16384 ? 32 : 16);
 }
 
+// The order of k_split_attn's workgroups: 1 = row groups of all sequences by length, 0 = sequence by sequence.
+// By length where all workgroups run at once (two per compute unit, whose pair is then a long and a short one), where rows are
+// short, and where one and a half to two rounds of them come from three sequences or more.  Between these the first round's
+// shortest groups end together and the second round starts with all that is left; beyond them an XCD's L2 would hold the K and V of all
+// sequences at a time, not of one.  And only where a prompt's row groups differ in length: rows behind as many keys or more are
+// about equally long (softmax of 2 x 509 rows behind 1022 keys 69.6 us, by length 70.9).
+// Standard layer, sequence by sequence / by length in us: 2 x 201 tokens of 32 heads (448 workgroups) 13.3 / 10.9, 4 x 333 of 8 (352)
+// 15.2 / 12.6, 2 x 265 of 32 (576) 15.2 / 17.0, 2 x 301 of 32 (640) 19.0 / 21.0; short rows, 8 x 65 of 32 (768) 15.3 / 12.6, 4 x 99 of 40 (640)
+// 14.4 / 12.3; 4 x 777 of 8 (800) 33.7 / 30.1, 16 x 201 of 8 (896) 20.9 / 18.8, 5 x 227 of 24 (960) 23 / 21; 3 x 301 of 40 (1200) 26 / 28,
+// 16 x 129 rows of 229 keys, 32 heads (2560) 54.6 / 62.4, 8 x 777 of 40 (8000) 257 / 322, 32 x 777 of 40 1000 / 1705.
+int split_attn_order(const lisa_desc* d, int n_rows, int parts) {
+  const long long groups = (n_rows + SP_ROWS - 1) / SP_ROWS, wgs = groups * parts * d->H * d->B;
+  if (d->Lk - d->Lq >= d->Lq) return 0;
+  if (wgs <= 2 * kComputeUnits || (groups <= 4 && wgs <= 5 * kComputeUnits)) return 1;
+  return groups >= 6 && d->B >= 3 && wgs >= 3 * kComputeUnits && wgs <= 4 * kComputeUnits;
+}
+
 int run_split_attn(const lisa_desc* d, const void* q, const void* k, const void* v, const float* given, bool given_tiled,
                    int row0, int n_rows, void* scores, void* out, hipStream_t st) {
   if (f32_attn_takes(d, given, given_tiled, row0, n_rows, out)) return run_f32_attn(d, q, k, v, given, row0, n_rows, scores, out, st);
@@ -218,10 +235,7 @@ int run_split_attn(const lisa_desc* d, const void* q, const void* k, const void*
   // at least
   a.parts = out ? 1 : (int)std::max<long long>(1, std::min<long long>((d->Lk + 8 * SP_TK - 1) / (8 * SP_TK),
                                                                       kComputeUnits / ((long long)groups * d->H * d->B)));
-  // A prompt's row groups differ in length: by length, over all sequences (2 x 704 rows of 40 heads, standard layer, 42.5 -> 35 us,
-  // 3 x 501 52 -> 47.5).  Rows behind as many keys or more are about equally long: a sequence at a time, whose V the L2s then hold
-  // (softmax of 2 x 509 rows behind 1022 keys 69.6 us, by length 70.9).
-  a.by_length = d->Lk - d->Lq < d->Lq;
+  a.by_length = split_attn_order(d, n_rows, a.parts);
   const dim3 grid = a.by_length ? dim3(d->H, d->B, groups * a.parts) : dim3(d->H, groups * a.parts, d->B);
   StageScope prof(given ? "k_split_softmax_v" : "k_split_attn", st);
   if (given) k_split_attn<true, true><<<grid, 256, 0, st>>>(a);

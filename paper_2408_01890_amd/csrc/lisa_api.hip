@@ -1380,6 +1380,20 @@ int lisa_tune_set(int knob, int value) {
   return LISA_OK;
 }
 
+int lisa_launch_choice(const lisa_desc* desc, int which, int32_t* out) {
+  if (!desc || !out) return LISA_ERR_NULL;
+  switch (which) {
+    case LISA_CHOICE_STD_ORDER:
+      if (check_common(desc) != LISA_OK) return LISA_ERR_UNSUPPORTED;
+      if (std_prefill_fast_ok(desc)) out[0] = std_by_length(desc);
+      else if (desc->score_tiled) return LISA_ERR_UNSUPPORTED;
+      else if (split_attn_ok(desc)) out[0] = split_attn_order(desc, desc->Lq, 1);
+      else return LISA_ERR_UNSUPPORTED;
+      return 1;
+  }
+  return LISA_ERR_SHAPE;
+}
+
 int lisa_probe_hbm_read(const void* src, size_t bytes, void* sink, void* hip_stream) {
   if (!src || !sink) return LISA_ERR_NULL;
   if (!aligned16(src) || !aligned16(sink)) return LISA_ERR_ALIGN;

@@ -31,8 +31,9 @@ EXPORTS = (
     "lisa_profile_collect", "lisa_cache_fill", "lisa_project_qkv", "lisa_layer_prefill",
     "lisa_layer_offsets", "lisa_layer_decode", "lisa_tune_set", "lisa_attn_decode_static",
     "lisa_decode_stack", "lisa_stack_workspace_bytes", "lisa_scores_elems", "lisa_kd_huber",
-    "lisa_probe_hbm_read", "lisa_probe_hbm_write", "lisa_probe_mfma",
+    "lisa_probe_hbm_read", "lisa_probe_hbm_write", "lisa_probe_mfma", "lisa_launch_choice",
 )
+CHOICE_STD_ORDER = 0
 TUNE_PREFILL_GROUPS, TUNE_PREFILL_SPLIT, TUNE_PREFILL_PAIR, TUNE_STD_PAIR, TUNE_PROJECT_TN, TUNE_PREFILL_SLICES = range(6)
 
 
@@ -139,6 +140,8 @@ def _lib():
         h.lisa_decode_stack.restype = C.c_int
         h.lisa_stack_workspace_bytes.argtypes = [dp]
         h.lisa_stack_workspace_bytes.restype = sz
+        h.lisa_launch_choice.argtypes = [dp, C.c_int, C.POINTER(C.c_int32)]
+        h.lisa_launch_choice.restype = C.c_int
         h.lisa_tune_set.argtypes = [C.c_int, C.c_int]
         h.lisa_tune_set.restype = C.c_int
         h.lisa_profile_collect.argtypes = [C.POINTER(StageTime), C.c_int]
@@ -247,6 +250,17 @@ def _supported(desc_ref) -> int:
 
 def last_path() -> str:
     return _lib().lisa_last_path().decode()
+
+
+def launch_choice(desc: Desc, which: int):
+    """What the dispatch chooses for a call (see lisa_launch_choice): a tuple of numbers, None where other kernels run."""
+    out = (C.c_int32 * 8)()
+    n = _lib().lisa_launch_choice(C.byref(desc), which, out)
+    if n == -3:
+        return None
+    if n < 0:
+        raise LisaError(n, "lisa_launch_choice")
+    return tuple(out[:n])
 
 
 class tune:

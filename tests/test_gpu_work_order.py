@@ -19,7 +19,8 @@ def qkv(B, H, Hkv, L, dk, dtype, seed):
 @pytest.mark.parametrize("B,H,Hkv,L,tiled", [
     (2, 8, 2, 520, True), (3, 8, 8, 264, False),          # by length
     (5, 40, 40, 520, True), (9, 32, 8, 392, False),       # sequence by sequence: more than 640 row groups
-    (3, 8, 2, 333, False), (2, 16, 16, 97, False)])       # rows of odd length: 32 rows a workgroup
+    (3, 8, 2, 333, False), (2, 16, 16, 97, False),        # rows of odd length: 32 rows a workgroup, by length
+    (2, 32, 8, 265, False), (5, 8, 8, 777, False), (3, 40, 8, 301, False)])   # sequence by sequence, by length, and again not
 def test_batch_equals_its_sequences(B, H, Hkv, L, tiled):
     q, k, v = qkv(B, H, Hkv, L, 128, torch.bfloat16, L)
     vis = torch.ones(L, L, dtype=torch.bool, device=DEV).tril()

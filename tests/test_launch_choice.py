@@ -1,0 +1,18 @@
+"""What the dispatch chooses on both sides of its lines (host only): each line was drawn where the two sides' times cross, and
+the sizes here are ones at which the other side was measured slower."""
+import pytest
+
+from paper_2408_01890_amd import lisa
+
+
+def std(B, H, Hkv, Lq, past=0, **kw):
+    return lisa.make_desc(lisa.BF16, B, H, Hkv, Lq, Lq + past, 128, **kw)
+
+
+@pytest.mark.parametrize("B,H,Lq,past,order", [
+    (2, 32, 201, 0, 1), (4, 8, 333, 0, 1), (2, 32, 509, 1022, 0),                           # all at once; rows behind more keys
+    (2, 32, 265, 0, 0), (2, 32, 301, 0, 0), (3, 32, 199, 0, 0), (8, 32, 65, 0, 1), (4, 40, 99, 0, 1),
+    (4, 8, 777, 0, 1), (5, 24, 227, 0, 1), (2, 32, 395, 0, 0), (3, 40, 301, 0, 0),
+    (16, 32, 129, 100, 0), (8, 32, 501, 0, 0), (8, 40, 777, 0, 0), (32, 40, 777, 0, 0)])
+def test_order_of_ragged_standard_layers(B, H, Lq, past, order):
+    assert lisa.launch_choice(std(B, H, H, Lq, past), lisa.CHOICE_STD_ORDER) == (order,)
