@@ -427,7 +427,7 @@ int lisa_tune_set(int knob, int value);
 /*
  * What the dispatch chooses for a call (host only, nothing is launched; for tests and reports, no call needs it).
  *   LISA_CHOICE_STD_ORDER     out[0] = order of the workgroups of the standard layer's prefill kernel (with V): 0 = sequence by
- *                             sequence, 1 = row groups of all sequences by length
+ *                             sequence, 1 = row groups of all sequences by length, 2 = the same, every other 256 backwards
  * Returns the number of values written to `out` (room for LISA_CHOICE_MAX), or LISA_ERR_NULL / LISA_ERR_SHAPE (unknown
  * `which`) / LISA_ERR_UNSUPPORTED (the call runs on other kernels).
  */

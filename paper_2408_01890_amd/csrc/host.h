@@ -63,6 +63,7 @@ int run_stack_chained(const lisa_desc* d, const lisa_stack_layer* layers, int n_
 bool f32_attn_ok(const lisa_desc* d);
 int run_f32_attn(const lisa_desc* d, const void* q, const void* k, const void* v, const float* given, int row0, int n_rows,
                  void* scores, void* out, hipStream_t st);
+int f32_attn_order(const lisa_desc* d, int n_rows, int parts);
 int f32_chunk_rows(const lisa_desc* d);
 size_t f32_chunk_bytes(const lisa_desc* d);
 bool f32_scores_ok(const lisa_desc* d);

@@ -49,19 +49,19 @@ struct F32AttnArgs {
   S* scores;              // [B,H,Lq,Lk] or null
   void* out;              // [B,Lq,H,DK] (float where out_f32, else T) or null
   int B, H, Hkv, Lq, Lk, causal, out_f32;
-  int flat;               // more workgroups than compute units: their order counts (a division or four cost 0.25 us a launch)
+  int order;              // of the workgroups, see f32_attn_order()
   int row0, n_rows;       // query rows of this launch (row0 a multiple of 16)
   int parts;              // workgroups that the tiles of a row block are dealt to (1 unless scores only)
   float scale;
 };
 
-// grid (H, B, parts ceil(n_rows / 16)), or all of it in x (flat), block 64 NW: 16 query rows of one head, the 16-key tiles dealt to the NW
+// grid (parts ceil(n_rows / 16), H, B), (H, B, parts ceil(n_rows / 16)) or all of it in x (order 0, 1, 2), block 64 NW: 16 query rows of one head, the 16-key tiles dealt to the NW
 // waves (scores only: of `parts` workgroups), their softmax states merged through the LDS at the end.  16x16x4 float32 MFMAs with the
 // query row on lane % 16 for both products, so that a lane's four scores are its B operands of the
 // second one.  Short sequences are a matter of latency: a wave holds the operands of its next tile while
 // it works on this one, and nothing passes through the LDS before the end.
-// The workgroups are ordered by length, long ones first, every other 256 of them backwards: a compute unit has numbers i, i + 256,
-// .. where all run at once, and with the row blocks as the fastest index these were equally long (two sequences of 504 tokens,
+// Order 2 has them by length over all heads, long ones first, every other 256 of them backwards: a compute unit has numbers i, i + 256,
+// .. where all run at once, and with the row blocks as the fastest index these are equally long (two sequences of 504 tokens,
 // 8 heads: 18.4 -> 14.7 us, three of 504 25 -> 19).
 // The contraction over the features is numbered so that a lane's operands are pieces of four: step s of
 // piece i takes feature 16 i + 4 g + s.  For P V the 16 rows of output block i are the features 4 m + i.
@@ -74,7 +74,9 @@ __global__ __launch_bounds__(64 * NW) void k_f32_attn(F32AttnArgs<T, S> a) {
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, g = lane >> 4;
   int h = blockIdx.x, b = blockIdx.y, xr = gridDim.z - 1 - blockIdx.z;   // long row blocks first
-  if (a.flat) {
+  if (a.order == 0) {
+    xr = gridDim.x - 1 - blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+  } else if (a.order == 2) {
     const int heads = a.H * a.B, chunk = blockIdx.x & ~255u;
     const int pos = chunk & 256 ? chunk + min((int)gridDim.x, chunk + 256) - 1 - (int)blockIdx.x : blockIdx.x;
     xr = (int)gridDim.x / heads - 1 - pos / heads, h = pos % heads % a.H, b = pos % heads / a.H;

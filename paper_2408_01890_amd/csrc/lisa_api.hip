@@ -1388,6 +1388,7 @@ int lisa_launch_choice(const lisa_desc* desc, int which, int32_t* out) {
       if (std_prefill_fast_ok(desc)) out[0] = std_by_length(desc);
       else if (desc->score_tiled) return LISA_ERR_UNSUPPORTED;
       else if (split_attn_ok(desc)) out[0] = split_attn_order(desc, desc->Lq, 1);
+      else if (f32_attn_ok(desc)) out[0] = f32_attn_order(desc, desc->Lq, 1);
       else return LISA_ERR_UNSUPPORTED;
       return 1;
   }

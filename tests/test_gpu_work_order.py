@@ -35,7 +35,7 @@ def test_batch_equals_its_sequences(B, H, Hkv, L, tiled):
 
 
 @pytest.mark.parametrize("B,H,Hkv,L,dk", [(1, 4, 2, 255, 64), (1, 4, 2, 273, 64), (2, 8, 8, 257, 64), (3, 8, 4, 401, 64),
-                                          (2, 4, 4, 300, 128), (7, 8, 8, 305, 64)])
+                                          (2, 4, 4, 300, 128), (7, 8, 8, 305, 64), (9, 32, 8, 129, 64)])
 def test_float32_rows_in_every_order(B, H, Hkv, L, dk):
     q, k, v = qkv(B, H, Hkv, L, dk, torch.float32, L + B)
     vis = torch.ones(L, L, dtype=torch.bool, device=DEV).tril()

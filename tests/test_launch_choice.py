@@ -16,3 +16,11 @@ def std(B, H, Hkv, Lq, past=0, **kw):
     (16, 32, 129, 100, 0), (8, 32, 501, 0, 0), (8, 40, 777, 0, 0), (32, 40, 777, 0, 0)])
 def test_order_of_ragged_standard_layers(B, H, Lq, past, order):
     assert lisa.launch_choice(std(B, H, H, Lq, past), lisa.CHOICE_STD_ORDER) == (order,)
+
+
+@pytest.mark.parametrize("B,H,Lq,dk,order", [
+    (1, 8, 128, 64, 1), (2, 8, 504, 64, 2), (8, 16, 512, 64, 2), (3, 32, 1000, 128, 2), (8, 32, 128, 128, 2),
+    (8, 16, 1500, 64, 0), (13, 12, 410, 64, 0), (16, 32, 600, 64, 0), (8, 32, 700, 128, 0), (8, 32, 1000, 128, 0), (1000, 32, 9, 128, 0)])
+def test_order_of_float32_standard_layers(B, H, Lq, dk, order):
+    d = lisa.make_desc(lisa.F32, B, H, H, Lq, Lq, dk)
+    assert lisa.launch_choice(d, lisa.CHOICE_STD_ORDER) == (order,)
