@@ -413,7 +413,8 @@ const char* lisa_last_path(void);
  *   LISA_TUNE_PREFILL_SPLIT   key splits per row block: 1, 2 or 4 (other values are ignored)
  *   LISA_TUNE_PREFILL_PAIR    1: a workgroup takes a long and a short unit, 0: one unit
  *   LISA_TUNE_STD_PAIR        the same for the standard layer's prefill kernel
- *   LISA_TUNE_PROJECT_TN      tile width of the projection kernel: 192 or 256
+ *   LISA_TUNE_PROJECT_TN      tile shape of the projection kernel: 0 .. 6 (see lisa_project_choice()); 192 and 256 are
+ *                             shapes 1 and 0
  *   LISA_TUNE_PREFILL_SLICES  slices of 16 query rows per workgroup of the fused prefill kernel:
  *                             1, 2 or 4 (where the shape has them: ReLU, 33..96 hidden units)
  * Returns LISA_OK, or LISA_ERR_SHAPE for an unknown knob.
@@ -434,6 +435,9 @@ int lisa_tune_set(int knob, int value);
 #define LISA_CHOICE_MAX 8
 typedef enum { LISA_CHOICE_STD_ORDER = 0 } lisa_choice;
 int lisa_launch_choice(const lisa_desc* desc, int which, int32_t* out);
+/* The tile shape that lisa_project_qkv() takes: 0 = 256 x 256, 1 = 256 x 192, 2 = 128 x 256, 3 = 128 x 192 in a single round of
+ * workgroups, 4 = 128 x 192 in several, 5 = 128 x 128, 6 = 128 x 64; LISA_ERR_UNSUPPORTED where it runs on other kernels. */
+int lisa_project_choice(const lisa_proj_desc* desc);
 
 /*
  * Reference kernels for benchmarks (diagnostic; nothing of the method is computed).  The caller times

@@ -844,6 +844,45 @@ int lisa_cache_fill(const lisa_desc* d, const void* k_lr, const void* v, void* k
   return rc;
 }
 
+// Tile shape of k_project_mfma: the one of least cost, a sum of rounds of workgroups and of tiles per compute unit (a round's
+// time grows with how full it is).  The weights were set on one half of 181 problems, 129 - 9000 tokens, d = 2048 - 5120, of the LLaMA2-7B,
+// LLaMA3-8B, LLaMA2-13B and two smaller shapes, each with weights from HBM and with weights that the caches hold.  On the other half
+// the choice is 0.4 % behind the fastest shape on average, and no more than 2.4 % slower than 256 wide tiles and 128 x 64 ones alone
+// where the weights come from HBM (9 % faster on average).  A full single round of 256 x 192 stays with them (LLaMA2-7B, 2048 tokens,
+// HBM / caches, us: 110 / 100, 128 x 192 in two rounds 112 / 107); where such a round is half full, 128 x 192 in two rounds gains from HBM what
+// it loses from the caches (1400 tokens 101 / 84, 90 / 92).  With 256 wide tiles and 128 x 64 ones alone and with this choice, HBM: LLaMA2-7B, 777
+// tokens 65 / 54, 2816 197 / 168; LLaMA3-8B, 2204 63 / 52, 2596 83 / 56; LLaMA2-13B, 640 90 / 67, 2304 245 / 216.
+struct ProjShape {
+  int tm, tn, round, fill;
+  bool single;                                              // for a single round only
+};
+constexpr ProjShape kProjShapes[] = {{256, 256, 111, 33, false}, {256, 192, 75, 55, false}, {128, 256, 71, 22, false}, {128, 192, 53, 1, true},
+                                     {128, 192, 64, 12, false},   {128, 128, 51, 2, false},  {128, 64, 23, 0, true}};
+constexpr int kNumProjShapes = sizeof(kProjShapes) / sizeof(kProjShapes[0]);
+
+static bool project_fast(const lisa_proj_desc* d) {
+  return d->dtype == LISA_BF16 && d->d_model % PJ_TK == 0 && d->r <= PJ_HEADW && d->d_k % 32 == 0;
+}
+constexpr int kProjFewRows = 128;      // token rows up to which the kernels that stream the weights once take over
+static long long project_columns(const lisa_proj_desc* d) {
+  return (long long)PJ_HEADW * (d->H + d->Hkv) + (long long)d->Hkv * d->d_k;
+}
+
+static int project_shape(long long M, long long n_virtual) {
+  const int forced = g_tune[LISA_TUNE_PROJECT_TN];           // (tests)
+  if (forced >= 0 && forced < kNumProjShapes) return forced;
+  if (forced == 192 || forced == 256) return forced == 192;
+  int best = 0;
+  double least = 1e300;
+  for (int i = 0; i < kNumProjShapes; ++i) {
+    const ProjShape& s = kProjShapes[i];
+    const long long t = ((M + s.tm - 1) / s.tm) * ((n_virtual + s.tn - 1) / s.tn);
+    const double cost = (double)s.round * ((t + kComputeUnits - 1) / kComputeUnits) + (double)s.fill * t / kComputeUnits;
+    if (cost < least && !(s.single && t > kComputeUnits)) least = cost, best = i;
+  }
+  return best;
+}
+
 // `ffn`: an FFN whose weights the launch puts in operand order on the side, where it is one of the few-row
 // kernels (then *ffn_done is set).
 static int project_qkv(const lisa_proj_desc* d, const void* x, const void* w, void* q_lr, void* k_lr, void* v,
@@ -872,10 +911,9 @@ static int project_qkv(const lisa_proj_desc* d, const void* x, const void* w, vo
   a.freq_log2 = a.rope ? -2.0 * std::log2((double)d->rope_theta) / d->r : 0.0;
   const long long M = (long long)d->B * d->L;
   const long long n_real = (long long)(d->H + d->Hkv) * d->r + (long long)d->Hkv * d->d_k;
-  const bool fast = d->dtype == LISA_BF16 && d->d_model % PJ_TK == 0 && d->r <= PJ_HEADW &&
-                    d->d_k % 32 == 0;
+  const bool fast = project_fast(d);
   const char* path;
-  const long long col_blocks = ((long long)PJ_HEADW * (d->H + d->Hkv) + (long long)d->Hkv * d->d_k + 31) / 32;
+  const long long n_virtual = project_columns(d), col_blocks = (n_virtual + 31) / 32;
   if (fast && M <= 4 && col_blocks <= kComputeUnits / 2 && d->d_model % 512 == 0 && (!a.rope || d->r % 2 == 0)) {
     // one to four token rows where the blocks of 32 columns would leave half of the compute units or more without work: a
     // wave per pair of weight rows.  One layer from the hidden states, LLaMA3-8B heads (73 blocks), 1 / 2 / 4 users, 300
@@ -893,9 +931,8 @@ static int project_qkv(const lisa_proj_desc* d, const void* x, const void* w, vo
     else if (M == 2) k_project_rows<2><<<grid, 256, 0, st>>>(a);
     else k_project_rows<4><<<grid, 256, 0, st>>>(a);
     path = "project_skinny";
-  } else if (fast && M <= 128) {
+  } else if (fast && M <= kProjFewRows) {
     // a decode step: few rows, bound by one pass over the weights
-    const long long n_virtual = (long long)PJ_HEADW * (d->H + d->Hkv) + (long long)d->Hkv * d->d_k;
     const int mb = (int)((M + 31) / 32);
     // both operands through the LDS (whole-line loads) where the reduction axis splits into whole
     // chunks per wave and the staging regions fit
@@ -921,31 +958,8 @@ static int project_qkv(const lisa_proj_desc* d, const void* x, const void* w, vo
     if (lrc) return lrc;
     path = "project_skinny";
   } else if (fast) {
-    const long long n_virtual = (long long)PJ_HEADW * (d->H + d->Hkv) + (long long)d->Hkv * d->d_k;
-    // Tile shape: the one of least cost, a sum of rounds of workgroups and of tiles per compute unit (a round's time grows with
-    // how full it is).  The weights are set so that the choice is at most 2.3 % behind the fastest shape in 111 problems,
-    // 129 - 6500 tokens of the LLaMA2-7B, LLaMA3-8B and LLaMA2-13B shapes, weights from HBM.  With 256 wide tiles
-    // and 128 x 64 ones alone and with this choice (us): LLaMA2-7B, 777 tokens 64 / 52, 1024 70 / 55, 2596 163 / 140;
-    // LLaMA3-8B, 2204 63 / 52, 2596 83 / 56, 4300 148 / 97; LLaMA2-13B, 640 90 / 67, 1101 125 / 113.
-    struct Shape {
-      int tm, tn, round, fill;
-      bool single;                                          // for a single round only
-    };
-    static const Shape shapes[] = {{256, 256, 111, 33, false}, {256, 192, 87, 67, false}, {128, 256, 71, 22, false}, {128, 192, 53, 1, true},
-                                   {128, 192, 64, 0, false},   {128, 128, 51, 2, false},  {128, 64, 23, 0, true}};
-    auto tiles_of = [&](const Shape& s) { return ((M + s.tm - 1) / s.tm) * ((n_virtual + s.tn - 1) / s.tn); };
-    int best = 0;
-    double least = 1e300;
-    for (int i = 0; i < 7; ++i) {
-      const long long t = tiles_of(shapes[i]);
-      const double cost = (double)shapes[i].round * ((t + kComputeUnits - 1) / kComputeUnits) + (double)shapes[i].fill * t / kComputeUnits;
-      if (cost < least && !(shapes[i].single && t > kComputeUnits)) least = cost, best = i;
-    }
-    {                                                       // tests force either of the large ones
-      const int v = g_tune[LISA_TUNE_PROJECT_TN];
-      if (v == 192 || v == 256) best = v == 192;
-    }
-    const Shape& shape = shapes[best];
+    const int best = project_shape(M, n_virtual);
+    const ProjShape& shape = kProjShapes[best];
     a.n_m = (int)((M + shape.tm - 1) / shape.tm);
     a.n_n = (int)((n_virtual + shape.tn - 1) / shape.tn);
     const long long n_tiles = (long long)a.n_m * a.n_n;
@@ -998,6 +1012,13 @@ static int project_qkv(const lisa_proj_desc* d, const void* x, const void* w, vo
   int rc = check_launch();
   if (rc == LISA_OK) g_path = path;
   return rc;
+}
+
+int lisa_project_choice(const lisa_proj_desc* d) {
+  if (!d) return LISA_ERR_NULL;
+  if (d->B <= 0 || d->L <= 0 || d->d_model <= 0 || d->H <= 0 || d->Hkv <= 0 || d->r <= 0 || d->d_k <= 0) return LISA_ERR_SHAPE;
+  const long long M = (long long)d->B * d->L;
+  return project_fast(d) && M > kProjFewRows ? project_shape(M, project_columns(d)) : LISA_ERR_UNSUPPORTED;
 }
 
 int lisa_project_qkv(const lisa_proj_desc* d, const void* x, const void* w, void* q_lr, void* k_lr, void* v,

@@ -32,6 +32,7 @@ EXPORTS = (
     "lisa_layer_offsets", "lisa_layer_decode", "lisa_tune_set", "lisa_attn_decode_static",
     "lisa_decode_stack", "lisa_stack_workspace_bytes", "lisa_scores_elems", "lisa_kd_huber",
     "lisa_probe_hbm_read", "lisa_probe_hbm_write", "lisa_probe_mfma", "lisa_launch_choice",
+    "lisa_project_choice",
 )
 CHOICE_STD_ORDER = 0
 TUNE_PREFILL_GROUPS, TUNE_PREFILL_SPLIT, TUNE_PREFILL_PAIR, TUNE_STD_PAIR, TUNE_PROJECT_TN, TUNE_PREFILL_SLICES = range(6)
@@ -142,6 +143,8 @@ def _lib():
         h.lisa_stack_workspace_bytes.restype = sz
         h.lisa_launch_choice.argtypes = [dp, C.c_int, C.POINTER(C.c_int32)]
         h.lisa_launch_choice.restype = C.c_int
+        h.lisa_project_choice.argtypes = [C.POINTER(ProjDesc)]
+        h.lisa_project_choice.restype = C.c_int
         h.lisa_tune_set.argtypes = [C.c_int, C.c_int]
         h.lisa_tune_set.restype = C.c_int
         h.lisa_profile_collect.argtypes = [C.POINTER(StageTime), C.c_int]
@@ -261,6 +264,13 @@ def launch_choice(desc: Desc, which: int):
     if n < 0:
         raise LisaError(n, "lisa_launch_choice")
     return tuple(out[:n])
+
+
+def project_choice(dtype, B, L, d_model, H, Hkv, r, d_k):
+    """Tile shape of the projection kernel (see lisa_project_choice), None where other kernels run."""
+    code = {torch.float32: F32, torch.bfloat16: BF16}[dtype]
+    n = _lib().lisa_project_choice(C.byref(ProjDesc(code, B, L, d_model, H, Hkv, r, d_k, 0, 0, 0, 0.0)))
+    return n if n >= 0 else None
 
 
 class tune:
