@@ -12,7 +12,7 @@ DEV = "cuda"
 EDGES = [  # B, H, Hkv, L, d_model, d_k, r, theta, pos0, dim_major, extra
     (1, 8, 2, 129, 128, 128, 22, 10000.0, 0, True, 7), (1, 3, 3, 257, 64, 32, 7, None, 5, False, 0),
     (3, 33, 11, 85, 192, 64, 32, 500000.0, 0, True, 1),
-    (1, 64, 64, 300, 192, 128, 32, None, 0, False, 0)]      # more tiles than compute units: two buffers
+    (1, 64, 64, 300, 192, 128, 32, None, 0, False, 0)]      # more small tiles than compute units: 128 x 192 instead
 
 
 @pytest.mark.parametrize("case", PROJ_MFMA + EDGES, ids=lambda c: f"B{c[0]}H{c[1]}-{c[2]}L{c[3]}d{c[4]}r{c[6]}")
