@@ -142,7 +142,10 @@ size_t lisa_scores_elems(const lisa_desc* desc);
  *   out         [B,Lq,H,d_k]   out  concatenated heads softmax(A_n) V, dtype
  *   scores_out  [B,H,Lq,Lk]    out  A_n, score type; required iff write_scores = 1; must not
  *                                   alias scores_prev
- *   workspace                  scratch of at least lisa_workspace_bytes(desc, LISA_WS_PREFILL)
+ *   workspace                  scratch of at least lisa_workspace_bytes(desc, LISA_WS_PREFILL): ask for each shape, the
+ *                                   need does not grow steadily with the lengths.  bf16 problems of few row blocks deal
+ *                                   the keys of a block to two or four shares, whose partial results take up to 68 MB
+ *                                   (136 MB: SiLU with 16 or 32 heads; 204 MB: 24 heads) that longer prompts do not need
  *                              bytes (may be NULL when that is 0); contents undefined after.
  *                              The fused kernels keep A_n in float32 registers up to the
  *                              softmax and the generic kernels stage it here as float32; the
@@ -429,11 +432,13 @@ int lisa_tune_set(int knob, int value);
  * What the dispatch chooses for a call (host only, nothing is launched; for tests and reports, no call needs it).
  *   LISA_CHOICE_STD_ORDER     out[0] = order of the workgroups of the standard layer's prefill kernel (with V): 0 = sequence by
  *                             sequence, 1 = row groups of all sequences by length, 2 = the same, every other 256 backwards
+ *   LISA_CHOICE_PREFILL       out[0..4] = geometry of the fused prefill kernel: slices of 16 query rows per workgroup, head
+ *                             groups, key shares per row block, 1 where a workgroup takes two units, neighbouring slots per XCD
  * Returns the number of values written to `out` (room for LISA_CHOICE_MAX), or LISA_ERR_NULL / LISA_ERR_SHAPE (unknown
  * `which`) / LISA_ERR_UNSUPPORTED (the call runs on other kernels).
  */
 #define LISA_CHOICE_MAX 8
-typedef enum { LISA_CHOICE_STD_ORDER = 0 } lisa_choice;
+typedef enum { LISA_CHOICE_STD_ORDER = 0, LISA_CHOICE_PREFILL = 1 } lisa_choice;
 int lisa_launch_choice(const lisa_desc* desc, int which, int32_t* out);
 /* The tile shape that lisa_project_qkv() takes: 0 = 256 x 256, 1 = 256 x 192, 2 = 128 x 256, 3 = 128 x 192 in a single round of
  * workgroups, 4 = 128 x 192 in several, 5 = 128 x 128, 6 = 128 x 64; LISA_ERR_UNSUPPORTED where it runs on other kernels. */

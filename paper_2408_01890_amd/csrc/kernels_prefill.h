@@ -53,14 +53,14 @@ constexpr int PF_ROWS = 16;       // query rows per workgroup
 // (see the grid of k_lisa_prefill_fused), and the largest number that leaves the fullest XCD (nearly) the fewest workgroups.  With
 // 32 / NG throughout, the 75 pairs of units of 2400 rows made 5 chunks of 16 for 8 XCDs, or 10 of 8; with chunks of one slot, 5 x 1088
 // tokens of the LLaMA2-7B shape take 284 us instead of 249, for want of neighbours that read the same K_LR and V.
-inline int pf_chunk(int ng, long long n_slots, int B, long long* most = nullptr) {
-  int best = 1;
-  long long least = -1;
+// (B * H and the rows of a sequence are below 2^16: the counts fit 32 bits)
+inline int pf_chunk(int ng, int n_slots, int B, int* most) {
+  int best = 1, least = -1;
   for (int c = 32 / ng > 0 ? 32 / ng : 1; c >= 1; --c) {
-    const long long load = ((n_slots + c - 1) / c * B + 7) / 8 * c;
-    if (least < 0 || 16 * load <= 15 * least) least = load, best = c;
+    const int load = ((n_slots + c - 1) / c * B + 7) / 8 * c;
+    if (least < 0 || load <= least - (least + 15) / 16) least = load, best = c;   // (a sixteenth fewer)
   }
-  if (most) *most = least * ng;
+  *most = least * ng;
   return best;
 }
 constexpr int PF_TK = 32;         // keys per tile
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(NW * 64) void k_lisa_prefill_fused(PrefillArgs a) {
   const int group = H / a.Hkv;
   const float LOG2E = 1.4426950408889634f;
   const int n_units = (Lq + R - 1) / R * a.split;
-  // workgroup id -> (XCD, chunk of PF_CHUNK(NG) neighbouring slots of one sequence, slot in the chunk, head group)
+  // workgroup id -> (XCD, chunk of a.chunk neighbouring slots of one sequence, slot in the chunk, head group)
   const int n_slots = a.pair ? (n_units + 1) / 2 : n_units;
   int slot, b, grp;
   {

@@ -487,54 +487,79 @@ bool prefill_fused_ok(const lisa_desc* d) {
 
 
 // Geometry of the fused prefill launch: row slices per workgroup (R = 16 * slices query rows), head
-// groups, key splits, paired units.
+// groups, key splits, paired units, neighbouring slots per XCD.
 //   slices  A workgroup of R rows fetches each K_LR / V tile once for all its rows; needs one head per wave (groups of
 //           8 heads) and a ReLU layer with 33..96 hidden units.
 //   groups  H = 32 (16) runs as two (one) groups of 16 heads, two heads per wave, or as four (two)
 //           groups of 8, one head per wave: the first FFN layer is computed once more per extra
 //           group, but there are more units and row slices become possible.
-//   split   small problems have too few units to fill the chip and their longest unit (the last
-//           row block) sets the run time: the key tiles of a row block are dealt to 2 units.
+//   split   few units leave compute units idle and the longest one (the last row block, or any of a few rows behind many
+//           keys) sets the run time: the key tiles of a row block are dealt to 2 or 4 units.
 //   pair    two units (a long and a short one) per workgroup: equal work per workgroup, FFN weights staged once for both.
+//   chunk   see pf_chunk()
 // prefill_cost() weighs them against each other.
 struct PrefillGeom {
-  int slices, groups, split, pair;
+  int slices, groups, split, pair, chunk;
 };
 
 bool prefill_slices_ok(const lisa_desc* d) {
   return d->act == LISA_ACT_RELU && d->F > 32 && d->F <= 96 && (d->H == 8 || d->H == 16 || d->H == 32 || d->H == 40);
 }
 
+// Key tiles of all row blocks of R rows (R = 16, 32 or 64): block j ends before row e = min((j + 1) R, Lq) and sees
+// ceil((e + shift) / 32) of them.
+long long prefill_tiles(const lisa_desc* d, int R) {
+  const long long n = (d->Lq + R - 1) / R, last = (d->Lk + PF_TK - 1) / PF_TK, shift = d->Lk - d->Lq;
+  if (!d->causal) return n * last;
+  const long long even = (shift + PF_TK - 1) / PF_TK, m = n - 1;   // (all but the last block are whole)
+  if (R >= PF_TK) return R / PF_TK * (m * (m + 1) / 2) + m * even + last;
+  const long long odd = (shift + R + PF_TK - 1) / PF_TK, h = m / 2;   // blocks 1, 3, .. end at a multiple of 32 rows
+  return (h * (h + 1) / 2 + h * even) + ((m - h) * (m - h - 1) / 2 + (m - h) * odd) + last;
+}
+
+// Key tiles of a row block that ends before row `rows`.
+int prefill_block_tiles(const lisa_desc* d, int rows) {
+  return ((d->causal ? std::min(rows, d->Lq) + d->Lk - d->Lq : d->Lk) + PF_TK - 1) / PF_TK;
+}
+
 // What a launch of a geometry takes, in us, up to what all of them have in common: the workgroups of the fullest XCD on its 32
 // compute units, `start` for each (its Q_LR rows, the first tiles on their way) and `step` for 16 rows x 32 keys, which grows with
-// how full the chip is.  A workgroup of two units (a long and a short one, equal work for all) has kPair more of the former; single
-// units, long ones first, fill the units unevenly by about kTail of one.  Key shares pay a combine pass and the bytes of the
-// partial results.  The numbers are set over 118 problems, 224 - 7552 tokens and 1 - 8 sequences of the LLaMA2-7B, LLaMA3-8B and
-// LLaMA2-13B shapes on tiled scores, all 6 - 10 geometries timed: the choice is 0.7 % behind the fastest one on average, 9 % at most.
-// Before, counts of units alone decided (us, then / now): LLaMA2-7B, 768 tokens 69 / 51, 3 x 1312 299 / 185; LLaMA3-8B, 1248
-// 110 / 78, 2720 345 / 214, 4 x 640 106 / 66; LLaMA2-13B, 640 79 / 61, 3 x 512 124 / 76; four key shares are never the best one.
-double prefill_cost(const lisa_desc* d, const PrefillGeom& g, long long tiles_all, int tiles_max) {
+// the blocks of the FFN and with how full the chip is.  A workgroup of two units (a long and a short one, equal work for all) has
+// kPair more of the former; single units, long ones first, fill the units unevenly by about kTail of one, and the first XCD,
+// whose chunks are the longer ones, has more of the work: about kSpread of what the lengths of its units say.  Key shares pay a
+// combine pass and the bytes of the partial results.  The numbers are set over 1293 problems, all 6 - 14 geometries timed: prompts of
+// the LLaMA2-7B, LLaMA3-8B and LLaMA2-13B shapes, 2 - 1024 rows behind 200 - 16000 keys, 8 - 40 heads, 8 - 128 hidden units, ReLU and SiLU, causal
+// or not, both score layouts.  Set on one half alone, the choice on the other half is behind the fastest geometry by (in brackets: counts of
+// units alone, which decided before) 0.7 % (16) on average for prompts of the three models, 2 % (19) in the row-major layout, 2 % (8) for
+// few rows behind many keys, 2 % (17) for other head counts and widths, 2.5 % (21) with all keys visible, 6.6 % (15) with SiLU, mostly for
+// the head groups that it does not try.  Of all, 2 are more than 3 % slower than with the counts, none more than 6 %.
+double prefill_cost(const lisa_desc* d, const PrefillGeom& g, long long tiles_all, int load) {
   struct Form {
-    double start, step, full;
+    double start, base, ffn, full;
   };
-  constexpr double kPair = 2.3, kTail = 0.465, kCombine = 4.0, kPerMB = 0.373;
-  const bool heavy = d->H > 32 || d->F > 64;
+  static constexpr Form kForms[] = {{4.51, 1.42, 0.271, 0.337}, {2.93, 1.53, 0.191, 0.447},   // a head per wave; two slices
+                                    {5.09, 2.13, 0.236, 0.127}, {4.33, 1.87, 0.506, 0.668},   // two that share K and V; two
+                                    {8.65, 4.51, 0.322, 1.28}};                               // three
+  constexpr double kPair = 4.32, kTail = 0.522, kSpread = 0.364, kCombine = 3.85, kPerMB = 0.406, kSilu = 0.736;
   const int hpw = d->H / (8 * g.groups);                    // heads per wave
-  Form f = hpw == 1 ? (g.slices > 1 ? (heavy ? Form{8.6, 2.33, 0.4} : Form{7.8, 1.8, 0.28})
-                                    : (heavy ? Form{7.0, 2.5, 0.42} : Form{4.2, 1.87, 0.26}))
-           : (d->H / d->Hkv) % hpw == 0 && hpw != 3 ? Form{5.9, 1.98, 0.54} : Form{5.2, 2.32, 1.15};
-  if (hpw > 2) f.step *= 0.5 * hpw, f.full *= 0.5 * hpw;
-  const long long rbs = (d->Lq + 16 * g.slices - 1) / (16 * g.slices), units = rbs * g.split;
-  long long load;
-  pf_chunk(g.groups, g.pair ? (units + 1) / 2 : units, d->B, &load);
+  const Form& f = kForms[hpw == 1 ? g.slices > 1 : hpw == 3 ? 4 : (d->H / d->Hkv) % hpw == 0 ? 2 : 3];
+  const int R = PF_ROWS * g.slices, fs = (d->F + 31) / 32, units = (d->Lq + R - 1) / R * g.split, tiles_max = prefill_block_tiles(d, d->Lq);
   const double mean = (double)tiles_all * g.slices / units, per_unit = load / 32.0;
-  const double step = f.step + f.full * std::min(1.0, per_unit);
+  const double step = f.base + f.ffn * fs * ((d->H + 31) / 32) + (d->act == LISA_ACT_SILU ? kSilu * fs : 0.) + f.full * std::min(1.0, per_unit);
   const int longest = (tiles_max / (2 * g.split) * 2 + std::min(tiles_max % (2 * g.split), 2)) * g.slices;
   double us;
   // (equal workgroups go in rounds; over many of them a last one that is not full is made up for)
-  if (g.pair) us = (per_unit > 8 ? per_unit : std::ceil(per_unit)) * (f.start + kPair + step * 2 * mean);
-  else if (load <= 32) us = f.start + step * longest;
-  else us = std::max(f.start + step * longest, f.start * per_unit + step * mean * (per_unit + kTail));
+  if (g.pair) {
+    us = (per_unit > 8 ? per_unit : std::ceil(per_unit)) * (f.start + kPair + step * 2 * mean);
+  } else if (load <= 32) {
+    us = f.start + step * longest;
+  } else {
+    // mean length of the first XCD's units: chunks 0, 8, ..
+    const int rounds = ((units + g.chunk - 1) / g.chunk * d->B + 7) / 8;
+    const double at = std::min(1.0, (4.0 * (rounds - 1) / d->B + 0.5) * g.chunk / units), per = (double)g.slices / g.split;
+    const double first = std::max(mean, per * (tiles_max - (tiles_max - prefill_block_tiles(d, R)) * at));
+    us = std::max(f.start + step * longest, f.start * per_unit + step * (mean + kSpread * (first - mean)) * (per_unit + kTail));
+  }
   // (over many rounds single units lose the neighbours that read the same tiles: 4 x 8192 tokens of LLaMA3-8B, 16 rounds, 5.89 ms
   // against 5.69 in pairs, 8 x 4096 of LLaMA2-13B, 20, 7.87 / 7.77; LLaMA2-7B, 4 x 4096, 8, 2.16 / 2.19)
   if (!g.pair && per_unit > 12) us *= 1.03;
@@ -556,32 +581,36 @@ PrefillGeom prefill_geom(const lisa_desc* d) {
             want_split = g_tune[LISA_TUNE_PREFILL_SPLIT], want_pair = g_tune[LISA_TUNE_PREFILL_PAIR];
   const bool forced_slices = prefill_slices_ok(d) && (want_slices == 1 || want_slices == 2 || want_slices == 4);
   const bool forced_split = want_split == 1 || want_split == 2 || want_split == 4;
-  auto tiles_of = [&](long long rows) {                     // key tiles of a row block that ends before `rows`
-    const int last = (int)std::min<long long>(rows, d->Lq) - 1;
-    return ((d->causal ? std::min(d->Lk, last + 1 + d->Lk - d->Lq) : d->Lk) + PF_TK - 1) / PF_TK;
-  };
-  PrefillGeom best{1, 1, 1, 0};
+  const int tiles_max = prefill_block_tiles(d, d->Lq);
+  // Key shares of four tiles at least (of two, 0.7 % would be gained), and of fewer than kPartUnits units counted in the smallest head
+  // groups that the layer's activation has: their partial results (16 rows x the group's heads x 520 bytes) stay under 68 MB (136 MB for
+  // groups of 16 heads, 204 MB for 24) whatever the lengths.  Without that line prompts of LLaMA2-7B up to 6720 tokens took two shares for
+  // gains of 0 - 8 % and 306 MB, where 8192 tokens need 101 MB.
+  constexpr long long kPartUnits = 4 * kComputeUnits;
+  const int part_groups = d->act == LISA_ACT_SILU ? few : many;
+  const long long blocks16 = (long long)((d->Lq + PF_ROWS - 1) / PF_ROWS) * d->B;
+  PrefillGeom best{1, 1, 1, 0, 1};
   double least = -1.;
   for (int slices = 1; slices <= 4; slices *= 2) {
-    if (forced_slices ? slices != want_slices : slices == 4 || (slices == 2 && !prefill_slices_ok(d))) continue;
-    long long tiles_all = 0;
-    const int R = PF_ROWS * slices;
-    for (long long i = 0; i < d->Lq; i += R) tiles_all += tiles_of(i + R);
-    const int tiles_max = tiles_of(d->Lq);
+    if (forced_slices ? slices != want_slices : slices == 4 || (slices == 2 && (!prefill_slices_ok(d) || (forced_split && want_split > 1)))) continue;
+    const long long tiles_all = prefill_tiles(d, PF_ROWS * slices);
     // SiLU costs two quarter-rate instructions per hidden unit, once more per extra group: measured
     // 0.27 ms with two groups (and a key split) against 0.32 ms with four on the LLaMA2-7B shape.
     const int lo = slices > 1 || !two_forms ? many : want >= 0 ? (want == many ? many : few) : few;
     const int hi = slices > 1 || !two_forms ? many : want >= 0 ? lo : d->act == LISA_ACT_SILU ? few : many;
     for (int groups = lo; groups <= hi; groups += hi > lo ? hi - lo : 1)
       for (int split = 1; split <= 4; split *= 2) {
-        if (slices > 1 ? split > 1 : forced_split ? split != want_split : split > 2 || (split > 1 && tiles_max < 4)) continue;
+        if (slices > 1 ? split > 1 : forced_split ? split != want_split
+                                   : split > 1 && (tiles_max < 4 * split || split * blocks16 * part_groups >= kPartUnits)) continue;
+        const int units = (d->Lq + 16 * slices - 1) / (16 * slices) * split;
         for (int pair = 0; pair < 2; ++pair) {
           if (want_pair >= 0 && pair != (want_pair != 0)) continue;
-          PrefillGeom g{1, 1, 1, 0};
-          g.groups = whole_ok && slices == 1 && want == 1 ? 1 : groups;
-          g.slices = slices, g.split = split, g.pair = pair;
-          const double us = prefill_cost(d, g, tiles_all, tiles_max);
+          PrefillGeom g{slices, whole_ok && slices == 1 && want == 1 ? 1 : groups, split, pair, 1};
+          int load;
+          g.chunk = pf_chunk(g.groups, pair ? (units + 1) / 2 : units, d->B, &load);
+          const double us = prefill_cost(d, g, tiles_all, load);
           if (least < 0 || us < least) least = us, best = g;
+          if (load <= 32 && want_pair < 0) break;           // (all of them at once: a pair takes longer than its long unit)
         }
       }
   }
@@ -618,10 +647,9 @@ PrefillWs prefill_fused_ws(const lisa_desc* d) {
   return w;
 }
 
-int run_prefill_fused(const lisa_desc* d, const void* q_lr, const void* k_lr, const void* v,
+int run_prefill_fused(const lisa_desc* d, const PrefillWs& w, const void* q_lr, const void* k_lr, const void* v,
                       const void* prev, const void* w1, const void* w2, void* out, void* scores,
                       void* workspace, bool pass_through, hipStream_t st) {
-  const PrefillWs w = prefill_fused_ws(d);
   const PrefillGeom& geo = w.geom;
   char* ws = (char*)workspace;
   PrefillArgs a{};
@@ -647,10 +675,7 @@ int run_prefill_fused(const lisa_desc* d, const void* q_lr, const void* k_lr, co
   a.dscale = pick_scale(d->delta_scale, d->r);
   a.split = geo.split;
   a.pair = geo.pair;
-  {
-    const long long units = (long long)((d->Lq + 16 * geo.slices - 1) / (16 * geo.slices)) * geo.split;
-    a.chunk = pf_chunk(geo.groups, geo.pair ? (units + 1) / 2 : units, d->B);
-  }
+  a.chunk = geo.chunk;
   a.part_o = (float*)(ws + w.part_o);
   a.part_ml = (float*)(ws + w.part_ml);
   {
@@ -1412,6 +1437,15 @@ int lisa_launch_choice(const lisa_desc* desc, int which, int32_t* out) {
       else if (f32_attn_ok(desc)) out[0] = f32_attn_order(desc, desc->Lq, 1);
       else return LISA_ERR_UNSUPPORTED;
       return 1;
+    case LISA_CHOICE_PREFILL: {
+      if (check_lisa(desc) != LISA_OK) return LISA_ERR_UNSUPPORTED;
+      lisa_desc eq;
+      const lisa_desc* d = prefill_fused_ok(desc) ? desc : relu_equivalent(desc, &eq) && prefill_fused_ok(&eq) ? &eq : nullptr;
+      if (!d) return LISA_ERR_UNSUPPORTED;
+      const PrefillGeom g = prefill_geom(d);
+      out[0] = g.slices, out[1] = g.groups, out[2] = g.split, out[3] = g.pair, out[4] = g.chunk;
+      return 5;
+    }
   }
   return LISA_ERR_SHAPE;
 }
@@ -1458,22 +1492,25 @@ int lisa_attn_prefill(const lisa_desc* desc, const void* q_lr, const void* k_lr,
   const void* ptrs[] = {q_lr, k_lr, v, scores_prev, w1, w2, out, scores_out, workspace};
   for (const void* p : ptrs)
     if (p && !aligned16(p)) return LISA_ERR_ALIGN;
-  if (!workspace || workspace_bytes < lisa_workspace_bytes(desc, LISA_WS_PREFILL))
+  lisa_desc eq;
+  const lisa_desc* fused = prefill_fused_ok(desc) ? desc : relu_equivalent(desc, &eq) && prefill_fused_ok(&eq) ? &eq : nullptr;
+  PrefillWs fws;                                             // (one choice of the geometry per call)
+  if (fused) fws = prefill_fused_ws(fused);
+  if (!workspace || workspace_bytes < (fused == desc ? fws.total : fused ? round_up(fws.total, 256) + synth_ffn_bytes(desc)
+                                                                          : lisa_workspace_bytes(desc, LISA_WS_PREFILL)))
     return LISA_ERR_WORKSPACE;
   void* scores = desc->write_scores ? scores_out : nullptr;
   float* exact = (float*)workspace;
   hipStream_t st = (hipStream_t)hip_stream;
   const KeyStrides ks = dense_keys(desc, desc->Lk, desc->r);
   const KeyStrides vs = dense_keys(desc, desc->Lk, desc->d_k);
-  if (prefill_fused_ok(desc))
-    return run_prefill_fused(desc, q_lr, k_lr, v, scores_prev, w1, w2, out, scores, workspace, false, st);
-  lisa_desc eq;
-  if (relu_equivalent(desc, &eq) && prefill_fused_ok(&eq)) {
+  if (fused == desc)
+    return run_prefill_fused(desc, fws, q_lr, k_lr, v, scores_prev, w1, w2, out, scores, workspace, false, st);
+  if (fused) {
     const void *w1e, *w2e;
-    rc = synth_relu_ffn(desc, w1, workspace, round_up(prefill_fused_ws(&eq).total, 256), &w1e, &w2e, &q_lr, &k_lr,
-                        st);
+    rc = synth_relu_ffn(desc, w1, workspace, round_up(fws.total, 256), &w1e, &w2e, &q_lr, &k_lr, st);
     if (rc) return rc;
-    return run_prefill_fused(&eq, q_lr, k_lr, v, scores_prev, w1e, w2e, out, scores, workspace, !has_ffn(desc), st);
+    return run_prefill_fused(&eq, fws, q_lr, k_lr, v, scores_prev, w1e, w2e, out, scores, workspace, !has_ffn(desc), st);
   }
   // tiles are read and written by the fused kernels and by the matrix-core CONCAT pipeline alone
   if (desc->score_tiled && !concat_tiled_ok(desc) && !(relu_equivalent(desc, &eq) && concat_tiled_ok(&eq)))

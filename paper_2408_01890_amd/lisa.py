@@ -34,7 +34,7 @@ EXPORTS = (
     "lisa_probe_hbm_read", "lisa_probe_hbm_write", "lisa_probe_mfma", "lisa_launch_choice",
     "lisa_project_choice",
 )
-CHOICE_STD_ORDER = 0
+CHOICE_STD_ORDER, CHOICE_PREFILL = 0, 1
 TUNE_PREFILL_GROUPS, TUNE_PREFILL_SPLIT, TUNE_PREFILL_PAIR, TUNE_STD_PAIR, TUNE_PROJECT_TN, TUNE_PREFILL_SLICES = range(6)
 
 

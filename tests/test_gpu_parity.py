@@ -393,8 +393,9 @@ def test_lisa_prefill_fused_paired_units_odd_count():
     cfg = synth.LayerShape("pair_odd", "bf16", 8, 8, 8, 1040, 1024, 128, 22, 32)
     inp = synth.make_prefill_inputs(cfg, 31, DEV, ffn="fan_in")
     prev = std_prev(inp)
-    out, scores = lisa.lisa_attn_prefill(inp["q_lr"], inp["k_lr"], inp["v"], prev, inp["w1"],
-                                         inp["w2"])
+    with lisa.tune(prefill_pair=1, prefill_split=1):
+        out, scores = lisa.lisa_attn_prefill(inp["q_lr"], inp["k_lr"], inp["v"], prev, inp["w1"],
+                                             inp["w2"])
     torch.cuda.synchronize()
     assert lisa.last_path() == "mfma_fused"
     rows_by_b = {b: synth.sample_rows(cfg.L, 48, 200 + b) for b in range(cfg.B)}

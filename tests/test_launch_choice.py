@@ -39,3 +39,47 @@ def test_order_of_more_row_blocks_than_one_grid_axis_holds():
     (40, 40, 5120, 900, 2), (32, 32, 4096, 8192, 0), (32, 32, 4096, 128, None)])
 def test_projection_tile_shape(H, Hkv, d_model, L, shape):
     assert lisa.project_choice(torch.bfloat16, 1, L, d_model, H, Hkv, 22, 128) == shape
+
+
+def prefill(H, Hkv, F, B, Lq, past=0, **kw):
+    return lisa.make_desc(lisa.BF16, B, H, Hkv, Lq, Lq + past, 128, r=22, F=F, write_scores=1, score_tiled=1, **kw)
+
+
+@pytest.mark.parametrize("H,Hkv,F,B,Lq,past,geometry", [
+    # slices, head groups, key shares, pairs
+    (32, 8, 64, 1, 16, 8192, (1, 4, 4, 0)), (32, 32, 64, 4, 32, 8192, (1, 4, 4, 0)), (40, 40, 80, 1, 136, 960, (1, 5, 4, 0)),
+    (8, 8, 16, 1, 128, 8192, (1, 1, 4, 0)), (24, 8, 48, 1, 512, 8192, (1, 1, 4, 0)), (16, 4, 32, 4, 16, 8192, (1, 2, 4, 0)),
+    (24, 24, 48, 1, 704, 0, (1, 1, 4, 0)), (8, 2, 64, 1, 704, 0, (1, 1, 4, 0)),
+    (32, 32, 128, 1, 352, 0, (1, 4, 2, 0)), (32, 8, 64, 1, 1248, 0, (1, 2, 2, 0)),
+    (32, 8, 64, 4, 8192, 0, (1, 2, 1, 1)), (32, 32, 64, 3, 1312, 0, (1, 2, 1, 1)),
+    (40, 40, 80, 8, 4096, 0, (2, 5, 1, 1)), (40, 40, 80, 3, 704, 0, (2, 5, 1, 1)), (8, 2, 64, 1, 2816, 0, (1, 1, 2, 1))])
+def test_geometry_of_the_fused_prefill(H, Hkv, F, B, Lq, past, geometry):
+    """Few rows behind many keys take four key shares, whatever the layer: with two they ran up to twice as long."""
+    assert lisa.launch_choice(prefill(H, Hkv, F, B, Lq, past), lisa.CHOICE_PREFILL)[:4] == geometry
+
+
+@pytest.mark.parametrize("act", [lisa.ACT_RELU, lisa.ACT_SILU])
+@pytest.mark.parametrize("H,Hkv,F", [(8, 8, 16), (16, 4, 64), (24, 8, 48), (32, 32, 64), (32, 8, 64), (40, 40, 80)])
+def test_prefill_workspace_with_key_shares_is_bounded(H, Hkv, F, act):
+    """Partial results of fewer than 1024 units (16 rows of the heads of the smallest head group, 520 bytes each), whatever the
+    length; none beyond the lengths that had them when counts of units alone decided."""
+    group = 24 if H == 24 else 16 if act == lisa.ACT_SILU and H in (16, 32) else 8
+    for B in (1, 3, 8):
+        for past in (0, 2048):
+            for Lq in [*range(16, 2400, 37), *range(2400, 9000, 331)]:
+                d = prefill(H, Hkv, F, B, Lq, past, act=act)
+                need = lisa.workspace_bytes(d, lisa.WS_PREFILL)
+                with lisa.tune(prefill_split=1):
+                    plain = lisa.workspace_bytes(d, lisa.WS_PREFILL)
+                assert plain - 2 ** 17 <= need <= plain + 1024 * 16 * group * 520 + 2 ** 17     # (the FFN image: 1 - 2 head groups)
+                units = -(-Lq // 16) * B * (H // group)
+                if units >= 512 or Lq + past <= 7 * 32:
+                    assert need <= plain + 2 ** 17
+
+
+def test_forced_key_shares_are_taken_where_row_slices_exist():
+    for split in (2, 4):
+        with lisa.tune(prefill_split=split):
+            assert lisa.launch_choice(prefill(40, 40, 80, 8, 4096), lisa.CHOICE_PREFILL)[:3] == (1, 5, split)
+    with lisa.tune(prefill_slices=2, prefill_split=2):       # (slices have one share)
+        assert lisa.launch_choice(prefill(40, 40, 80, 8, 4096), lisa.CHOICE_PREFILL)[:3] == (2, 5, 1)
