@@ -49,7 +49,7 @@ struct F32AttnArgs {
   S* scores;              // [B,H,Lq,Lk] or null
   void* out;              // [B,Lq,H,DK] (float where out_f32, else T) or null
   int B, H, Hkv, Lq, Lk, causal, out_f32;
-  int order;              // of the workgroups, see f32_attn_order()
+  int order, blocks;      // of the workgroups, see f32_attn_order(); parts * row blocks
   int row0, n_rows;       // query rows of this launch (row0 a multiple of 16)
   int parts;              // workgroups that the tiles of a row block are dealt to (1 unless scores only)
   float scale;
@@ -73,13 +73,12 @@ __global__ __launch_bounds__(64 * NW) void k_f32_attn(F32AttnArgs<T, S> a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, g = lane >> 4;
-  int h = blockIdx.x, b = blockIdx.y, xr = gridDim.z - 1 - blockIdx.z;   // long row blocks first
-  if (a.order == 0) {
-    xr = gridDim.x - 1 - blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  } else if (a.order == 2) {
+  const bool z = a.order != 0;                               // (nothing of the grid is read: one load of the arguments less to wait for)
+  int h = z ? blockIdx.x : blockIdx.y, b = z ? blockIdx.y : blockIdx.z, xr = a.blocks - 1 - (z ? blockIdx.z : blockIdx.x);   // long row blocks first
+  if (a.order == 2) {
     const int heads = a.H * a.B, chunk = blockIdx.x & ~255u;
-    const int pos = chunk & 256 ? chunk + min((int)gridDim.x, chunk + 256) - 1 - (int)blockIdx.x : blockIdx.x;
-    xr = (int)gridDim.x / heads - 1 - pos / heads, h = pos % heads % a.H, b = pos % heads / a.H;
+    const int pos = chunk & 256 ? chunk + min(a.blocks * heads, chunk + 256) - 1 - (int)blockIdx.x : blockIdx.x;
+    xr = a.blocks - 1 - pos / heads, h = pos % heads % a.H, b = pos % heads / a.H;
   }
   int rb = xr, t_first = wv, t_step = NW;
   if (a.parts > 1) {

@@ -10,12 +10,12 @@ namespace lisa {
 // side, of many heads an L2 of 4 MB holds too little of any.  Standard layer, order 0 / 2 in us, heads in all, width 64: 128 heads, 512
 // tokens (4096 workgroups) 115 / 78, 1500 (12032) 525 / 598; 156, 200 (2028) 21.9 / 20.7, 410 (4056) 60 / 69, 900 (8892) 272 / 390;
 // 512, 600 (19456) 411 / 560; width 128: 96, 1000 (6048) 392 / 347, 1500 (9024) 783 / 747; 256, 128 (2048) 46.7 / 43.5, 200 (3328)
-// 81.8 / 82.5, 700 (11264) 503 / 649, 1000 (16128) 974 / 1295.  One row block: nothing to order, and 32000 divisions cost 4 %
-// (bf16, 1000 sequences of 9 tokens, 216 / 225).
+// 81.8 / 82.5, 700 (11264) 503 / 649, 1000 (16128) 974 / 1295.  One or two row blocks: little to order, and the divisions cost more
+// (bf16, 1000 sequences of 9 tokens, 216 / 225; 8 x 17 tokens of 32 heads of 128 7.6 / 8.2).
 int f32_attn_order(const lisa_desc* d, int n_rows, int parts) {
   const long long blocks = (n_rows + 15) / 16, heads = (long long)d->H * d->B, wgs = blocks * parts * heads;
   if (wgs <= kComputeUnits) return 1;
-  return blocks > 1 && wgs <= (heads <= 128 ? 36 : 8) * kComputeUnits ? 2 : 0;
+  return blocks > 2 && wgs <= (heads <= 128 ? 36 : 8) * kComputeUnits ? 2 : 0;
 }
 
 bool f32_attn_ok(const lisa_desc* d) { return d->Lq > 1 && d->dtype == LISA_F32 && (d->d_k == 64 || d->d_k == 128); }
@@ -30,7 +30,7 @@ int launch_attn(const lisa_desc* d, F32AttnArgs<T, S> a, hipStream_t st) {
   // 430 tokens (216) 14.8 / 13.4, 700 (352) 19.4 / 19.2, 2 x 504 (512) 16.7 / 17.7.
   const bool wide = sizeof(T) == 4 && a.out && d->Lk > 256 && wgs <= (a.given ? 4 : 1) * kComputeUnits;
   a.order = f32_attn_order(d, a.n_rows, a.parts);
-  const int blocks = (a.n_rows + 15) / 16 * a.parts;
+  const int blocks = a.blocks = (a.n_rows + 15) / 16 * a.parts;
   const dim3 grid = a.order == 0 ? dim3(blocks, d->H, d->B) : a.order == 1 ? dim3(d->H, d->B, blocks) : dim3((unsigned)wgs);
   StageScope prof(a.given ? "k_f32_softmax_v" : "k_f32_attn", st);
   auto kern = a.given ? k_f32_attn<T, S, NDK, true, 4> : k_f32_attn<T, S, NDK, false, 4>;

@@ -21,7 +21,7 @@ def test_order_of_ragged_standard_layers(B, H, Lq, past, order):
 
 @pytest.mark.parametrize("B,H,Lq,dk,order", [
     (1, 8, 128, 64, 1), (2, 8, 504, 64, 2), (8, 16, 512, 64, 2), (3, 32, 1000, 128, 2), (8, 32, 128, 128, 2),
-    (8, 16, 1500, 64, 0), (13, 12, 410, 64, 0), (16, 32, 600, 64, 0), (8, 32, 700, 128, 0), (8, 32, 1000, 128, 0), (1000, 32, 9, 128, 0)])
+    (8, 16, 1500, 64, 0), (13, 12, 410, 64, 0), (16, 32, 600, 64, 0), (8, 32, 700, 128, 0), (8, 32, 1000, 128, 0), (1000, 32, 9, 128, 0), (8, 32, 17, 128, 0), (8, 32, 33, 128, 2)])
 def test_order_of_float32_standard_layers(B, H, Lq, dk, order):
     d = lisa.make_desc(lisa.F32, B, H, H, Lq, Lq, dk)
     assert lisa.launch_choice(d, lisa.CHOICE_STD_ORDER) == (order,)
