@@ -142,11 +142,13 @@ size_t lisa_scores_elems(const lisa_desc* desc);
  *   out         [B,Lq,H,d_k]   out  concatenated heads softmax(A_n) V, dtype
  *   scores_out  [B,H,Lq,Lk]    out  A_n, score type; required iff write_scores = 1; must not
  *                                   alias scores_prev
- *   workspace                  scratch of at least lisa_workspace_bytes(desc, LISA_WS_PREFILL): ask for each shape, the
- *                                   need does not grow steadily with the lengths.  bf16 problems of few row blocks deal
- *                                   the keys of a block to two or four shares, whose partial results take up to 68 MB
- *                                   (136 MB: SiLU with 16 or 32 heads; 204 MB: 24 heads) that longer prompts do not need
+ *   workspace                  scratch of at least lisa_workspace_bytes(desc, LISA_WS_PREFILL)
  *                              bytes (may be NULL when that is 0); contents undefined after.
+ *                              Ask for each shape: the need does not grow steadily with the
+ *                              lengths.  bf16 problems of few row blocks deal the keys of a block
+ *                              to two or four shares, whose partial results take up to 68 MB
+ *                              (136 MB: SiLU with 16 or 32 heads; 204 MB: 24 heads) that longer
+ *                              prompts do not need.
  *                              The fused kernels keep A_n in float32 registers up to the
  *                              softmax and the generic kernels stage it here as float32; the
  *                              matrix-core kernels of the CONCAT form pass it between their two
