@@ -28,8 +28,11 @@ def test_batch_equals_its_sequences(B, H, Hkv, L, tiled):
     for b in range(B):
         a1, o1 = lisa.std_attn_scores(q[b:b + 1], k[b:b + 1], v[b:b + 1], tiled=tiled)
         torch.cuda.synchronize()
-        if not tiled:
-            assert torch.equal(a[b][:, vis], a1[0][:, vis])
+        if tiled:
+            a_b, a_1 = (lisa.untile_scores(t, L, L)[0] for t in (a[b:b + 1], a1))
+        else:
+            a_b, a_1 = a[b], a1[0]
+        assert torch.equal(a_b[:, vis], a_1[:, vis])
         # (a sequence alone may take two waves per row block: bf16 probabilities against another maximum)
         assert (o[b] - o1[0]).norm() <= 4e-3 * o1[0].norm()
 
