@@ -15,7 +15,7 @@
 
 namespace lisa {
 
-constexpr int KD_UN = 2;       // pieces of a lane whose loads are in flight together, tiled scores (4: 2 - 12 % longer, see kd_shares)
+constexpr int KD_UN = 2;       // pieces of a lane whose loads are in flight together, tiled scores
 constexpr int KD_ROW_UN = 4;   // row-major scores
 
 // 16 bytes of a score tensor, read once by this kernel: a non-temporal load
