@@ -1,5 +1,7 @@
 """What the dispatch chooses on both sides of its lines (host only): each line was drawn where the two sides' times cross, and
 the sizes here are ones at which the other side was measured slower."""
+import ctypes as C
+
 import pytest
 import torch
 
@@ -83,3 +85,17 @@ def test_forced_key_shares_are_taken_where_row_slices_exist():
             assert lisa.launch_choice(prefill(40, 40, 80, 8, 4096), lisa.CHOICE_PREFILL)[:3] == (1, 5, split)
     with lisa.tune(prefill_slices=2, prefill_split=2):       # (slices have one share)
         assert lisa.launch_choice(prefill(40, 40, 80, 8, 4096), lisa.CHOICE_PREFILL)[:3] == (2, 5, 1)
+
+
+@pytest.mark.parametrize("kw", [
+    dict(), dict(act=lisa.ACT_SILU), dict(mix=lisa.MIX_PLUS), dict(act=lisa.ACT_SINGLE, F=32), dict(mix=lisa.MIX_SHARE, r=0),
+    dict(mix=lisa.MIX_CONCAT, F=256), dict(score_tiled=0, Lq=97, Lk=97)])
+def test_prefill_refuses_one_byte_less_than_the_workspace_needs(kw):
+    args = dict(dtype=lisa.BF16, B=1, H=32, Hkv=8, Lq=96, Lk=1024, d_k=128, r=22, F=64, write_scores=1, score_tiled=1)
+    args.update(kw)
+    d = lisa.make_desc(**args)
+    need = lisa.workspace_bytes(d, lisa.WS_PREFILL)
+    fake = C.c_void_p(0x10000)                               # never dereferenced on the host
+    call = [fake] * 9
+    call[7] = C.c_void_p(0x20000)                            # (scores_out is not scores_prev)
+    assert need > 0 and lisa.library().lisa_attn_prefill(C.byref(d), *call, need - 1, None) == -5
